@@ -133,3 +133,20 @@ def test_mid_size_class_matrices_list_and_schedule_in_one_launch(Mb, N, Br, kind
         got = index_to_numpy(idx)
         assert_index_equal(got, mask, Br, 64)
     assert got["sched"][1] >= 32 and (kind != "window" or got["sched"][0] > 0)       # the window masks have cut rows
+
+
+@pytest.mark.parametrize("Nq,Nk,offset", [(64, 15, 0), (70, 16, 3), (129, 17, 0), (130, 255, 1), (130, 257, 0), (5, 511, 7), (300, 513, 0),
+                                          (128, 272, 16), (2900, 2993, 5)])
+def test_block_mask_at_any_address(Nq, Nk, offset):
+    """Rows that start at any byte: row lengths around the 16-byte chunk and the two segment lengths, and a mask above the
+    size from which such rows are read in the longer segments."""
+    rng = np.random.default_rng(Nq + Nk)
+    mask = ((rng.random((1, Nq, Nk)) < 0.2) * rng.integers(1, 256, (1, Nq, Nk))).astype(np.uint8)
+    mask[:, :, :64] = np.minimum(mask[:, :, :64], 0 if Nk > 64 else 255)     # an all-zero block column
+    mask[:, :min(Nq, 128), 64:128] = 255                                     # a full block (where the mask reaches it)
+    buf = torch.zeros(Nq * (Nk + offset) + offset, dtype=torch.uint8, device="cuda")
+    view = buf[offset:].view(1, Nq, Nk + offset)[:, :, :Nk]
+    view.copy_(torch.from_numpy(mask))
+    idx = _bbm().bbm_build_block_mask_rect(view, 128, 64)
+    torch.cuda.synchronize()
+    assert_index_equal(index_to_numpy(idx), mask, 128, 64)
