@@ -2,63 +2,17 @@
 // compact per-row list of non-zero blocks.  Both read only the small [Mb][nbr][nbc] class matrix; one
 // wavefront owns one block row and works on 64 classes at a time through wave-wide ballots.
 #include "bbm_internal.h"
+#include "bbm_line_index.h"
 
 namespace {
 
 constexpr int kWavesPerWG = 4;
 
-__device__ __forceinline__ int ctz64(uint64_t x) { return x ? __builtin_ctzll(x) : 64; }
-
-// Longest run of FULL blocks of one block row (leftmost on ties) and the span of its non-zero blocks, fed 64 block
-// columns at a time in ascending order (bit t of `full` / `nz` = block column base + t).
-struct RunScan {
-  int best_len = 0, best_start = 0;  // longest finished run so far
-  int cur_len = 0, cur_start = 0;    // run that touches the end of the previous chunk (0 = none)
-  int lo = 0, hi = 0, cnt = 0;
-  __device__ __forceinline__ void feed(uint64_t full, uint64_t nz, int base) {
-    if (nz) {
-      if (cnt == 0) lo = base + ctz64(nz);
-      hi = base + 64 - __builtin_clzll(nz);
-      cnt += __popcll(nz);
-    }
-    if (cur_len > 0) {  // continue the run that reached the chunk boundary
-      const int ones = ctz64(~full);
-      cur_len += ones;
-      if (ones == 64) return;
-      if (cur_len > best_len) { best_len = cur_len; best_start = cur_start; }
-      cur_len = 0;
-      full &= ~((1ull << ones) - 1ull);
-    }
-    while (full) {
-      const int s = ctz64(full);
-      const int ones = ctz64(~(full >> s));  // full >> s has zeros shifted in, so ones <= 64 - s
-      if (s + ones == 64) {                  // run reaches the chunk end: decide when it ends
-        cur_start = base + s;
-        cur_len = ones;
-        return;
-      }
-      if (ones > best_len) { best_len = ones; best_start = base + s; }
-      full &= ~(((1ull << ones) - 1ull) << s);
-    }
-  }
-  __device__ __forceinline__ void finish() {
-    if (cur_len > best_len) { best_len = cur_len; best_start = cur_start; }
-  }
-};
-
-// Exclusive prefix sum over the 64 lanes with data-parallel-primitive moves (register to register; a shuffle goes
-// through LDS): shifts by 1, 2, 4, 8 inside each row of 16 lanes (a lane without a source adds 0), then lane 15 of a
-// row added to the next row (rows 1 and 3), then lane 31 to rows 2 and 3.
-__device__ __forceinline__ int wave_excl_scan(int x, int /*lane*/) {
-  int incl = x;
-  incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);  // row_shr:1
-  incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);  // row_shr:2
-  incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);  // row_shr:4
-  incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);  // row_shr:8
-  incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
-  incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
-  return incl - x;
-}
+using bbm::RunScan;
+using bbm::ctz64;
+using bbm::launch_group_rows;
+using bbm::wave_excl_scan;
+using bbm::wave_sum;
 
 // One wave per block row.  With `row_ptr` (rows per plane: nbr) the row's count of non-zero blocks is also left at
 // row_ptr[m][i+1], which is pass 1 of the list: the index stage in one call then needs no list_count_kernel.
@@ -115,7 +69,7 @@ __global__ __launch_bounds__(64) void list_scan_kernel(int64_t nbr, int32_t* __r
   int carry = 0;
   for (int64_t base = 0; base < nbr; base += 64) {
     int x = (base + lane < nbr) ? p[base + lane + 1] : 0;
-    x += wave_excl_scan(x, lane);
+    x += wave_excl_scan(x);
     x += carry;
     if (base + lane < nbr) p[base + lane + 1] = x;
     carry = __shfl(x, 63);
@@ -141,7 +95,7 @@ __global__ __launch_bounds__(kWavesPerWG * 64) void list_fill_kernel(const uint8
     const int32_t* cp = counts + m * nbr;
     int part = 0;
     for (int64_t b = lane; b < i; b += 64) part += cp[b];
-    start = __builtin_amdgcn_readlane(wave_excl_scan(part, lane) + part, 63);
+    start = __builtin_amdgcn_readlane(wave_excl_scan(part) + part, 63);
     if (lane == 0) {
       row_ptr[m * (nbr + 1) + i] = start;
       if (i == nbr - 1) row_ptr[m * (nbr + 1) + nbr] = start + cp[i];
@@ -162,10 +116,6 @@ __global__ __launch_bounds__(kWavesPerWG * 64) void list_fill_kernel(const uint8
   }
 }
 
-// Rows per launch-order group: neighbouring rows are kept together only while rows are short (split threshold at its
-// floor, i.e. mean list length <= 16); with long rows the plain longest-first order balances the tail better.
-__device__ __forceinline__ int launch_group_rows(int T) { return T == bbm::kSchedMinSplit ? bbm::kSchedGroupRows : 1; }
-
 // Position of block row i in the launch order of its plane.  len[0 .. nbr) = list lengths of the plane's rows,
 // gmax[0 .. ceil(nbr/gsz)) = longest list of every group of gsz consecutive rows.  Order: the group holding the longest
 // row first (ties: higher rows first); inside a group the longest row first (ties: higher row first).
@@ -184,13 +134,6 @@ __device__ __forceinline__ int launch_rank(const int* len, const int* gmax, int 
   const int c = len[i];
   for (int j = g * gsz; j < min(nbr, (g + 1) * gsz); ++j) rank += (len[j] > c) || (len[j] == c && j > i);
   return rank;
-}
-
-// Sum over the 64 lanes, returned in every lane.
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d);
-  return x;
 }
 
 // list_fill_kernel and sched_kernel in one launch, for index stages that already have every row's list length
@@ -392,7 +335,7 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(const int32_t* __r
   }
   // exclusive scan over the threads: inside each wave with register moves, then the four wave totals through LDS
   const int lane = tid & 63, wave = tid >> 6;
-  const int q_in_wave = wave_excl_scan(nparts, lane), rho_in_wave = wave_excl_scan(ncut, lane);
+  const int q_in_wave = wave_excl_scan(nparts), rho_in_wave = wave_excl_scan(ncut);
   if (lane == 63) {
     pre[0][wave] = q_in_wave + nparts;
     pre[1][wave] = rho_in_wave + ncut;
@@ -434,371 +377,6 @@ __global__ __launch_bounds__(kSchedThreads) void sched_kernel(const int32_t* __r
   }
 }
 
-// The same products for the smallest class matrices -- at most 64 block rows per plane, at most 256 block columns in
-// whole 16-byte groups, at most 16 planes (4 planes of a 4096 x 4096 mask in 128 x 64 or 64 x 64 tiles) -- with one
-// WAVE per plane and one LANE per block row: a lane reads its row as 16-byte words and turns it into a non-zero and a
-// full bit mask in registers, so counting, run search and list positions need no ballots and no LDS; row_ptr is a
-// shuffle scan over the lanes.  Only the split threshold (a mean over all planes) and the launch-order ranks cross
-// lanes through LDS, behind two barriers.
-constexpr int kTinyMaxPlanes = 16, kTinyMaxRows = 64, kTinyMaxChunks = 4;
-
-// 16 class bytes -> 16 bits: bit t = (byte t != 0) in the low half, (byte t == BBM_BLOCK_FULL) in the high half.
-__device__ __forceinline__ uint32_t class_bits16(uint4 x) {
-  auto nz4 = [](uint32_t w) {  // 4 bytes -> 4 bits (bit t = byte t non-zero)
-    const uint32_t y = (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u;
-    return (((y >> 7) * 0x00204081u) >> 21) & 0xfu;
-  };
-  const uint32_t f = 0x01010101u * BBM_BLOCK_FULL;
-  const uint32_t nz = nz4(x.x) | (nz4(x.y) << 4) | (nz4(x.z) << 8) | (nz4(x.w) << 12);
-  const uint32_t ne = nz4(x.x ^ f) | (nz4(x.y ^ f) << 4) | (nz4(x.z ^ f) << 8) | (nz4(x.w ^ f) << 12);  // byte != FULL
-  return nz | ((~ne & 0xffffu) << 16);
-}
-
-
-__global__ __launch_bounds__(kTinyMaxPlanes * 64) void tiny_index_kernel(const uint8_t* __restrict__ cls, int Mb, int nbr,
-                                                                        int nbc, int32_t* __restrict__ row_ptr,
-                                                                        uint32_t* __restrict__ col_idx,
-                                                                        int32_t* __restrict__ sched,
-                                                                        int32_t* __restrict__ offset,
-                                                                        int32_t* __restrict__ total_ones,
-                                                                        int32_t* __restrict__ nz_lo,
-                                                                        int32_t* __restrict__ nz_hi,
-                                                                        int32_t* __restrict__ nz_cnt) {
-  using namespace bbm;
-  __shared__ int tot_s[kTinyMaxPlanes][2];   // per plane: list entries, non-empty rows
-  __shared__ int part_s[kTinyMaxPlanes][2];  // per plane: parts, cut rows
-  __shared__ int len_s[kTinyMaxPlanes][kTinyMaxRows];
-  __shared__ int gmax_s[kTinyMaxPlanes][kTinyMaxRows];
-  const int lane = threadIdx.x & 63;
-  const int m = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // plane of this wave
-  const int i = lane;                                              // block row of this lane
-  const bool live = i < nbr;
-  const int CH = (nbc + 63) / 64;
-
-  // ---- the row as bit masks
-  uint64_t nz[kTinyMaxChunks], full[kTinyMaxChunks];
-  {
-    const uint4* rowp = reinterpret_cast<const uint4*>(cls + ((int64_t)m * nbr + (live ? i : 0)) * nbc);
-    const int words = nbc / 16;
-    uint4 w[kTinyMaxChunks * 4];
-#pragma unroll
-    for (int t = 0; t < kTinyMaxChunks * 4; ++t) w[t] = (live && t < words) ? rowp[t] : make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int ch = 0; ch < kTinyMaxChunks; ++ch) {
-      nz[ch] = full[ch] = 0;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint32_t b = class_bits16(w[4 * ch + t]);
-        nz[ch] |= (uint64_t)(b & 0xffffu) << (16 * t);
-        full[ch] |= (uint64_t)(b >> 16) << (16 * t);
-      }
-    }
-  }
-  int c = 0;
-#pragma unroll
-  for (int ch = 0; ch < kTinyMaxChunks; ++ch) c += __popcll(nz[ch]);
-
-  // ---- list: position by a scan over the rows of the plane, entries written row by row.  A cross-lane step costs
-  // an LDS round trip, so two quantities share each scan (counts stay below 2^16: at most 64 rows of at most 256
-  // entries) and totals are read from lane 63 of the scan instead of being reduced again.
-  const int packed_c = c | ((c > 0 ? 1 : 0) << 16);
-  const int scan_c = wave_excl_scan(packed_c, lane);
-  const int start = scan_c & 0xffff;
-  if (live) {
-    row_ptr[(int64_t)m * (nbr + 1) + i] = start;
-    if (i == nbr - 1) row_ptr[(int64_t)m * (nbr + 1) + nbr] = start + c;
-    uint32_t* out = col_idx + (int64_t)m * nbr * nbc + start;
-#pragma unroll
-    for (int ch = 0; ch < kTinyMaxChunks; ++ch) {
-      uint64_t x = nz[ch];
-      while (x) {
-        const int b = ctz64(x);
-        *out++ = (uint32_t)(64 * ch + b) | (((full[ch] >> b) & 1ull) ? 0x80000000u : 0u);
-        x &= x - 1;
-      }
-    }
-    if (offset) {  // run index
-      RunScan rs;
-      for (int ch = 0; ch < CH; ++ch) rs.feed(full[ch], nz[ch], 64 * ch);
-      rs.finish();
-      offset[m * nbr + i] = rs.best_start;
-      total_ones[m * nbr + i] = rs.best_len;
-      nz_lo[m * nbr + i] = rs.lo;
-      nz_hi[m * nbr + i] = rs.hi;
-      nz_cnt[m * nbr + i] = rs.cnt;
-    }
-  }
-  if (!sched) return;
-
-  // ---- schedule (same definition as sched_kernel)
-  const int last_c = __builtin_amdgcn_readlane(scan_c + packed_c, 63);
-  const int plane_total = last_c & 0xffff, plane_nonempty = last_c >> 16;
-  if (lane == 0) {
-    tot_s[m][0] = plane_total;
-    tot_s[m][1] = plane_nonempty;
-  }
-  if (live) len_s[m][i] = c;
-  __syncthreads();
-  int total = 0, nonempty = 0;
-  for (int p = 0; p < Mb; ++p) {
-    total += tot_s[p][0];
-    nonempty += tot_s[p][1];
-  }
-  const int mean = nonempty > 0 ? (total + nonempty - 1) / nonempty : 0;
-  const int T = max(kSchedMinSplit, 2 * mean);
-  const int np = c > T ? (c + T - 1) / T : 0;
-  const int packed_np = np | ((np > 0 ? 1 : 0) << 16);
-  const int scan_np = wave_excl_scan(packed_np, lane);
-  const int q_in_plane = scan_np & 0xffff, rho_in_plane = scan_np >> 16;
-  const int last_np = __builtin_amdgcn_readlane(scan_np + packed_np, 63);
-  const int plane_parts = last_np & 0xffff, plane_cut = last_np >> 16;
-  if (lane == 0) {
-    part_s[m][0] = plane_parts;
-    part_s[m][1] = plane_cut;
-  }
-  const int gsz = launch_group_rows(T), ngp = (nbr + gsz - 1) / gsz;
-  if (lane < ngp) {
-    int t = 0;
-    for (int j = lane * gsz; j < min(nbr, (lane + 1) * gsz); ++j) t = max(t, len_s[m][j]);
-    gmax_s[m][lane] = t;
-  }
-  __syncthreads();
-  int q = q_in_plane, rho = rho_in_plane, parts_all = 0, cut_all = 0;
-  for (int p = 0; p < Mb; ++p) {
-    if (p < m) {
-      q += part_s[p][0];
-      rho += part_s[p][1];
-    }
-    parts_all += part_s[p][0];
-    cut_all += part_s[p][1];
-  }
-  if (threadIdx.x == 0) {
-    sched[kSchedNParts] = parts_all;
-    sched[kSchedSplitT] = T;
-    sched[kSchedNCutRows] = cut_all;
-    for (int x = 3; x < kSchedPartBase; ++x) sched[x] = 0;
-  }
-  if (!live) return;
-  // list entry number n of this row, from the masks (the same value the fill above stored)
-  auto entry_at = [&](int n) {
-#pragma unroll
-    for (int ch = 0; ch < kTinyMaxChunks; ++ch) {
-      uint64_t x = nz[ch];
-      const int cnt = __popcll(x);
-      if (n < cnt) {
-        for (int t = 0; t < n; ++t) x &= x - 1;
-        const int b = ctz64(x);
-        return (int)((uint32_t)(64 * ch + b) | (((full[ch] >> b) & 1ull) ? 0x80000000u : 0u));
-      }
-      n -= cnt;
-    }
-    return -1;
-  };
-  if (np > 0) {
-    const int chunk = (c + np - 1) / np;
-    for (int k = 0; k < np; ++k) {
-      int32_t* rec = sched + kSchedPartBase + (int64_t)kSchedPartInts * (q + k);
-      rec[0] = m * nbr + i;
-      rec[1] = start + k * chunk;
-      rec[2] = min(chunk, c - k * chunk);
-      rec[3] = k;
-      rec[4] = np;
-      rec[5] = q;
-      rec[6] = rho;
-      rec[7] = entry_at(k * chunk);
-    }
-  }
-  const int rank = launch_rank(len_s[m], gmax_s[m], nbr, gsz, i);
-  reinterpret_cast<int4*>(sched + sched_order_base(Mb, nbr))[(int64_t)m * nbr + rank] = make_int4(i, start, c, entry_at(0));
-}
-
-// Whole sparse index (row_ptr, col_idx and, if asked for, the schedule), and if asked for the run index as well,
-// in ONE launch of one work-group, for class matrices of at most kSmallPairs (row, 64-column chunk) pairs -- e.g. 4 planes of a 4096 x 4096 mask in 128 x 64
-// tiles.  At this size the four launches of the general path cost far more than the work itself.  Pair p = (row r,
-// chunk ch) with p = r*CH + ch is owned by slot p % 16 of wave p / 16; lists are row-major and ascending, so the
-// position of a pair's first entry in its plane's list is the exclusive prefix sum of the pairs' popcounts.
-constexpr int kSmallWaves = 16, kSmallSlots = 16, kSmallPairs = kSmallWaves * kSmallSlots;
-
-__global__ __launch_bounds__(kSmallWaves * 64) void small_index_kernel(const uint8_t* __restrict__ cls, int Mb, int nbr,
-                                                                       int nbc, int32_t* __restrict__ row_ptr,
-                                                                       uint32_t* col_idx, int32_t* __restrict__ sched,
-                                                                       int32_t* __restrict__ offset,
-                                                                       int32_t* __restrict__ total_ones,
-                                                                       int32_t* __restrict__ nz_lo,
-                                                                       int32_t* __restrict__ nz_hi,
-                                                                       int32_t* __restrict__ nz_cnt) {
-  using namespace bbm;
-  __shared__ int pc[kSmallPairs];     // non-zero blocks of a pair
-  __shared__ int pos[kSmallPairs];    // position of the pair's first entry in the plane's list
-  __shared__ int len_s[kSmallPairs];  // list length of a row
-  __shared__ int gmax_s[kSmallPairs]; // longest list of a launch-order group (groups never span planes)
-  __shared__ int np_s[kSmallPairs];   // parts of a row (0 = not cut)
-  __shared__ int tot_s[4];            // list entries, non-empty rows, parts, cut rows
-  __shared__ int gpre_s[kSmallPairs], wsum_s[kSmallPairs / 64];
-  __shared__ uint64_t full_s[kSmallPairs], nz_s[kSmallPairs];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: pair -> (row, chunk) arithmetic stays off the vector ALU
-  const int CH = (nbc + 63) / 64, PP = nbr * CH, npairs = Mb * PP, nrows = Mb * nbr;
-  const int64_t plane_entries = (int64_t)nbr * nbc;
-  if (tid < 4) tot_s[tid] = 0;
-
-  // (row, chunk, plane) of the wave's first pair by division, of the following ones by counting (integer division is
-  // dozens of instructions)
-  const int r_first = wave * kSmallSlots / CH, ch_first = wave * kSmallSlots - r_first * CH, m_first = r_first / nbr;
-  uint8_t v[kSmallSlots];
-  uint64_t nz[kSmallSlots];
-  {
-    int r = r_first, ch = ch_first;
-#pragma unroll
-    for (int k = 0; k < kSmallSlots; ++k) {
-      const int p = wave * kSmallSlots + k, col = ch * 64 + lane;
-      v[k] = (p < npairs && col < nbc) ? cls[(int64_t)r * nbc + col] : (uint8_t)0;
-      if (++ch == CH) {
-        ch = 0;
-        ++r;
-      }
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < kSmallSlots; ++k) {
-    const int p = wave * kSmallSlots + k;
-    nz[k] = __ballot(v[k] != BBM_BLOCK_EMPTY);
-    const uint64_t full = __ballot(v[k] == BBM_BLOCK_FULL);
-    if (lane == 0 && p < npairs) {
-      pc[p] = __popcll(nz[k]);
-      nz_s[p] = nz[k];
-      full_s[p] = full;
-    }
-  }
-  __syncthreads();
-  // exclusive prefix sums of pc over all pairs (the first four waves scan 64 pairs each), then made plane-relative
-  if (wave < kSmallPairs / 64) {
-    const int x = tid < npairs ? pc[tid] : 0;
-    int incl = x;
-    for (int d = 1; d < 64; d <<= 1) {
-      const int y = __shfl_up(incl, d);
-      if (lane >= d) incl += y;
-    }
-    if (lane == 63) wsum_s[wave] = incl;
-    gpre_s[tid] = incl - x;
-  }
-  __syncthreads();
-  if (tid < npairs) {
-    const int q0 = tid / PP * PP;  // first pair of this pair's plane
-    int own = 0, first = 0;
-    for (int w = 0; w < kSmallPairs / 64; ++w) {
-      own += w < wave ? wsum_s[w] : 0;
-      first += w < (q0 >> 6) ? wsum_s[w] : 0;
-    }
-    pos[tid] = gpre_s[tid] + own - (gpre_s[q0] + first);
-  }
-  __syncthreads();
-  int c = 0, start = 0;  // list length and list position of row `tid`
-  if (tid < nrows) {
-    const int m = tid / nbr, i = tid - m * nbr, p0 = tid * CH;
-    start = pos[p0];
-    const int end = (i == nbr - 1) ? pos[p0 + CH - 1] + pc[p0 + CH - 1] : pos[p0 + CH];
-    c = end - start;
-    row_ptr[(int64_t)m * (nbr + 1) + i] = start;
-    if (i == nbr - 1) row_ptr[(int64_t)m * (nbr + 1) + nbr] = end;
-    len_s[tid] = c;
-    if (c > 0) {
-      atomicAdd(&tot_s[0], c);
-      atomicAdd(&tot_s[1], 1);
-    }
-  }
-  {
-    int r = r_first, ch = ch_first, m = m_first;
-#pragma unroll
-    for (int k = 0; k < kSmallSlots; ++k) {
-      const int p = wave * kSmallSlots + k;
-      if (p < npairs && ((nz[k] >> lane) & 1ull))
-        col_idx[(int64_t)m * plane_entries + pos[p] + __popcll(nz[k] & ((1ull << lane) - 1ull))] =
-            (uint32_t)(ch * 64 + lane) | (v[k] == BBM_BLOCK_FULL ? 0x80000000u : 0u);
-      if (++ch == CH) {
-        ch = 0;
-        if (++r == (m + 1) * nbr) ++m;
-      }
-    }
-  }
-  if (offset && tid < nrows) {  // run index: this thread walks the chunks of its row
-    RunScan rs;
-    for (int ch = 0; ch < CH; ++ch) rs.feed(full_s[tid * CH + ch], nz_s[tid * CH + ch], 64 * ch);
-    rs.finish();
-    offset[tid] = rs.best_start;
-    total_ones[tid] = rs.best_len;
-    nz_lo[tid] = rs.lo;
-    nz_hi[tid] = rs.hi;
-    nz_cnt[tid] = rs.cnt;
-  }
-  if (!sched) return;
-  __syncthreads();  // totals complete
-  // list entry number n of row r, from the chunk masks (the same value the fill above stores)
-  auto entry_at = [&](int r, int n) {
-    for (int ch = 0; ch < CH; ++ch) {
-      uint64_t x = nz_s[r * CH + ch];
-      const int cnt = __popcll(x);
-      if (n < cnt) {
-        for (int t = 0; t < n; ++t) x &= x - 1;
-        const int bit = ctz64(x);
-        return (int)((uint32_t)(64 * ch + bit) | (((full_s[r * CH + ch] >> bit) & 1ull) ? 0x80000000u : 0u));
-      }
-      n -= cnt;
-    }
-    return -1;
-  };
-
-  // ---- schedule (same definition as sched_kernel; everything sits in LDS here)
-  const int total = tot_s[0], nonempty = tot_s[1];
-  const int mean = nonempty > 0 ? (total + nonempty - 1) / nonempty : 0;
-  const int T = max(kSchedMinSplit, 2 * mean);
-  const int np = (tid < nrows && c > T) ? (c + T - 1) / T : 0;
-  if (tid < nrows) np_s[tid] = np;
-  if (np > 0) {
-    atomicAdd(&tot_s[2], np);
-    atomicAdd(&tot_s[3], 1);
-  }
-  const int gsz = launch_group_rows(T), ngp = (nbr + gsz - 1) / gsz;  // launch-order groups: rows each, groups per plane
-  if (tid < Mb * ngp) {
-    const int m = tid / ngp, g = tid - m * ngp;
-    int t = 0;
-    for (int j = g * gsz; j < min(nbr, (g + 1) * gsz); ++j) t = max(t, len_s[m * nbr + j]);
-    gmax_s[tid] = t;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    sched[kSchedNParts] = tot_s[2];
-    sched[kSchedSplitT] = T;
-    sched[kSchedNCutRows] = tot_s[3];
-    for (int x = 3; x < kSchedPartBase; ++x) sched[x] = 0;
-  }
-  if (tid < nrows) {
-    const int m = tid / nbr, i = tid - m * nbr;
-    if (np > 0) {
-      int q = 0, rho = 0;
-      for (int r = 0; r < tid; ++r) {
-        q += np_s[r];
-        rho += np_s[r] > 0;
-      }
-      const int chunk = (c + np - 1) / np;
-      for (int k = 0; k < np; ++k) {
-        int32_t* rec = sched + kSchedPartBase + (int64_t)kSchedPartInts * (q + k);
-        rec[0] = tid;
-        rec[1] = start + k * chunk;
-        rec[2] = min(chunk, c - k * chunk);
-        rec[3] = k;
-        rec[4] = np;
-        rec[5] = q;
-        rec[6] = rho;
-        rec[7] = entry_at(tid, k * chunk);
-      }
-    }
-    const int rank = launch_rank(len_s + m * nbr, gmax_s + m * ngp, nbr, gsz, i);
-    reinterpret_cast<int4*>(sched + sched_order_base(Mb, nbr))[(int64_t)m * nbr + rank] =
-        make_int4(i, start, c, entry_at(tid, 0));
-  }
-}
-
 }  // namespace
 
 namespace {
@@ -833,26 +411,14 @@ int launch_runs(const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc, 
   return bbm::launch_status("bbm_build_runs");
 }
 
-bool is_small(int64_t Mb, int64_t nbr, int64_t nbc) { return Mb * nbr * bbm::ceil_div(nbc, (int64_t)64) <= kSmallPairs; }
-bool is_tiny(const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc) {
-  return Mb <= kTinyMaxPlanes && nbr <= kTinyMaxRows && nbc <= 64 * kTinyMaxChunks && nbc % 16 == 0 && bbm::aligned(blk_class, 16);
-}
-
-// One-launch paths for small class matrices; returns false if neither applies.
+// One launch for class matrices of ordinary size; returns false if this one is larger.
 bool launch_one_kernel(const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc, int32_t* row_ptr, uint32_t* col_idx,
                        int32_t* sched, int32_t* offset, int32_t* total_ones, int32_t* nz_lo, int32_t* nz_hi, int32_t* nz_cnt,
                        hipStream_t s) {
-  if (is_tiny(blk_class, Mb, nbr, nbc)) {
-    tiny_index_kernel<<<1, (unsigned)Mb * 64, 0, s>>>(blk_class, (int)Mb, (int)nbr, (int)nbc, row_ptr, col_idx, sched, offset,
-                                                       total_ones, nz_lo, nz_hi, nz_cnt);
-    return true;
-  }
-  if (is_small(Mb, nbr, nbc)) {
-    small_index_kernel<<<1, kSmallWaves * 64, 0, s>>>(blk_class, (int)Mb, (int)nbr, (int)nbc, row_ptr, col_idx, sched, offset,
-                                                      total_ones, nz_lo, nz_hi, nz_cnt);
-    return true;
-  }
-  return false;
+  if (!bbm::line_index_fits(false, Mb, nbr, nbc)) return false;
+  bbm::line_index_kernel<false><<<(unsigned)bbm::ceil_div(Mb * nbr, bbm::kLineWaves), bbm::kLineWaves * 64, 0, s>>>(
+      blk_class, (int)Mb, (int)nbr, (int)nbc, row_ptr, col_idx, sched, offset, total_ones, nz_lo, nz_hi, nz_cnt);
+  return true;
 }
 
 // `counts`: per-row list lengths [Mb][nbr] already on the stream (the runs kernel's nz_cnt), or NULL.  With them the

@@ -1,0 +1,365 @@
+// The whole index of a class matrix of ordinary size in one launch: per line (block row, or block column for the
+// backward pass) the ascending list of its non-zero blocks, the schedule and, for block rows, the run index.
+#pragma once
+#include "bbm_internal.h"
+
+namespace bbm {
+namespace {
+
+__device__ __forceinline__ int ctz64(uint64_t x) { return x ? __builtin_ctzll(x) : 64; }
+
+// Longest run of FULL blocks of one block row (leftmost on ties) and the span of its non-zero blocks, fed 64 block
+// columns at a time in ascending order (bit t of `full` / `nz` = block column base + t).
+struct RunScan {
+  int best_len = 0, best_start = 0;  // longest finished run so far
+  int cur_len = 0, cur_start = 0;    // run that touches the end of the previous chunk (0 = none)
+  int lo = 0, hi = 0, cnt = 0;
+  __device__ __forceinline__ void feed(uint64_t full, uint64_t nz, int base) {
+    if (nz) {
+      if (cnt == 0) lo = base + ctz64(nz);
+      hi = base + 64 - __builtin_clzll(nz);
+      cnt += __popcll(nz);
+    }
+    if (cur_len > 0) {  // continue the run that reached the chunk boundary
+      const int ones = ctz64(~full);
+      cur_len += ones;
+      if (ones == 64) return;
+      if (cur_len > best_len) { best_len = cur_len; best_start = cur_start; }
+      cur_len = 0;
+      full &= ~((1ull << ones) - 1ull);
+    }
+    while (full) {
+      const int s = ctz64(full);
+      const int ones = ctz64(~(full >> s));  // full >> s has zeros shifted in, so ones <= 64 - s
+      if (s + ones == 64) {                  // run reaches the chunk end: decide when it ends
+        cur_start = base + s;
+        cur_len = ones;
+        return;
+      }
+      if (ones > best_len) { best_len = ones; best_start = base + s; }
+      full &= ~(((1ull << ones) - 1ull) << s);
+    }
+  }
+  __device__ __forceinline__ void finish() {
+    if (cur_len > best_len) { best_len = cur_len; best_start = cur_start; }
+  }
+};
+
+// Exclusive prefix sum over the 64 lanes with data-parallel-primitive moves (register to register; a shuffle goes
+// through LDS): shifts by 1, 2, 4, 8 inside each row of 16 lanes (a lane without a source adds 0), then lane 15 of a
+// row added to the next row (rows 1 and 3), then lane 31 to rows 2 and 3.
+__device__ __forceinline__ int wave_excl_scan(int x) {
+  int incl = x;
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);  // row_shr:1
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);  // row_shr:2
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);  // row_shr:4
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);  // row_shr:8
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
+  return incl - x;
+}
+
+// Sum over the 64 lanes, returned in every lane.
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_excl_scan(x) + x, 63); }
+
+// Rows per launch-order group: neighbouring rows are kept together only while rows are short (split threshold at its
+// floor, i.e. mean list length <= 16); with long rows the plain longest-first order balances the tail better.
+__device__ __forceinline__ int launch_group_rows(int T) { return T == kSchedMinSplit ? kSchedGroupRows : 1; }
+
+// Largest of 64 non-negative values, returned in every lane.
+__device__ __forceinline__ int wave_max(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
+// RunScan with a lane per block column: the lane at which a run starts measures it, so a chunk costs a dozen
+// instructions however many runs it has.
+struct WaveRunScan {
+  int best_len = 0, best_start = 0;  // per lane: longest run that started and ended in a chunk at this lane
+  int cur_len = 0, cur_start = 0;    // uniform: run that touches the end of the previous chunk (0 = none)
+  int car_len = 0, car_start = 0;    // uniform: longest finished run that crossed a chunk boundary
+  int lo = 0, hi = 0, cnt = 0;       // uniform
+  __device__ __forceinline__ void feed(uint64_t full, uint64_t nz, int base, int lane) {
+    if (nz) {
+      if (cnt == 0) lo = base + ctz64(nz);
+      hi = base + 64 - __builtin_clzll(nz);
+      cnt += __popcll(nz);
+    }
+    uint64_t inner = full;
+    if (cur_len > 0) {  // continue the run that reached the chunk boundary
+      const int ones = ctz64(~full);
+      cur_len += ones;
+      if (ones == 64) return;
+      if (cur_len > car_len) { car_len = cur_len; car_start = cur_start; }
+      cur_len = 0;
+      inner &= ~((1ull << ones) - 1ull);
+    }
+    const int tail = full == ~0ull ? 64 : __builtin_clzll(~full);  // ones at the chunk's end
+    if (tail > 0) {                                                // decided when that run ends
+      cur_len = tail;
+      cur_start = base + 64 - tail;
+      inner = tail == 64 ? 0ull : inner & ((1ull << (64 - tail)) - 1ull);
+    }
+    const bool starts = ((inner & ~(inner << 1)) >> lane) & 1ull;
+    const int ones = ctz64(~(inner >> lane));
+    if (starts && ones > best_len) { best_len = ones; best_start = base + lane; }
+  }
+  // longest run, leftmost on ties, uniform
+  __device__ __forceinline__ void finish(int& len, int& start) {
+    if (cur_len > car_len) { car_len = cur_len; car_start = cur_start; }
+    len = max(wave_max(best_len), car_len);
+    const int none = 0x7fffffff;
+    int s = none - wave_max(best_len == len ? none - best_start : 0);
+    if (car_len == len) s = min(s, car_start);
+    start = len > 0 ? s : 0;
+  }
+};
+
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
+// Bytes that are not zero: 4 bytes -> 0x01 in each such byte.
+__device__ __forceinline__ uint32_t nz_bytes(uint32_t w) { return ((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) >> 7) & 0x01010101u; }
+
+// What bounds an index build is latency: kernel starts, memory round trips and serial chains over a few kilobytes.  So
+// nothing is handed from one work-group to another: every work-group counts the non-zero blocks of ALL lines itself
+// (16 class bytes per load) into LDS, behind one barrier, and each of its waves then produces one line from those
+// counts: the line's place in its plane, the split threshold, the parts and cut lines before its own and its rank are
+// sums over the counts, spread over the lanes.  One launch; the redundant reads are class bytes x work-groups out of L2.
+// Microseconds a call in a graph, before -> now (before: one work-group with serial loops for small matrices, two
+// launches for larger ones, and two to four launches for the columns), block rows / block columns of 0.3 density:
+// 2 x 4 7.8 -> 3.9 / 5.7 -> 4.5; 2 x 260 10.6 -> 5.5 / 19.0 -> 5.1; 4 planes of 32 x 64 9.5 -> 4.8 / 11.8 -> 5.2;
+// 128 x 256 8.9 -> 6.3 / 16.0 -> 6.5; 256 x 512 12.4 -> 11.1 / 39 -> 8.7.  512 x 512 rows would take 16.0 against 14.5
+// in two launches, columns 11.0 against 39: hence the two limits.
+constexpr int kLineWaves = 8;
+constexpr int64_t kLineMaxLines = 4096, kLineMaxBytesRows = 128 << 10, kLineMaxBytesCols = 256 << 10;  // beyond: the multi-launch paths
+
+inline bool line_index_fits(bool cols, int64_t Mb, int64_t nbr, int64_t nbc) {
+  return Mb * (cols ? nbc : nbr) <= kLineMaxLines && Mb * nbr * nbc <= (cols ? kLineMaxBytesCols : kLineMaxBytesRows);
+}
+
+// COLS = false: lines are block rows (`ptr` = row_ptr, `list` = col_idx); true: block columns (col_ptr, row_idx).
+// `sched` and the five arrays of the run index (block rows only) may be NULL.
+template <bool COLS>
+__global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8_t* __restrict__ cls, int Mb, int nbr, int nbc,
+                                                                     int32_t* __restrict__ ptr, uint32_t* __restrict__ list,
+                                                                     int32_t* __restrict__ sched, int32_t* __restrict__ offset,
+                                                                     int32_t* __restrict__ total_ones, int32_t* __restrict__ nz_lo,
+                                                                     int32_t* __restrict__ nz_hi, int32_t* __restrict__ nz_cnt) {
+  __shared__ int len_s[kLineMaxLines];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int L = COLS ? nbc : nbr, depth = COLS ? nbr : nbc;  // lines per plane, blocks per line
+  const int nlines = Mb * L;
+  const int line = (int)blockIdx.x * kLineWaves + wave;      // this wave's line (waves past the last only count)
+  const int own = min(line, nlines - 1);
+  const int m = own / L, i = own - m * L;
+  const uint8_t* const mine = cls + (int64_t)m * nbr * nbc + (COLS ? i : (int64_t)i * nbc);
+  const int step = COLS ? nbc : 1;                           // bytes from one block of the line to the next
+  auto own_block = [&](int base) { return base + lane < depth ? mine[(int64_t)(base + lane) * step] : (uint8_t)0; };
+  uint8_t next = own_block(0);  // asked for before the counting
+
+  // ---- non-zero blocks of every line
+  const int C16 = (nbc + 15) / 16;  // 16-byte chunks of a class row; the last one is read as the row's last 16 bytes
+  if (!COLS && nbc < 16) {
+    for (int r = tid; r < nlines; r += kLineWaves * 64) {
+      int cnt = 0;
+#pragma unroll 1
+      for (int t = 0; t < nbc; ++t) cnt += cls[(int64_t)r * nbc + t] != 0 ? 1 : 0;
+      len_s[r] = cnt;
+    }
+  } else if (!COLS) {
+    int lpr = 1;  // lanes per row
+    while (lpr < C16 && lpr < 64) lpr <<= 1;
+    const int rpw = 64 / lpr, sub = lane / lpr, c_first = (lane & (lpr - 1)) * 16;
+    constexpr int kFly = 4;  // rows a lane has in flight
+    const int hop = kLineWaves * rpw;
+    for (int r0 = wave * rpw + sub; r0 - sub < nlines; r0 += kFly * hop) {
+      int cnt[kFly];
+#pragma unroll
+      for (int f = 0; f < kFly; ++f) cnt[f] = 0;
+      for (int c = c_first; c < nbc; c += lpr * 16) {
+        const int at = min(c, nbc - 16);
+        // bit s of byte t counts byte 4s + t of the 16; those below c belong to the chunk before
+        uint32_t keep = 0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int skip = min(max(c - at - 4 * s, 0), 4);
+          keep |= (skip < 4 ? 0x01010101u << (8 * skip) : 0u) << s;
+        }
+        u32x4_any x[kFly];
+#pragma unroll
+        for (int f = 0; f < kFly; ++f) x[f] = *reinterpret_cast<const u32x4_any*>(cls + (int64_t)min(r0 + f * hop, nlines - 1) * nbc + at);
+#pragma unroll
+        for (int f = 0; f < kFly; ++f)
+          cnt[f] += __popc((nz_bytes(x[f].x) | (nz_bytes(x[f].y) << 1) | (nz_bytes(x[f].z) << 2) | (nz_bytes(x[f].w) << 3)) & keep);
+      }
+      for (int d = 1; d < lpr; d <<= 1) {
+#pragma unroll
+        for (int f = 0; f < kFly; ++f) cnt[f] += __shfl_xor(cnt[f], d);
+      }
+      if ((lane & (lpr - 1)) == 0) {
+#pragma unroll
+        for (int f = 0; f < kFly; ++f)
+          if (r0 + f * hop < nlines) len_s[r0 + f * hop] = cnt[f];
+      }
+    }
+  } else {
+    for (int b = tid; b < nlines; b += kLineWaves * 64) len_s[b] = 0;
+    __syncthreads();
+    // a thread adds up 16 columns over every RG-th row of a plane, in byte counters
+    const int units = Mb * C16;
+    const int RG = max(1, min(nbr, kLineWaves * 64 / units));
+    for (int it = tid; it < units * RG; it += kLineWaves * 64) {
+      const int u = it % units, rg = it / units;
+      const int pm = u / C16, c = (u - pm * C16) * 16, at = nbc >= 16 ? min(c, nbc - 16) : 0;
+      const uint8_t* const plane = cls + (int64_t)pm * nbr * nbc + at;
+      for (int rb = rg; rb < nbr; rb += 255 * RG) {  // a byte counter holds 255 rows
+        uint32_t sum[4] = {0, 0, 0, 0};
+        const int re = (int)min<int64_t>(nbr, rb + (int64_t)255 * RG);
+        if (nbc >= 16) {
+#pragma unroll 4
+          for (int r = rb; r < re; r += RG) {
+            const u32x4_any x = *reinterpret_cast<const u32x4_any*>(plane + (int64_t)r * nbc);
+            sum[0] += nz_bytes(x.x);
+            sum[1] += nz_bytes(x.y);
+            sum[2] += nz_bytes(x.z);
+            sum[3] += nz_bytes(x.w);
+          }
+        } else {
+          for (int r = rb; r < re; r += RG)
+#pragma unroll
+            for (int t = 0; t < 16; ++t)
+              if (t < nbc && plane[(int64_t)r * nbc + t] != 0) sum[t >> 2] += 1u << (8 * (t & 3));
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+          const int n = (int)((sum[t >> 2] >> (8 * (t & 3))) & 0xffu);
+          if (n != 0 && at + t >= c) atomicAdd(&len_s[pm * nbc + at + t], n);  // columns below c belong to the chunk before
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (line >= nlines) return;
+
+  // ---- this wave's line: its place in the plane's list, and the split threshold (a mean over all lines)
+  const int* const cp = len_s + m * L;
+  const int n = cp[i];
+  int above = 0, total = 0, nonempty = 0;
+  for (int b = lane; b < nlines; b += 64) {
+    const int x = len_s[b];
+    total += x;
+    nonempty += x > 0 ? 1 : 0;
+    above += b >= m * L && b < line ? x : 0;
+  }
+  const int start = wave_sum(above);
+  total = wave_sum(total);
+  nonempty = wave_sum(nonempty);
+  const int mean = nonempty > 0 ? (total + nonempty - 1) / nonempty : 0;
+  const int T = max(COLS ? kColSchedMinSplit : kSchedMinSplit, 2 * mean);
+  if (lane == 0) {
+    ptr[(int64_t)m * (L + 1) + i] = start;
+    if (i == L - 1) ptr[(int64_t)m * (L + 1) + L] = start + n;
+  }
+
+  // parts and cut lines: before this line (lines in (plane, line) order), and in all
+  const int np = n > T ? (n + T - 1) / T : 0;
+  const int chunk = np > 0 ? (n + np - 1) / np : 1;
+  int32_t* parts = nullptr;
+  if (sched && (np > 0 || line == 0)) {
+    int q = 0, rho = 0, all_parts = 0, all_cut = 0;
+    for (int b = lane; b < nlines; b += 64) {
+      const int x = len_s[b];
+      const int np_b = x > T ? (x + T - 1) / T : 0;
+      all_parts += np_b;
+      all_cut += np_b > 0 ? 1 : 0;
+      q += b < line ? np_b : 0;
+      rho += b < line && np_b > 0 ? 1 : 0;
+    }
+    q = wave_sum(q);
+    rho = wave_sum(rho);
+    if (line == 0) {
+      all_parts = wave_sum(all_parts);
+      all_cut = wave_sum(all_cut);
+      if (lane < kSchedPartBase)
+        sched[lane] = lane == kSchedNParts ? all_parts : lane == kSchedSplitT ? T : lane == kSchedNCutRows ? all_cut : 0;
+    }
+    parts = sched + kSchedPartBase + (int64_t)kSchedPartInts * q;
+    for (int k = lane; k < np; k += 64) {
+      int32_t* rec = parts + kSchedPartInts * k;
+      rec[0] = line;
+      rec[1] = start + k * chunk;
+      rec[2] = min(chunk, n - k * chunk);
+      rec[3] = k;
+      rec[4] = np;
+      rec[5] = q;
+      rec[6] = rho;
+    }
+  }
+
+  // the list; the lane that writes the entry a part starts with also leaves it in the part's record
+  uint32_t* const out = list + (int64_t)m * nbr * nbc + start;
+  int written = 0, first = -1;
+  WaveRunScan rs;
+#pragma unroll 1  // short code: at this length of a launch, fetching instructions is a good part of it
+  for (int base = 0; base < depth; base += 64) {
+    const uint8_t c = next;
+    next = own_block(base + 64);
+    const uint64_t nz = __ballot(c != BBM_BLOCK_EMPTY);
+    const uint64_t full = __ballot(c == BBM_BLOCK_FULL);
+    if (!COLS && offset) rs.feed(full, nz, base, lane);
+    if (written == 0 && nz != 0) {  // the line's first entry (this happens once: written > 0 from here on)
+      const int bit = ctz64(nz);
+      first = (int)((uint32_t)(base + bit) | (((full >> bit) & 1ull) ? 0x80000000u : 0u));
+    }
+    if (c != BBM_BLOCK_EMPTY) {
+      const int pos = written + __popcll(nz & ((1ull << lane) - 1ull));
+      const uint32_t entry = (uint32_t)(base + lane) | (c == BBM_BLOCK_FULL ? 0x80000000u : 0u);
+      out[pos] = entry;
+      if (np > 0 && sched && pos % chunk == 0 && pos / chunk < np) parts[kSchedPartInts * (pos / chunk) + 7] = (int32_t)entry;
+    }
+    written += __popcll(nz);
+  }
+  if (!COLS && offset) {
+    int run_len, run_start;
+    rs.finish(run_len, run_start);
+    if (lane == 0) {
+      offset[line] = run_start;
+      total_ones[line] = run_len;
+      nz_lo[line] = rs.lo;
+      nz_hi[line] = rs.hi;
+      nz_cnt[line] = rs.cnt;
+    }
+  }
+  if (!sched) return;
+
+  // launch-order record: groups of gsz lines by their longest list, longest first (ties: the higher group first); inside
+  // a group the longest line first (ties: the higher line first)
+  const int gsz = COLS ? 1 : launch_group_rows(T);
+  const int ng = (L + gsz - 1) / gsz, g = i / gsz;
+  auto group_max = [&](int gg) {
+    int t = 0;
+    for (int j = gg * gsz; j < min(L, (gg + 1) * gsz); ++j) t = max(t, cp[j]);
+    return t;
+  };
+  const int longest = group_max(g);
+  int before = 0;
+  for (int gg = lane; gg < ng; gg += 64) {
+    const int t = group_max(gg);
+    before += (t > longest || (t == longest && gg > g)) ? 1 : 0;
+  }
+  int rank = wave_sum(before) * gsz;
+  const int last = ng - 1, last_lines = L - last * gsz;  // the last group may be short
+  if (last != g && group_max(last) >= longest) rank -= gsz - last_lines;
+  for (int j = g * gsz; j < min(L, (g + 1) * gsz); ++j) rank += (cp[j] > n || (cp[j] == n && j > i)) ? 1 : 0;
+  if (lane == 0)
+    reinterpret_cast<int4*>(sched + kSchedPartBase + (int64_t)kSchedPartInts * nlines)[(int64_t)m * L + rank] = make_int4(i, start, n, first);
+}
+
+}  // namespace
+}  // namespace bbm

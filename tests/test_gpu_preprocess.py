@@ -150,3 +150,24 @@ def test_block_mask_at_any_address(Nq, Nk, offset):
     idx = _bbm().bbm_build_block_mask_rect(view, 128, 64)
     torch.cuda.synchronize()
     assert_index_equal(index_to_numpy(idx), mask, 128, 64)
+
+
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("Mb,Nq,Nk,Br,Bc", [
+    (1, 10, 10, 64, 64), (2, 40, 239, 8, 16), (3, 520, 250, 64, 16), (1, 200, 8300, 64, 16),     # < 16, 15, 16, 519 block columns
+    (2, 4600, 130, 1, 64), (1, 4099, 300, 1, 256), (17, 260, 64, 64, 64),                        # many lines, more planes than waves
+    (1, 8300, 8210, 16, 16)])                                                                    # past the one-launch size
+def test_index_and_columns_at_their_limits(Mb, Nq, Nk, Br, Bc, fused):
+    """Row and column index around the one-launch kernel's limits: few and many blocks per line, line counts around a
+    work-group's eight waves and its 4096 lines, class matrices past its size."""
+    rng = np.random.default_rng(Nq * 7 + Nk)
+    nbr, nbc = -(-Nq // Br), -(-Nk // Bc)
+    kind = rng.random((Mb, nbr, nbc))
+    kind[:, : max(1, nbr // 40)] *= 0.3                       # a few long lines (cut into parts)
+    block = np.repeat(np.repeat(kind, Br, axis=1), Bc, axis=2)[:, :Nq, :Nk]
+    mask = (block < 0.2).astype(np.uint8)
+    mask[:, ::3, ::5] &= (block[:, ::3, ::5] < 0.1)
+    bbm = _bbm()
+    idx = bbm.build_index(torch.from_numpy(mask).cuda(), Br, Bc, fused=fused, columns=True)
+    torch.cuda.synchronize()
+    assert_index_equal(index_to_numpy(idx), mask, Br, Bc)
