@@ -5,9 +5,9 @@
 // The ordering is the published algorithm with every choice fixed (the library header states them): neighbours of node
 // i are the non-zero entries of mask row i, a component starts at its unvisited node of minimum degree (ties: smallest
 // index), each breadth-first level is ordered by (position of the earliest parent, degree, index), the result is
-// reversed.  Two kernels: a parallel one packs the mask rows to bits and counts degrees; a single work-group then
-// walks the levels -- every node's row is scanned exactly once, when the node is in the frontier -- with no host
-// round trip and no grid-wide barrier: its loops end when every node has been placed.
+// reversed.  One kernel packs the mask rows to bits and counts degrees; the levels are then walked by pairs of kernels
+// (expand, rank) with no host round trip and no grid-wide barrier, every node's row being scanned once, when the node is
+// in the frontier; a last kernel of one work-group walks whatever the fixed number of pairs left.
 #include "bbm_internal.h"
 
 #include <climits>
@@ -17,6 +17,7 @@ namespace {
 constexpr int kMaxNodes = 65536;            // visited set and one mask row must fit in LDS
 constexpr int kOrderThreads = 1024;
 constexpr int kPackThreads = 256;
+constexpr int kRounds = 48;                 // parallel rounds (one breadth-first level, or one component start, each)
 constexpr int kRankChunk = 2048;            // keys of a level staged in LDS at a time
 constexpr int kRankPerThread = 4;           // keys a thread ranks per sweep
 constexpr int kBatch = 8;                   // row words a thread of the level walk has in flight
@@ -27,11 +28,21 @@ __device__ __forceinline__ uint32_t nz_nibble(uint32_t x) {
   return (((y >> 7) * 0x00204081u) >> 21) & 0xfu;
 }
 
-enum { kStDone = 0, kStLvlLo = 1, kStLvlHi = 2, kStCand = 3, kStInts = 8 };  // state of the level walk (int32)
+// State of the level walk in the workspace: two records of kStInts int32 that the rounds use in turn.  A round reads its own
+// record, counts its candidates there and writes the other one whole, so no kernel resets what another may still be
+// reading.  A record holds whether the walk has ended, the frontier's places [lo, hi) in the ordering (everything placed
+// lies below hi), and the number of candidates.
+enum { kStDone = 0, kStLvlLo = 1, kStLvlHi = 2, kStCand = 3, kStInts = 4 };
+
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));  // 16 bytes at any address: one instruction
 
 // One work-group per mask row: bits[row][w] (row-major, bits past N zero), degree[row], parent_pos[row] = "none".
+// Bound by the mask's bytes, which are read once (streaming loads): a lane reads 16 of them, neighbouring lanes
+// neighbouring pieces, four loads in flight, and writes the 16 bits as one piece of a word.  The piece that reaches past
+// column N is read as the row's last 16 bytes and shifted down, so rows of any length and alignment run the same
+// instructions.
 __global__ __launch_bounds__(kPackThreads) void rcm_pack_kernel(const uint8_t* __restrict__ mask, int N, int64_t row_stride, int W,
-                                                                uint64_t* __restrict__ bits, int32_t* __restrict__ degree,
+                                                                uint16_t* __restrict__ bits, int32_t* __restrict__ degree,
                                                                 int32_t* __restrict__ parent_pos, uint64_t* __restrict__ visited,
                                                                 uint64_t* __restrict__ claimed, int32_t* __restrict__ state) {
   __shared__ int red_s[kPackThreads / 64];
@@ -44,24 +55,35 @@ __global__ __launch_bounds__(kPackThreads) void rcm_pack_kernel(const uint8_t* _
     if (tid < kStInts) state[tid] = 0;
   }
   const uint8_t* __restrict__ src = mask + (int64_t)row * row_stride;
-  const bool vec = ((reinterpret_cast<uintptr_t>(mask) | (uintptr_t)row_stride) & 15) == 0;
+  uint16_t* __restrict__ dst = bits + (int64_t)row * W * 4;
+  const int pieces = 4 * W;
   int count = 0;
-  for (int w = tid; w < W; w += kPackThreads) {
-    uint64_t word = 0;
-    const int c0 = 64 * w;
-    if (vec && c0 + 64 <= N) {
+  if (N >= 16) {
+    constexpr int kUnroll = 4;
+    for (int p0 = tid; p0 < pieces; p0 += kUnroll * kPackThreads) {
+      u32x4_any x[kUnroll];
+      int shift[kUnroll];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint4 x = *reinterpret_cast<const uint4*>(src + c0 + 16 * t);
-        const uint64_t b16 = nz_nibble(x.x) | (nz_nibble(x.y) << 4) | (nz_nibble(x.z) << 8) | (nz_nibble(x.w) << 12);
-        word |= b16 << (16 * t);
+      for (int u = 0; u < kUnroll; ++u) {
+        const int col = 16 * (p0 + u * kPackThreads), at = min(col, N - 16);
+        shift[u] = min(col - at, 31);
+        x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(src + at));
       }
-    } else {
-      for (int t = 0; t < 64; ++t)
-        if (c0 + t < N && src[c0 + t] != 0) word |= 1ull << t;
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const uint32_t b = (nz_nibble(x[u].x) | (nz_nibble(x[u].y) << 4) | (nz_nibble(x[u].z) << 8) | (nz_nibble(x[u].w) << 12)) >> shift[u];
+        if (p0 + u * kPackThreads < pieces) {
+          dst[p0 + u * kPackThreads] = (uint16_t)b;
+          count += __popc(b);
+        }
+      }
     }
-    bits[(int64_t)row * W + w] = word;
-    count += __popcll(word);
+  } else if (tid < pieces) {  // fewer than 16 columns: one word of four pieces
+    uint32_t b = 0;
+    for (int t = 0; t < 16; ++t)
+      if (16 * tid + t < N && src[16 * tid + t] != 0) b |= 1u << t;
+    dst[tid] = (uint16_t)b;
+    count = __popc(b);
   }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) count += __shfl_xor(count, d);
@@ -75,10 +97,6 @@ __global__ __launch_bounds__(kPackThreads) void rcm_pack_kernel(const uint8_t* _
   }
 }
 
-// State of the level walk in the workspace (int32): the walk is cut into kernels -- a fixed number of rounds of a
-// parallel expansion (many work-groups) and a one-work-group advance, then a one-work-group finisher that does both
-// itself for whatever is left (graphs with more levels or components than rounds).  No kernel waits for another.
-constexpr int kRounds = 48;                 // parallel rounds (one breadth-first level, or one component start, each)
 constexpr int kExpandWGs = 1024, kExpandThreads = 256;
 
 __device__ __forceinline__ uint64_t level_key(int parent, int degree, int v) {
@@ -115,80 +133,154 @@ __device__ __forceinline__ void rank_level(const uint64_t* keys, int L, uint64_t
   }
 }
 
-// The unvisited node of minimum (degree, index), or -1: every thread of the work-group gets the result.
-template <typename Visited>
+// The unvisited node of minimum (degree, index), or -1: every one of the work-group's THREADS threads gets the result.
+// A thread looks at four neighbouring nodes at a time, with kFly such groups in flight: the scan is a chain of loads.
+template <int THREADS, typename Visited>
 __device__ __forceinline__ int min_degree_unvisited(const int32_t* __restrict__ degree, int N, Visited visited_word,
                                                     unsigned long long* min_s, int tid) {
+  constexpr int kFly = 4;
   const int lane = tid & 63, wave = tid >> 6;
   unsigned long long best = ~0ull;
-  for (int i = tid; i < N; i += kOrderThreads)
-    if (!((visited_word(i >> 6) >> (i & 63)) & 1ull)) best = min(best, ((unsigned long long)(uint32_t)degree[i] << 32) | (uint32_t)i);
+  const int last4 = (N - 1) & ~3;  // degree is a 256-byte aligned array padded to whole 256 bytes: groups of four are readable
+  for (int i0 = 4 * tid; i0 < N; i0 += 4 * kFly * THREADS) {
+    int4 dg[kFly];
+    uint64_t vw[kFly];
+#pragma unroll
+    for (int u = 0; u < kFly; ++u) {
+      const int i = min(i0 + 4 * u * THREADS, last4);  // past the end: the last group once more
+      dg[u] = *reinterpret_cast<const int4*>(degree + i);
+      vw[u] = visited_word(i >> 6) >> (i & 63);
+    }
+#pragma unroll
+    for (int u = 0; u < kFly; ++u) {
+      const int i = min(i0 + 4 * u * THREADS, last4);
+      const int d4[4] = {dg[u].x, dg[u].y, dg[u].z, dg[u].w};
+#pragma unroll
+      for (int t = 0; t < 4; ++t)  // nodes past N count as visited
+        if (!((vw[u] >> t) & 1ull)) best = min(best, ((unsigned long long)(uint32_t)d4[t] << 32) | (uint32_t)(i + t));
+    }
+  }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) best = min(best, (unsigned long long)__shfl_xor(best, d));
   __syncthreads();  // min_s may still be read from an earlier call
   if (lane == 0) min_s[wave] = best;
   __syncthreads();
   best = min_s[0];
-  for (int w = 1; w < kOrderThreads / 64; ++w) best = min(best, min_s[w]);
+  for (int w = 1; w < THREADS / 64; ++w) best = min(best, min_s[w]);
   return best == ~0ull ? -1 : (int)(best & 0xffffffffull);
 }
 
-// Parallel expansion of the current level: every frontier node's bit row is scanned once; an unvisited neighbour is
-// claimed by its earliest parent (atomic minimum of the parent's position) and entered in the candidate list by
-// whoever sets its bit in the `claimed` set first.  Returns at once when there is no frontier.
+// Parallel expansion of the current level: every frontier node's bit row is scanned once, an unvisited neighbour gets its
+// earliest parent (atomic minimum of the parent's position) and enters the candidate list once.  Returns at once when there
+// is no frontier.
+// What bounds it is the atomics, so a wave takes 64 words of a run of consecutive frontier nodes and each lane remembers
+// the bits of its word that it has seen: only the first node of the run that has a bit sends an atomic (later ones have
+// later positions), and the `claimed` set is asked once per run and word instead of once per edge.  Runs of 8 nodes keep
+// enough waves for small levels; longer runs from 1024 nodes on save atomics.
 __global__ __launch_bounds__(kExpandThreads) void rcm_expand_kernel(const uint64_t* __restrict__ bits, const int32_t* __restrict__ order,
                                                                     const uint64_t* __restrict__ visited, uint64_t* claimed,
                                                                     int32_t* parent_pos, int32_t* cand, int32_t* state, int W) {
   const int lvl_lo = state[kStLvlLo], lvl_hi = state[kStLvlHi];
   if (state[kStDone] || lvl_lo >= lvl_hi) return;
-  const int64_t total = (int64_t)(lvl_hi - lvl_lo) * W;
-  const int64_t stride = (int64_t)gridDim.x * kExpandThreads;
-  for (int64_t x0 = (int64_t)blockIdx.x * kExpandThreads + threadIdx.x; x0 < total; x0 += kBatch * stride) {
-    uint64_t word[kBatch];
-    int f[kBatch], w[kBatch];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int F = lvl_hi - lvl_lo;
+  const int run = F <= 1024 ? kBatch : F <= 2048 ? 2 * kBatch : 4 * kBatch;
+  const int strips = (W + 63) / 64, tasks = strips * ((F + run - 1) / run);
+  for (int task = blockIdx.x * (kExpandThreads / 64) + wave; task < tasks; task += gridDim.x * (kExpandThreads / 64)) {
+    const int w = (task % strips) * 64 + lane;
+    const int f_first = lvl_lo + (task / strips) * run, f_end = min(f_first + run, lvl_hi);
+    const uint64_t before = w < W ? visited[w] : ~0ull;
+    uint64_t seen = before;
+    for (int f0 = f_first; f0 < f_end; f0 += kBatch) {
+      uint64_t word[kBatch];
 #pragma unroll
-    for (int t = 0; t < kBatch; ++t) {
-      const int64_t x = x0 + t * stride;
-      word[t] = 0;
-      f[t] = w[t] = 0;
-      if (x < total) {
-        f[t] = lvl_lo + (int)(x / W);
-        w[t] = (int)(x % W);
-        word[t] = bits[(int64_t)order[f[t]] * W + w[t]] & ~visited[w[t]];
+      for (int t = 0; t < kBatch; ++t)  // past the run's end: its last node once more, which has nothing new
+        word[t] = w < W ? bits[(int64_t)order[min(f0 + t, f_end - 1)] * W + w] : 0;
+#pragma unroll
+      for (int t = 0; t < kBatch; ++t) {
+        uint64_t b = word[t] & ~seen;
+        seen |= b;
+        while (b) {
+          atomicMin(&parent_pos[64 * w + __builtin_ctzll(b)], f0 + t);  // result unused: the atomics pipeline
+          b &= b - 1;
+        }
       }
     }
+    uint64_t fresh = seen & ~before;
+    if (fresh) fresh &= ~atomicOr(reinterpret_cast<unsigned long long*>(&claimed[w]), (unsigned long long)fresh);
+    // one entry of the candidate list per fresh bit: a scan over the wave, one addition to the counter per wave
+    const int n = __popcll(fresh);
+    int upto = n;
 #pragma unroll
-    for (int t = 0; t < kBatch; ++t) {
-      uint64_t b = word[t];
-      while (b) {
-        const int v = 64 * w[t] + __builtin_ctzll(b);
-        b &= b - 1;
-        atomicMin(&parent_pos[v], f[t]);
-        const unsigned long long bit = 1ull << (v & 63);
-        if (!(atomicOr(reinterpret_cast<unsigned long long*>(&claimed[v >> 6]), bit) & bit)) cand[atomicAdd(&state[kStCand], 1)] = v;
-      }
+    for (int d = 1; d < 64; d <<= 1) {
+      const int other = __shfl_up(upto, d);
+      if (lane >= d) upto += other;
+    }
+    const int total = __shfl(upto, 63);
+    if (total == 0) continue;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&state[kStCand], total);
+    base = __shfl(base, 0) + upto - n;
+    while (fresh) {
+      cand[base++] = 64 * w + __builtin_ctzll(fresh);
+      fresh &= fresh - 1;
     }
   }
 }
 
-// Ranking of the candidates the expansion found (many work-groups): a thread ranks one candidate by counting the
-// smaller keys -- every work-group stages all keys of the level through LDS, building them from the candidate list
-// as it goes --, places it behind the nodes ordered so far and marks it visited.  Reads the state, changes none of it
-// (the advance that follows does).  One work-group ranking a level of 3500 nodes alone takes 0.3 ms.
-constexpr int kRankWGs = 256, kRankThreads = 256, kRankStage = 4;  // kRankStage keys of a thread's staging share in flight
+// Ranking of the candidates the expansion found, and the next round's record (many work-groups).  A candidate's rank is the
+// number of smaller keys: every work-group stages all keys of the level through LDS, building them from the candidate
+// list as it goes, and 16, 4 or 1 neighbouring lanes share the counting for one candidate, so that levels of up to 4096
+// nodes still use all work-groups (one lane per candidate: 54 us for a level of 3500 nodes).  The candidate is placed
+// behind the nodes ordered so far and marked visited.  Work-group 0 also writes the record of the next round, the level
+// these candidates make; when the expansion found none (a component is finished, or nothing has started yet) it starts
+// the next component at its node of minimum degree.
+// The whole ordering of the 32768-node power-law graph: 1.54 ms with three kernels a round, an atomic per edge and one lane
+// per candidate; 0.61 ms now, of which 0.23 ms are the packing (5.2 TB/s) and about 0.2 ms the rounds left over at its end.
+constexpr int kRankWGs = 256, kRankThreads = 256, kRankStage = 8;  // kRankStage keys of a thread's staging share in flight
 __global__ __launch_bounds__(kRankThreads) void rcm_rank_kernel(const int32_t* __restrict__ degree, const int32_t* __restrict__ parent_pos,
                                                                 const int32_t* __restrict__ cand, int32_t* __restrict__ order,
-                                                                uint64_t* visited, const int32_t* __restrict__ state) {
-  __shared__ __attribute__((aligned(16))) uint64_t chunk_s[kRankChunk + 8];
+                                                                int32_t* __restrict__ perm, uint64_t* visited,
+                                                                const int32_t* __restrict__ state, int32_t* __restrict__ next, int N) {
+  __shared__ __attribute__((aligned(16))) uint64_t chunk_s[kRankChunk];
+  __shared__ unsigned long long min_s[kRankThreads / 64];
   const int tid = threadIdx.x;
-  if (state[kStDone]) return;
+  auto write_next = [&](int done, int lo, int hi) {
+    next[kStDone] = done;
+    next[kStLvlLo] = lo;
+    next[kStLvlHi] = hi;
+    next[kStCand] = 0;
+  };
+  if (state[kStDone]) {
+    if (blockIdx.x == 0 && tid == 0) write_next(1, 0, 0);
+    return;
+  }
   const int n_done = state[kStLvlHi], L = state[kStCand];
+  if (L == 0) {
+    if (blockIdx.x != 0) return;
+    const int start = min_degree_unvisited<kRankThreads>(degree, N, [&](int w) { return visited[w]; }, min_s, tid);
+    if (tid == 0) {
+      if (start < 0) {
+        write_next(1, 0, 0);
+      } else {
+        order[n_done] = start;
+        perm[N - 1 - n_done] = start;
+        visited[start >> 6] |= 1ull << (start & 63);
+        write_next(0, n_done, n_done + 1);
+      }
+    }
+    return;
+  }
+  if (blockIdx.x == 0 && tid == 0) write_next(0, n_done, n_done + L);
   auto key_of = [&](int c) {
     const int v = cand[c];
     return level_key(parent_pos[v], degree[v], v);
   };
-  for (int c0 = (int)blockIdx.x * kRankThreads; c0 < L; c0 += (int)gridDim.x * kRankThreads) {  // uniform in the work-group
-    const int c = c0 + tid;
+  const int ways_log2 = L <= 16 * kRankWGs ? 4 : L <= 64 * kRankWGs ? 2 : 0;  // lanes that share one candidate
+  const int ways = 1 << ways_log2, per_wg = kRankThreads >> ways_log2, way = tid & (ways - 1);
+  for (int c0 = (int)blockIdx.x * per_wg; c0 < L; c0 += (int)gridDim.x * per_wg) {  // uniform in the work-group
+    const int c = c0 + (tid >> ways_log2);
     const uint64_t mine = c < L ? key_of(c) : 0;
     int r = 0;
     for (int j0 = 0; j0 < L; j0 += kRankChunk) {
@@ -197,7 +289,7 @@ __global__ __launch_bounds__(kRankThreads) void rcm_rank_kernel(const int32_t* _
       for (int j = tid; j < n; j += kRankStage * kRankThreads) {  // a key is three dependent loads: keep several going
         int v[kRankStage], pp[kRankStage], dg[kRankStage];
 #pragma unroll
-        for (int t = 0; t < kRankStage; ++t) v[t] = j + t * kRankThreads < n ? cand[j0 + j + t * kRankThreads] : 0;
+        for (int t = 0; t < kRankStage; ++t) v[t] = cand[j0 + min(j + t * kRankThreads, n - 1)];
 #pragma unroll
         for (int t = 0; t < kRankStage; ++t) {
           pp[t] = parent_pos[v[t]];
@@ -207,56 +299,29 @@ __global__ __launch_bounds__(kRankThreads) void rcm_rank_kernel(const int32_t* _
         for (int t = 0; t < kRankStage; ++t)
           if (j + t * kRankThreads < n) chunk_s[j + t * kRankThreads] = level_key(pp[t], dg[t], v[t]);
       }
-      if (tid < 8) chunk_s[n + tid] = ~0ull;  // pad to a multiple of 8 with keys that count for nobody
+      const int padded = (n + 8 * ways - 1) & ~(8 * ways - 1);  // at most kRankChunk, a multiple of 8 * ways
+      if (tid < padded - n) chunk_s[n + tid] = ~0ull;           // keys that count for nobody
       __syncthreads();
-      for (int j = 0; j < n; j += 8) {  // 8 keys per LDS round trip
+      for (int j = way; j < padded; j += 8 * ways) {  // 8 keys per LDS round trip
         uint64_t k[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) k[t] = chunk_s[j + t];
+        for (int t = 0; t < 8; ++t) k[t] = chunk_s[j + t * ways];
 #pragma unroll
         for (int t = 0; t < 8; ++t) r += k[t] < mine ? 1 : 0;
       }
     }
-    if (c < L) {
+    for (int d = 1; d < ways; d <<= 1) r += __shfl_xor(r, d);
+    if (c < L && way == 0) {
       const int v = (int)(mine & 0xfffffull);
       order[n_done + r] = v;
+      perm[N - 1 - n_done - r] = v;
       atomicOr(reinterpret_cast<unsigned long long*>(&visited[v >> 6]), 1ull << (v & 63));
     }
   }
 }
 
-// One advance, one work-group: make the candidates the expansion found (ranked and placed by rcm_rank_kernel) the next
-// level -- or, when it found none (a component is finished, or nothing has started yet), start the next component.
-__global__ __launch_bounds__(kOrderThreads) void rcm_advance_kernel(const int32_t* __restrict__ degree, int32_t* order,
-                                                                   uint64_t* visited, int32_t* state, int N) {
-  __shared__ unsigned long long min_s[kOrderThreads / 64];
-  const int tid = threadIdx.x;
-  if (state[kStDone]) return;
-  const int n_done = state[kStLvlHi], L = state[kStCand];  // every placed node lies below the end of the current level
-  __syncthreads();                                         // everyone has read the state before thread 0 rewrites it
-  if (L > 0) {
-    if (tid == 0) {
-      state[kStLvlLo] = n_done;
-      state[kStLvlHi] = n_done + L;
-      state[kStCand] = 0;
-    }
-  } else {
-    const int start = min_degree_unvisited(degree, N, [&](int w) { return visited[w]; }, min_s, tid);
-    if (tid == 0) {
-      if (start < 0) {
-        state[kStDone] = 1;
-      } else {
-        order[n_done] = start;
-        visited[start >> 6] |= 1ull << (start & 63);
-        state[kStLvlLo] = n_done;
-        state[kStLvlHi] = n_done + 1;
-      }
-    }
-  }
-}
-
 // The finisher, one work-group: whatever the rounds left (nothing, for graphs of few levels and components) is walked
-// here with the expansion done by the same work-group; then the ordering is reversed into perm.  Global arrays written
+// here with the expansion done by the same work-group.  Global arrays written
 // by some threads and read by others are separated by an agent-scope fence and a barrier.
 __global__ __launch_bounds__(kOrderThreads) void rcm_finish_kernel(const uint64_t* __restrict__ bits, const int32_t* __restrict__ degree,
                                                                    int32_t* parent_pos, int32_t* order, int32_t* cand, uint64_t* keys,
@@ -272,10 +337,10 @@ __global__ __launch_bounds__(kOrderThreads) void rcm_finish_kernel(const uint64_
     __threadfence();
     __syncthreads();
   };
-  const bool done = state[kStDone] != 0;
+  if (state[kStDone]) return;
   int lvl_lo = state[kStLvlLo], lvl_hi = state[kStLvlHi];
   int n_done = lvl_hi;
-  if (!done) {
+  {
     for (int w = tid; w < kMaxNodes / 64; w += kOrderThreads) {
       visited[w] = w < W ? visited_g[w] : ~0ull;  // nodes past N were marked visited when the set was initialised
       claimed[w] = 0;
@@ -321,6 +386,7 @@ __global__ __launch_bounds__(kOrderThreads) void rcm_finish_kernel(const uint64_
         sync_global();
         rank_level(keys, L, chunk_s, tid, [&](int r, int v) {
           order[n_done + r] = v;
+          perm[N - 1 - n_done - r] = v;
           atomicOr(reinterpret_cast<unsigned long long*>(&visited[v >> 6]), 1ull << (v & 63));
         });
         if (tid == 0) count_s = 0;
@@ -330,10 +396,11 @@ __global__ __launch_bounds__(kOrderThreads) void rcm_finish_kernel(const uint64_
         sync_global();
       }
       // ---- next component
-      const int start = min_degree_unvisited(degree, N, [&](int w) { return visited[w]; }, min_s, tid);
+      const int start = min_degree_unvisited<kOrderThreads>(degree, N, [&](int w) { return visited[w]; }, min_s, tid);
       if (start < 0) break;
       if (tid == 0) {
         order[n_done] = start;
+        perm[N - 1 - n_done] = start;
         visited[start >> 6] |= 1ull << (start & 63);
       }
       lvl_lo = n_done;
@@ -342,9 +409,6 @@ __global__ __launch_bounds__(kOrderThreads) void rcm_finish_kernel(const uint64_
       sync_global();
     }
   }
-  sync_global();
-  // the ordering reversed
-  for (int k = tid; k < N; k += kOrderThreads) perm[k] = order[N - 1 - k];
 }
 
 // out[m][i][j] = mask[m][perm[i]][perm[j]]: one work-group per output row stages the source row in LDS.
@@ -421,7 +485,7 @@ struct RcmLayout {
     claimed = o;
     o += round256(W * 8);
     state = o;
-    o += round256(kStInts * 4);
+    o += round256(2 * kStInts * 4);
     total = o;
   }
 };
@@ -458,20 +522,21 @@ extern "C" __attribute__((visibility("default"))) int bbm_rcm_order(const uint8_
   uint64_t* visited = reinterpret_cast<uint64_t*>(ws + lay.visited);
   uint64_t* claimed = reinterpret_cast<uint64_t*>(ws + lay.claimed);
   int32_t* state = reinterpret_cast<int32_t*>(ws + lay.state);
-  rcm_pack_kernel<<<(unsigned)N, kPackThreads, 0, s>>>(mask, (int)N, row_stride_bytes, W, bits, degree, parent, visited, claimed, state);
+  rcm_pack_kernel<<<(unsigned)N, kPackThreads, 0, s>>>(mask, (int)N, row_stride_bytes, W, reinterpret_cast<uint16_t*>(bits), degree, parent, visited,
+                                                       claimed, state);
   int rc = launch_status("bbm_rcm_order (pack)");
   if (rc != BBM_OK) return rc;
-  // the first advance starts the first component; then kRounds rounds of (parallel expansion, ranking, advance); the finisher
-  // walks whatever is left and writes perm.  Kernels that find the walk finished return at once.
-  rcm_advance_kernel<<<1, kOrderThreads, 0, s>>>(degree, order, visited, state, (int)N);
-  for (int r = 0; r < kRounds; ++r) {
-    rcm_expand_kernel<<<kExpandWGs, kExpandThreads, 0, s>>>(bits, order, visited, claimed, parent, cand, state, W);
-    rcm_rank_kernel<<<kRankWGs, kRankThreads, 0, s>>>(degree, parent, cand, order, visited, state);
-    rcm_advance_kernel<<<1, kOrderThreads, 0, s>>>(degree, order, visited, state, (int)N);
+  // the first ranking, of no candidates, starts the first component; then kRounds rounds of (expansion, ranking); the finisher
+  // walks whatever is left.  Kernels that find the walk finished return at once.
+  rcm_rank_kernel<<<1, kRankThreads, 0, s>>>(degree, parent, cand, order, perm, visited, state, state + kStInts, (int)N);
+  for (int r = 1; r <= kRounds; ++r) {
+    int32_t *const st = state + kStInts * (r & 1), *const next = state + kStInts * (~r & 1);
+    rcm_expand_kernel<<<kExpandWGs, kExpandThreads, 0, s>>>(bits, order, visited, claimed, parent, cand, st, W);
+    rcm_rank_kernel<<<kRankWGs, kRankThreads, 0, s>>>(degree, parent, cand, order, perm, visited, st, next, (int)N);
   }
   rc = launch_status("bbm_rcm_order (rounds)");
   if (rc != BBM_OK) return rc;
-  rcm_finish_kernel<<<1, kOrderThreads, 0, s>>>(bits, degree, parent, order, cand, keys, visited, state, (int)N, W, perm);
+  rcm_finish_kernel<<<1, kOrderThreads, 0, s>>>(bits, degree, parent, order, cand, keys, visited, state + kStInts * ((kRounds + 1) & 1), (int)N, W, perm);
   return launch_status("bbm_rcm_order");
 }
 

@@ -24,6 +24,13 @@ def _sym(N, seed, p):
     return a.astype(np.uint8)
 
 
+def _star(N):
+    a = np.eye(N, dtype=np.uint8)
+    a[:, 3] = a[3, :] = 1
+    a[np.arange(0, N - 1, 3), np.arange(1, N, 3)] = 1
+    return a
+
+
 def _cases():
     yield "random sparse", _sym(300, 1, 0.01)                       # several components, ragged N
     yield "random denser", _sym(130, 2, 0.1)
@@ -43,6 +50,7 @@ def _cases():
     big[np.arange(0, 4999, 2), np.arange(1, 5000, 2)] = 1                # unequal degrees among the 4999 nodes of the level
     big[np.arange(1, 5000, 2), np.arange(0, 4999, 2)] = 1
     yield "big star", big                                            # a level larger than one ranking sweep (4096 keys)
+    yield "huge star", _star(16500)                                  # more than 64 * 256 nodes in a level: one lane per candidate
     yield "graph workload", masks.graph_mask(1024, 5, reorder="none", xm=8.0, cap=60)[0]
     yield "single node", np.ones((1, 1), dtype=np.uint8)
     yield "no self loops", (_sym(64, 4, 0.05) * (1 - np.eye(64, dtype=np.uint8))).astype(np.uint8)
@@ -65,6 +73,16 @@ def test_rcm_order_with_a_padded_row_stride_and_unaligned_rows():
     buf = torch.zeros((150, 173), dtype=torch.uint8, device="cuda")       # stride 173: the byte-wise path
     buf[:, :150] = torch.from_numpy(A).cuda()
     perm = bbm.bbm_rcm_order(buf[:, :150])
+    torch.cuda.synchronize()
+    assert np.array_equal(perm.cpu().numpy().astype(np.int64), oracle.reverse_cuthill_mckee(A))
+
+
+@pytest.mark.parametrize("N", [2, 15, 16, 17, 63, 65, 127, 1000, 1040])
+def test_rcm_order_at_the_edges_of_the_packing(N):
+    bbm = _bbm()
+    A = _sym(N, 20 + N, min(0.5, 2.0 / N))
+    print(f"rcm N={N}", flush=True)
+    perm = bbm.bbm_rcm_order(torch.from_numpy(A).cuda())
     torch.cuda.synchronize()
     assert np.array_equal(perm.cpu().numpy().astype(np.int64), oracle.reverse_cuthill_mckee(A))
 
