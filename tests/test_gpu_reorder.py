@@ -87,6 +87,21 @@ def test_rcm_order_at_the_edges_of_the_packing(N):
     assert np.array_equal(perm.cpu().numpy().astype(np.int64), oracle.reverse_cuthill_mckee(A))
 
 
+@pytest.mark.parametrize("N,stride,planes", [(1, 1, 1), (3, 3, 2), (15, 16, 1), (16, 16, 3), (17, 17, 2), (31, 40, 1), (1001, 1001, 1),
+                                             (1030, 1040, 2), (40960, 40960, 1), (40961, 40961, 1)])
+def test_permute_mask_at_the_edges_of_its_pieces(N, stride, planes):
+    """Byte values, not only 0 and 1; rows that end inside a piece; the last size that takes four rows and the first of two."""
+    bbm = _bbm()
+    print(f"permute N={N} stride={stride} planes={planes}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    buf = torch.randint(0, 256, (planes, N, stride), generator=gen, device="cuda", dtype=torch.uint8)
+    mask = buf[:, :, :N]
+    perm = torch.randperm(N, generator=gen, device="cuda")
+    out = bbm.bbm_permute_mask(mask, perm.to(torch.int32))
+    for m in range(planes):
+        assert torch.equal(out[m], mask[m].index_select(0, perm).index_select(1, perm))
+
+
 def test_permute_mask_and_gather_rows_match_numpy():
     bbm = _bbm()
     N = 333
