@@ -86,6 +86,30 @@ struct TL {
   static constexpr int ELEMS = NBLK * TBLK;
 };
 
+// An asynchronous copy of SIZE bytes per lane into LDS, from byte `off` (per lane) of the `bytes` bytes at the wave-uniform p.
+// D = 128 uses the buffer form: the compiler counts the global form as possibly touching LDS through the flat path, and
+// with one in flight it waits for ALL outstanding LDS reads at every use of one, which undoes the reads that run ahead
+// (mfma_ring).  D = 64 keeps the global form and the compiler's order: with both changed a 16384-token window layer went
+// from 408 to 414-435 us, against 2 % gained on a causal layer of 4096 tokens (683 -> 669).
+template <int D, int SIZE>
+__device__ __forceinline__ void copy_async(const void* p, int bytes, uint32_t off, void* dst) {
+  static_assert(SIZE == 16 || SIZE == 4, "the builtins want literal sizes");
+  auto* const lds = (void __attribute__((address_space(3)))*)dst;
+  if constexpr (D == 128) {
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
+    if constexpr (SIZE == 16)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(src, lds, 16, off, 0, 0, 0);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(src, lds, 4, off, 0, 0, 0);
+  } else {
+    const auto* const src = (const void __attribute__((address_space(1)))*)(static_cast<const char*>(p) + off);
+    if constexpr (SIZE == 16)
+      __builtin_amdgcn_global_load_lds(src, lds, 16, 0, 0);
+    else
+      __builtin_amdgcn_global_load_lds(src, lds, 4, 0, 0);
+  }
+}
+
 // Asynchronous global -> LDS copy of rows row0 .. row0+63 of a [N][D] matrix.  Lane l of a copy instruction lands at
 // block base + 16*l, i.e. slot l / RC, chunk position l % RC.  Rows past N re-read row N-1 (callers make sure such
 // rows contribute nothing).
@@ -96,16 +120,15 @@ __device__ __forceinline__ void tile_copy_async(const __bf16* __restrict__ src, 
   static_assert(L::NBLK % NW == 0, "tile must split evenly over the waves");
   const int slot = lane / L::RC, pos = lane % L::RC;
   const int64_t first = min(row0, N - 1);  // a tile that starts past N re-reads row N-1 throughout
-  const char* tile = reinterpret_cast<const char*>(src + first * D);
   const int last = (int)min<int64_t>(63, N - 1 - first);
+  const __bf16* tile = src + first * D;
 #pragma unroll
   for (int n = 0; n < LPW; ++n) {
     const int blk = n * NW + wave;
     const int row = blk + L::NBLK * slot;
     const int c = pos ^ ((row >> 2) & 3);
     const uint32_t off = (uint32_t)(min(row, last) * D + c * 8) * 2u;
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(tile + off),
-                                     (void __attribute__((address_space(3)))*)(dst + blk * L::TBLK), 16, 0, 0);
+    copy_async<D, 16>(tile, (last + 1) * D * 2, off, dst + blk * L::TBLK);
   }
 }
 
@@ -144,6 +167,24 @@ struct TileAddr {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7));
   }
 };
+
+// A chain of COUNT matrix instructions whose LDS operands are read R instructions ahead: load(n) reads the operand of
+// instruction n, mul(n, operand) issues it.  Left alone the compiler reads one operand, waits, multiplies and only then
+// reads the next, so that every matrix instruction stands behind a whole LDS latency; the scheduling barriers keep it
+// from going back to that order where registers are short.
+template <int COUNT, int R, typename Load, typename Mul>
+__device__ __forceinline__ void mfma_ring(Load load, Mul mul) {
+  bf16x8 f[R];
+#pragma unroll
+  for (int n = 0; n < R; ++n) f[n] = load(n);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int n = 0; n < COUNT; ++n) {
+    mul(n, f[n % R]);
+    if (n + R < COUNT) f[n % R] = load(n + R);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
 
 // acc * mult, rounded to bf16, to rows row0 .. of a [N][D] matrix: lane l holds row l%32 of the wave's 32-row slab,
 // columns 32*db + 8*(e/4) + 4*(l/32) + e%4.  The slab is staged in LDS (`stage`, 32*D elements, this wave's own) so
@@ -200,6 +241,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   constexpr int BR = NW * 32;
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;
+  constexpr int kRing = 3;
   constexpr int REGS = DB * 16;
   static_assert(2 * 32 * D <= L::ELEMS && NW <= 8, "two 32 x D output slabs must fit in each tile buffer");
 
@@ -310,10 +352,20 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
             dp[e] = nd_lane;
           }
         }
+        if constexpr (D == 64) {
 #pragma unroll
-        for (int t = 0; t < KS; ++t) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(k_cur, kb, t), qf[t], s, 0, 0, 0);
+          for (int t = 0; t < KS; ++t) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(k_cur, kb, t), qf[t], s, 0, 0, 0);
 #pragma unroll
-        for (int t = 0; t < KS; ++t) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(v_cur, kb, t), dof[t], dp, 0, 0, 0);
+          for (int t = 0; t < KS; ++t) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(v_cur, kb, t), dof[t], dp, 0, 0, 0);
+        } else {
+        mfma_ring<2 * KS, kRing>([&](int n) { return A.row_frag(n & 1 ? v_cur : k_cur, kb, n >> 1); },
+                                 [&](int n, bf16x8 f) {
+                                   if (n & 1)
+                                     dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, dof[n >> 1], dp, 0, 0, 0);
+                                   else
+                                     s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[n >> 1], s, 0, 0, 0);
+                                 });
+        }
         // element mask where the list cannot rule out zeros: masked scores become -inf, i.e. probability 0
         if ((e0 >> 31) == 0) {
           const uint32_t w = (uint32_t)(mw >> (32 * kb)) >> (4 * hh);
@@ -453,6 +505,10 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   }
 }
 
+// A work-group barrier that orders LDS accesses alone: requests to global memory, asynchronous copies into LDS among them,
+// stay in flight across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // ------------------------------------------------------------------------------------------------------------------
 // dK, dV
 // ------------------------------------------------------------------------------------------------------------------
@@ -472,16 +528,15 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;
   constexpr int REGS = DB * 16;
+  constexpr int kRing = 3;
   static_assert(2 * 32 * D <= L::ELEMS, "two 32 x D output slabs must fit in a tile buffer");
 
-  __shared__ __attribute__((aligned(16))) __bf16 q_s0[L::ELEMS];
-  __shared__ __attribute__((aligned(16))) __bf16 q_s1[L::ELEMS];
-  __shared__ __attribute__((aligned(16))) __bf16 g_s0[L::ELEMS];  // dO tiles
-  __shared__ __attribute__((aligned(16))) __bf16 g_s1[L::ELEMS];
-  __shared__ __attribute__((aligned(16))) float nl_s0[64];
-  __shared__ __attribute__((aligned(16))) float nl_s1[64];
-  __shared__ __attribute__((aligned(16))) float nd_s0[64];
-  __shared__ __attribute__((aligned(16))) float nd_s1[64];
+  // One variable per parity for what the roles read at the same place of their own operand: a select between two
+  // variables hides from the compiler which asynchronous copies a read has to wait for, and it then waits for all.
+  __shared__ __attribute__((aligned(16))) __bf16 t_s0[2 * L::ELEMS];  // [Q, dO] tiles
+  __shared__ __attribute__((aligned(16))) __bf16 t_s1[2 * L::ELEMS];
+  __shared__ __attribute__((aligned(16))) float st_s0[2 * 64];  // [-lse*log2 e, -D] of the sub-tile's queries
+  __shared__ __attribute__((aligned(16))) float st_s1[2 * 64];
   __shared__ __attribute__((aligned(16))) uint32_t mk_s0[2][64];  // [key half][query row of the sub-tile]
   __shared__ __attribute__((aligned(16))) uint32_t mk_s1[2][64];
   __shared__ uint32_t tiles_s[kWin];
@@ -560,25 +615,24 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
   // its 64 queries (-lse*log2 e and -D: one wave each), and the two 32-bit halves of the mask words if the block is
   // partial (the waves of role 0, each its own half).  Query rows past N get -inf / 0 so that their probabilities are
   // exactly 0.
-  auto request = [&](uint32_t e, int sub, __bf16* qd, __bf16* gd, float* nld, float* ndd, uint32_t (*mkd)[64]) {
+  auto request = [&](uint32_t e, int sub, __bf16* td, float* sts, uint32_t (*mkd)[64]) {
     const int64_t row0 = ((int64_t)(e & 0x7fffffffu) << qs_shift) * 64 + (int64_t)sub * 64;
-    tile_copy_async<D, NW>(Qg, row0, N, qd, wave, lane);
-    tile_copy_async<D, NW>(Gg, row0, N, gd, wave, lane);
+    tile_copy_async<D, NW>(Qg, row0, N, td, wave, lane);
+    tile_copy_async<D, NW>(Gg, row0, N, td + L::ELEMS, wave, lane);
     const int64_t r = row0 + lane;
     const bool lse_wave = wave == 0, delta_wave = wave == (RS ? 2 : 1);  // one wave of each role when the roles are split
     if (lse_wave || delta_wave) {
-      float* const sd = lse_wave ? nld : ndd;
+      float* const sd = sts + (lse_wave ? 0 : 64);
       const float* const sg = lse_wave ? nlg : ndg;
       if (r < N)
-        __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(sg + r),
-                                         (void __attribute__((address_space(3)))*)sd, 4, 0, 0);
+        copy_async<D, 4>(sg + row0, 64 * 4, lane * 4, sd);
       else
         sd[lane] = lse_wave ? -INFINITY : 0.0f;
     }
     if (role == 0 && (e >> 31) == 0) {
-      const int64_t rc = min(r, N - 1);
-      __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(mcol + 2 * rc),
-                                       (void __attribute__((address_space(3)))*)mkd[kh], 4, 0, 0);
+      const int64_t first = min(row0, N - 1);
+      const int last = (int)min<int64_t>(63, N - 1 - first);
+      copy_async<D, 4>(mcol + 2 * first, 64 * 8, min(lane, last) * 8, mkd[kh]);
     }
   };
 
@@ -588,19 +642,19 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
     constexpr int PB = decltype(pb)::value;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    __bf16* const q_cur = PB ? q_s1 : q_s0;
-    __bf16* const g_cur = PB ? g_s1 : g_s0;
-    const float* const nl_cur = PB ? nl_s1 : nl_s0;
-    const float* const nd_cur = PB ? nd_s1 : nd_s0;
+    __bf16* const q_cur = PB ? t_s1 : t_s0;
+    __bf16* const g_cur = q_cur + L::ELEMS;
+    const float* const nl_cur = PB ? st_s1 : st_s0;
+    const float* const nd_cur = nl_cur + 64;
     const uint32_t(*mk_cur)[64] = PB ? mk_s1 : mk_s0;
     const uint32_t e0 = entry_of(s);
     if (s + 1 < n_steps) {
       const uint32_t e1 = entry_of(s + 1);
       const int sub1 = (s + 1) & ((1 << qs_shift) - 1);
       if (PB)
-        request(e1, sub1, q_s0, g_s0, nl_s0, nd_s0, mk_s0);
+        request(e1, sub1, t_s0, st_s0, mk_s0);
       else
-        request(e1, sub1, q_s1, g_s1, nl_s1, nd_s1, mk_s1);
+        request(e1, sub1, t_s1, st_s1, mk_s1);
     }
     const bool partial = (e0 >> 31) == 0;
     // a partial sub-tile in which none of the 64 queries sees one of this wave's 32 keys contributes exact zeros
@@ -609,8 +663,8 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
       f32x16 acc2[2];  // role 0: S^T, then P; role 1: dP^T
       bf16x8 pf[4];
       if (live) {
-        const float* const init = role == 0 ? nl_cur : nd_cur;
-        const __bf16* const rows = role == 0 ? q_cur : g_cur;
+        const float* const init = nl_cur + role * 64;
+        const __bf16* const rows = q_cur + role * L::ELEMS;
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
 #pragma unroll
@@ -618,9 +672,9 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
             const float4 a = *reinterpret_cast<const float4*>(init + 32 * qb + 8 * g + 4 * hh);
             acc2[qb][4 * g + 0] = a.x, acc2[qb][4 * g + 1] = a.y, acc2[qb][4 * g + 2] = a.z, acc2[qb][4 * g + 3] = a.w;
           }
-#pragma unroll
-          for (int t = 0; t < KS; ++t) acc2[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(rows, qb, t), kf[t], acc2[qb], 0, 0, 0);
         }
+        mfma_ring<2 * KS, kRing>([&](int n) { return A.row_frag(rows, n & 1, n >> 1); },
+                                 [&](int n, bf16x8 f) { acc2[n & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kf[n >> 1], acc2[n & 1], 0, 0, 0); });
         if (role == 0) {
 #pragma unroll
           for (int qb = 0; qb < 2; ++qb) {
@@ -648,9 +702,11 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
           }
         }
       }
-      __syncthreads();  // P of this step is in LDS (the next step's first barrier comes after its last reader)
+      // P of this step is in LDS (the next step's first barrier comes after its last reader).  Only LDS is waited for:
+      // __syncthreads() also waits for the next sub-tile's copies, requested a moment ago, and exposes their latency.
+      lds_barrier();
       if (live) {
-        const __bf16* const cols = role == 0 ? g_cur : q_cur;
+        const __bf16* const cols = q_cur + (1 - role) * L::ELEMS;
         if (role != 0) {  // dS = P o dP, rounded to bf16, in place of P
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
@@ -659,10 +715,8 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
             for (int e = 0; e < 8; ++e) pf[u][e] = (__bf16)((float)pu[e] * acc2[u >> 1][8 * (u & 1) + e]);
           }
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int db = 0; db < DB; ++db) dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.tr_frag(cols, u, db), pf[u], dk[db], 0, 0, 0);
+        mfma_ring<4 * DB, kRing>([&](int n) { return A.tr_frag(cols, n / DB, n % DB); },
+                                 [&](int n, bf16x8 f) { dk[n % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, pf[n / DB], dk[n % DB], 0, 0, 0); });
       }
       return;
     }
@@ -721,7 +775,7 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
       for (int t = tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
       __syncthreads();
       n_steps = count << qs_shift;
-      request(tiles_s[0], 0, q_s0, g_s0, nl_s0, nd_s0, mk_s0);
+      request(tiles_s[0], 0, t_s0, st_s0, mk_s0);
       for (int s = 0; s < n_steps; s += 2) {
         step(IntC<0>{}, s);
         if (s + 1 < n_steps) step(IntC<1>{}, s + 1);
@@ -734,12 +788,12 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
     const int64_t row0 = (int64_t)j * 64 + kh * 32;
     if constexpr (RS) {
       if (role == 0)
-        store_slab<D>(dk, 1.0f, g_s0 + kh * 32 * D, P.dv + head_off, row0, N, lane);
+        store_slab<D>(dk, 1.0f, t_s0 + L::ELEMS + kh * 32 * D, P.dv + head_off, row0, N, lane);
       else
-        store_slab<D>(dk, P.scale, q_s0 + kh * 32 * D, P.dk + head_off, row0, N, lane);
+        store_slab<D>(dk, P.scale, t_s0 + kh * 32 * D, P.dk + head_off, row0, N, lane);
     } else {
-      store_slab<D>(dk, P.scale, q_s0 + kh * 32 * D, P.dk + head_off, row0, N, lane);
-      store_slab<D>(dv, 1.0f, g_s0 + kh * 32 * D, P.dv + head_off, row0, N, lane);
+      store_slab<D>(dk, P.scale, t_s0 + kh * 32 * D, P.dk + head_off, row0, N, lane);
+      store_slab<D>(dv, 1.0f, t_s0 + L::ELEMS + kh * 32 * D, P.dv + head_off, row0, N, lane);
     }
   };
   // where this thread's sums sit in a parked record: [dK registers | dV registers][NTP lanes]
