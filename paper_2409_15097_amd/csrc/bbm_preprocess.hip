@@ -3,9 +3,9 @@
 // Br*Bc, so the kernel carries an OR and an AND of the non-zero bits instead of a count.
 //
 // One work-group (8 wavefronts) owns one block row (Br mask rows) x 16*LPR mask columns.  LPR lanes of a wavefront read
-// one row segment, 16 B each, so a load instruction of a wavefront covers 64 / LPR rows; each lane turns its 16 bytes
-// into 16 bits and keeps a running OR / AND over the rows it sees.  The bits go to LDS as uint16 quarters of the 64-bit
-// words and leave word-column major, so the global writes of the packed mask are contiguous too.
+// one row segment, 16 B each, so a load instruction of a wavefront covers 64 / LPR rows, with U of them in flight; each lane
+// turns its 16 bytes into 16 bits and keeps a running OR / AND over the rows it sees.  The bits go to LDS as uint16
+// quarters of the 64-bit words and leave word-column major, so the global writes of the packed mask are contiguous too.
 #include "bbm_internal.h"
 
 namespace {
@@ -35,7 +35,7 @@ __device__ __forceinline__ uint32_t bits16(u32x4_any x) {
   return nz_nibble(x.x) | (nz_nibble(x.y) << 4) | (nz_nibble(x.z) << 8) | (nz_nibble(x.w) << 12);
 }
 
-template <int LPR, bool STREAM>
+template <int LPR, int U, bool STREAM>
 __global__ __launch_bounds__(kThreads) void block_reduce_kernel(const uint8_t* __restrict__ mask, int64_t Nr, int64_t N,
                                                                 int64_t row_stride, int Br, int Bc, int64_t nbr,
                                                                 int64_t nbc, uint8_t* __restrict__ blk_class,
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kThreads) void block_reduce_kernel(const uint8_t* _
   constexpr int kCols = 16 * LPR;              // mask columns of a work-group
   constexpr int kWords = LPR / 4;              // 64-bit words of a row
   constexpr int kRowsPerLoad = kWaves * 64 / LPR;  // rows the work-group's wavefronts read with one load each
-  constexpr int kUnroll = LPR == 32 ? 8 : 4;  // independent loads a lane has in flight
+  constexpr int kBatchRows = U * kRowsPerLoad;     // rows of a batch: every lane has U independent loads in flight
   __shared__ __attribute__((aligned(8))) uint16_t stage[kWords * (kMaxBr + 1) * 4];  // [word][row in block (+1 pad)][quarter]
   __shared__ uint32_t acc[kWaves][LPR];        // per wave and 16-column chunk: any16 | all16 << 16
   __shared__ uint32_t word_any[kWords];        // per 64-column word: does any of the block row's rows set a bit?
@@ -65,19 +65,20 @@ __global__ __launch_bounds__(kThreads) void block_reduce_kernel(const uint8_t* _
   const int shift = (int)(col - at < 31 ? col - at : 31);
   uint32_t any16 = 0, all16 = 0xffffu;
   uint16_t* const s = stage + ((chunk >> 2) * BrP) * 4 + (chunk & 3);
-  // rows past the last are clamped to it: the same bits once more, neutral in OR and AND
+  // rows past the last are clamped to it: the same bits once more, neutral in OR and AND (the dispatch takes a batch no
+  // longer than the block, or loads that all repeat the last row would be most of them)
   auto take = [&](int r, uint32_t b) {
     any16 |= b;
     all16 &= b;
     if (packed) s[r * 4] = (uint16_t)b;
   };
   if (N >= 16) {
-    for (int rb = wave * (64 / LPR) + sub; rb - sub < rows; rb += kUnroll * kRowsPerLoad) {
-      u32x4_any x[kUnroll];
+    for (int rb = wave * (64 / LPR) + sub; rb - sub < rows; rb += kBatchRows) {
+      u32x4_any x[U];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) x[u] = load16<STREAM>(base + (int64_t)min(rb + u * kRowsPerLoad, rows - 1) * row_stride + at);
+      for (int u = 0; u < U; ++u) x[u] = load16<STREAM>(base + (int64_t)min(rb + u * kRowsPerLoad, rows - 1) * row_stride + at);
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) take(min(rb + u * kRowsPerLoad, rows - 1), bits16(x[u]) >> shift);
+      for (int u = 0; u < U; ++u) take(min(rb + u * kRowsPerLoad, rows - 1), bits16(x[u]) >> shift);
     }
   } else {  // masks of fewer than 16 columns: byte by byte
     for (int r = wave * (64 / LPR) + sub; r < rows; r += kRowsPerLoad) {
@@ -131,11 +132,16 @@ __global__ __launch_bounds__(kThreads) void block_reduce_kernel(const uint8_t* _
     const int64_t W = (N + 63) / 64;
     const int64_t w0 = c0 / 64;
     const uint64_t* stage64 = reinterpret_cast<const uint64_t*>(stage);
-    constexpr int kWavesPerWord = kWords < kWaves ? kWaves / kWords : 1;
-    for (int wl = wave / kWavesPerWord; wl < kWords; wl += kWaves / kWavesPerWord) {
-      if (w0 + wl >= W || word_any[wl] == 0) continue;
-      uint64_t* const dst = packed + (m * W + w0 + wl) * Nr + r0;
-      for (int rl = (wave % kWavesPerWord) * 64 + lane; rl < rows; rl += kWavesPerWord * 64) dst[rl] = stage64[wl * BrP + rl];
+    if constexpr (kBatchRows >= 64) {
+      constexpr int kWavesPerWord = kWords < kWaves ? kWaves / kWords : 1;
+      for (int wl = wave / kWavesPerWord; wl < kWords; wl += kWaves / kWavesPerWord) {
+        if (w0 + wl >= W || word_any[wl] == 0) continue;
+        uint64_t* const dst = packed + (m * W + w0 + wl) * Nr + r0;
+        for (int rl = (wave % kWavesPerWord) * 64 + lane; rl < rows; rl += kWavesPerWord * 64) dst[rl] = stage64[wl * BrP + rl];
+      }
+    } else {  // blocks of one short batch: a wavefront writes several words' rows side by side
+      const int wl = threadIdx.x / kBatchRows, rl = threadIdx.x % kBatchRows;
+      if (wl < kWords && w0 + wl < W && rl < rows && word_any[wl] != 0) packed[(m * W + w0 + wl) * Nr + r0 + rl] = stage64[wl * BrP + rl];
     }
   }
 }
@@ -162,24 +168,31 @@ int build_block_mask_impl(const char* fn, const uint8_t* mask, int64_t Mb, int64
   const int64_t nbr = ceil_div(Nq, Br), nbc = ceil_div(Nk, Bc);
   if (nbr > 65535 || Mb > 65535) return fail(BBM_EUNSUPPORTED, "%s: nbr=%lld or Mb=%lld exceeds 65535", fn, (long long)nbr, (long long)Mb);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  auto go = [&](auto lpr, auto stream_loads) {
-    constexpr int LPR = decltype(lpr)::value;
-    block_reduce_kernel<LPR, decltype(stream_loads)::value != 0><<<dim3((unsigned)ceil_div(Nk, 16 * LPR), (unsigned)nbr, (unsigned)Mb), kThreads, 0, s>>>(
-        mask, Nq, Nk, row_stride_bytes, Br, Bc, nbr, nbc, blk_class, bin_blk_mat, packed_mask);
-  };
+  const int64_t bytes = Mb * Nq * Nk;
   // masks from kStreamFromBytes on (half the 256 MB last-level cache) are streamed: block reduction 6 % faster on a 1 GiB mask
   // and the attention kernel behind it finds more of Q, K, V still cached (whole step -2.5 % at 1 GiB, -3.5 % at 256 MiB);
   // a 64 MiB mask that is rebuilt from the cache it still sits in loses 20 % that way
-  // 256-byte row segments (LPR = 16) give the most work-groups and the shortest chain of loads.  Rows that do not start on
-  // 128-byte lines cost one line more per segment, so from kWideFromBytes on those are read in 512-byte segments.
-  // Microseconds with LPR = 16 / 32 (in a graph, rotating over 3 masks): 256 x 1280 3.5 / 4.0, 2048^2 x 2 3.9 / 4.3,
-  // 16384^2 53.4 / 53.3; unaligned 2001^2 4.0 / 4.7, 3000^2 5.5 / 4.6, 9001^2 21.2 / 18.6.  (1 KiB segments, the only split
-  // before: 5.2, 5.8, 59.5; and unaligned rows byte by byte: 3001^2 x 2 41 us, now 7.8.)
+  const bool streamed = bytes >= kStreamFromBytes;
+  auto go = [&](auto lpr, auto unroll) {
+    constexpr int LPR = decltype(lpr)::value, U = decltype(unroll)::value;
+    const auto kernel = streamed ? block_reduce_kernel<LPR, U, true> : block_reduce_kernel<LPR, U, false>;
+    kernel<<<dim3((unsigned)ceil_div(Nk, 16 * LPR), (unsigned)nbr, (unsigned)Mb), kThreads, 0, s>>>(
+        mask, Nq, Nk, row_stride_bytes, Br, Bc, nbr, nbc, blk_class, bin_blk_mat, packed_mask);
+  };
+  // What a work-group reads is Br rows x 16*LPR bytes.  Blocks of more than 64 rows: 256-byte segments (LPR = 16) give the most
+  // work-groups and the shortest chain of loads; rows that do not start on 128-byte lines cost one line more per segment, so
+  // from kWideFromBytes on those are read in 512-byte segments.  Lower blocks take longer segments, or starting work-groups
+  // costs more than the reading, and a batch of loads that is no longer than the block.
+  // Microseconds with LPR = 16 / 32 (in a graph, rotating over 3 masks), Br = 128: 256 x 1280 3.5 / 4.0, 2048^2 x 2 3.9 / 4.3,
+  // 16384^2 53.4 / 53.3; unaligned 2001^2 4.0 / 4.7, 3000^2 5.5 / 4.6, 9001^2 21.2 / 18.6.
+  // 16384^2 by height, this rule / batches of 128 rows x 256 bytes for every height: 8 rows 75 / 330, 16 rows 51 / 179, 32 rows
+  // 48 / 115, 64 rows 49 / 66 (60 with batches of 64 x 256); 256 x 1280 3.1-3.4 / 3.5-3.6.
   const bool line_rows = aligned(mask, 128) && row_stride_bytes % 128 == 0;
-  const bool wide = (!line_rows && Mb * Nq * Nk > kWideFromBytes);  // either holds whole blocks of up to 256 columns
-  const bool streamed = Mb * Nq * Nk >= kStreamFromBytes;
-  if (wide) streamed ? go(IntC<32>{}, IntC<1>{}) : go(IntC<32>{}, IntC<0>{});
-  else streamed ? go(IntC<16>{}, IntC<1>{}) : go(IntC<16>{}, IntC<0>{});
+  if (Br <= 8) go(IntC<64>{}, IntC<1>{});
+  else if (Br <= 16) go(IntC<64>{}, IntC<2>{});
+  else if (Br <= 32) go(IntC<64>{}, IntC<4>{});
+  else if (Br <= 64) bytes > kWideFromBytes ? go(IntC<32>{}, IntC<4>{}) : go(IntC<16>{}, IntC<2>{});
+  else bytes > kWideFromBytes && !line_rows ? go(IntC<32>{}, IntC<8>{}) : go(IntC<16>{}, IntC<4>{});
   return launch_status(fn);
 }
 }  // namespace

@@ -152,6 +152,47 @@ def test_block_mask_at_any_address(Nq, Nk, offset):
     assert_index_equal(index_to_numpy(idx), mask, 128, 64)
 
 
+@pytest.mark.parametrize("Br", [1, 7, 8, 9, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("Nq,Nk,Bc", [(67, 1023, 16), (130, 1100, 256), (257, 2049, 64), (2950, 2993, 32)])
+def test_block_mask_at_the_edges_of_its_heights(Nq, Nk, Bc, Br):
+    """Block heights around those at which segment length and batch change (8, 16, 32, 64), a last block row of few rows,
+    the last mask above the size from which 64-row blocks take the longer segments."""
+    rng = np.random.default_rng(Nq + Br)
+    kind = rng.random((-(-Nq // Br), -(-Nk // Bc)))
+    block = np.repeat(np.repeat(kind, Br, axis=0), Bc, axis=1)[:Nq, :Nk]
+    mask = ((block < 0.2) | ((block < 0.5) & (rng.random((Nq, Nk)) < 0.02))).astype(np.uint8)[None]
+    idx = _bbm().bbm_build_block_mask_rect(torch.from_numpy(mask).cuda(), Br, Bc)
+    torch.cuda.synchronize()
+    assert_index_equal(index_to_numpy(idx), mask, Br, Bc)
+
+
+def _device_ms(call, n=10):
+    call()
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for _ in range(3):
+        e0.record()
+        for _ in range(n):
+            call()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1) / n)
+    return best
+
+
+def test_low_blocks_cost_little_more_than_tall_ones():
+    """The same 256 MiB are read at every block height.  Batches of 128 rows for all of them made 8-row blocks 6 times and
+    32-row blocks 2.1 times as slow as 128-row ones; with batches no longer than the block 1.4 and 0.9 were measured."""
+    bbm = _bbm()
+    mask = torch.zeros((1, 16384, 16384), dtype=torch.uint8, device="cuda")
+    mask[0, :, 5000:6000] = 1
+    t = {}
+    for Br in (8, 32, 128):
+        idx = bbm.bbm_build_block_mask(mask, Br, 64)
+        t[Br] = _device_ms(lambda: bbm.bbm_build_block_mask(mask, Br, 64, idx=idx))
+    assert t[8] < 3 * t[128] and t[32] < 1.5 * t[128], t
+
+
 @pytest.mark.parametrize("fused", [True, False])
 @pytest.mark.parametrize("Mb,Nq,Nk,Br,Bc", [
     (1, 10, 10, 64, 64), (2, 40, 239, 8, 16), (3, 520, 250, 64, 16), (1, 200, 8300, 64, 16),     # < 16, 15, 16, 519 block columns
