@@ -125,6 +125,10 @@ typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 // Bytes that are not zero: 4 bytes -> 0x01 in each such byte.
 __device__ __forceinline__ uint32_t nz_bytes(uint32_t w) { return ((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) >> 7) & 0x01010101u; }
 
+// 4 class bytes -> 4 bits, 16 -> 16 (bit t = byte t not zero).
+__device__ __forceinline__ uint32_t nz_bits4(uint32_t w) { return ((nz_bytes(w) * 0x10204080u) >> 28) & 0xfu; }
+__device__ __forceinline__ uint32_t nz_bits16(u32x4_any x) { return nz_bits4(x.x) | (nz_bits4(x.y) << 4) | (nz_bits4(x.z) << 8) | (nz_bits4(x.w) << 12); }
+
 // What bounds an index build is latency: kernel starts, memory round trips and serial chains over a few kilobytes.  So
 // nothing is handed from one work-group to another: every work-group counts the non-zero blocks of ALL lines itself
 // (16 class bytes per load) into LDS, behind one barrier, and each of its waves then produces one line from those
@@ -143,8 +147,9 @@ inline bool line_index_fits(bool cols, int64_t Mb, int64_t nbr, int64_t nbc) {
 }
 
 // COLS = false: lines are block rows (`ptr` = row_ptr, `list` = col_idx); true: block columns (col_ptr, row_idx).
+// SHORT: class rows of fewer than 16 blocks, which are counted another way.
 // `sched` and the five arrays of the run index (block rows only) may be NULL.
-template <bool COLS>
+template <bool COLS, bool SHORT>
 __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8_t* __restrict__ cls, int Mb, int nbr, int nbc,
                                                                      int32_t* __restrict__ ptr, uint32_t* __restrict__ list,
                                                                      int32_t* __restrict__ sched, int32_t* __restrict__ offset,
@@ -165,12 +170,35 @@ __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8
 
   // ---- non-zero blocks of every line
   const int C16 = (nbc + 15) / 16;  // 16-byte chunks of a class row; the last one is read as the row's last 16 bytes
-  if (!COLS && nbc < 16) {
-    for (int r = tid; r < nlines; r += kLineWaves * 64) {
+  // SHORT: 16 bytes from a row's start on, the last rows' moved back to end with the matrix; as bits, that row's first.  (A load
+  // per byte took 256 planes of 15 x 15 from 14.8 to 25 us, their columns from 17.5 to 46.)
+  const int bytes = nlines * depth;  // at most kLineMaxBytesCols
+  auto short_rows_at = [&](int r) { return min(r * nbc, bytes - 16); };
+  auto short_rows_bits = [&](u32x4_any x, int r) { return nz_bits16(x) >> (r * nbc - short_rows_at(r)); };
+  const uint32_t row_bits = SHORT ? (1u << nbc) - 1u : 0xffffu;
+  if (SHORT && (bytes < 16 || (!COLS && nbc <= 4 && nlines <= kLineWaves * 64))) {  // next to nothing to count
+    for (int b = tid; b < nlines; b += kLineWaves * 64) {
+      const int bm = b / L, bi = b - bm * L;
       int cnt = 0;
 #pragma unroll 1
-      for (int t = 0; t < nbc; ++t) cnt += cls[(int64_t)r * nbc + t] != 0 ? 1 : 0;
-      len_s[r] = cnt;
+      for (int t = 0; t < depth; ++t) cnt += cls[(int64_t)bm * nbr * nbc + (COLS ? t * nbc + bi : bi * nbc + t)] != 0 ? 1 : 0;
+      len_s[b] = cnt;
+    }
+  } else if (!COLS && SHORT) {
+    // rows a thread takes from one load: what 16 bytes hold, but no more than it needs to have one load
+    const int per = min(16 / nbc, (nlines + kLineWaves * 64 - 1) / (kLineWaves * 64)), hop = kLineWaves * 64 * per;
+    constexpr int kFly = 4;
+    for (int r0 = tid * per; r0 < nlines; r0 += kFly * hop) {
+      u32x4_any x[kFly];
+#pragma unroll
+      for (int f = 0; f < kFly; ++f) x[f] = *reinterpret_cast<const u32x4_any*>(cls + short_rows_at(min(r0 + f * hop, nlines - 1)));
+#pragma unroll
+      for (int f = 0; f < kFly; ++f) {
+        const int r = r0 + f * hop, re = min(r + per, nlines);
+        uint32_t b = r < nlines ? short_rows_bits(x[f], r) : 0;
+#pragma unroll 1
+        for (int k = r; k < re; ++k, b >>= nbc) len_s[k] = __popc(b & row_bits);
+      }
     }
   } else if (!COLS) {
     int lpr = 1;  // lanes per row
@@ -216,12 +244,12 @@ __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8
     const int RG = max(1, min(nbr, kLineWaves * 64 / units));
     for (int it = tid; it < units * RG; it += kLineWaves * 64) {
       const int u = it % units, rg = it / units;
-      const int pm = u / C16, c = (u - pm * C16) * 16, at = nbc >= 16 ? min(c, nbc - 16) : 0;
+      const int pm = u / C16, c = (u - pm * C16) * 16, at = SHORT ? 0 : min(c, nbc - 16);
       const uint8_t* const plane = cls + (int64_t)pm * nbr * nbc + at;
       for (int rb = rg; rb < nbr; rb += 255 * RG) {  // a byte counter holds 255 rows
         uint32_t sum[4] = {0, 0, 0, 0};
         const int re = (int)min<int64_t>(nbr, rb + (int64_t)255 * RG);
-        if (nbc >= 16) {
+        if (!SHORT) {
 #pragma unroll 4
           for (int r = rb; r < re; r += RG) {
             const u32x4_any x = *reinterpret_cast<const u32x4_any*>(plane + (int64_t)r * nbc);
@@ -230,11 +258,21 @@ __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8
             sum[2] += nz_bytes(x.z);
             sum[3] += nz_bytes(x.w);
           }
+        } else if (nbc <= 2) {  // one or two byte loads are cheaper than taking 16 bytes apart
+#pragma unroll 4
+          for (int r = rb; r < re; r += RG) {
+            const uint8_t* const p = plane + (int64_t)r * nbc;
+            sum[0] += p[0] != 0 ? 1u : 0u;
+            if (nbc == 2) sum[0] += p[1] != 0 ? 256u : 0u;
+          }
         } else {
-          for (int r = rb; r < re; r += RG)
+#pragma unroll 4
+          for (int r = rb; r < re; r += RG) {
+            const int row = pm * nbr + r;
+            const uint32_t b = short_rows_bits(*reinterpret_cast<const u32x4_any*>(cls + short_rows_at(row)), row) & row_bits;
 #pragma unroll
-            for (int t = 0; t < 16; ++t)
-              if (t < nbc && plane[(int64_t)r * nbc + t] != 0) sum[t >> 2] += 1u << (8 * (t & 3));
+            for (int g = 0; g < 4; ++g) sum[g] += (((b >> (4 * g)) & 0xfu) * 0x00204081u) & 0x01010101u;  // 4 bits -> 4 bytes
+          }
         }
 #pragma unroll
         for (int t = 0; t < 16; ++t) {

@@ -28,6 +28,55 @@ def index_to_numpy(idx):
     return out
 
 
+def index_of_classes(cls: np.ndarray):
+    """A BlockIndex of [Mb, nbr, nbc] class bytes given directly: the index stage without a mask."""
+    import paper_2409_15097_amd as bbm
+    Mb, nbr, nbc = cls.shape
+    return bbm.BlockIndex(128, 64, Mb, nbr, nbc, 128 * nbr, Nk=64 * nbc, blk_class=torch.from_numpy(cls).cuda())
+
+
+def assert_class_index_equal(got: dict, cls: np.ndarray):
+    """Run index, lists and schedules that were built from class bytes, bit-exact against the oracle."""
+    Mb, nbr, nbc = cls.shape
+    want = oracle.run_index(cls)
+    want["row_ptr"], want["col_idx"] = oracle.sparse_index(cls)
+    want["col_ptr"], want["row_idx"] = oracle.column_index(cls)
+    want["sched"] = oracle.schedule(want["row_ptr"], want["col_idx"])
+    want["col_sched"] = oracle.column_schedule(want["col_ptr"], want["row_idx"])
+    for name in ("offset", "total_ones", "nz_lo", "nz_hi", "nz_cnt", "row_ptr", "col_ptr"):
+        if got[name] is not None:
+            assert np.array_equal(got[name], want[name]), name
+    for ptr, lst, sched, lines in (("row_ptr", "col_idx", "sched", nbr), ("col_ptr", "row_idx", "col_sched", nbc)):
+        if got[ptr] is None:
+            continue
+        for m in range(Mb):
+            lo = m * nbr * nbc
+            hi = lo + int(want[ptr][m, -1])
+            assert np.array_equal(got[lst][lo:hi], want[lst][lo:hi]), (lst, m)
+        n = oracle.blocks.SCHED_PART_BASE + oracle.blocks.SCHED_PART_INTS * int(want[sched][0])
+        assert np.array_equal(got[sched][:n], want[sched][:n]), sched
+        assert np.array_equal(got[sched][-4 * Mb * lines:], want[sched][-4 * Mb * lines:]), sched
+
+
+def device_us(call, n=20) -> float:
+    """Microseconds of one call on the device, from n of them in a graph (so that submitting them costs nothing)."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(n):
+            call()
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for _ in range(5):
+        e0.record()
+        graph.replay()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, 1e3 * e0.elapsed_time(e1) / n)
+    return best
+
+
 def assert_index_equal(got: dict, mask: np.ndarray, Br: int, Bc: int):
     """Bit-exact comparison of everything the preprocessing stage wrote against the oracle."""
     want = oracle.block_index(mask, Br, Bc)

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from workloads import masks, small_variant, make_config
-from gpu_util import index_to_numpy, assert_index_equal
+from gpu_util import index_to_numpy, assert_index_equal, device_us
 
 pytestmark = pytest.mark.gpu
 
@@ -166,20 +166,6 @@ def test_block_mask_at_the_edges_of_its_heights(Nq, Nk, Bc, Br):
     assert_index_equal(index_to_numpy(idx), mask, Br, Bc)
 
 
-def _device_ms(call, n=10):
-    call()
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    best = float("inf")
-    for _ in range(3):
-        e0.record()
-        for _ in range(n):
-            call()
-        e1.record()
-        torch.cuda.synchronize()
-        best = min(best, e0.elapsed_time(e1) / n)
-    return best
-
-
 def test_low_blocks_cost_little_more_than_tall_ones():
     """The same 256 MiB are read at every block height.  Batches of 128 rows for all of them made 8-row blocks 6 times and
     32-row blocks 2.1 times as slow as 128-row ones; with batches no longer than the block 1.4 and 0.9 were measured."""
@@ -189,7 +175,7 @@ def test_low_blocks_cost_little_more_than_tall_ones():
     t = {}
     for Br in (8, 32, 128):
         idx = bbm.bbm_build_block_mask(mask, Br, 64)
-        t[Br] = _device_ms(lambda: bbm.bbm_build_block_mask(mask, Br, 64, idx=idx))
+        t[Br] = device_us(lambda: bbm.bbm_build_block_mask(mask, Br, 64, idx=idx))
     assert t[8] < 3 * t[128] and t[32] < 1.5 * t[128], t
 
 
