@@ -69,9 +69,9 @@ def test_column_index_of_a_plane_with_more_than_4096_block_columns():
 
 
 def test_column_index_of_planes_with_more_than_64_block_rows():
-    """Class matrices of more than 64 block rows take the three-launch path (one wave per block column, 64 block rows
-    per ballot step): 130 rows = two full steps and a ragged one, 71 columns = a ragged last work-group, an empty and a
-    completely full column, two planes."""
+    """One launch, a wave per block column, 64 block rows per ballot step: 130 rows = two full steps and a ragged one, 71
+    columns = a ragged last work-group, an empty and a completely full column, two planes.  (Class matrices past the one launch
+    are in test_gpu_class_index.py.)"""
     bbm = _bbm()
     from paper_2409_15097_amd.binding import BlockIndex
     rng = np.random.default_rng(43)

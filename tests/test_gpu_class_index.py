@@ -56,3 +56,53 @@ def test_rows_of_15_blocks_cost_what_rows_of_16_do():
         idx = index_of_classes(_classes(256, n, n))
         t[n] = [device_us(lambda: build(idx)) for build in (bbm.bbm_build_index, bbm.bbm_build_col_index)]
     assert t[15][0] < 1.4 * t[16][0] and t[15][1] < 1.6 * t[16][1], t
+
+
+def _with_long_lines(Mb, nbr, nbc, density, seed=0):
+    """Short lists but for a few full rows and columns in different planes (lines that the schedules cut), an empty column and
+    an empty row."""
+    rng = np.random.default_rng(nbr + nbc + seed)
+    cls = _classes(Mb, nbr, nbc, density, seed)
+    cls[:, nbr // 3] = 0
+    cls[:, :, nbc // 5] = 0
+    for m in range(Mb):
+        cls[m, rng.integers(0, nbr, 2)] = 1 + m % 2
+        cls[m, :, rng.integers(0, nbc, 2)] = 2 - m % 2
+    return cls
+
+
+# by rows: list and schedule in the second of two launches, from 128 KiB of classes up to 1024 rows a plane and 4096 in all
+@pytest.mark.parametrize("Mb,nbr,nbc,density", [
+    (3, 199, 256, 0.02),           # lists of about 8: threshold at its floor, rows in launch-order groups of 4, the last one short
+    (3, 199, 256, 0.6),            # long lists: rows ranked singly
+    (4, 1024, 40, 0.05),           # the most rows
+    (2, 130, 1100, 0.01)])         # lists over many ballot steps
+def test_list_and_schedule_in_the_second_launch(Mb, nbr, nbc, density):
+    assert Mb * nbr * nbc > 128 << 10 and nbr <= 1024 and Mb * nbr <= 4096      # past the one launch, within the two
+    cls = _with_long_lines(Mb, nbr, nbc, density)
+    got = _check(cls, fused=True)
+    assert (got["sched"][1] == 32) == (density < 0.1 and nbc < 1000)            # the split threshold: at its floor, or above
+    assert got["sched"][0] > 0 or density > 0.1                                 # rows were cut into parts
+    _check(cls, fused=False)                                                    # the same in the separate kernels
+
+
+# by columns: count, scan, fill and schedule in launches of their own, from 256 KiB of classes or 4096 columns on
+@pytest.mark.parametrize("Mb,nbr,nbc,density", [
+    (3, 330, 300, 0.02), (3, 330, 300, 0.5), (2, 70, 2100, 0.05), (3, 200, 1500, 0.03), (2, 2, 4097, 0.3), (1, 40, 8200, 0.02),
+    (70, 2, 65, 0.5)])
+def test_columns_in_several_launches(Mb, nbr, nbc, density):
+    assert Mb * nbc > 4096 or Mb * nbr * nbc > 256 << 10
+    cls = _with_long_lines(Mb, nbr, nbc, density)
+    got = _check(cls, fused=True)
+    if nbr >= 40 and density < 0.1:
+        assert got["col_sched"][0] > 0                                          # columns were cut into parts
+
+
+def test_column_index_past_4096_columns_costs_little_more():
+    """With one wave scanning a plane's counts, 8192 columns took 4.2 times as long as the one launch of 4096; now 1.4 times."""
+    bbm = _bbm()
+    t = []
+    for nbc in (4096, 8192):
+        idx = index_of_classes(_classes(1, 16, nbc))
+        t.append(device_us(lambda: bbm.bbm_build_col_index(idx)))
+    assert t[1] < 2.5 * t[0], t

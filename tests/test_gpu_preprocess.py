@@ -50,10 +50,10 @@ def test_index_bit_exact_ragged_sizes(N, Br, Bc):
     rng = np.random.default_rng(N)
     blk = masks.random_blocks(64 * (-(-N // 64)), N, blk=32, p_empty=0.35, p_full=0.4)[0][:N, :N]
     mask = (blk * rng.integers(1, 255, blk.shape, dtype=np.uint8)).astype(np.uint8)[None]
-    idx = _run(mask, Br, Bc)                       # rows not 16-byte aligned unless N % 16 == 0: byte path
+    idx = _run(mask, Br, Bc)                       # rows that start at any byte unless N % 16 == 0
     assert_index_equal(index_to_numpy(idx), mask, Br, Bc)
     stride = 16 * (-(-N // 16)) + 16
-    idx = _run(mask, Br, Bc, row_stride=stride, fused=False)    # padded, aligned rows: vector path with a ragged tail
+    idx = _run(mask, Br, Bc, row_stride=stride, fused=False)    # padded, aligned rows with a ragged tail
     assert_index_equal(index_to_numpy(idx), mask, Br, Bc)
 
 
@@ -106,9 +106,9 @@ def test_index_bit_exact_full_size(name):
 @pytest.mark.parametrize("Mb,N,Br,kind", [(3, 6000, 64, "window"), (2, 9000, 128, "packed"), (1, 14000, 128, "graph"), (5, 3333, 32, "window"),
                                           (2, 8192, 64, "blocks"), (1, 12000, 128, "window")])
 def test_mid_size_class_matrices_list_and_schedule_in_one_launch(Mb, N, Br, kind):
-    """More than 256 (block row, chunk) pairs and at most 1024 block rows per plane: the one-call index stage takes the
-    general path, whose second launch fills the lists and writes the schedule.  Short rows (ranked in groups of four),
-    long rows (ranked singly), rows the schedule cuts, several planes; the two-call stage runs the separate kernels."""
+    """Class matrices of 17 to 33 KB, built in one launch by either entry point.  Short rows (ranked in groups of four), long rows
+    (ranked singly), rows the schedule cuts, several planes.  (Larger ones, whose second launch fills the lists and writes the
+    schedule, are in test_gpu_class_index.py.)"""
     rng = np.random.default_rng(N + Br)
     i, j = np.arange(N)[:, None], np.arange(N)[None, :]
     mask = np.zeros((Mb, N, N), dtype=np.uint8)
