@@ -219,7 +219,7 @@ extern "C" __attribute__((visibility("default"))) int bbm_build_col_index(const 
   if (nbr * nbc >= (1ll << 31) || Mb >= (1ll << 31)) return fail(BBM_EINVAL, "bbm_build_col_index: nbr*nbc and Mb must be below 2^31");
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (line_index_fits(true, Mb, nbr, nbc)) {
-    const auto kernel = nbc < 16 ? line_index_kernel<true, true> : line_index_kernel<true, false>;
+    const auto kernel = nbc < 16 ? line_index_kernel<true, kLineShort> : line_index_kernel<true, kLineNormal>;
     kernel<<<(unsigned)ceil_div(Mb * nbc, kLineWaves), kLineWaves * 64, 0, st>>>(
         blk_class, (int)Mb, (int)nbr, (int)nbc, col_ptr, row_idx, col_sched, nullptr, nullptr, nullptr, nullptr, nullptr);
     return launch_status("bbm_build_col_index(one launch)");

@@ -416,8 +416,11 @@ bool launch_one_kernel(const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_
                        int32_t* sched, int32_t* offset, int32_t* total_ones, int32_t* nz_lo, int32_t* nz_hi, int32_t* nz_cnt,
                        hipStream_t s) {
   if (!bbm::line_index_fits(false, Mb, nbr, nbc)) return false;
-  const auto kernel = nbc < 16 ? bbm::line_index_kernel<false, true> : bbm::line_index_kernel<false, false>;
-  kernel<<<(unsigned)bbm::ceil_div(Mb * nbr, bbm::kLineWaves), bbm::kLineWaves * 64, 0, s>>>(
+  const bool strips = !offset && nbc >= bbm::kLineLongFrom;
+  const auto kernel = strips ? bbm::line_index_kernel<false, bbm::kLineLong>
+                      : nbc < 16 ? bbm::line_index_kernel<false, bbm::kLineShort> : bbm::line_index_kernel<false, bbm::kLineNormal>;
+  const int64_t units = Mb * nbr * (strips ? bbm::ceil_div(nbc, bbm::kLineStrip) : 1);
+  kernel<<<(unsigned)bbm::ceil_div(units, bbm::kLineWaves), bbm::kLineWaves * 64, 0, s>>>(
       blk_class, (int)Mb, (int)nbr, (int)nbc, row_ptr, col_idx, sched, offset, total_ones, nz_lo, nz_hi, nz_cnt);
   return true;
 }

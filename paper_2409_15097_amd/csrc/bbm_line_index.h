@@ -147,26 +147,38 @@ inline bool line_index_fits(bool cols, int64_t Mb, int64_t nbr, int64_t nbc) {
 }
 
 // COLS = false: lines are block rows (`ptr` = row_ptr, `list` = col_idx); true: block columns (col_ptr, row_idx).
-// SHORT: class rows of fewer than 16 blocks, which are counted another way.
+// KIND: kLineShort: class rows of fewer than 16 blocks, which are counted another way.  kLineLong: block rows of kLineLongFrom
+// blocks and more whose run index is not asked for: a wave takes a strip of kLineStrip blocks of a row instead of the
+// whole row, and the counts are kept by strip (one wave per row: 1 x 16384 blocks 58 us, 2 x 8192 32, 1 x 2000 10.1,
+// 1 x 1024 6.9; strips: 7.0, 6.8, 6.4, 6.0).  With a run index a row is walked by one wave, which finds it on the way.
 // `sched` and the five arrays of the run index (block rows only) may be NULL.
-template <bool COLS, bool SHORT>
+enum { kLineNormal = 0, kLineShort = 1, kLineLong = 2 };
+constexpr int kLineLongFrom = 1024, kLineStrip = 512;
+constexpr int kLineMaxStrips = (int)(kLineMaxBytesRows / kLineStrip + kLineMaxBytesRows / kLineLongFrom);  // whole strips + a partial one a row
+template <bool COLS, int KIND>
 __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8_t* __restrict__ cls, int Mb, int nbr, int nbc,
                                                                      int32_t* __restrict__ ptr, uint32_t* __restrict__ list,
                                                                      int32_t* __restrict__ sched, int32_t* __restrict__ offset,
                                                                      int32_t* __restrict__ total_ones, int32_t* __restrict__ nz_lo,
                                                                      int32_t* __restrict__ nz_hi, int32_t* __restrict__ nz_cnt) {
-  __shared__ int len_s[kLineMaxLines];
+  constexpr bool SHORT = KIND == kLineShort, LONG = KIND == kLineLong;
+  static_assert(!(COLS && LONG), "strips are of block rows");
+  __shared__ int len_s[LONG ? kLineMaxBytesRows / kLineLongFrom : kLineMaxLines];
+  __shared__ int strip_s[LONG ? kLineMaxStrips : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int L = COLS ? nbc : nbr, depth = COLS ? nbr : nbc;  // lines per plane, blocks per line
   const int nlines = Mb * L;
-  const int line = (int)blockIdx.x * kLineWaves + wave;      // this wave's line (waves past the last only count)
+  const int S = LONG ? (depth + kLineStrip - 1) / kLineStrip : 1;  // strips of a line
+  const int unit = (int)blockIdx.x * kLineWaves + wave;      // this wave's strip, or line (waves past the last only count)
+  const int line = LONG ? unit / S : unit, seg = LONG ? unit - line * S : 0;
   const int own = min(line, nlines - 1);
   const int m = own / L, i = own - m * L;
+  const int first_block = LONG ? seg * kLineStrip : 0, past_block = LONG ? min(depth, first_block + kLineStrip) : depth;
   const uint8_t* const mine = cls + (int64_t)m * nbr * nbc + (COLS ? i : (int64_t)i * nbc);
   const int step = COLS ? nbc : 1;                           // bytes from one block of the line to the next
-  auto own_block = [&](int base) { return base + lane < depth ? mine[(int64_t)(base + lane) * step] : (uint8_t)0; };
-  uint8_t next = own_block(0);  // asked for before the counting
+  auto own_block = [&](int base) { return base + lane < past_block ? mine[(int64_t)(base + lane) * step] : (uint8_t)0; };
+  uint8_t next = own_block(first_block);  // asked for before the counting
 
   // ---- non-zero blocks of every line
   const int C16 = (nbc + 15) / 16;  // 16-byte chunks of a class row; the last one is read as the row's last 16 bytes
@@ -199,6 +211,34 @@ __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8
 #pragma unroll 1
         for (int k = r; k < re; ++k, b >>= nbc) len_s[k] = __popc(b & row_bits);
       }
+    }
+  } else if (LONG) {
+    constexpr int kLanes = kLineStrip / 16, kFly = 4, kPer = 64 / kLanes;  // lanes of a strip, loads in flight, strips of a load
+    for (int u0 = wave * kPer + lane / kLanes; u0 - lane / kLanes < nlines * S; u0 += kFly * kLineWaves * kPer) {
+      int cnt[kFly];
+#pragma unroll
+      for (int f = 0; f < kFly; ++f) {
+        const int u = min(u0 + f * kLineWaves * kPer, nlines * S - 1), r = u / S;
+        const int c = (u - r * S) * kLineStrip + 16 * (lane % kLanes), at = min(c, nbc - 16);
+        const u32x4_any x = *reinterpret_cast<const u32x4_any*>(cls + r * nbc + at);
+        cnt[f] = c < nbc ? __popc(nz_bits16(x) >> (c - at)) : 0;
+      }
+#pragma unroll
+      for (int d = 1; d < kLanes; d <<= 1) {
+#pragma unroll
+        for (int f = 0; f < kFly; ++f) cnt[f] += __shfl_xor(cnt[f], d);
+      }
+      if (lane % kLanes == 0) {
+#pragma unroll
+        for (int f = 0; f < kFly; ++f)
+          if (u0 + f * kLineWaves * kPer < nlines * S) strip_s[u0 + f * kLineWaves * kPer] = cnt[f];
+      }
+    }
+    __syncthreads();
+    for (int b = tid; b < nlines; b += kLineWaves * 64) {
+      int sum = 0;
+      for (int k = 0; k < S; ++k) sum += strip_s[b * S + k];
+      len_s[b] = sum;
     }
   } else if (!COLS) {
     int lpr = 1;  // lanes per row
@@ -300,7 +340,7 @@ __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8
   nonempty = wave_sum(nonempty);
   const int mean = nonempty > 0 ? (total + nonempty - 1) / nonempty : 0;
   const int T = max(COLS ? kColSchedMinSplit : kSchedMinSplit, 2 * mean);
-  if (lane == 0) {
+  if (lane == 0 && seg == 0) {
     ptr[(int64_t)m * (L + 1) + i] = start;
     if (i == L - 1) ptr[(int64_t)m * (L + 1) + L] = start + n;
   }
@@ -321,14 +361,14 @@ __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8
     }
     q = wave_sum(q);
     rho = wave_sum(rho);
-    if (line == 0) {
+    if (line == 0 && seg == 0) {
       all_parts = wave_sum(all_parts);
       all_cut = wave_sum(all_cut);
       if (lane < kSchedPartBase)
         sched[lane] = lane == kSchedNParts ? all_parts : lane == kSchedSplitT ? T : lane == kSchedNCutRows ? all_cut : 0;
     }
     parts = sched + kSchedPartBase + (int64_t)kSchedPartInts * q;
-    for (int k = lane; k < np; k += 64) {
+    for (int k = lane; k < (seg == 0 ? np : 0); k += 64) {
       int32_t* rec = parts + kSchedPartInts * k;
       rec[0] = line;
       rec[1] = start + k * chunk;
@@ -343,9 +383,11 @@ __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8
   // the list; the lane that writes the entry a part starts with also leaves it in the part's record
   uint32_t* const out = list + (int64_t)m * nbr * nbc + start;
   int written = 0, first = -1;
+  if (LONG)
+    for (int k = 0; k < seg; ++k) written += strip_s[line * S + k];
   WaveRunScan rs;
 #pragma unroll 1  // short code: at this length of a launch, fetching instructions is a good part of it
-  for (int base = 0; base < depth; base += 64) {
+  for (int base = first_block; base < past_block; base += 64) {
     const uint8_t c = next;
     next = own_block(base + 64);
     const uint64_t nz = __ballot(c != BBM_BLOCK_EMPTY);
@@ -374,7 +416,7 @@ __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8
       nz_cnt[line] = rs.cnt;
     }
   }
-  if (!sched) return;
+  if (!sched || (LONG && first == -1 && (n > 0 || seg > 0))) return;  // the record is left to the wave that has the line's first entry
 
   // launch-order record: groups of gsz lines by their longest list, longest first (ties: the higher group first); inside
   // a group the longest line first (ties: the higher line first)

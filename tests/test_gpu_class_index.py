@@ -71,6 +71,32 @@ def _with_long_lines(Mb, nbr, nbc, density, seed=0):
     return cls
 
 
+@pytest.mark.parametrize("Mb,nbr,nbc,density", [
+    (1, 1, 1023, 0.3), (1, 1, 1024, 0.3), (1, 1, 1025, 0.9), (3, 2, 1535, 0.3), (1, 3, 1536, 0.02), (5, 3, 1551, 0.001), (1, 128, 1024, 0.05),
+    (2, 16, 4095, 0.1), (1, 1, 131072, 0.01)])
+def test_long_rows_listed_in_strips(Mb, nbr, nbc, density):
+    """The list without the run index, rows of 1024 blocks and more: strips that are full, partial, empty, and empty up to
+    the last one; parts that begin in any strip; the largest class matrix of the one launch."""
+    cls = _classes(Mb, nbr, nbc, density)
+    cls[0, 0, :nbc - 1] = 0
+    cls[0, 0, -1] = 2
+    cls[-1, -1, nbc // 3: nbc // 2] = 1
+    if nbr > 2:
+        cls[-1, 1] = 0                                                          # an empty row
+        cls[0, 2] = 2                                                           # a full one, cut into parts
+    _check(cls, fused=False)
+
+
+def test_long_rows_are_not_walked_by_one_wave():
+    """A row of 16384 blocks, walked by one wave, took 8.4 times as long as one of 1024; in strips 1.2 times."""
+    bbm = _bbm()
+    t = []
+    for nbc in (1024, 16384):
+        idx = index_of_classes(_classes(1, 1, nbc))
+        t.append(device_us(lambda: bbm.bbm_build_sparse_index(idx)))
+    assert t[1] < 3 * t[0], t
+
+
 # by rows: list and schedule in the second of two launches, from 128 KiB of classes up to 1024 rows a plane and 4096 in all
 @pytest.mark.parametrize("Mb,nbr,nbc,density", [
     (3, 199, 256, 0.02),           # lists of about 8: threshold at its floor, rows in launch-order groups of 4, the last one short
