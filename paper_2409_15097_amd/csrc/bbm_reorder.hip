@@ -23,6 +23,7 @@ constexpr int kRounds = 48;                 // parallel rounds (one breadth-firs
 constexpr int kRankChunk = 2048;            // keys of a level staged in LDS at a time
 constexpr int kRankPerThread = 4;           // keys a thread ranks per sweep
 constexpr int kBatch = 8;                   // row words a thread of the level walk has in flight
+constexpr int64_t kSmallMaskBytes = 512 * 512;  // masks up to here are permuted a byte per lane
 
 // 4 mask bytes -> 4 bits (bit t = byte t non-zero).
 __device__ __forceinline__ uint32_t nz_nibble(uint32_t x) {
@@ -423,7 +424,18 @@ __global__ __launch_bounds__(kOrderThreads) void rcm_finish_kernel(const uint64_
   }
 }
 
-// out[m][i][j] = mask[m][perm[i]][perm[j]].  One work-group per R output rows: it stages the R source rows in LDS, byte c of
+// out[m][i][j] = mask[m][perm[i]][perm[j]], a byte per lane, for masks that are all latency: two dependent reads and a store.
+__global__ __launch_bounds__(256) void permute_small_mask_kernel(const uint8_t* __restrict__ mask, int N, int64_t row_stride,
+                                                                 const int32_t* __restrict__ perm, uint8_t* __restrict__ out) {
+  const int j = blockIdx.x * 64 + (threadIdx.x & 63), i = blockIdx.y * 4 + (threadIdx.x >> 6);
+  const int64_t m = blockIdx.z;
+  if (i >= N || j >= N) return;
+  // entries of perm outside [0, N) are clamped: a wrong permutation gives a wrong mask, never a wild access
+  const int pi = min(max(perm[i], 0), N - 1), pj = min(max(perm[j], 0), N - 1);
+  out[(m * N + i) * N + j] = mask[(m * N + pi) * row_stride + pj];
+}
+
+// The same for N >= 16.  One work-group per R output rows: it stages the R source rows in LDS, byte c of
 // all R rows side by side, so that one LDS read delivers column perm[j] of all of them, then gathers 16 columns per lane
 // and turns the R-byte columns into 16-byte pieces of R rows.  Rows of any length and alignment: the last piece of a row
 // is moved back to end with the row (bytes handled twice get the same value).
@@ -441,11 +453,6 @@ __global__ __launch_bounds__(1024) void permute_mask_kernel(const uint8_t* __res
   for (int r = 0; r < R; ++r)  // entries of perm outside [0, N) are clamped: a wrong permutation gives a wrong mask, never a wild access
     src[r] = mask + (m * N + min(max(perm[min(i0 + r, N - 1)], 0), N - 1)) * row_stride;
   uint8_t* const dst = out + (m * N + i0) * (int64_t)N;
-  if (N < 16) {
-    for (int x = tid; x < R * N; x += NT)
-      if (i0 + x / N < N) dst[x] = mask[(m * N + min(max(perm[i0 + x / N], 0), N - 1)) * row_stride + min(max(perm[x % N], 0), N - 1)];
-    return;
-  }
   for (int c = 16 * tid; c < N; c += 16 * NT) {
     const int at = min(c, N - 16);
     u32x4_any x[R];
@@ -605,6 +612,11 @@ extern "C" __attribute__((visibility("default"))) int bbm_permute_mask(const uin
   if (N > kMaxNodes || Mb > 65535) return fail(BBM_EUNSUPPORTED, "bbm_permute_mask: N=%lld exceeds %d or Mb=%lld exceeds 65535", (long long)N, kMaxNodes, (long long)Mb);
   if (row_stride_bytes < N) return fail(BBM_EINVAL, "bbm_permute_mask: row_stride_bytes=%lld < N=%lld", (long long)row_stride_bytes, (long long)N);
   hipStream_t s = static_cast<hipStream_t>(stream);
+  // a byte per lane / rows staged in LDS, us: 250^2 2.2 / 2.8, 512^2 2.3 / 2.7, 700^2 2.7 / 2.8, 1024^2 3.2 / 2.8
+  if (N < 16 || Mb * N * N <= kSmallMaskBytes) {
+    permute_small_mask_kernel<<<dim3((unsigned)ceil_div(N, 64), (unsigned)ceil_div(N, 4), (unsigned)Mb), 256, 0, s>>>(mask, (int)N, row_stride_bytes, perm, out);
+    return launch_status("bbm_permute_mask");
+  }
   // four rows a work-group as long as they fit the 160 KiB of LDS (up to 40960 columns), two up to kMaxNodes: see the kernel
   const size_t cols = (size_t)(N + 15) / 16 * 16;
   const unsigned threads = (unsigned)std::min<size_t>(1024, (cols / 16 + 63) / 64 * 64);

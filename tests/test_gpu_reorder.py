@@ -70,7 +70,7 @@ def test_rcm_order_matches_oracle(name, A):
 def test_rcm_order_with_a_padded_row_stride_and_unaligned_rows():
     bbm = _bbm()
     A = _sym(150, 6, 0.03)
-    buf = torch.zeros((150, 173), dtype=torch.uint8, device="cuda")       # stride 173: the byte-wise path
+    buf = torch.zeros((150, 173), dtype=torch.uint8, device="cuda")       # stride 173: rows that start at any byte
     buf[:, :150] = torch.from_numpy(A).cuda()
     perm = bbm.bbm_rcm_order(buf[:, :150])
     torch.cuda.synchronize()
@@ -88,7 +88,9 @@ def test_rcm_order_at_the_edges_of_the_packing(N):
 
 
 @pytest.mark.parametrize("N,stride,planes", [(1, 1, 1), (3, 3, 2), (15, 16, 1), (16, 16, 3), (17, 17, 2), (31, 40, 1), (1001, 1001, 1),
-                                             (1030, 1040, 2), (40960, 40960, 1), (40961, 40961, 1)])
+                                             (1030, 1040, 2), (40960, 40960, 1), (40961, 40961, 1),
+                                             (10, 12, 3000), (512, 512, 1), (513, 520, 1),  # the largest a byte per lane, the first in LDS
+                                             (16, 16, 1030), (17, 17, 910), (31, 40, 300), (63, 63, 70)])  # short rows in LDS
 def test_permute_mask_at_the_edges_of_its_pieces(N, stride, planes):
     """Byte values, not only 0 and 1; rows that end inside a piece; the last size that takes four rows and the first of two."""
     bbm = _bbm()
