@@ -505,10 +505,6 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   }
 }
 
-// A work-group barrier that orders LDS accesses alone: requests to global memory, asynchronous copies into LDS among them,
-// stay in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // ------------------------------------------------------------------------------------------------------------------
 // dK, dV
 // ------------------------------------------------------------------------------------------------------------------
@@ -702,9 +698,7 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
           }
         }
       }
-      // P of this step is in LDS (the next step's first barrier comes after its last reader).  Only LDS is waited for:
-      // __syncthreads() also waits for the next sub-tile's copies, requested a moment ago, and exposes their latency.
-      lds_barrier();
+      __syncthreads();  // P of this step is in LDS (the next step's first barrier comes after its last reader)
       if (live) {
         const __bf16* const cols = q_cur + (1 - role) * L::ELEMS;
         if (role != 0) {  // dS = P o dP, rounded to bf16, in place of P
