@@ -101,6 +101,9 @@ def parse():
     ap.add_argument("--operands", action="store_true",
                     help="instead of the benchmark: the matrix-only probe and the dense attention kernel on normal, four-valued and "
                          "constant operands (how much of the gap to the published peak is the chip's clock under load)")
+    ap.add_argument("--stages", action="store_true",
+                    help="instead of the benchmark: microseconds of the preprocessing calls (block reduction, index, ordering, mask "
+                         "permutation) over sizes, from graphs of many calls, so that submitting them costs nothing")
     ap.add_argument("--no-ceilings", action="store_true", help="skip the measured ceilings (matrix-only probe, device copy)")
     ap.add_argument("--B", type=int, default=0, help="with --only-kernel: override the workload's batch size")
     ap.add_argument("--H", type=int, default=0, help="with --only-kernel: override the workload's head count")
@@ -457,6 +460,68 @@ def operand_study(a, bbm, torch):
     return 0
 
 
+def graph_us(torch, calls, repeats=4, replays=10):
+    """Mean microseconds per call of `calls`, captured `repeats` times over in one graph (best of five runs of it)."""
+    for c in calls:
+        c()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(repeats):
+            for c in calls:
+                c()
+    return min(time_gpu(graph.replay, 1, replays) for _ in range(5)) * 1e3 / (repeats * len(calls))
+
+
+def stage_study(a, bbm, torch):
+    """The calls that are bound by latency or by the mask's bytes, each rotating over separate buffers (three; two from
+    200 MB on)."""
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    rows = []
+
+    def report(**row):
+        rows.append(row)
+        print(row, file=sys.stderr, flush=True)
+
+    for Mb, Nq, Nk in ((1, 256, 1280), (2, 2048, 2048), (2, 3001, 3001), (4, 4096, 4096), (1, 9001, 9001), (1, 16384, 16384)):
+        masks = [torch.zeros((Mb, Nq, Nk), dtype=torch.uint8, device="cuda") for _ in range(3 if Mb * Nq * Nk < 200e6 else 2)]
+        for m in masks:                                   # a third of the rows' 64-column blocks full, a third half full
+            kind = torch.rand((Mb, -(-Nq // 64), -(-Nk // 64)), generator=gen, device="cuda").repeat_interleave(64, 2)[:, :, :Nk]
+            for r in range(0, Nq, 64):
+                half = torch.rand((Mb, min(64, Nq - r), Nk), generator=gen, device="cuda") < 0.5
+                k = kind[:, r // 64, None, :]
+                m[:, r:r + 64] = (k < 1 / 3) | ((k < 2 / 3) & half)
+        for Br in (8, 16, 32, 64, 128, 256):
+            idx = [bbm.bbm_build_block_mask_rect(m, Br, 64) for m in masks]
+            report(call="block reduction", Mb=Mb, Nq=Nq, Nk=Nk, Br=Br,
+                   us=graph_us(torch, [lambda m=m, i=i: bbm.bbm_build_block_mask_rect(m, Br, 64, idx=i) for m, i in zip(masks, idx)]))
+        del masks, idx
+    for Mb, nbr, nbc in ((1, 2, 4), (1, 2, 260), (4, 32, 64), (256, 15, 15), (1, 128, 256), (1, 256, 512), (4, 1024, 32), (1, 1, 2000), (1, 2, 8192),
+                         (1, 1, 16384), (3, 330, 300), (1, 512, 512), (1, 512, 1000)):
+        idx = []
+        for _ in range(3):
+            some = torch.rand((Mb, nbr, nbc), generator=gen, device="cuda") < 0.3
+            cls = (torch.randint(1, 3, (Mb, nbr, nbc), generator=gen, device="cuda") * some).to(torch.uint8)
+            idx.append(bbm.BlockIndex(128, 64, Mb, nbr, nbc, 128 * nbr, Nk=64 * nbc, blk_class=cls))
+        torch.cuda.synchronize()
+        report(call="index", Mb=Mb, nbr=nbr, nbc=nbc, **{
+            name: graph_us(torch, [lambda i=i: build(i) for i in idx])
+            for name, build in (("us_with_runs", bbm.bbm_build_index), ("us_list_only", bbm.bbm_build_sparse_index), ("us_columns", bbm.bbm_build_col_index))})
+    for N in (250, 2048, 8192, 16384, 20001, 32768):      # a scattered band: N / 1500 levels and more
+        place = torch.randperm(N, generator=gen, device="cuda")
+        mask = torch.empty((1, N, N), dtype=torch.uint8, device="cuda")
+        for r in range(0, N, 2048):
+            mask[0, r:r + 2048] = (place[r:r + 2048, None] - place[None, :]).abs() <= min(1500, N // 4)
+        perm = bbm.bbm_rcm_order(mask[0])
+        out = torch.empty_like(mask)
+        ws = torch.empty(bbm.bbm_rcm_workspace_bytes(N), dtype=torch.uint8, device="cuda")
+        report(call="ordering and permutation", N=N, us_order=graph_us(torch, [lambda: bbm.bbm_rcm_order(mask[0], perm=perm, workspace=ws)], 2),
+               us_permute=graph_us(torch, [lambda: bbm.bbm_permute_mask(mask, perm, out=out)], 16))
+        del mask, out, ws
+    print(json.dumps({"study": "preprocessing calls", "rows": rows}))
+    return 0
+
+
 def main():
     a = parse()
     if a.gpus != 1:
@@ -475,6 +540,8 @@ def main():
         return scaling_study(a, bbm, torch)
     if a.operands:
         return operand_study(a, bbm, torch)
+    if a.stages:
+        return stage_study(a, bbm, torch)
 
     main_res, main_cfg = measure_mask(bbm, a.workload, a.Br, a.warmup, a.steps, torch, not a.no_backward, not a.no_cold)
     rows = [main_res]
