@@ -92,8 +92,8 @@ int bbm_version(void);
  *
  *   mask             device, uint8 [Mb][N][row_stride_bytes]; element (m, r, c) at
  *                    mask + (m*N + r)*row_stride_bytes + c; any non-zero byte means "query r may attend key c".
- *                    row_stride_bytes >= N.  The fast path needs mask and row_stride_bytes 16-byte aligned;
- *                    other alignments take a slower byte-wise path with identical results.
+ *                    row_stride_bytes >= N.  Any pointer and stride take the same 16-byte loads; rows that start on
+ *                    128-byte lines touch the fewest lines.
  *   Br, Bc           block size; 1 <= Br <= 256; Bc in {16, 32, 64, 128, 256}.
  *   blk_class        device out, uint8 [Mb][nbr][nbc], BBM_BLOCK_* (required).
  *   bin_blk_mat      device out, uint8 [Mb][nbr][nbc], 0/1; may be NULL.
@@ -347,8 +347,8 @@ int bbm_attn_bwd(const void* q, const void* k, const void* v, const void* o, con
  * starts at its unvisited node of minimum degree (ties: smallest index); breadth-first, each level ordered by (position
  * of the node's earliest parent in the ordering, degree, index); the ordering is reversed at the end.
  *
- *   mask             device in, uint8 [N][row_stride_bytes], one plane, row_stride_bytes >= N (16-byte aligned pointer
- *                    and stride take the fast path).
+ *   mask             device in, uint8 [N][row_stride_bytes], one plane, row_stride_bytes >= N (any pointer and stride
+ *                    run the same loads).
  *   perm             device out, int32 [N]: perm[k] = old index of the node placed at position k; the reordered mask is
  *                    mask[perm][:, perm] (bbm_permute_mask), reordered Q/K/V rows are row perm[k] at position k
  *                    (bbm_gather_rows), and O comes back with the inverse (bbm_gather_rows with inverse = 1).

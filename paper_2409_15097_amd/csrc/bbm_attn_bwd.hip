@@ -89,8 +89,9 @@ struct TL {
 // An asynchronous copy of SIZE bytes per lane into LDS, from byte `off` (per lane) of the `bytes` bytes at the wave-uniform p.
 // D = 128 uses the buffer form: the compiler counts the global form as possibly touching LDS through the flat path, and
 // with one in flight it waits for ALL outstanding LDS reads at every use of one, which undoes the reads that run ahead
-// (mfma_ring).  D = 64 keeps the global form and the compiler's order: with both changed a 16384-token window layer went
-// from 408 to 414-435 us, against 2 % gained on a causal layer of 4096 tokens (683 -> 669).
+// (mfma_ring).  D = 64 keeps the global form and the compiler's order: with buffer form and ring together, in both kernels, a
+// 16384-token window layer went from 408 to 414-435 us, against 2 % gained on a causal layer of 4096 tokens (683 -> 669).
+// Neither was measured without the other, nor in one kernel alone.
 template <int D, int SIZE>
 __device__ __forceinline__ void copy_async(const void* p, int bytes, uint32_t off, void* dst) {
   static_assert(SIZE == 16 || SIZE == 4, "the builtins want literal sizes");
@@ -358,13 +359,13 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 #pragma unroll
           for (int t = 0; t < KS; ++t) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(v_cur, kb, t), dof[t], dp, 0, 0, 0);
         } else {
-        mfma_ring<2 * KS, kRing>([&](int n) { return A.row_frag(n & 1 ? v_cur : k_cur, kb, n >> 1); },
-                                 [&](int n, bf16x8 f) {
-                                   if (n & 1)
-                                     dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, dof[n >> 1], dp, 0, 0, 0);
-                                   else
-                                     s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[n >> 1], s, 0, 0, 0);
-                                 });
+          mfma_ring<2 * KS, kRing>([&](int n) { return A.row_frag(n & 1 ? v_cur : k_cur, kb, n >> 1); },
+                                   [&](int n, bf16x8 f) {
+                                     if (n & 1)
+                                       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, dof[n >> 1], dp, 0, 0, 0);
+                                     else
+                                       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[n >> 1], s, 0, 0, 0);
+                                   });
         }
         // element mask where the list cannot rule out zeros: masked scores become -inf, i.e. probability 0
         if ((e0 >> 31) == 0) {

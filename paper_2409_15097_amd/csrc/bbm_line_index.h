@@ -134,11 +134,11 @@ __device__ __forceinline__ uint32_t nz_bits16(u32x4_any x) { return nz_bits4(x.x
 // (16 class bytes per load) into LDS, behind one barrier, and each of its waves then produces one line from those
 // counts: the line's place in its plane, the split threshold, the parts and cut lines before its own and its rank are
 // sums over the counts, spread over the lanes.  One launch; the redundant reads are class bytes x work-groups out of L2.
-// Microseconds a call in a graph, before -> now (before: one work-group with serial loops for small matrices, two
-// launches for larger ones, and two to four launches for the columns), block rows / block columns of 0.3 density:
-// 2 x 4 7.8 -> 3.9 / 5.7 -> 4.5; 2 x 260 10.6 -> 5.5 / 19.0 -> 5.1; 4 planes of 32 x 64 9.5 -> 4.8 / 11.8 -> 5.2;
-// 128 x 256 8.9 -> 6.3 / 16.0 -> 6.5; 256 x 512 12.4 -> 11.1 / 39 -> 8.7.  512 x 512 rows would take 16.0 against 14.5
-// in two launches, columns 11.0 against 39: hence the two limits.
+// Microseconds a call in a graph (bench.py --stages), several launches before -> now, block rows / block columns of 0.3 density:
+// 2 x 4 7.8 -> 3.9 / 5.7 -> 3.1; 2 x 260 13 -> 5.5 / 19 -> 4.7; 4 planes of 32 x 64 9.7 -> 4.9 / 11.7 -> 4.7; 128 x 256 10.7 -> 6.2 /
+// 16 -> 6.0; 256 x 512 16 -> 11.4 / 39 -> 8.4.  The limits, one launch / several: rows of 300 x 450 blocks 13.1 / 15.4, 512 x 512
+// 16.6 / 17.5, 1024 x 160 16.0 / 15.0, 600 x 700 31 / 21, 3 planes of 330 x 300 24.5 / 15.4, 8 of 128 x 256 14.9 / 13.8 (one plane would
+// gain up to 256 KiB, several lose from 128 on); columns of 512 x 512 11.4 / 24.9, 8 planes of 181 x 181 14.7 / 13.9.
 constexpr int kLineWaves = 8;
 constexpr int64_t kLineMaxLines = 4096, kLineMaxBytesRows = 128 << 10, kLineMaxBytesCols = 256 << 10;  // beyond: the multi-launch paths
 

@@ -50,8 +50,10 @@ enum { kStDone = 0, kStLvlLo = 1, kStLvlHi = 2, kStCand = 3, kStInts = 4 };
 typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));  // 16 bytes at any address: one instruction
 
 // One work-group per mask row: bits[row][w] (row-major, bits past N zero), degree[row], parent_pos[row] = "none".
-// Bound by the mask's bytes, which are read once (streaming loads): a lane reads 16 of them, neighbouring lanes
-// neighbouring pieces, four loads in flight, and writes the 16 bits as one piece of a word.  The piece that reaches past
+// Bound by the mask's bytes (N = 32768: 0.20 ms, 6.0 TB/s read and written): a lane reads 16 of them, neighbouring lanes
+// neighbouring pieces, four loads in flight, and writes the 16 bits as one piece of a word.  The loads are streaming ones at
+// every size although the permutation reads the mask again: with ordinary loads, here or in the permutation or in both,
+// ordering + permutation + index of 8192 nodes take 286-294 us (streaming 293), of 16384 490-500 (483), of 32768 1214-1261 (1178).  The piece that reaches past
 // column N is read as the row's last 16 bytes and shifted down, so rows of any length and alignment run the same
 // instructions.
 __global__ __launch_bounds__(kPackThreads) void rcm_pack_kernel(const uint8_t* __restrict__ mask, int N, int64_t row_stride, int W,
@@ -154,7 +156,7 @@ __device__ __forceinline__ int min_degree_unvisited(const int32_t* __restrict__ 
   constexpr int kFly = 4;
   const int lane = tid & 63, wave = tid >> 6;
   unsigned long long best = ~0ull;
-  const int last4 = (N - 1) & ~3;  // degree is a 256-byte aligned array padded to whole 256 bytes: groups of four are readable
+  const int last4 = (N - 1) & ~3;  // degree is 16-byte aligned and padded to whole 256 bytes: groups of four are readable
   for (int i0 = 4 * tid; i0 < N; i0 += 4 * kFly * THREADS) {
     int4 dg[kFly];
     uint64_t vw[kFly];
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(kExpandThreads) void rcm_expand_kernel(const uint64
 // these candidates make; when the expansion found none (a component is finished, or nothing has started yet) it starts
 // the next component at its node of minimum degree.
 // The whole ordering of the 32768-node power-law graph: 1.54 ms with three kernels a round, an atomic per edge and one lane
-// per candidate; 0.61 ms now, of which 0.23 ms are the packing (5.2 TB/s) and about 0.2 ms the rounds left over at its end.
+// per candidate; 0.62 ms now, of which 0.20 ms are the packing and about 0.1 ms the rounds left over at its end (2 us a launch).
 constexpr int kRankWGs = 256, kRankThreads = 256, kRankStage = 8;  // kRankStage keys of a thread's staging share in flight
 __global__ __launch_bounds__(kRankThreads) void rcm_rank_kernel(const int32_t* __restrict__ degree, const int32_t* __restrict__ parent_pos,
                                                                 const int32_t* __restrict__ cand, int32_t* __restrict__ order,
