@@ -9,19 +9,21 @@
 //               kernel): walks the row's list of key tiles, S^T = K Q^T and dP^T = V dO^T with the tile rows as the
 //               A operand, dQ^T += K^T dS^T with K read through transposing LDS reads.  It also computes D_i and
 //               leaves -D_i and -lse_i*log2(e) in the workspace for the second kernel.
-//   dkv kernel  one work-group (2 waves) per block column of 64 keys, one lane per key: walks the column's list of
-//               query blocks in sub-tiles of 64 queries, S = Q K^T and dP = dO V^T with the tile rows as A operand,
+//   dkv kernel  one work-group (4 waves) per block column of 64 keys, one lane per key and query half: walks the column's
+//               list of query blocks in sub-tiles of 64 queries, S = Q K^T and dP = dO V^T with the tile rows as A operand,
 //               dV^T += dO^T P and dK^T += Q^T dS with transposing LDS reads of the same two tiles.
 // Both start the score accumulators at -lse (in exponent units) and the dP accumulators at -D, so that exp2 and one
 // multiplication per element give P and dS.
 #include "bbm_internal.h"
 
 #include <algorithm>
+#include <utility>
 
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -72,6 +74,24 @@ __device__ __forceinline__ float partner_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+template <int V>
+struct IntC {
+  static constexpr int value = V;
+};
+
+// Sum over each group of RC = 8 or 16 consecutive lanes, in all of them.
+template <int RC>
+__device__ __forceinline__ float row_sum(float x) {
+  auto other = [](float v, auto ctrl) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  x += other(x, IntC<0xB1>{});              // lane ^ 1
+  x += other(x, IntC<0x4E>{});              // lane ^ 2
+  x += other(x, IntC<0x141>{});             // mirrored within 8 lanes
+  if constexpr (RC == 16) x += other(x, IntC<0x140>{});  // mirrored within 16 lanes
+  return x;
+}
+
 // LDS layout of a 64-row x D tile, shared by every tile of both kernels.  One asynchronous copy instruction of a wave
 // fills one 1 KiB block with RPB rows that lie NBLK rows apart: row r sits in block r % NBLK at slot r / NBLK; blocks
 // are 1 KiB + 64 B apart, and the 16-byte chunk c of row r sits at chunk position c ^ ((r >> 2) & 3).  With that both
@@ -86,52 +106,62 @@ struct TL {
   static constexpr int ELEMS = NBLK * TBLK;
 };
 
-// An asynchronous copy of SIZE bytes per lane into LDS, from byte `off` (per lane) of the `bytes` bytes at the wave-uniform p.
-// D = 128 uses the buffer form: the compiler counts the global form as possibly touching LDS through the flat path, and
-// with one in flight it waits for ALL outstanding LDS reads at every use of one, which undoes the reads that run ahead
-// (mfma_ring).  D = 64 keeps the global form and the compiler's order: with buffer form and ring together, in both kernels, a
-// 16384-token window layer went from 408 to 414-435 us, against 2 % gained on a causal layer of 4096 tokens (683 -> 669).
-// Neither was measured without the other, nor in one kernel alone.
-template <int D, int SIZE>
-__device__ __forceinline__ void copy_async(const void* p, int bytes, uint32_t off, void* dst) {
-  static_assert(SIZE == 16 || SIZE == 4, "the builtins want literal sizes");
-  auto* const lds = (void __attribute__((address_space(3)))*)dst;
-  if constexpr (D == 128) {
-    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
-    if constexpr (SIZE == 16)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(src, lds, 16, off, 0, 0, 0);
-    else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(src, lds, 4, off, 0, 0, 0);
-  } else {
-    const auto* const src = (const void __attribute__((address_space(1)))*)(static_cast<const char*>(p) + off);
-    if constexpr (SIZE == 16)
-      __builtin_amdgcn_global_load_lds(src, lds, 16, 0, 0);
-    else
-      __builtin_amdgcn_global_load_lds(src, lds, 4, 0, 0);
-  }
+__device__ __forceinline__ uint32_t scalar(uint32_t uniform) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)uniform); }
+
+// Two floats rounded to bf16, the first in the low half; eight of them as a matrix operand.
+__device__ __forceinline__ uint32_t pack(float a, float b) {
+  const bf16x2 v = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ bf16x8 operand(const uint32_t (&w)[4]) {
+  const uint4 v = make_uint4(w[0], w[1], w[2], w[3]);
+  return __builtin_bit_cast(bf16x8, v);
 }
 
-// Asynchronous global -> LDS copy of rows row0 .. row0+63 of a [N][D] matrix.  Lane l of a copy instruction lands at
-// block base + 16*l, i.e. slot l / RC, chunk position l % RC.  Rows past N re-read row N-1 (callers make sure such
-// rows contribute nothing).
-template <int D, int NW>
-__device__ __forceinline__ void tile_copy_async(const __bf16* __restrict__ src, int64_t row0, int64_t N, __bf16* dst, int wave, int lane) {
-  using L = TL<D>;
-  constexpr int LPW = L::NBLK / NW;
-  static_assert(L::NBLK % NW == 0, "tile must split evenly over the waves");
-  const int slot = lane / L::RC, pos = lane % L::RC;
-  const int64_t first = min(row0, N - 1);  // a tile that starts past N re-reads row N-1 throughout
-  const int last = (int)min<int64_t>(63, N - 1 - first);
-  const __bf16* tile = src + first * D;
-#pragma unroll
-  for (int n = 0; n < LPW; ++n) {
-    const int blk = n * NW + wave;
-    const int row = blk + L::NBLK * slot;
-    const int c = pos ^ ((row >> 2) & 3);
-    const uint32_t off = (uint32_t)(min(row, last) * D + c * 8) * 2u;
-    copy_async<D, 16>(tile, (last + 1) * D * 2, off, dst + blk * L::TBLK);
-  }
+// The lane's number, found anew at each use: for what is needed once a step and not worth a register throughout the loop.
+__device__ __forceinline__ int lane_now() {
+  int x;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
+  return x;
 }
+
+// An asynchronous copy of SIZE bytes per lane into LDS, from byte `off` (per lane) of the `bytes` bytes at the wave-uniform p;
+// lanes whose bytes lie past those write zeros (the bounds check of the buffer resource).  The buffer form also matters to the
+// compiler: it counts the global form as possibly touching LDS through the flat path, and with one in flight it waits for ALL
+// outstanding LDS reads at every use of one, which undoes the reads that run ahead (mfma_ring).
+template <int SIZE>
+__device__ __forceinline__ void copy_async(const void* p, int bytes, uint32_t off, void* dst) {
+  static_assert(SIZE == 16 || SIZE == 4, "the builtin wants literal sizes");
+  auto* const lds = (void __attribute__((address_space(3)))*)dst;
+  const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)scalar(bytes), 0x00027000);
+  if constexpr (SIZE == 16)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, lds, 16, off, 0, 0, 0);
+  else
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, lds, 4, off, 0, 0, 0);
+}
+
+// Asynchronous global -> LDS copy of the first `rows` (0 .. 64) of the 64 rows of a [..][D] matrix at `tile`; zeros for the rest.
+// This is copy instruction n of the NBLK / NW of a wave.  Lane l of a copy instruction lands at block base + 16*l, i.e. slot
+// l / RC, chunk position l % RC.  One address register per lane (`base`, from tile_copy_base) serves all instructions: the XOR
+// of the chunk position splits into a part of the lane and one of the block.
+template <int D, int NW>
+__device__ __forceinline__ uint32_t tile_copy_base(int wave, int lane) {
+  using L = TL<D>;
+  static_assert(L::NBLK % 16 == 0 || L::NBLK == 8, "(row >> 2) & 3 must be the XOR of the lane's part and the block's part");
+  const int slot = lane / L::RC, pos = lane % L::RC;
+  return (uint32_t)((wave + L::NBLK * slot) * D + (pos ^ ((L::NBLK * slot >> 2) & 3)) * 8) * 2u;
+}
+template <int D, int NW>
+__device__ __forceinline__ void tile_copy_piece(const __bf16* __restrict__ tile, int rows, uint32_t base, __bf16* dst, int n, int wave) {
+  using L = TL<D>;
+  static_assert(L::NBLK % NW == 0, "tile must split evenly over the waves");
+  const int blk = n * NW + wave;
+  asm volatile("" : "+v"(base));  // one register throughout the tile loop, not one per block
+  copy_async<16>(tile, rows * D * 2, (base ^ (uint32_t)(((blk >> 2) & 3) << 4)) + n * NW * D * 2, dst + blk * L::TBLK);
+}
+// How many of the 64 rows from row0 on lie below N.  (A scalar by force: the compiler clamps in a vector register, and a buffer
+// resource in one costs a loop around every copy.)
+__device__ __forceinline__ int rows_of_tile(int row0, int N) { return (int)scalar(max(0, min(64, N - row0))); }
 
 // Per-lane base addresses (in elements) of the two read patterns.
 template <int D>
@@ -169,22 +199,29 @@ struct TileAddr {
   }
 };
 
-// A chain of COUNT matrix instructions whose LDS operands are read R instructions ahead: load(n) reads the operand of
-// instruction n, mul(n, operand) issues it.  Left alone the compiler reads one operand, waits, multiplies and only then
-// reads the next, so that every matrix instruction stands behind a whole LDS latency; the scheduling barriers keep it
-// from going back to that order where registers are short.
-template <int COUNT, int R, typename Load, typename Mul>
-__device__ __forceinline__ void mfma_ring(Load load, Mul mul) {
+// A chain of COUNT matrix instructions (or groups of them) whose LDS operands are read R instructions ahead: load(n) reads the
+// operand of instruction n, mul(n, operand) issues it, between(n) is whatever is to be issued behind it.  Left alone the
+// compiler reads one operand, waits, multiplies and only then reads the next, so that every matrix instruction stands behind
+// a whole LDS latency; the scheduling barriers keep it from going back to that order where registers are short.
+// (n comes as a type, IntC<n>: the chain has to be unrolled whole, longer than the compiler unrolls a loop.)
+template <typename F, int... N>
+__device__ __forceinline__ void for_each_n(F f, std::integer_sequence<int, N...>) {
+  (f(IntC<N>{}), ...);
+}
+template <int COUNT, int R, typename Load, typename Mul, typename Between>
+__device__ __forceinline__ void mfma_ring(Load load, Mul mul, Between between) {
   bf16x8 f[R];
-#pragma unroll
-  for (int n = 0; n < R; ++n) f[n] = load(n);
+  for_each_n([&](auto n) { f[decltype(n)::value] = load(n); }, std::make_integer_sequence<int, R>{});
   __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int n = 0; n < COUNT; ++n) {
-    mul(n, f[n % R]);
-    if (n + R < COUNT) f[n % R] = load(n + R);
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  for_each_n(
+      [&](auto i) {
+        constexpr int n = decltype(i)::value;
+        mul(i, f[n % R]);
+        if constexpr (n + R < COUNT) f[n % R] = load(IntC<n + R>{});
+        between(i);
+        __builtin_amdgcn_sched_barrier(0);
+      },
+      std::make_integer_sequence<int, COUNT>{});
 }
 
 // acc * mult, rounded to bf16, to rows row0 .. of a [N][D] matrix: lane l holds row l%32 of the wave's 32-row slab,
@@ -192,8 +229,11 @@ __device__ __forceinline__ void mfma_ring(Load load, Mul mul) {
 // that the global stores are whole rows: 16-byte chunk ch of row r sits at chunk position ch ^ (r % RC).
 template <int D>
 __device__ __forceinline__ void store_slab(const f32x16 (&acc)[D / 32], float mult, __bf16* stage, __bf16* __restrict__ dst,
-                                           int64_t row0, int64_t N, int lane) {
+                                           int row0, int N, int lane) {
   using L = TL<D>;
+  // behind an optimisation barrier: otherwise the staging addresses are hoisted out of the loop over items and stay in
+  // registers (or in scratch memory) throughout the tile loop
+  asm volatile("" : "+v"(lane));
   const int lq = lane & 31, hh = lane >> 5, gro = lane / L::RC, gco = lane % L::RC;
 #pragma unroll
   for (int db = 0; db < D / 32; ++db) {
@@ -204,7 +244,7 @@ __device__ __forceinline__ void store_slab(const f32x16 (&acc)[D / 32], float mu
       *reinterpret_cast<bf16x4*>(stage + lq * D + (((4 * db + g) ^ (lq % L::RC)) * 8) + 4 * hh) = ov;
     }
   }
-  __bf16* og = dst + row0 * D;
+  __bf16* og = dst + (int64_t)row0 * D;
 #pragma unroll
   for (int n = 0; n < 32 / L::RPB; ++n) {
     const int r = n * L::RPB + gro;
@@ -213,10 +253,31 @@ __device__ __forceinline__ void store_slab(const f32x16 (&acc)[D / 32], float mu
   }
 }
 
-template <int V>
-struct IntC {
-  static constexpr int value = V;
-};
+// A parked partial sum: [register / 4][STRIDE lanes][register % 4], 16 bytes a lane and access; `at` = base + 4 * this lane.
+template <int DB, int STRIDE>
+__device__ __forceinline__ void park(float* at, const f32x16 (&acc)[DB]) {
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<float4*>(at + (db * 4 + g) * 4 * STRIDE) = make_float4(acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]);
+}
+template <int DB, int STRIDE>
+__device__ __forceinline__ void add_parked(const float* at, f32x16 (&acc)[DB]) {
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+    for (int g = 0; g < 4; ++g) {
+      const float4 x = *reinterpret_cast<const float4*>(at + (db * 4 + g) * 4 * STRIDE);
+      acc[db][4 * g] += x.x, acc[db][4 * g + 1] += x.y, acc[db][4 * g + 2] += x.z, acc[db][4 * g + 3] += x.w;
+    }
+}
+
+// 16 bytes at p (readable either way), or zeros: masked, since a choice between the two makes the compiler branch per load.
+__device__ __forceinline__ bf16x8 load_or_zero(const __bf16* __restrict__ p, bool ok) {
+  uint4 x = *reinterpret_cast<const uint4*>(p);
+  const uint32_t keep = ok ? 0xffffffffu : 0u;
+  x.x &= keep, x.y &= keep, x.z &= keep, x.w &= keep;
+  return __builtin_bit_cast(bf16x8, x);
+}
 
 // XCD-aware logical work-group id: work-groups are handed to the 8 XCDs round-robin; give each XCD a contiguous range
 // of logical ids so that the work-groups of one head (which share its tensors) meet in one XCD's L2.
@@ -235,6 +296,9 @@ __device__ __forceinline__ int logical_wg(int wg, int total) {
 // statistics.
 // EXACT (softmax scales sharper than 1/sqrt(d)): only the power-of-two part of softmax_scale*log2(e) is folded into
 // the bf16 operand, the rest multiplies the recomputed score inside the exponential, as in the forward kernel.
+// Kernel time with the copies spread, the phases in one chain, one loop for parts and own row and the rows of Q, dO and O fetched
+// whole, against each of these not so: packed sequences of 4096, D = 64, 65.1 -> 55.8 us, of 3001, D = 128, 40.7 -> 35.9; 2 x 32
+// heads of 8192 causal tokens, D = 128, 1470 -> 1400; 4 x 16 of 4096, D = 64, 226 -> 220 (exponentials beside the matrix pipe).
 template <int D, int NW, bool EXACT>
 __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW == 4) ? 3 : 1) void attn_bwd_dq_kernel(const BwdParams P) {
   using L = TL<D>;
@@ -252,11 +316,12 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   __shared__ __attribute__((aligned(16))) __bf16 v_s1[L::ELEMS];
   __shared__ uint32_t tiles_s[kWin + 4];
   __shared__ int item_s[2];
+  __shared__ float delta_s[NW][32];  // <dO, O> of the waves' rows
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const int64_t N = P.N;
+  const int N = (int)P.N;
   const float c = P.qscale;
   const float rr = EXACT ? P.rmul : 1.0f;
   auto ex2 = [&](float x) { return __builtin_amdgcn_exp2f(EXACT ? rr * x : x); };
@@ -268,150 +333,220 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   const __bf16* __restrict__ Vg;
   const uint64_t* __restrict__ mrow;
   bf16x8 qf[KS], dof[KS];
-  f32x16 s_init, dp_init, dq[DB];
+  f32x16 dp_init, dq[DB];
   float nl_lane = 0.0f, nd_lane = 0.0f;
-
-  // this lane's query: Q * scale * log2(e) and dO as B operands, D = <dO, O>, the negated statistics
-  auto begin_item = [&](bool write_stats) {
-    head_off = (int64_t)bh * N * D;
-    Kg = P.k + head_off;
-    Vg = P.v + head_off;
-    const int64_t qrow = (int64_t)i * BR + wave * 32 + lq;
-    const bool q_ok = qrow < N;
-    mrow = P.packed + (int64_t)m * P.W * N + (q_ok ? qrow : 0);
-    float dsum = 0.0f;
-#pragma unroll
-    for (int t = 0; t < KS; ++t) {
-      bf16x8 of;
-      if (q_ok) {
-        const int64_t at = head_off + qrow * D + 16 * t + 8 * hh;
-        qf[t] = *reinterpret_cast<const bf16x8*>(P.q + at);
-        dof[t] = *reinterpret_cast<const bf16x8*>(P.d_o + at);
-        of = *reinterpret_cast<const bf16x8*>(P.o + at);
-      } else {
-        for (int e = 0; e < 8; ++e) qf[t][e] = dof[t][e] = of[e] = (__bf16)0.0f;
-      }
-      for (int e = 0; e < 8; ++e) {
-        dsum += (float)dof[t][e] * (float)of[e];
-        qf[t][e] = (__bf16)((float)qf[t][e] * c);
-      }
-    }
-    const float delta = partner_sum(dsum);
-    const float lse_i = q_ok ? P.lse[(int64_t)bh * N + qrow] : -INFINITY;
-    const float nl = (lse_i == -INFINITY) ? -INFINITY : -lse_i * (kLog2e / rr);
-    if (write_stats && q_ok && hh == 0) {
-      P.nl2[(int64_t)bh * N + qrow] = nl;
-      P.ndelta[(int64_t)bh * N + qrow] = -delta;
-    }
-    nl_lane = nl;
-    nd_lane = -delta;
-    if constexpr (D == 64) {
-      for (int e = 0; e < 16; ++e) {
-        s_init[e] = nl;
-        dp_init[e] = -delta;
-      }
-    }
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-      for (int e = 0; e < 16; ++e) dq[db][e] = 0.0f;
-  };
 
   TileAddr<D> A;
   A.init(lane);
 
   auto tile_of = [](uint32_t e) { return (int)(e & 0x7fffffffu); };
-  uint32_t e0, e1;
+  // e0: this step's list entry, e1: the next one's (as it came from LDS: made a scalar when the step starts)
+  uint32_t e0, e1_v;
   uint64_t mw_nxt = 0;
-  auto request = [&](uint32_t e, __bf16* kd, __bf16* vd) {
-    tile_copy_async<D, NW>(Kg, (int64_t)tile_of(e) * 64, N, kd, wave, lane);
-    tile_copy_async<D, NW>(Vg, (int64_t)tile_of(e) * 64, N, vd, wave, lane);
+  const uint32_t copy_base = tile_copy_base<D, NW>(wave, lane);
+  constexpr int LPW = L::NBLK / NW;  // copy instructions of a wave per tile
+  // Tile e, n = 0 .. 2*LPW-1.  Keys past N come as zeros; their tile is never full, so the mask gives them probability 0.
+  auto copy_piece = [&](uint32_t e, int rows, __bf16* kd, __bf16* vd, int n) {
+    const int64_t at = (int64_t)tile_of(e) * 64 * D;
+    if (n < LPW)
+      tile_copy_piece<D, NW>(Kg + at, rows, copy_base, kd, n, wave);
+    else
+      tile_copy_piece<D, NW>(Vg + at, rows, copy_base, vd, n - LPW, wave);
+  };
+  auto copy_all = [&](uint32_t e, __bf16* kd, __bf16* vd) {
+    const int rows = rows_of_tile(tile_of(e) * 64, N);
+#pragma unroll
+    for (int n = 0; n < 2 * LPW; ++n) copy_piece(e, rows, kd, vd, n);
+  };
+  auto request_mask = [&](uint32_t e) {
     if ((e >> 31) == 0) mw_nxt = mrow[(int64_t)tile_of(e) * N];
   };
 
-  auto step = [&](auto pb, int it) {
+  // One tile: a chain of matrix instructions over its two 32-key halves, S0, dP0, S1, dP1, dQ0, dQ1, with everything else
+  // behind them: the next tile's copies behind S0, the exponentials of a half behind its dP, dS0 behind S1, dS1 behind dQ0.
+  auto step = [&](auto pb, int it) __attribute__((always_inline)) {
     constexpr int PB = decltype(pb)::value;
     const uint64_t mw = mw_nxt;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     __bf16* const k_cur = PB ? k_s1 : k_s0;
-    __bf16* const k_oth = PB ? k_s0 : k_s1;
     __bf16* const v_cur = PB ? v_s1 : v_s0;
+    __bf16* const k_oth = PB ? k_s0 : k_s1;
     __bf16* const v_oth = PB ? v_s0 : v_s1;
-    if (e1 != kNoTile) request(e1, k_oth, v_oth);
+    // The next tile's copies go out one by one between the matrix instructions of this one: requested in one go they fill
+    // the memory pipe's queue, and every wave of the work-group stands there for 700-850 cycles of a step (D = 128).  Behind
+    // the last tile they copy zero rows into buffers that nobody reads any more, cheaper than a branch around each.
+    const uint32_t e1 = scalar(e1_v);
+    const bool more = e1 != kNoTile, partial = (e0 >> 31) == 0;
+    const int rows1 = more ? rows_of_tile(tile_of(e1) * 64, N) : 0;
+    if (more) request_mask(e1);
+    e0 = e1;
+    e1_v = tiles_s[it + 2];
     // a partial tile in which none of this wave's 32 queries sees a key contributes exact zeros: skip it
-    if ((e0 >> 31) != 0 || __ballot(mw != 0ull) != 0ull) {
-      // the two 32-key halves of the tile one after the other (at D = 128 their accumulators do not fit side by side)
+    const bool live = !partial || __ballot(mw != 0ull) != 0ull;
+    if (!live && more) copy_all(e1, k_oth, v_oth);
+    if (!live) return;
+    constexpr int N1 = KS, N2 = 2 * KS, N3 = 3 * KS, N4 = 4 * KS, N5 = N4 + 2 * DB, N6 = N5 + 2 * DB;
+    constexpr int PER = D == 128 ? 4 : 8;  // elements behind a matrix instruction
+    static_assert(PER * (KS - 2) >= 16 && PER * (2 * DB - 2) >= 16, "all 16 must find room");
+    f32x16 s[2], dp[2];
+    uint32_t dsf[2][2][4];  // dS of [half][16-key step], pairs of bf16
+    // The scores start at the negated log-sum-exp, or at -inf, i.e. P = 0, where the mask has no bit.
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+      for (int e = 0; e < 16; ++e) s[kb][e] = nl_lane;
+    if (partial) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
-        f32x16 s, dp;
-        if constexpr (D == 64) {
-          s = s_init;
-          dp = dp_init;
-        } else {  // D = 128: registers are short, the start values are kept as two scalars per lane
-          for (int e = 0; e < 16; ++e) {
-            s[e] = nl_lane;
-            dp[e] = nd_lane;
-          }
-        }
-        if constexpr (D == 64) {
-#pragma unroll
-          for (int t = 0; t < KS; ++t) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(k_cur, kb, t), qf[t], s, 0, 0, 0);
-#pragma unroll
-          for (int t = 0; t < KS; ++t) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(v_cur, kb, t), dof[t], dp, 0, 0, 0);
-        } else {
-          mfma_ring<2 * KS, kRing>([&](int n) { return A.row_frag(n & 1 ? v_cur : k_cur, kb, n >> 1); },
-                                   [&](int n, bf16x8 f) {
-                                     if (n & 1)
-                                       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, dof[n >> 1], dp, 0, 0, 0);
-                                     else
-                                       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[n >> 1], s, 0, 0, 0);
-                                   });
-        }
-        // element mask where the list cannot rule out zeros: masked scores become -inf, i.e. probability 0
-        if ((e0 >> 31) == 0) {
-          const uint32_t w = (uint32_t)(mw >> (32 * kb)) >> (4 * hh);
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int bit = 8 * (e / 4) + (e % 4);
-            const uint32_t keep = (uint32_t)((int32_t)(w << (31 - bit)) >> 31);
-            s[e] = __uint_as_float((__float_as_uint(s[e]) & keep) | (0xff800000u & ~keep));
-          }
-        }
-#pragma unroll
-        for (int u2 = 0; u2 < 2; ++u2) {
-          bf16x8 dsf;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) dsf[e] = (__bf16)(ex2(s[8 * u2 + e]) * dp[8 * u2 + e]);
-#pragma unroll
-          for (int db = 0; db < DB; ++db) dq[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.tr_frag(k_cur, 2 * kb + u2, db), dsf, dq[db], 0, 0, 0);
+        const uint32_t w = (uint32_t)(mw >> (32 * kb)) >> (4 * hh);
+        for (int e = 0; e < 16; ++e) {
+          const uint32_t keep = (uint32_t)((int32_t)(w << (31 - (8 * (e / 4) + e % 4))) >> 31);  // all ones iff the bit is set
+          s[kb][e] = __uint_as_float((__float_as_uint(nl_lane) & keep) | (0xff800000u & ~keep));
         }
       }
     }
-    e0 = e1;
-    e1 = tiles_s[it + 2];
+    auto dp_start = [&](f32x16& acc) {
+      if constexpr (D == 64) {
+        acc = dp_init;
+      } else {  // registers are short: the start value is kept as one scalar per lane
+        for (int e = 0; e < 16; ++e) acc[e] = nd_lane;
+      }
+    };
+    auto exps = [&](int kb, int slot) {
+#pragma unroll
+      for (int e = slot * PER; e < min(16, (slot + 1) * PER); ++e) s[kb][e] = ex2(s[kb][e]);
+    };
+    auto ds = [&](int kb, int slot) {
+#pragma unroll
+      for (int e = slot * PER; e < min(16, (slot + 1) * PER); e += 2)
+        dsf[kb][e / 8][e % 8 / 2] = pack(s[kb][e] * dp[kb][e], s[kb][e + 1] * dp[kb][e + 1]);
+    };
+    mfma_ring<N6, kRing>(
+        [&](auto i) {
+          constexpr int n = decltype(i)::value;
+          if constexpr (n < N4)
+            return A.row_frag(n / KS % 2 ? v_cur : k_cur, n / N2, n % KS);
+          else
+            return A.tr_frag(k_cur, (n - N4) / DB, (n - N4) % DB);
+        },
+        [&](auto i, bf16x8 f) {
+          constexpr int n = decltype(i)::value;
+          if constexpr (n == N1) dp_start(dp[0]);
+          if constexpr (n == N3) dp_start(dp[1]);
+          if constexpr (n < N4 && n / KS % 2 == 0) {
+            s[n / N2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[n % KS], s[n / N2], 0, 0, 0);
+          } else if constexpr (n < N4) {
+            dp[n / N2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, dof[n % KS], dp[n / N2], 0, 0, 0);
+          } else {
+            constexpr int m = n - N4, u = m / DB;
+            dq[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, operand(dsf[u / 2][u % 2]), dq[m % DB], 0, 0, 0);
+          }
+        },
+        [&](auto i) {
+          constexpr int n = decltype(i)::value;
+          constexpr int GAP = 2 * LPW < KS ? KS / (2 * LPW) : 1;  // matrix instructions per copy
+          if constexpr (n % GAP == 0 && n / GAP < 2 * LPW) copy_piece(e1, rows1, k_oth, v_oth, n / GAP);
+          // a product is complete two matrix instructions after its last one was issued
+          if constexpr (n >= N1 + 2 && n < N2) exps(0, n - N1 - 2);
+          if constexpr (n >= N2 + 2 && n < N3) ds(0, n - N2 - 2);
+          if constexpr (n >= N3 + 2 && n < N4) exps(1, n - N3 - 2);
+          if constexpr (n >= N4 + 2 && n < N5) ds(1, n - N4 - 2);
+        });
   };
 
-  // the tiles list[0 .. n_list), window by window
-  auto run_list = [&](const uint32_t* __restrict__ list, int n_list) {
-    for (int w0 = 0; w0 < n_list; w0 += kWin) {
+  // this lane's query: Q * scale * log2(e) and dO as B operands, D = <dO, O>, the negated statistics
+  auto begin_item = [&](bool write_stats) {
+    head_off = (int64_t)bh * N * D;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));  // keeps the addresses out of the loop over items, see store_slab
+    const int wrow = i * BR + wave * 32, qrow = wrow + (ln & 31);
+    const bool q_ok = qrow < N;
+    mrow = P.packed + (int64_t)m * P.W * N + (q_ok ? qrow : 0);
+    // The wave's 32 rows of Q, dO and O are contiguous pieces of memory and are fetched as such, 1 KiB an instruction: a lane
+    // that picks its row up in 16-byte pieces touches 64 cache lines an instruction.  Q goes to a staging slab in the tile
+    // buffers (of parity 1 while at most four waves want one), dO follows through registers, where <dO, O> is formed; chunk c of row r sits at position c ^ (r % RC).
+    __bf16* const stage = (wave / 2 == 0 ? k_s1 : wave / 2 == 1 ? v_s1 : wave / 2 == 2 ? k_s0 : v_s0) + (wave % 2) * 32 * D;
+    const int g_row = ln / L::RC, g_chunk = ln % L::RC, rows = max(0, min(32, N - wrow));
+    bf16x8 gr[32 / L::RPB], orow[32 / L::RPB];
+#pragma unroll
+    for (int n = 0; n < 32 / L::RPB; ++n) {
+      const int r = n * L::RPB + g_row;
+      copy_async<16>(P.q + head_off + (int64_t)wrow * D, rows * D * 2, (uint32_t)(r * D + (g_chunk ^ (r % L::RC)) * 8) * 2u, stage + n * 512);
+      const int64_t at = head_off + (int64_t)(r < rows ? wrow + r : 0) * D + g_chunk * 8;
+      gr[n] = load_or_zero(P.d_o + at, r < rows);
+      orow[n] = load_or_zero(P.o + at, r < rows);
+    }
+#pragma unroll
+    for (int n = 0; n < 32 / L::RPB; ++n) {
+      float x = 0.0f;
+      for (int e = 0; e < 8; ++e) x += (float)gr[n][e] * (float)orow[n][e];
+      x = row_sum<L::RC>(x);
+      if (g_chunk == 0) delta_s[wave][n * L::RPB + g_row] = x;
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's own copies have landed (no other wave touches its slab)
+    auto frag = [&](int t) { return *reinterpret_cast<const bf16x8*>(stage + (ln & 31) * D + ((2 * t + (ln >> 5)) ^ (ln % L::RC)) * 8); };
+#pragma unroll
+    for (int t = 0; t < KS; ++t) {
+      qf[t] = frag(t);
+      for (int e = 0; e < 8; ++e) qf[t][e] = (__bf16)((float)qf[t][e] * c);
+    }
+#pragma unroll
+    for (int n = 0; n < 32 / L::RPB; ++n) {
+      const int r = n * L::RPB + g_row;
+      *reinterpret_cast<bf16x8*>(stage + r * D + (g_chunk ^ (r % L::RC)) * 8) = gr[n];
+    }
+#pragma unroll
+    for (int t = 0; t < KS; ++t) dof[t] = frag(t);
+    const float delta = delta_s[wave][ln & 31];
+    const float lse_i = q_ok ? P.lse[(int64_t)bh * N + qrow] : -INFINITY;
+    const float nl = (lse_i == -INFINITY) ? -INFINITY : -lse_i * (kLog2e / rr);
+    if (write_stats && q_ok && (ln >> 5) == 0) {
+      P.nl2[(int64_t)bh * N + qrow] = nl;
+      P.ndelta[(int64_t)bh * N + qrow] = -delta;
+    }
+    nl_lane = nl;
+    nd_lane = -delta;
+    if constexpr (D == 64)
+      for (int e = 0; e < 16; ++e) dp_init[e] = -delta;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      for (int e = 0; e < 16; ++e) dq[db][e] = 0.0f;
+  };
+
+  // The tiles list[0 .. n_list) (the first of which, `first`, is known already) for this work-group's queries.
+  auto run_list = [&](const uint32_t* __restrict__ list, int n_list, uint32_t first, bool write_stats) {
+    Kg = P.k + (int64_t)bh * N * D;
+    Vg = P.v + (int64_t)bh * N * D;
+    auto start_window = [&](int w0, uint32_t e) {  // the first tile's copies and the list
+      e0 = e;
+      copy_all(e0, k_s0, v_s0);
       const int count = min(kWin, n_list - w0);
       for (int t = tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
       if (tid < 3) tiles_s[count + tid] = kNoTile;
+    };
+    constexpr bool EARLY = NW <= 4;  // the waves' slabs of Q leave the buffers of parity 0 to the first tile
+    if (EARLY && n_list > 0) start_window(0, first);
+    begin_item(write_stats);
+    if (!EARLY || n_list == 0) __syncthreads();  // .. or to the epilogue, once every wave has read its slab
+    if (!EARLY && n_list > 0) start_window(0, first);
+    for (int w0 = 0; w0 < n_list; w0 += kWin) {
+      const int count = min(kWin, n_list - w0);
+      if (w0 > 0) start_window(w0, scalar(list[w0]));
+      request_mask(e0);
       __syncthreads();
-      e0 = tiles_s[0];
-      e1 = tiles_s[1];
-      request(e0, k_s0, v_s0);
+      e1_v = tiles_s[1];
       for (int it = 0; it < count; it += 2) {
         step(IntC<0>{}, it);
         if (it + 1 < count) step(IntC<1>{}, it + 1);
       }
+      __builtin_amdgcn_s_waitcnt(0);  // (the zero rows that the last step copied)
       __syncthreads();  // the next window rewrites the tile list and the buffers; the epilogue stages into them
     }
   };
 
   auto write_dq = [&]() {
     __bf16* const stage = ((wave >> 1) == 0 ? k_s0 : (wave >> 1) == 1 ? k_s1 : (wave >> 1) == 2 ? v_s0 : v_s1) + (wave & 1) * 32 * D;
-    store_slab<D>(dq, P.scale, stage, P.dq + head_off, (int64_t)i * BR + wave * 32, N, lane);
+    store_slab<D>(dq, P.scale, stage, P.dq + head_off, i * BR + wave * 32, N, lane);
   };
 
   // ---- which block row is this work-group's own: rank-major interleave of G (batch, head) planes, as in the forward
@@ -425,6 +560,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     own_m = (P.Mb == 1) ? 0 : own_bh / P.H;
   }
   int own_i, list_pos, n_list, nparts_all = 0, split_T = 0x7fffffff;
+  uint32_t own_first = 0;
   if (P.sched) {
     const int2 hdr = *reinterpret_cast<const int2*>(P.sched);
     const int4 rec = *reinterpret_cast<const int4*>(P.sched + bbm::sched_order_base(P.Mb, P.nbr) +
@@ -434,75 +570,72 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     own_i = rec.x;
     list_pos = rec.y;
     n_list = rec.z;
+    own_first = (uint32_t)rec.w;
   } else {
     own_i = P.nbr - 1 - rank;
     list_pos = P.row_ptr[(int64_t)own_m * (P.nbr + 1) + own_i];
     n_list = P.row_ptr[(int64_t)own_m * (P.nbr + 1) + own_i + 1] - list_pos;
+    if (n_list > 0) own_first = P.col_idx[(int64_t)own_m * P.nbr * P.nbc + list_pos];
   }
 
-  // ---- the first n_extra work-groups serve the queue of cut-row parts (nothing to do when no row was cut)
-  if (nparts_all > 0 && (int)blockIdx.x < P.n_extra) {
-    const int32_t* __restrict__ S = P.sched;
-    const int n_items = nparts_all * P.hbp;
-    int item = blockIdx.x;  // the first item is the work-group's own index; later ones come from the counter
-    while (item < n_items) {
-      int next_item = 0;
+  // The first n_extra work-groups serve the queue of cut-row parts before their own row (nothing to do when no row was cut):
+  // one loop for parts and own row, so that the tile loop is in the program once.
+  const bool leading = nparts_all > 0 && (int)blockIdx.x < P.n_extra;
+  const int n_items = leading ? nparts_all * P.hbp : 0;
+  int item = blockIdx.x;  // the first item is the work-group's own index; later ones come from the counter
+  for (;;) {
+    const bool is_part = item < n_items;
+    int pos = list_pos, n_run = n_list <= split_T ? n_list : 0;  // (of a row that the schedule cut only the statistics are left)
+    int next_item = 0, part = 0, nparts = 0, q_first = 0, rho = 0, hb = 0;
+    uint32_t first = own_first;
+    if (is_part) {
       if (tid == 0) next_item = P.n_extra + atomicAdd(P.row_queue, 1);
-      const int hb = item / nparts_all;
-      const int32_t* seg = S + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
-      const int row = seg[0], p0 = seg[1], nt = seg[2], part = seg[3], nparts = seg[4], q_first = seg[5], rho = seg[6];
+      hb = item / nparts_all;
+      const int32_t* seg = P.sched + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
+      const int row = seg[0];
+      pos = seg[1], n_run = seg[2], part = seg[3], nparts = seg[4], q_first = seg[5], rho = seg[6], first = (uint32_t)seg[7];
       m = row / P.nbr;
       i = row - m * P.nbr;
       bh = (P.Mb == 1) ? hb : m * P.H + hb;
-      begin_item(false);
-      run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + p0, nt);
-      // park the partial sums; the last part of the row to arrive adds them all up in part order
-      float* rec = P.row_partials + ((int64_t)(q_first + part) * P.hbp + hb) * (REGS * NT) + tid;
+    } else {
+      if (leading && tid == 0 && atomicAdd(P.row_queue + 1, 1) == P.n_extra - 1) {  // the last leading work-group to leave the queue
+        P.row_queue[0] = 0;
+        P.row_queue[1] = 0;
+      }
+      m = own_m, i = own_i, bh = own_bh;
+    }
+    run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + pos, n_run, scalar(first), !is_part);
+    if (!is_part) {
+      if (n_list <= split_T) write_dq();
+      return;
+    }
+    // park the partial sums; the last part of the row to arrive adds them all up in part order
+    float* const rec0 = P.row_partials + ((int64_t)q_first * P.hbp + hb) * (REGS * NT);
+    const int64_t pstride = (int64_t)P.hbp * (REGS * NT);
+    int at = 4 * tid;
+    asm volatile("" : "+v"(at));  // see store_slab
+    park<DB, NT>(rec0 + part * pstride + at, dq);
+    // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
+    // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
+    __syncthreads();
+    if (tid == 0) {
+      __threadfence();
+      const int arrived = atomicAdd(P.row_queue + 8 + rho * P.hbp + hb, 1);
+      if (arrived == nparts - 1) __threadfence();  // only the merging work-group has to see the others' parts
+      item_s[1] = arrived;
+      item_s[0] = next_item;
+    }
+    __syncthreads();
+    if (item_s[1] == nparts - 1) {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
-        for (int e = 0; e < 16; ++e) rec[(db * 16 + e) * NT] = dq[db][e];
-      // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
-      // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
-      __syncthreads();
-      if (tid == 0) {
-        __threadfence();
-        const int arrived = atomicAdd(P.row_queue + 8 + rho * P.hbp + hb, 1);
-        if (arrived == nparts - 1) __threadfence();  // only the merging work-group has to see the others' parts
-        item_s[1] = arrived;
-      }
-      __syncthreads();
-      if (item_s[1] == nparts - 1) {
-        const float* r0 = P.row_partials + ((int64_t)q_first * P.hbp + hb) * (REGS * NT) + tid;
-        const int64_t pstride = (int64_t)P.hbp * (REGS * NT);
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-          for (int e = 0; e < 16; ++e) dq[db][e] = 0.0f;
-        for (int k = 0; k < nparts; ++k) {
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-            for (int e = 0; e < 16; ++e) dq[db][e] += r0[k * pstride + (db * 16 + e) * NT];
-        }
-        write_dq();
-        if (tid == 0) P.row_queue[8 + rho * P.hbp + hb] = 0;  // last user of this counter: zero for the next call
-      }
-      if (tid == 0) item_s[0] = next_item;
-      __syncthreads();
-      item = item_s[0];
-      __syncthreads();
+        for (int e = 0; e < 16; ++e) dq[db][e] = 0.0f;
+      for (int k = 0; k < nparts; ++k) add_parked<DB, NT>(rec0 + k * pstride + at, dq);
+      write_dq();
+      if (tid == 0) P.row_queue[8 + rho * P.hbp + hb] = 0;  // last user of this counter: zero for the next call
     }
-    if (tid == 0 && atomicAdd(P.row_queue + 1, 1) == P.n_extra - 1) {  // the last leading work-group to leave
-      P.row_queue[0] = 0;
-      P.row_queue[1] = 0;
-    }
-  }
-
-  bh = own_bh;
-  m = own_m;
-  i = own_i;
-  begin_item(true);
-  if (n_list <= split_T) {  // a row the schedule cut belongs to the queue
-    run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + list_pos, n_list);
-    write_dq();
+    item = (int)scalar((uint32_t)item_s[0]);  // (a scalar: everything that addresses the item follows from it)
+    __syncthreads();  // everyone has read the item, and the staged sums, before the next item's copies and list land
   }
 }
 
@@ -511,41 +644,44 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 // ------------------------------------------------------------------------------------------------------------------
 // One work-group per (block column, batch, head); the first P.n_extra work-groups first serve the queue of
 // the parts of cut block columns, as the dQ kernel does for cut block rows.
-// RS = false: two waves, one per key half (32 keys); each computes all four products for its keys.
-// RS = true: four waves, (key half) x (role).  Role 0 computes S, P and dV, role 1 computes dP, dS and dK; P (rounded to
-// bf16, as the dV product consumes it) crosses from role 0 to role 1 through LDS at a barrier in the middle of a step.
-// Each wave then holds one operand (K or V) and one accumulator set, about half the registers: at D = 128, where the
-// tile buffers let two work-groups share a CU, that puts two waves on every SIMD instead of one, and one wave's
-// exponentials and LDS reads run under the other's matrix products.
-template <int D, bool RS, bool EXACT>
-__global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kernel(const BwdParams P) {
+// Four waves, (key half) x (query half of every 64-query sub-tile): each computes all four products of its 32 keys and its 32
+// queries, so P and dS never leave its registers; the sums of the two query halves meet through LDS behind the last sub-tile.
+// What bounds it is the way from one phase of a sub-tile to the next, so the phases are one chain of matrix instructions with
+// everything else behind them (mfma_ring): in the loop the matrix pipe is 75 % busy.  It took the place, at D = 128, of a split
+// of the waves by product, P crossing through LDS behind a second barrier, where either role waited for the other (a step of
+// 3620 cycles, now 2740), and at D = 64 of two waves that took one key half each.  Kernel time: 2 x 32 heads of 8192 causal
+// tokens, D = 128, 2370 -> 1900-1960 us; 4 x 16 heads of 4096, D = 64, 350 -> 303 us; a 16384-token window with global tokens
+// 195 -> 188; packed sequences of 4096, D = 64, 73.7 -> 72.4, of 3001, D = 128, 45.2 -> 41.9.
+// Registers are what the form lives by.  D = 128: 256, two operand pieces in LDS, two waves a SIMD; one register more in scratch
+// memory inside the loop costs a wait for the tile copies in flight (a form with 16 of them took 3240 us).  D = 64: 168, three.
+template <int D, bool EXACT>
+__global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(const BwdParams P) {
   using L = TL<D>;
-  constexpr int NW = RS ? 4 : 2, NT = 64 * NW;
-  constexpr int NTP = 128;  // lanes per role: stride of the parked records
+  constexpr int NW = 4, NT = 64 * NW;
+  constexpr int NTP = 128;  // lanes that hold one of the two sums: stride of the parked records
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;
   constexpr int REGS = DB * 16;
   constexpr int kRing = 3;
   static_assert(2 * 32 * D <= L::ELEMS, "two 32 x D output slabs must fit in a tile buffer");
 
-  // One variable per parity for what the roles read at the same place of their own operand: a select between two
-  // variables hides from the compiler which asynchronous copies a read has to wait for, and it then waits for all.
-  __shared__ __attribute__((aligned(16))) __bf16 t_s0[2 * L::ELEMS];  // [Q, dO] tiles
+  __shared__ __attribute__((aligned(16))) __bf16 t_s0[2 * L::ELEMS];  // [Q, dO] tiles, one variable per parity
   __shared__ __attribute__((aligned(16))) __bf16 t_s1[2 * L::ELEMS];
   __shared__ __attribute__((aligned(16))) float st_s0[2 * 64];  // [-lse*log2 e, -D] of the sub-tile's queries
   __shared__ __attribute__((aligned(16))) float st_s1[2 * 64];
   __shared__ __attribute__((aligned(16))) uint32_t mk_s0[2][64];  // [key half][query row of the sub-tile]
   __shared__ __attribute__((aligned(16))) uint32_t mk_s1[2][64];
-  __shared__ uint32_t tiles_s[kWin];
+  __shared__ uint32_t tiles_s[kWin + 2];  // entries past the last one are read but not used
   __shared__ int item_s[2];
-  __shared__ __attribute__((aligned(16))) bf16x8 p_s[RS ? 2 : 1][4][64];  // RS: P of [key half][16-query step][lane]
+  // D = 128: the last pieces of the K operand, which find no room in the registers
+  constexpr int KL = D == 128 ? 2 : 0;
+  __shared__ __attribute__((aligned(16))) bf16x8 kl_s[KL ? KL : 1][NW][64];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kh = wave & 1;              // key half of the column block
-  const int role = RS ? wave >> 1 : 0;  // RS: 0 = S, P, dV; 1 = dP, dS, dK
-  const int lq = lane & 31, hh = lane >> 5;
-  const int64_t N = P.N;
+  const int kh = wave & 1;   // key half of the column block
+  const int qh = wave >> 1;  // query half of the sub-tile; behind the last one, 0: this wave writes dV, 1: dK
+  const int N = (int)P.N;
   const float c = P.qscale;
   const float rr = EXACT ? P.rmul : 1.0f;
   auto ex2 = [&](float x) { return __builtin_amdgcn_exp2f(EXACT ? rr * x : x); };
@@ -558,337 +694,336 @@ __global__ __launch_bounds__(RS ? 256 : 128, RS ? 2 : 1) void attn_bwd_dkv_kerne
   const float* __restrict__ nlg;
   const float* __restrict__ ndg;
   const uint32_t* __restrict__ mcol;
-  bf16x8 kf[KS], vf[KS];  // RS: kf is the wave's one operand (role 0: K scaled, role 1: V), vf unused
-  f32x16 dk[DB], dv[DB];  // RS: dk is the wave's one accumulator set (role 0: dV, role 1: dK), dv unused
+  bf16x8 kf[KS - KL], vf[KS];
+  f32x16 dk[DB], dv[DB];  // behind the last sub-tile dk holds this wave's output, dV or dK
 
-  // this lane's key: K * scale * log2(e) and V as B operands (keys past N: zeros, never stored)
-  auto begin_item = [&]() {
+  TileAddr<D> A;
+  A.init(lane);
+  for (int i = 0; i < 2; ++i) {  // this wave's half of the tile's rows
+    A.ra[i] += qh * (32 / L::NBLK) * D;
+    A.ta[i] += 2 * qh * (D == 64 ? 2 * D : D);
+  }
+
+  const int qs_shift = P.br == 64 ? 0 : P.br == 128 ? 1 : 2;  // 64-query sub-tiles per block row: 1, 2, 4
+  // Copies of the 64-query sub-tile from row0 on into the buffers of one parity: Q and dO tiles, the negated statistics of its
+  // queries (-lse*log2 e and -D) and, if the block is partial, the two 32-bit halves of its mask words, a wave for each of the
+  // four.  Queries past N come as zeros everywhere: with Q = dO = D = 0 they add exact zeros.
+  const uint32_t copy_base = tile_copy_base<D, NW>(wave, lane);
+  constexpr int LPW = L::NBLK / NW;  // copy instructions of a wave per tile
+  auto copy_piece = [&](int row0, int rows, __bf16* td, int n) {  // n = 0 .. 2*LPW-1
+    const int64_t at = (int64_t)row0 * D;
+    if (n < LPW)
+      tile_copy_piece<D, NW>(Qg + at, rows, copy_base, td, n, wave);
+    else
+      tile_copy_piece<D, NW>(Gg + at, rows, copy_base, td + L::ELEMS, n - LPW, wave);
+  };
+  auto copy_stats = [&](int row0, int rows, bool partial, float* sts, uint32_t (*mkd)[64]) {
+    if (qh == 0)
+      copy_async<4>((kh == 0 ? nlg : ndg) + row0, rows * 4, lane_now() * 4, sts + kh * 64);
+    else if (partial)  // (the words lie 8 bytes apart; this wave's half is the first or the second 4 bytes of each)
+      copy_async<4>(mcol + 2 * (int64_t)row0, max(0, rows * 8 - 4), lane_now() * 8, mkd[kh]);
+  };
+  auto copy_all = [&](int row0, int rows, __bf16* td) {
+#pragma unroll
+    for (int n = 0; n < 2 * LPW; ++n) copy_piece(row0, rows, td, n);
+  };
+
+  // Step s: list entry e0 = tiles_s[s >> qs_shift], the entry of step s + 1 is e1 (both read a step ahead).
+  int n_steps = 0;
+  uint32_t e0 = 0, e1 = 0;
+  auto entry_of = [&](int s) { return scalar(tiles_s[s >> qs_shift]); };
+  auto row_of = [&](uint32_t e, int s) { return (int)(((e & 0x7fffffffu) << qs_shift) + (s & ((1 << qs_shift) - 1))) * 64; };
+  auto step = [&](auto pb, int s) __attribute__((always_inline)) {
+    constexpr int PB = decltype(pb)::value;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    __bf16* const q_cur = PB ? t_s1 : t_s0;
+    __bf16* const g_cur = q_cur + L::ELEMS;
+    __bf16* const t_oth = PB ? t_s0 : t_s1;
+    const float* const nl_cur = (PB ? st_s1 : st_s0) + 32 * qh;
+    const float* const nd_cur = nl_cur + 64;
+    const uint32_t* const mk_cur = &(PB ? mk_s1 : mk_s0)[kh][32 * qh];
+    const bool partial = (e0 >> 31) == 0;
+    // The next sub-tile's copies go out one by one between the matrix instructions of this one: requested in one go they
+    // fill the memory pipe's queue, and every wave of the work-group stands there for 700-850 cycles of a step (D = 128).
+    // Behind the last sub-tile they copy zero rows into buffers that nobody reads any more, cheaper than a branch around each.
+    const bool more = s + 1 < n_steps;
+    const int row1 = row_of(e1, s + 1), rows1 = more ? rows_of_tile(row1, N) : 0;
+    if (more) copy_stats(row1, rows1, (e1 >> 31) == 0, PB ? st_s0 : st_s1, PB ? mk_s0 : mk_s1);
+    e0 = e1;
+    const uint32_t e2 = tiles_s[(s + 2) >> qs_shift];
+    // a partial sub-tile in which none of this wave's 32 queries sees one of its 32 keys contributes exact zeros
+    const bool live = !partial || __ballot(mk_cur[lane_now() & 31] != 0u) != 0ull;
+    if (!live && more) copy_all(row1, rows1, t_oth);
+    if (live) {
+      f32x16 sc, dp;
+      const int ln = lane_now(), hh4 = ln >> 5 << 2;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 x = *reinterpret_cast<const float4*>(nl_cur + 8 * g + hh4);
+        sc[4 * g + 0] = x.x, sc[4 * g + 1] = x.y, sc[4 * g + 2] = x.z, sc[4 * g + 3] = x.w;
+      }
+      if (partial) {  // -inf, i.e. P = 0, where the mask word (32 keys of a query row) has no bit
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const uint4 w = *reinterpret_cast<const uint4*>(mk_cur + 8 * g + hh4);
+          const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)ww[e], ln & 31, 1);  // all ones iff bit lq is set
+            sc[4 * g + e] = __uint_as_float((__float_as_uint(sc[4 * g + e]) & keep) | (0xff800000u & ~keep));
+          }
+        }
+      }
+      // One chain of matrix instructions, S, dP, dV, dK, with everything else behind them: the next sub-tile's copies behind
+      // S, the exponentials behind dP, dS behind dV.  At D = 128 the fp32 probabilities do not outlive dP (registers): dS is
+      // formed from P as the dV product consumes it, rounded to bf16.
+      constexpr bool P32 = D == 64;
+      constexpr int N1 = KS, N2 = 2 * KS, N3 = N2 + 2 * DB, N4 = N3 + 2 * DB;
+      constexpr int PER = D == 128 ? 4 : 8;  // elements behind a matrix instruction
+      static_assert(PER * (KS - 2) >= 16 && PER * (2 * DB - 2) >= 16, "all 16 must find room");
+      uint32_t pf[2][4], dsf[2][4];  // pairs of bf16
+      bf16x8 kl[2];
+      mfma_ring<N4, kRing>(
+          [&](auto i) {
+            constexpr int n = decltype(i)::value;
+            if constexpr (n < N2)
+              return A.row_frag(n < N1 ? q_cur : g_cur, 0, n % KS);
+            else
+              return A.tr_frag(n < N3 ? g_cur : q_cur, (n - N2) % (2 * DB) / DB, n % DB);
+          },
+          [&](auto i, bf16x8 f) {
+            constexpr int n = decltype(i)::value, db = n % DB, u = (n - N2) % (2 * DB) / DB;
+            static_assert(KS % DB == 0, "the two counts of column blocks start at multiples of DB");
+            if constexpr (n < N1 - KL)
+              sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kf[n], sc, 0, 0, 0);
+            else if constexpr (n < N1)
+              sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kl[n & 1], sc, 0, 0, 0);
+            else if constexpr (n < N2)
+              dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, vf[n - N1], dp, 0, 0, 0);
+            else if constexpr (n < N3)
+              dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, operand(pf[u]), dv[db], 0, 0, 0);
+            else
+              dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, operand(dsf[u]), dk[db], 0, 0, 0);
+          },
+          [&](auto i) {
+            constexpr int n = decltype(i)::value;
+            static_assert(2 * LPW == KS, "one copy behind every matrix instruction of S");
+            if constexpr (n < N1) copy_piece(row1, rows1, t_oth, n);
+            if constexpr (n >= N1 - KL - 2 && n < N1 - 2) kl[n & 1] = kl_s[n - (N1 - KL - 2)][wave][lane_now()];
+            if constexpr (n == N1 - 2) {
+              const float* const nd = nd_cur + (lane_now() >> 5 << 2);
+#pragma unroll
+              for (int g = 0; g < 4; ++g) {
+                const float4 x = *reinterpret_cast<const float4*>(nd + 8 * g);
+                dp[4 * g + 0] = x.x, dp[4 * g + 1] = x.y, dp[4 * g + 2] = x.z, dp[4 * g + 3] = x.w;
+              }
+            }
+            if constexpr (n >= N1 + 2 && n < N2) {  // S is complete two matrix instructions after its last one was issued
+#pragma unroll
+              for (int e = (n - N1 - 2) * PER; e < min(16, (n - N1 - 1) * PER); e += 2) {
+                sc[e] = ex2(sc[e]);
+                sc[e + 1] = ex2(sc[e + 1]);
+                pf[e / 8][e % 8 / 2] = pack(sc[e], sc[e + 1]);
+                // (hides the pair's origin: the compiler otherwise rounds each of the two once more where dS takes it apart)
+                if constexpr (!P32) asm("" : "+v"(pf[e / 8][e % 8 / 2]));
+              }
+            }
+            if constexpr (n >= N2 + 2 && n < N3) {
+#pragma unroll
+              for (int e = (n - N2 - 2) * PER; e < min(16, (n - N2 - 1) * PER); e += 2) {
+                const uint32_t w = pf[e / 8][e % 8 / 2];
+                const float p0 = P32 ? sc[e] : __uint_as_float(w << 16), p1 = P32 ? sc[e + 1] : __uint_as_float(w & 0xffff0000u);
+                dsf[e / 8][e % 8 / 2] = pack(p0 * dp[e], p1 * dp[e + 1]);
+              }
+            }
+          });
+    }
+    e1 = scalar(e2);
+  };
+
+  // The query blocks list[0 .. n_list) (the first of which, `first`, is known already) of this work-group's 64 keys.
+  auto run_list = [&](const uint32_t* __restrict__ list, int n_list, uint32_t first) {
     head_off = (int64_t)bh * N * D;
     Qg = P.q + head_off;
     Gg = P.d_o + head_off;
     nlg = P.nl2 + (int64_t)bh * N;
     ndg = P.ndelta + (int64_t)bh * N;
     // this wave's 32-bit half of the packed mask words of block column j (one word per query row)
-    mcol = reinterpret_cast<const uint32_t*>(P.packed + ((int64_t)m * P.W + j) * N) + kh;
-    const int64_t krow = (int64_t)j * 64 + kh * 32 + lq;
-    const bool k_ok = krow < N;
-    if constexpr (RS) {
-      const __bf16* __restrict__ src = role == 0 ? P.k : P.v;
-      const float mult = role == 0 ? c : 1.0f;  // exact for V
+    mcol = reinterpret_cast<const uint32_t*>(P.packed + ((int64_t)m * P.W + j) * (int64_t)N) + kh;
 #pragma unroll
-      for (int t = 0; t < KS; ++t) {
-        if (k_ok)
-          kf[t] = *reinterpret_cast<const bf16x8*>(src + head_off + krow * D + 16 * t + 8 * hh);
-        else
-          for (int e = 0; e < 8; ++e) kf[t][e] = (__bf16)0.0f;
-        for (int e = 0; e < 8; ++e) kf[t][e] = (__bf16)((float)kf[t][e] * mult);
-      }
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-        for (int e = 0; e < 16; ++e) dk[db][e] = 0.0f;
-    } else {
-#pragma unroll
-      for (int t = 0; t < KS; ++t) {
-        if (k_ok) {
-          const int64_t at = head_off + krow * D + 16 * t + 8 * hh;
-          kf[t] = *reinterpret_cast<const bf16x8*>(P.k + at);
-          vf[t] = *reinterpret_cast<const bf16x8*>(P.v + at);
-        } else {
-          for (int e = 0; e < 8; ++e) kf[t][e] = vf[t][e] = (__bf16)0.0f;
-        }
-        for (int e = 0; e < 8; ++e) kf[t][e] = (__bf16)((float)kf[t][e] * c);
-      }
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-        for (int e = 0; e < 16; ++e) dk[db][e] = dv[db][e] = 0.0f;
-    }
-  };
-
-  TileAddr<D> A;
-  A.init(lane);
-
-  const int qs_shift = P.br == 64 ? 0 : P.br == 128 ? 1 : 2;  // 64-query sub-tiles per block row: 1, 2, 4
-  // Requests sub-tile `sub` of list entry e into the buffers of one parity: Q and dO tiles, the negated statistics of
-  // its 64 queries (-lse*log2 e and -D: one wave each), and the two 32-bit halves of the mask words if the block is
-  // partial (the waves of role 0, each its own half).  Query rows past N get -inf / 0 so that their probabilities are
-  // exactly 0.
-  auto request = [&](uint32_t e, int sub, __bf16* td, float* sts, uint32_t (*mkd)[64]) {
-    const int64_t row0 = ((int64_t)(e & 0x7fffffffu) << qs_shift) * 64 + (int64_t)sub * 64;
-    tile_copy_async<D, NW>(Qg, row0, N, td, wave, lane);
-    tile_copy_async<D, NW>(Gg, row0, N, td + L::ELEMS, wave, lane);
-    const int64_t r = row0 + lane;
-    const bool lse_wave = wave == 0, delta_wave = wave == (RS ? 2 : 1);  // one wave of each role when the roles are split
-    if (lse_wave || delta_wave) {
-      float* const sd = sts + (lse_wave ? 0 : 64);
-      const float* const sg = lse_wave ? nlg : ndg;
-      if (r < N)
-        copy_async<D, 4>(sg + row0, 64 * 4, lane * 4, sd);
-      else
-        sd[lane] = lse_wave ? -INFINITY : 0.0f;
-    }
-    if (role == 0 && (e >> 31) == 0) {
-      const int64_t first = min(row0, N - 1);
-      const int last = (int)min<int64_t>(63, N - 1 - first);
-      copy_async<D, 4>(mcol + 2 * first, 64 * 8, min(lane, last) * 8, mkd[kh]);
-    }
-  };
-
-  int n_steps = 0;
-  auto entry_of = [&](int s) { return tiles_s[s >> qs_shift]; };
-  auto step = [&](auto pb, int s) {
-    constexpr int PB = decltype(pb)::value;
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    __bf16* const q_cur = PB ? t_s1 : t_s0;
-    __bf16* const g_cur = q_cur + L::ELEMS;
-    const float* const nl_cur = PB ? st_s1 : st_s0;
-    const float* const nd_cur = nl_cur + 64;
-    const uint32_t(*mk_cur)[64] = PB ? mk_s1 : mk_s0;
-    const uint32_t e0 = entry_of(s);
-    if (s + 1 < n_steps) {
-      const uint32_t e1 = entry_of(s + 1);
-      const int sub1 = (s + 1) & ((1 << qs_shift) - 1);
-      if (PB)
-        request(e1, sub1, t_s0, st_s0, mk_s0);
-      else
-        request(e1, sub1, t_s1, st_s1, mk_s1);
-    }
-    const bool partial = (e0 >> 31) == 0;
-    // a partial sub-tile in which none of the 64 queries sees one of this wave's 32 keys contributes exact zeros
-    if constexpr (RS) {
-      const bool live = !partial || __ballot(mk_cur[kh][lane] != 0u) != 0ull;  // the same for both roles of a key half
-      f32x16 acc2[2];  // role 0: S^T, then P; role 1: dP^T
-      bf16x8 pf[4];
-      if (live) {
-        const float* const init = nl_cur + role * 64;
-        const __bf16* const rows = q_cur + role * L::ELEMS;
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const float4 a = *reinterpret_cast<const float4*>(init + 32 * qb + 8 * g + 4 * hh);
-            acc2[qb][4 * g + 0] = a.x, acc2[qb][4 * g + 1] = a.y, acc2[qb][4 * g + 2] = a.z, acc2[qb][4 * g + 3] = a.w;
-          }
-        }
-        mfma_ring<2 * KS, kRing>([&](int n) { return A.row_frag(rows, n & 1, n >> 1); },
-                                 [&](int n, bf16x8 f) { acc2[n & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kf[n >> 1], acc2[n & 1], 0, 0, 0); });
-        if (role == 0) {
-#pragma unroll
-          for (int qb = 0; qb < 2; ++qb) {
-            float p[16];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) p[e] = ex2(acc2[qb][e]);
-            if (partial) {
-#pragma unroll
-              for (int g = 0; g < 4; ++g) {
-                const uint4 w = *reinterpret_cast<const uint4*>(&mk_cur[kh][32 * qb + 8 * g + 4 * hh]);
-                const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)ww[e], lq, 1);  // all ones iff bit lq is set
-                  p[4 * g + e] = __uint_as_float(__float_as_uint(p[4 * g + e]) & keep);
-                }
-              }
-            }
-#pragma unroll
-            for (int u2 = 0; u2 < 2; ++u2) {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) pf[2 * qb + u2][e] = (__bf16)p[8 * u2 + e];
-              p_s[kh][2 * qb + u2][lane] = pf[2 * qb + u2];
-            }
-          }
-        }
-      }
-      __syncthreads();  // P of this step is in LDS (the next step's first barrier comes after its last reader)
-      if (live) {
-        const __bf16* const cols = q_cur + (1 - role) * L::ELEMS;
-        if (role != 0) {  // dS = P o dP, rounded to bf16, in place of P
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const bf16x8 pu = p_s[kh][u][lane];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) pf[u][e] = (__bf16)((float)pu[e] * acc2[u >> 1][8 * (u & 1) + e]);
-          }
-        }
-        mfma_ring<4 * DB, kRing>([&](int n) { return A.tr_frag(cols, n / DB, n % DB); },
-                                 [&](int n, bf16x8 f) { dk[n % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, pf[n / DB], dk[n % DB], 0, 0, 0); });
-      }
-      return;
-    }
-    if (partial && __ballot(mk_cur[kh][lane] != 0u) == 0ull) return;
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      f32x16 sc, dp;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 a = *reinterpret_cast<const float4*>(nl_cur + 32 * qb + 8 * g + 4 * hh);
-        const float4 b = *reinterpret_cast<const float4*>(nd_cur + 32 * qb + 8 * g + 4 * hh);
-        sc[4 * g + 0] = a.x, sc[4 * g + 1] = a.y, sc[4 * g + 2] = a.z, sc[4 * g + 3] = a.w;
-        dp[4 * g + 0] = b.x, dp[4 * g + 1] = b.y, dp[4 * g + 2] = b.z, dp[4 * g + 3] = b.w;
-      }
-#pragma unroll
-      for (int t = 0; t < KS; ++t) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(q_cur, qb, t), kf[t], sc, 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < KS; ++t) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.row_frag(g_cur, qb, t), vf[t], dp, 0, 0, 0);
-      float p[16];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) p[e] = ex2(sc[e]);
-      if (partial) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const uint4 w = *reinterpret_cast<const uint4*>(&mk_cur[kh][32 * qb + 8 * g + 4 * hh]);
-          const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)ww[e], lq, 1);  // all ones iff bit lq is set
-            p[4 * g + e] = __uint_as_float(__float_as_uint(p[4 * g + e]) & keep);
-          }
-        }
-      }
-#pragma unroll
-      for (int u2 = 0; u2 < 2; ++u2) {
-        bf16x8 pf, dsf;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          pf[e] = (__bf16)p[8 * u2 + e];
-          dsf[e] = (__bf16)(p[8 * u2 + e] * dp[8 * u2 + e]);
-        }
-        const int u = 2 * qb + u2;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.tr_frag(g_cur, u, db), pf, dv[db], 0, 0, 0);
-          dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.tr_frag(q_cur, u, db), dsf, dk[db], 0, 0, 0);
-        }
-      }
-    }
-  };
-
-  // the query blocks list[0 .. n_list), window by window
-  auto run_list = [&](const uint32_t* __restrict__ list, int n_list) {
+    for (int db = 0; db < DB; ++db)
+      for (int e = 0; e < 16; ++e) dk[db][e] = dv[db][e] = 0.0f;
     for (int w0 = 0; w0 < n_list; w0 += kWin) {
       const int count = min(kWin, n_list - w0);
+      e0 = w0 > 0 ? scalar(list[w0]) : first;
+      const int row0 = row_of(e0, 0), rows0 = rows_of_tile(row0, N);
+      copy_stats(row0, rows0, (e0 >> 31) == 0, st_s0, mk_s0);
+      copy_all(row0, rows0, t_s0);
+      if (w0 == 0) {
+        // K and V come through the tile buffers of parity 1 as well (keys past N as zeros): straight from memory a lane would
+        // pick its row up in 16-byte pieces, 64 cache lines an instruction, and stand there for 7000 cycles of a column at
+        // D = 64, 12000 at D = 128.
+        const int64_t at = head_off + (int64_t)j * 64 * D;
+        const int keys = rows_of_tile(j * 64, N);
+#pragma unroll
+        for (int n = 0; n < LPW; ++n) {
+          tile_copy_piece<D, NW>(P.k + at, keys, copy_base, t_s1, n, wave);
+          tile_copy_piece<D, NW>(P.v + at, keys, copy_base, t_s1 + L::ELEMS, n, wave);
+        }
+      }
       for (int t = tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
+      __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
       n_steps = count << qs_shift;
-      request(tiles_s[0], 0, t_s0, st_s0, mk_s0);
+      e1 = entry_of(1);
+      if (w0 == 0) {  // this lane's key: K * scale * log2(e) and V as B operands
+        const int half = (kh - qh) * (32 / L::NBLK) * D;  // (A addresses this wave's query half of a tile)
+#pragma unroll
+        for (int t = 0; t < KS; ++t) {
+          bf16x8 kt = A.row_frag(t_s1 + half, 0, t);
+          vf[t] = A.row_frag(t_s1 + L::ELEMS + half, 0, t);
+          for (int e = 0; e < 8; ++e) kt[e] = (__bf16)((float)kt[e] * c);
+          if (t >= KS - KL)
+            kl_s[t - (KS - KL)][wave][lane] = kt;  // (read back by this wave alone)
+          else
+            kf[t] = kt;
+        }
+      }
       for (int s = 0; s < n_steps; s += 2) {
         step(IntC<0>{}, s);
         if (s + 1 < n_steps) step(IntC<1>{}, s + 1);
       }
+      __builtin_amdgcn_s_waitcnt(0);  // (the zero rows that the last step copied)
       __syncthreads();  // the next window rewrites the list and the buffers; the epilogue stages into them
     }
+    // The two waves of a key half exchange: query half 0 hands over its dK and receives dV, query half 1 the other way round.
+    float4* const mine = reinterpret_cast<float4*>(qh == 0 ? t_s0 : t_s1) + kh * (REGS / 4) * 64;
+    const float4* const theirs = reinterpret_cast<const float4*>(qh == 0 ? t_s1 : t_s0) + kh * (REGS / 4) * 64;
+    static_assert(2 * REGS * 64 * sizeof(float) <= 2 * L::ELEMS * sizeof(__bf16), "two waves' sums must fit in the tile buffers of a parity");
+    int ln = lane;
+    asm volatile("" : "+v"(ln));  // see store_slab
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      for (int g = 0; g < 4; ++g) {
+        float4 x;
+        x.x = qh ? dv[db][4 * g + 0] : dk[db][4 * g + 0];
+        x.y = qh ? dv[db][4 * g + 1] : dk[db][4 * g + 1];
+        x.z = qh ? dv[db][4 * g + 2] : dk[db][4 * g + 2];
+        x.w = qh ? dv[db][4 * g + 3] : dk[db][4 * g + 3];
+        mine[(db * 4 + g) * 64 + ln] = x;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      for (int g = 0; g < 4; ++g) {
+        const float4 x = theirs[(db * 4 + g) * 64 + ln];
+        dk[db][4 * g + 0] = x.x + (qh ? dk[db][4 * g + 0] : dv[db][4 * g + 0]);
+        dk[db][4 * g + 1] = x.y + (qh ? dk[db][4 * g + 1] : dv[db][4 * g + 1]);
+        dk[db][4 * g + 2] = x.z + (qh ? dk[db][4 * g + 2] : dv[db][4 * g + 2]);
+        dk[db][4 * g + 3] = x.w + (qh ? dk[db][4 * g + 3] : dv[db][4 * g + 3]);
+      }
+    __syncthreads();  // the epilogue stages into the same buffers
   };
 
   auto write_dkv = [&]() {
-    const int64_t row0 = (int64_t)j * 64 + kh * 32;
-    if constexpr (RS) {
-      if (role == 0)
-        store_slab<D>(dk, 1.0f, t_s0 + L::ELEMS + kh * 32 * D, P.dv + head_off, row0, N, lane);
-      else
-        store_slab<D>(dk, P.scale, t_s0 + kh * 32 * D, P.dk + head_off, row0, N, lane);
-    } else {
+    const int row0 = j * 64 + kh * 32;
+    if (qh == 0)
+      store_slab<D>(dk, 1.0f, t_s0 + L::ELEMS + kh * 32 * D, P.dv + head_off, row0, N, lane);
+    else
       store_slab<D>(dk, P.scale, t_s0 + kh * 32 * D, P.dk + head_off, row0, N, lane);
-      store_slab<D>(dv, 1.0f, t_s0 + L::ELEMS + kh * 32 * D, P.dv + head_off, row0, N, lane);
-    }
   };
-  // where this thread's sums sit in a parked record: [dK registers | dV registers][NTP lanes]
-  const int rec_lane = kh * 64 + lane, rec_reg0 = (RS && role == 0) ? REGS : 0;
 
+  // This work-group's own block column: rank-major interleave of G (batch, head) planes as in the dQ kernel, ranks by list
+  // length (longest first) from the schedule's records
   int nparts_all = 0, split_T = 0x7fffffff;
-  if (P.csched) {
-    const int2 hdr = *reinterpret_cast<const int2*>(P.csched);
-    nparts_all = hdr.x;
-    split_T = hdr.y;
-  }
-  // ---- the first n_extra work-groups serve the queue of cut-column parts (nothing to do when no column was cut)
-  if (nparts_all > 0 && (int)blockIdx.x < P.n_extra) {
-    const int32_t* __restrict__ S = P.csched;
-    const int n_items = nparts_all * P.hbp;
-    int item = blockIdx.x;
-    while (item < n_items) {
-      int next_item = 0;
-      if (tid == 0) next_item = P.n_extra + atomicAdd(P.col_queue, 1);
-      const int hb = item / nparts_all;
-      const int32_t* seg = S + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
-      const int col = seg[0], p0 = seg[1], nt = seg[2], part = seg[3], nparts = seg[4], q_first = seg[5], rho = seg[6];
-      m = col / P.nbc;
-      j = col - m * P.nbc;
-      bh = (P.Mb == 1) ? hb : m * P.H + hb;
-      begin_item();
-      run_list(P.row_idx + (int64_t)m * P.nbr * P.nbc + p0, nt);
-      float* rec = P.col_partials + ((int64_t)(q_first + part) * P.hbp + hb) * (2 * REGS * NTP) + rec_lane;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-        for (int e = 0; e < 16; ++e) {
-          rec[(rec_reg0 + db * 16 + e) * NTP] = dk[db][e];
-          if constexpr (!RS) rec[(REGS + db * 16 + e) * NTP] = dv[db][e];
-        }
-      // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
-      // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
-      __syncthreads();
-      if (tid == 0) {
-        __threadfence();
-        const int arrived = atomicAdd(P.col_queue + 8 + rho * P.hbp + hb, 1);
-        if (arrived == nparts - 1) __threadfence();  // only the merging work-group has to see the others' parts
-        item_s[1] = arrived;
-      }
-      __syncthreads();
-      if (item_s[1] == nparts - 1) {
-        const float* r0 = P.col_partials + ((int64_t)q_first * P.hbp + hb) * (2 * REGS * NTP) + rec_lane;
-        const int64_t pstride = (int64_t)P.hbp * (2 * REGS * NTP);
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-          for (int e = 0; e < 16; ++e) dk[db][e] = dv[db][e] = 0.0f;
-        for (int k = 0; k < nparts; ++k) {
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-            for (int e = 0; e < 16; ++e) {
-              dk[db][e] += r0[k * pstride + (rec_reg0 + db * 16 + e) * NTP];
-              if constexpr (!RS) dv[db][e] += r0[k * pstride + (REGS + db * 16 + e) * NTP];
-            }
-        }
-        write_dkv();
-        if (tid == 0) P.col_queue[8 + rho * P.hbp + hb] = 0;
-      }
-      if (tid == 0) item_s[0] = next_item;
-      __syncthreads();
-      item = item_s[0];
-      __syncthreads();
-    }
-    if (tid == 0 && atomicAdd(P.col_queue + 1, 1) == P.n_extra - 1) {
-      P.col_queue[0] = 0;
-      P.col_queue[1] = 0;
-    }
-  }
-
+  int own_bh, own_m, own_j, own_pos, own_n;
+  uint32_t own_first = 0;
   {
-    // which block column is this work-group's own: rank-major interleave of G (batch, head) planes as in the dQ kernel,
-    // ranks by list length (longest first) from the schedule's records
     const int logical = logical_wg((int)blockIdx.x, P.total_wgs);
-    int list_pos, n_list;
     if (P.csched) {
+      const int2 hdr = *reinterpret_cast<const int2*>(P.csched);
+      nparts_all = hdr.x;
+      split_T = hdr.y;
       const int grp = logical / (P.Gc * P.nbc), within = logical - grp * (P.Gc * P.nbc);
       const int g_planes = min(P.Gc, P.total_wgs / P.nbc - grp * P.Gc);
       const int rank = within / g_planes;
-      bh = grp * P.Gc + (within - rank * g_planes);
-      m = (P.Mb == 1) ? 0 : bh / P.H;
+      own_bh = grp * P.Gc + (within - rank * g_planes);
+      own_m = (P.Mb == 1) ? 0 : own_bh / P.H;
       const int4 rec = *reinterpret_cast<const int4*>(P.csched + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * P.Mb * P.nbc +
-                                                      bbm::kSchedRowInts * (int64_t)(m * P.nbc + rank));
-      j = rec.x;
-      list_pos = rec.y;
-      n_list = rec.z;
+                                                      bbm::kSchedRowInts * (int64_t)(own_m * P.nbc + rank));
+      own_j = rec.x;
+      own_pos = rec.y;
+      own_n = rec.z;
+      own_first = (uint32_t)rec.w;
     } else {
-      bh = logical / P.nbc;
-      j = logical - bh * P.nbc;
-      m = (P.Mb == 1) ? 0 : bh / P.H;
-      list_pos = P.col_ptr[(int64_t)m * (P.nbc + 1) + j];
-      n_list = P.col_ptr[(int64_t)m * (P.nbc + 1) + j + 1] - list_pos;
+      own_bh = logical / P.nbc;
+      own_j = logical - own_bh * P.nbc;
+      own_m = (P.Mb == 1) ? 0 : own_bh / P.H;
+      own_pos = P.col_ptr[(int64_t)own_m * (P.nbc + 1) + own_j];
+      own_n = P.col_ptr[(int64_t)own_m * (P.nbc + 1) + own_j + 1] - own_pos;
+      if (own_n > 0) own_first = P.row_idx[(int64_t)own_m * P.nbr * P.nbc + own_pos];
     }
-    if (n_list <= split_T) {  // a column the schedule cut belongs to the queue
-      begin_item();
-      run_list(P.row_idx + (int64_t)m * P.nbr * P.nbc + list_pos, n_list);
+  }
+
+  // The first n_extra work-groups serve the queue of cut-column parts before their own column (nothing to do when no column
+  // was cut): one loop for parts and own column, so that the tile loop is in the program once.
+  const bool leading = nparts_all > 0 && (int)blockIdx.x < P.n_extra;
+  const int n_items = leading ? nparts_all * P.hbp : 0;
+  int item = blockIdx.x;  // the first item is the work-group's own index; later ones come from the counter
+  for (;;) {
+    const bool is_part = item < n_items;
+    int pos, n_list, next_item = 0, part = 0, nparts = 0, q_first = 0, rho = 0, hb = 0;
+    uint32_t first = own_first;
+    if (is_part) {
+      if (tid == 0) next_item = P.n_extra + atomicAdd(P.col_queue, 1);
+      hb = item / nparts_all;
+      const int32_t* seg = P.csched + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
+      const int col = seg[0];
+      pos = seg[1], n_list = seg[2], part = seg[3], nparts = seg[4], q_first = seg[5], rho = seg[6], first = (uint32_t)seg[7];
+      m = col / P.nbc;
+      j = col - m * P.nbc;
+      bh = (P.Mb == 1) ? hb : m * P.H + hb;
+    } else {
+      if (leading && tid == 0 && atomicAdd(P.col_queue + 1, 1) == P.n_extra - 1) {  // the last leading work-group to leave the queue
+        P.col_queue[0] = 0;
+        P.col_queue[1] = 0;
+      }
+      if (own_n > split_T) return;  // a column the schedule cut belongs to the queue
+      m = own_m, j = own_j, bh = own_bh, pos = own_pos, n_list = own_n;
+    }
+    run_list(P.row_idx + (int64_t)m * P.nbr * P.nbc + pos, n_list, scalar(first));
+    if (!is_part) {
       write_dkv();
+      return;
     }
+    float* const rec0 = P.col_partials + ((int64_t)q_first * P.hbp + hb) * (2 * REGS * NTP);
+    const int64_t pstride = (int64_t)P.hbp * (2 * REGS * NTP);
+    int at = 4 * (kh * 64 + lane);
+    asm volatile("" : "+v"(at));  // see store_slab
+    float* const rec = rec0 + (qh == 0 ? REGS * NTP : 0);  // a record: [dK | dV]
+    park<DB, NTP>(rec + part * pstride + at, dk);
+    // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
+    // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
+    __syncthreads();
+    if (tid == 0) {
+      __threadfence();
+      const int arrived = atomicAdd(P.col_queue + 8 + rho * P.hbp + hb, 1);
+      if (arrived == nparts - 1) __threadfence();  // only the merging work-group has to see the others' parts
+      item_s[1] = arrived;
+      item_s[0] = next_item;
+    }
+    __syncthreads();
+    if (item_s[1] == nparts - 1) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+        for (int e = 0; e < 16; ++e) dk[db][e] = 0.0f;
+      for (int k = 0; k < nparts; ++k) add_parked<DB, NTP>(rec + k * pstride + at, dk);
+      write_dkv();
+      if (tid == 0) P.col_queue[8 + rho * P.hbp + hb] = 0;
+    }
+    item = (int)scalar((uint32_t)item_s[0]);  // (a scalar: everything that addresses the item follows from it)
+    __syncthreads();  // everyone has read the item, and the staged sums, before the next item's copies and list land
   }
 }
 
@@ -920,8 +1055,7 @@ int launch_bwd(BwdParams& P, int64_t B, int64_t H, hipStream_t s) {
   P.total_wgs = (int32_t)(B * H * P.nbc);
   P.n_extra = std::min<int32_t>(P.total_wgs, kExtraWGs);
   P.Gc = P.G;
-  constexpr bool RS = D == 128;
-  attn_bwd_dkv_kernel<D, RS, EXACT><<<(unsigned)P.total_wgs, RS ? 256 : 128, 0, s>>>(P);
+  attn_bwd_dkv_kernel<D, EXACT><<<(unsigned)P.total_wgs, 256, 0, s>>>(P);
   return bbm::launch_status("bbm_attn_bwd (dk, dv)");
 }
 

@@ -144,6 +144,30 @@ def test_ragged_sizes_with_empty_rows_and_unattended_keys(N, d):
         assert torch.all(dk[:, :, dead] == 0) and torch.all(dv[:, :, dead] == 0)
 
 
+@pytest.mark.parametrize("N", [31, 33, 96, 129, 160, 288])
+@pytest.mark.parametrize("d", [64, 128])
+def test_edges_of_tile_halves_and_rows_without_tiles(N, d):
+    """Lengths around a wave's 32 rows, a 64-row tile and a block row, where copies past the last row come as zeros; one block row
+    of 32 to 256 queries without a single tile (its zeros leave through the slabs that Q came in by), a block column without
+    queries, and one 32 x 32 quarter of a tile alone, which only one of four waves may work on."""
+    B, H = 1, 3
+    q, k, v = make_qkv(B, H, N, d, seed=7 * N + d)
+    do = _d_o(B, H, N, d, seed=7 * N + d + 5)
+    rng = np.random.default_rng(N + d)
+    m = (rng.random((N, N)) < 0.3).astype(np.uint8)
+    m[N // 2:] = 0                                           # the lower half of the rows sees nothing ..
+    m[-1, max(0, N - 33):] = 1                               # .. but for the last row and the keys at the end
+    m[:, 64:96] = 0
+    mask = m[None]
+    ref = oracle.masked_attention_bwd(q, k, v, mask, do)
+    mags = oracle.masked_attention_bwd_magnitudes(q, k, v, mask, do)
+    for Br in (64, 128, 256):
+        dq, dk, dv = _gpu_grads(dict(q=q, k=k, v=v, mask=mask), do, Br)
+        _check((dq, dk, dv), ref, mags, tag=f"bwd edges N={N} d={d} Br={Br}")
+        assert torch.all(dq[:, :, N // 2:-1] == 0)
+        assert torch.all(dk[:, :, 64:96] == 0) and torch.all(dv[:, :, 64:96] == 0)
+
+
 def test_custom_scale_d128():
     """Scales flatter and sharper than 1/sqrt(d) against the same bars."""
     cfg = small_variant("C3", N=640, B=2, H=2)
