@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <utility>
 
 namespace {
 
@@ -55,7 +56,7 @@ struct AttnParams {
   const int32_t* sched;
   int32_t* queue;     // [0] part items handed out, [1] leading work-groups done, [8 + rho*hbp + hb] finished parts of
                       // cut row rho; all zero between calls (each call puts back the zeros it disturbed)
-  float* partials;    // [(cut part)*hbp + hb][regs + 2][threads]
+  float* partials;    // [(cut part)*hbp + hb][(regs + 2) * threads], layout: park_and_merge
   int32_t hbp;        // (batch, head) pairs per mask plane: B*H if Mb == 1, else H
   int32_t n_extra;    // leading work-groups that serve the queue of cut-row parts (LIST mode)
   int32_t G;          // (batch, head) planes whose block rows are interleaved in launch order
@@ -159,6 +160,32 @@ struct IntC {
   static constexpr int value = V;
 };
 
+__device__ __forceinline__ uint32_t scalar(uint32_t uniform) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)uniform); }
+
+// A chain of COUNT matrix instructions whose LDS operands are read R instructions ahead: load(n) reads the operand of
+// instruction n, mul(n, operand) issues it, between(n) is whatever is to be issued behind it.  Left alone the compiler reads
+// one operand, waits, multiplies and only then reads the next; the scheduling barriers pin the order.  (n comes as a type,
+// IntC<n>: the chain has to be unrolled whole.)
+template <typename F, int... N>
+__device__ __forceinline__ void for_each_n(F f, std::integer_sequence<int, N...>) {
+  (f(IntC<N>{}), ...);
+}
+template <int COUNT, int R, typename Load, typename Mul, typename Between>
+__device__ __forceinline__ void mfma_ring(Load load, Mul mul, Between between) {
+  bf16x8 f[R];
+  for_each_n([&](auto n) { f[decltype(n)::value] = load(n); }, std::make_integer_sequence<int, R>{});
+  __builtin_amdgcn_sched_barrier(0);
+  for_each_n(
+      [&](auto i) {
+        constexpr int n = decltype(i)::value;
+        mul(i, f[n % R]);
+        if constexpr (n + R < COUNT) f[n % R] = load(IntC<n + R>{});
+        between(i);
+        __builtin_amdgcn_sched_barrier(0);
+      },
+      std::make_integer_sequence<int, COUNT>{});
+}
+
 // One work-group per (block row, batch, head), tiles from build_window.  SCHED = 2 (LIST mode on a launch too small to
 // fill the chip): every block row is computed in P.split equal parts by as many work-groups, merged like cut rows.
 // With SCHED = 1 (LIST mode) the first
@@ -172,7 +199,7 @@ struct IntC {
 // scales): c = 2^k * r with r in [1, 2); Q is multiplied by 2^k, which is exact in bf16, and r multiplies the
 // accumulator inside the exponential; running maxima are then kept in units of 1/r.
 template <int D, int NW, int SCHED, bool EXACT>
-__global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const AttnParams P) {
+__global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 1) void attn_fwd_kernel(const AttnParams P) {
   constexpr int NT = NW * 64;
   constexpr int BR = NW * 32;
   // LDS tile layout ("blocks"): one asynchronous copy instruction of a wave fills one 1 KiB block with RPB rows
@@ -272,63 +299,31 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const AttnParams P) {
   };
 
   // Asynchronous global -> LDS copy (no registers in between).  One instruction moves 1 KiB per wave: lane l lands at
-  // LDS base + 16*l, i.e. slot l / RC, chunk l % RC of the block, so it fetches row (block + NBLK * slot).
-  // Addresses are (uniform 64-bit tile base) + (32-bit per-lane byte offset): one register per lane, not a pair per copy.
-  const uint32_t g_off = (uint32_t)(g_row * NBLK * D + g_chunk * 8) * 2u;
-  auto load_tile_async = [&](const __bf16* __restrict__ src, int jt, __bf16* dst, int blk_stride) {
-    const int64_t key0 = (int64_t)jt * kBc;
-    const char* tile = reinterpret_cast<const char*>(src + key0 * D);
-    if (key0 + kBc <= Nk) {
+  // LDS base + 16*l, i.e. slot l / RC, chunk l % RC of the block, so it fetches row (block + NBLK * slot).  copy_piece is
+  // instruction n (0 .. 2*LPW-1) of the wave for the tile of list entry e; keys past Nk (`rows` of the 64 lie below it) come as
+  // zeros from the bounds check of the buffer resource: they sit in a tile that is never "full", so the element mask gives them
+  // probability exactly 0, and zeros add nothing.
+  const uint32_t g_off = (uint32_t)((wave + g_row * NBLK) * D + g_chunk * 8) * 2u;
+  auto copy_piece = [&](int jt, int rows, __bf16* kd, __bf16* vd, int n) {
+    const int p = n % LPW, blk = p * NW + wave;
+    const __bf16* const tile = (n < LPW ? Kg : Vg) + (int64_t)jt * (kBc * D);
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(tile), 0, (int)scalar(rows * D * 2), 0x00027000);
+    uint32_t off = g_off;
+    asm volatile("" : "+v"(off));  // one register throughout the tile loop, not one per block
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (void __attribute__((address_space(3)))*)(n < LPW ? kd + blk * KBLK : vd + blk * VBLK), 16,
+                                             off + p * NW * D * 2, 0, 0, 0);
+  };
+  auto rows_of_tile = [&](int jt) { return (int)scalar((uint32_t)max(0, min(kBc, (int)Nk - jt * kBc))); };
+  auto copy_all = [&](int jt, __bf16* kd, __bf16* vd) {
+    const int rows = rows_of_tile(jt);
 #pragma unroll
-      for (int n = 0; n < LPW; ++n) {
-        const int q = n * NW + wave;  // block filled by this instruction
-        __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(tile + q * D * 2 + g_off),
-                                         (void __attribute__((address_space(3)))*)(dst + q * blk_stride), 16, 0, 0);
-      }
-    } else {
-      // Last tile of a ragged key count Nk.  Rows past Nk re-read row Nk-1: such keys sit in a tile that is never "full", the
-      // element mask gives them probability exactly 0, and a finite duplicate row then adds nothing.
-      const int last = (int)(Nk - 1 - key0);  // last real row of the tile
-#pragma unroll
-      for (int n = 0; n < LPW; ++n) {
-        const int q = n * NW + wave;
-        const uint32_t off = (uint32_t)(min(q + g_row * NBLK, last) * D + g_chunk * 8) * 2u;
-        __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(tile + off),
-                                         (void __attribute__((address_space(3)))*)(dst + q * blk_stride), 16, 0, 0);
-      }
-    }
+    for (int n = 0; n < 2 * LPW; ++n) copy_piece(jt, rows, kd, vd, n);
   };
 
   // K fragment of MFMA k-step t, key block kb: row 32*kb + lq, chunk 2t + hh.
   const int kaddr = (lq % NBLK) * KBLK + (lq / NBLK) * D + hh * 8;
-  // S^T = K Q^T for the 64 keys of one LDS tile x this wave's 32 queries
-  // The K fragments go through a ring of kRing register sets, each requested kRing matrix instructions before the one
-  // that consumes it; the scheduling hints pin that order (left to itself the compiler issues every LDS read right
-  // before its MFMA, which then waits out the LDS latency: d=128 dense -1.2 %, tree -3 %; a ring of 8 costs the d=64
-  // kernel its third wave per SIMD, the same treatment of the V fragments of the second product gains nothing).
-  auto qk = [&](const __bf16* ks, f32x16 (&s)[2]) {
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) s[kb] = s_init;
-    constexpr int NF = 2 * KS, kRing = 4;
-    auto frag = [&](int n) {  // fragment n: MFMA k-step n / 2, key block n % 2
-      return *reinterpret_cast<const bf16x8*>(ks + kaddr + (n & 1) * (32 / NBLK) * D + (n >> 1) * 16);
-    };
-    bf16x8 ring[kRing];
-#pragma unroll
-    for (int n = 0; n < kRing; ++n) ring[n] = frag(n);
-#pragma unroll
-    for (int n = 0; n < NF; ++n) {
-      const bf16x8 kf = ring[n % kRing];
-      if (n + kRing < NF) ring[n % kRing] = frag(n + kRing);
-      s[n & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[n >> 1], s[n & 1], 0, 0, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, kRing, 0);  // kRing LDS reads, then (MFMA, LDS read) pairs, then the last MFMAs
-#pragma unroll
-    for (int n = 0; n < NF - kRing; ++n) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, kRing, 0);
+  auto k_frag = [&](const __bf16* ks, int kb, int t) {
+    return *reinterpret_cast<const bf16x8*>(ks + kaddr + kb * (32 / NBLK) * D + t * 16);
   };
 
   // V fragment (transposing read) of 16-key step u, half a, column block db: the lane addresses row
@@ -348,14 +343,17 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const AttnParams P) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
-  auto tile_of = [](uint32_t e) { return e == kNoTile ? -1 : (int)(e & 0x3fffffffu); };
   const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
 
-  // One tile: S^T = K Q^T, mask, online softmax and O^T += V^T P^T for tile e0 whose K and V sit in buffer PB; the
-  // asynchronous copies of the next tile into the other buffer are started first.
-  uint32_t e0, e1;
+  // One tile: S^T = K Q^T, mask, online softmax and O^T += V^T P^T for tile e0 whose K and V sit in buffer PB, in two chains of
+  // matrix instructions with everything that can be behind them: the asynchronous copies of the next tile behind the first, the
+  // exponentials of the next 16 keys behind the second.  Against the copies in one go behind the first product and the
+  // compiler's own order in the second (kernel times, us): 2 x 32 heads of 8192 dense tokens, D = 128, 2075 -> 1971, 1020 -> 996
+  // causal; 4 x 16 causal heads of 4096, D = 64, 195 -> 185; packed sequences 46.6 -> 42.8; tree prefill 141 -> 133.  The maximum
+  // of the first 32 keys behind the products of the second 32, with the mask in the start values: 2-7 % slower everywhere.
+  uint32_t e0, e1_v;  // this step's list entry, and the next one's (as it came from LDS: made a scalar when the step starts)
   uint64_t mw_nxt;
-  auto step = [&](auto pb, int it) {
+  auto step = [&](auto pb, int it) __attribute__((always_inline)) {
     constexpr int PB = decltype(pb)::value;
     const uint64_t mw = mw_nxt;
     __builtin_amdgcn_s_waitcnt(0);  // this wave's asynchronous tile copies of the previous iteration have landed
@@ -364,29 +362,41 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const AttnParams P) {
     __bf16* const k_oth = PB ? k_s0 : k_s1;
     __bf16* const v_cur = PB ? v_s1 : v_s0;
     __bf16* const v_oth = PB ? v_s0 : v_s1;
+    // The next tile's copies go out one by one between the matrix instructions of the first product: requested in one go they
+    // fill the memory pipe's queue, and every wave of the work-group stands there.  Behind the last tile they copy zero rows into
+    // buffers that nobody reads any more, cheaper than a branch around each.
+    const uint32_t e1 = scalar(e1_v);
+    const bool more = e1 != kNoTile, partial = (e0 >> 31) == 0;
+    const int jt1 = more ? (int)(e1 & 0x3fffffffu) : 0, rows1 = more ? rows_of_tile(jt1) : 0;
+    if (more) mw_nxt = (e1 >> 30) == 0 ? mrow[(int64_t)jt1 * N] : 0;
+    e1_v = tiles_s[it + 2];
     // a partial tile in which none of this wave's 32 queries sees a key adds exact zeros: such a wave only takes part
     // in the copies and barriers of the step (not in the dense-tile baseline, which stands for a kernel that knows
     // nothing about the mask's structure)
-    const bool live = (e0 >> 31) != 0 || (SCHED == 0 && P.mode == BBM_MODE_DENSE_BASELINE) || __ballot(mw != 0ull) != 0ull;
-    f32x16 s[2];
-    // Wave priority: the two phases that feed the matrix pipe are raised above the address arithmetic, copy requests
-    // and maxima of the other waves on the SIMD, so a wave that has matrix work issues it first (dense masks: d=64
-    // -3 %, d=128 -1.5 %; neutral on the short rows of packed sequences).
-    __builtin_amdgcn_s_setprio(2);
-    if (live) qk(k_cur, s);
-    __builtin_amdgcn_s_setprio(0);
-    // the next tile's copies are requested behind the first product: their address arithmetic runs while the matrix
-    // pipe works (about 1 % on dense masks)
-    if (e1 != kNoTile) {
-      load_tile_async(Kg, tile_of(e1), k_oth, KBLK);
-      load_tile_async(Vg, tile_of(e1), v_oth, VBLK);
-      if ((e1 >> 30) == 0) mw_nxt = mrow[(int64_t)tile_of(e1) * N];
-      else mw_nxt = 0;
-    }
-
+    const bool live = !partial || (SCHED == 0 && P.mode == BBM_MODE_DENSE_BASELINE) || __ballot(mw != 0ull) != 0ull;
+    if (!live && more) copy_all(jt1, k_oth, v_oth);
+    e0 = e1;
     if (live) {
+      f32x16 s[2];
+      // Wave priority: the two phases that feed the matrix pipe are raised above the address arithmetic, copy requests
+      // and maxima of the other waves on the SIMD, so a wave that has matrix work issues it first (dense masks: d=64
+      // -3 %, d=128 -1.5 %; neutral on the short rows of packed sequences).
+      __builtin_amdgcn_s_setprio(2);
+      s[0] = s_init;
+      s[1] = s_init;
+      mfma_ring<2 * KS, 4>([&](auto i) { return k_frag(k_cur, decltype(i)::value & 1, decltype(i)::value >> 1); },
+                           [&](auto i, bf16x8 f) {
+                             constexpr int n = decltype(i)::value;
+                             s[n & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[n >> 1], s[n & 1], 0, 0, 0);
+                           },
+                           [&](auto i) {
+                             constexpr int n = decltype(i)::value, GAP = KS / LPW;  // matrix instructions per copy
+                             if constexpr (n % GAP == 0) copy_piece(jt1, rows1, k_oth, v_oth, n / GAP);
+                           });
+      __builtin_amdgcn_s_setprio(0);
+
       // ---- element mask (only where the schedule cannot rule out zeros): keep s where the bit is set, else -inf
-      if ((e0 >> 31) == 0) {
+      if (partial) {
   #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
           const uint32_t w = (uint32_t)(mw >> (32 * kb)) >> (4 * hh);
@@ -427,34 +437,38 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const AttnParams P) {
       }
 
       __builtin_amdgcn_s_setprio(1);
-  #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        bf16x8 pf;
-  #pragma unroll
-        for (int e = 0; e < 8; ++e) pf[e] = (__bf16)ex2(s[u / 2][8 * (u % 2) + e]);
-        // row sum of the ROUNDED probabilities (the same numbers the second product consumes), two per instruction
-  #pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          const bf16x2 pair = {pf[e], pf[e + 1]};
+      // ---- O^T += V^T P^T, the exponentials of a 16-key step behind the matrix instructions of the step before
+      bf16x8 pf[2];
+      auto exps = [&](int u, int e0, int e1) {
+#pragma unroll
+        for (int e = e0; e < e1; e += 2) {
+          pf[u & 1][e] = (__bf16)ex2(s[u / 2][8 * (u % 2) + e]);
+          pf[u & 1][e + 1] = (__bf16)ex2(s[u / 2][8 * (u % 2) + e + 1]);
+          // row sum of the ROUNDED probabilities (the same numbers the second product consumes), two per instruction
+          const bf16x2 pair = {pf[u & 1][e], pf[u & 1][e + 1]};
           l_run = __builtin_amdgcn_fdot2_f32_bf16(pair, ones2, l_run, false);
         }
-        // ---- O^T += V^T P^T
-  #pragma unroll
-        for (int db = 0; db < DB; ++db) oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(v_cur, u, db), pf, oacc[db], 0, 0, 0);
-      }
+      };
+      exps(0, 0, 8);
+      mfma_ring<4 * DB, 3>([&](auto i) { return v_frag(v_cur, decltype(i)::value / DB, decltype(i)::value % DB); },
+                           [&](auto i, bf16x8 f) {
+                             constexpr int n = decltype(i)::value;
+                             oacc[n % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, pf[n / DB & 1], oacc[n % DB], 0, 0, 0);
+                           },
+                           [&](auto i) {
+                             constexpr int n = decltype(i)::value, PER = 8 / DB;
+                             if constexpr (n / DB < 3) exps(n / DB + 1, n % DB * PER, (n % DB + 1) * PER);
+                           });
       __builtin_amdgcn_s_setprio(0);
     }
-    e0 = e1;
-    e1 = tiles_s[it + 2];
   };
 
   // Starts the asynchronous copies of a window's first tile e (into buffer 0) and asks for its mask word.
   auto start_tile0 = [&](uint32_t e) {
-    e0 = e;
-    mw_nxt = 0;
-    load_tile_async(Kg, tile_of(e0), k_s0, KBLK);
-    load_tile_async(Vg, tile_of(e0), v_s0, VBLK);
-    if ((e0 >> 30) == 0) mw_nxt = mrow[(int64_t)tile_of(e0) * N];
+    e0 = scalar(e);
+    const int jt = (int)(e0 & 0x3fffffffu);
+    copy_all(jt, k_s0, v_s0);
+    mw_nxt = (e0 >> 30) == 0 ? mrow[(int64_t)jt * N] : 0;
   };
 
   // Runs the tiles listed in tiles_s[0 .. count) (followed by sentinels) through the pipeline; `started` says that
@@ -471,11 +485,12 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const AttnParams P) {
       }
       q_pending = false;
     }
-    e1 = tiles_s[1];
+    e1_v = tiles_s[1];
     for (int it = 0; it < count; it += 2) {
       step(IntC<0>{}, it);
       if (it + 1 < count) step(IntC<1>{}, it + 1);
     }
+    __builtin_amdgcn_s_waitcnt(0);  // (the zero rows that the last step copied)
     __syncthreads();  // whoever comes next rewrites the tile list and the K/V buffers
   };
 
@@ -529,6 +544,56 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const AttnParams P) {
       P.lse[(int64_t)bh * N + qrow] = l_tot > 0.0f ? m_run * (rr / kLog2e) + __logf(l_tot) : -INFINITY;
   };
 
+  // Parks the unnormalised partial result of part `part` of `nparts` of the row whose records start at rec0, pstride apart, and
+  // -- in the work-group that arrives last at `counter` -- merges all of them in part order (the result does not depend on which
+  // part came last) and writes the row.  A record: [register / 4][thread][register % 4], then maximum and sum: 16 bytes a lane
+  // and access.
+  auto park_and_merge = [&](float* rec0, int64_t pstride, int part, int nparts, int32_t* counter, int next_item) {
+    int at = tid;
+    asm volatile("" : "+v"(at));  // keeps the addresses out of the tile loop
+    float* const rec = rec0 + part * pstride;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(rec + ((db * 4 + g) * NT + at) * 4) =
+            make_float4(oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]);
+    rec[REGS * NT + at] = m_run;
+    rec[(REGS + 1) * NT + at] = l_run;
+    // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
+    // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
+    __syncthreads();
+    if (tid == 0) {
+      __threadfence();
+      const int arrived = atomicAdd(counter, 1);
+      if (arrived == nparts - 1) __threadfence();  // only the merging work-group has to see the others' parts
+      item_s[1] = arrived;
+      item_s[0] = next_item;
+    }
+    __syncthreads();
+    if (item_s[1] != nparts - 1) return;
+    float m_all = -INFINITY;
+    for (int k = 0; k < nparts; ++k) m_all = fmaxf(m_all, rec0[k * pstride + REGS * NT + at]);
+    const float m_fin = (m_all == -INFINITY) ? 0.0f : m_all;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      for (int e = 0; e < 16; ++e) oacc[db][e] = 0.0f;
+    l_run = 0.0f;
+    for (int k = 0; k < nparts; ++k) {
+      const float* const rk = rec0 + k * pstride;
+      const float wgt = ex2(rk[REGS * NT + at] - m_fin);
+      l_run += wgt * rk[(REGS + 1) * NT + at];
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+        for (int g = 0; g < 4; ++g) {
+          const float4 x = *reinterpret_cast<const float4*>(rk + ((db * 4 + g) * NT + at) * 4);
+          oacc[db][4 * g] += wgt * x.x, oacc[db][4 * g + 1] += wgt * x.y, oacc[db][4 * g + 2] += wgt * x.z, oacc[db][4 * g + 3] += wgt * x.w;
+        }
+    }
+    m_run = m_all;
+    write_output();
+    if (tid == 0) *counter = 0;  // last user of this counter: leave it zero for the next call
+  };
+
   // ---- LIST mode on a small launch: work-group = (block row, part); the parts of a row run side by side and the last
   // one to finish merges them in part order (same arithmetic as the parts of a cut row)
   if constexpr (SCHED == 2) {
@@ -561,44 +626,8 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const AttnParams P) {
       q_pending = false;
     }
     const int row = m * P.nbr + i;
-    float* rec = P.partials + (((int64_t)row * S + part) * P.hbp + hb) * ((REGS + 2) * NT) + tid;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-      for (int e = 0; e < 16; ++e) rec[(db * 16 + e) * NT] = oacc[db][e];
-    rec[REGS * NT] = m_run;
-    rec[(REGS + 1) * NT] = l_run;
-    // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
-    // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
-    __syncthreads();
-    if (tid == 0) {
-      __threadfence();
-      const int arrived = atomicAdd(P.queue + 8 + row * P.hbp + hb, 1);
-      if (arrived == S - 1) __threadfence();  // only the merging work-group has to see the others' parts
-      item_s[1] = arrived;
-    }
-    __syncthreads();
-    if (item_s[1] == S - 1) {
-      const float* r0 = P.partials + ((int64_t)row * S * P.hbp + hb) * ((REGS + 2) * NT) + tid;
-      const int64_t pstride = (int64_t)P.hbp * ((REGS + 2) * NT);
-      float m_all = -INFINITY;
-      for (int k = 0; k < S; ++k) m_all = fmaxf(m_all, r0[k * pstride + REGS * NT]);
-      const float m_fin = (m_all == -INFINITY) ? 0.0f : m_all;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-        for (int e = 0; e < 16; ++e) oacc[db][e] = 0.0f;
-      l_run = 0.0f;
-      for (int k = 0; k < S; ++k) {
-        const float* rk = r0 + k * pstride;
-        const float wgt = ex2(rk[REGS * NT] - m_fin);
-        l_run += wgt * rk[(REGS + 1) * NT];
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-          for (int e = 0; e < 16; ++e) oacc[db][e] += wgt * rk[(db * 16 + e) * NT];
-      }
-      m_run = m_all;
-      write_output();
-      if (tid == 0) P.queue[8 + row * P.hbp + hb] = 0;  // last user of this counter: leave it zero for the next call
-    }
+    park_and_merge(P.partials + ((int64_t)row * S * P.hbp + hb) * ((REGS + 2) * NT), (int64_t)P.hbp * ((REGS + 2) * NT), part, S,
+                   P.queue + 8 + row * P.hbp + hb, 0);
     return;
   }
 
@@ -639,104 +668,58 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const AttnParams P) {
     }
   }
   // ---- LIST mode, the first n_extra work-groups: before their own block row they serve the queue of cut-row parts
-  // (nothing to do, and no cost, when the schedule cut no row)
+  // (nothing to do, and no cost, when the schedule cut no row).  The tile loop is in the program twice, here and below: with one
+  // loop for parts and own row the short rows of packed sequences took 44.9 us instead of 41.8, a 16384-token window 123 instead
+  // of 115 (the backward kernels, which are short of registers, gained from it).
   if (SCHED == 1 && (int)blockIdx.x < P.n_extra) {
-    const int32_t* __restrict__ S = P.sched;
-  const int n_items = nparts_all * P.hbp;
-  // The first item of a work-group is its own index; later ones come from the queue counter, which therefore stands
-  // for "n_extra items already handed out".
-  int item = blockIdx.x;
-  while (item < n_items) {
-    int next_item = 0;
-    if (tid == 0) next_item = P.n_extra + atomicAdd(P.queue, 1);  // asked now, needed after this item
-    const int hb = item / nparts_all;
-    const int32_t* seg = S + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
-    const int row = seg[0], p0 = seg[1], nt = seg[2], part = seg[3], nparts = seg[4], q_first = seg[5], rho = seg[6];
-    m = row / P.nbr;
-    i = row - m * P.nbr;
-    bh = (P.Mb == 1) ? hb : m * P.H + hb;
-    begin_item();
-    run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + p0, nt, (uint32_t)seg[7]);
-
-    {
-      // ---- park the unnormalised partial result; the last part of the row to arrive merges them all
-      float* rec = P.partials + ((int64_t)(q_first + part) * P.hbp + hb) * ((REGS + 2) * NT) + tid;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-        for (int e = 0; e < 16; ++e) rec[(db * 16 + e) * NT] = oacc[db][e];
-      rec[REGS * NT] = m_run;
-      rec[(REGS + 1) * NT] = l_run;
-      // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
-      // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
-      __syncthreads();
-      if (tid == 0) {
-        __threadfence();
-        const int arrived = atomicAdd(P.queue + 8 + rho * P.hbp + hb, 1);
-        if (arrived == nparts - 1) __threadfence();  // only the merging work-group has to see the others' parts
-        item_s[1] = arrived;
-      }
-      __syncthreads();
-      const bool last = item_s[1] == nparts - 1;
-      if (last) {
-        const float* r0 = P.partials + ((int64_t)q_first * P.hbp + hb) * ((REGS + 2) * NT) + tid;
-        const int64_t pstride = (int64_t)P.hbp * ((REGS + 2) * NT);
-        float m_all = -INFINITY;
-        for (int k = 0; k < nparts; ++k) m_all = fmaxf(m_all, r0[k * pstride + REGS * NT]);
-        const float m_fin = (m_all == -INFINITY) ? 0.0f : m_all;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-          for (int e = 0; e < 16; ++e) oacc[db][e] = 0.0f;
-        l_run = 0.0f;
-        for (int k = 0; k < nparts; ++k) {  // fixed order: the result does not depend on which part came last
-          const float* rk = r0 + k * pstride;
-          const float wgt = ex2(rk[REGS * NT] - m_fin);
-          l_run += wgt * rk[(REGS + 1) * NT];
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-            for (int e = 0; e < 16; ++e) oacc[db][e] += wgt * rk[(db * 16 + e) * NT];
-        }
-        m_run = m_all;
-        write_output();
-        if (tid == 0) P.queue[8 + rho * P.hbp + hb] = 0;  // last user of this counter: leave it zero for the next call
-      }
+    const int n_items = nparts_all * P.hbp;
+    // The first item of a work-group is its own index; later ones come from the queue counter, which therefore stands
+    // for "n_extra items already handed out".
+    int item = blockIdx.x;
+    while (item < n_items) {
+      int next_item = 0;
+      if (tid == 0) next_item = P.n_extra + atomicAdd(P.queue, 1);  // asked now, needed after this item
+      const int hb = item / nparts_all;
+      const int32_t* seg = P.sched + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
+      const int row = seg[0], p0 = seg[1], nt = seg[2], part = seg[3], nparts = seg[4], q_first = seg[5], rho = seg[6];
+      m = row / P.nbr;
+      i = row - m * P.nbr;
+      bh = (P.Mb == 1) ? hb : m * P.H + hb;
+      begin_item();
+      run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + p0, nt, (uint32_t)seg[7]);
+      park_and_merge(P.partials + ((int64_t)q_first * P.hbp + hb) * ((REGS + 2) * NT), (int64_t)P.hbp * ((REGS + 2) * NT), part, nparts,
+                     P.queue + 8 + rho * P.hbp + hb, next_item);
+      item = (int)scalar((uint32_t)item_s[0]);  // (a scalar: everything that addresses the item follows from it)
+      __syncthreads();  // everyone has read the item, and the staged output, before the next item's copies and list land
     }
-
-    if (tid == 0) item_s[0] = next_item;
-    __syncthreads();
-    item = item_s[0];
-    __syncthreads();  // everyone has read the item before thread 0 may publish another one
-  }
-  // the last leading work-group to leave the queue puts the two queue counters back to zero for the next call
-  if (n_items > 0 && tid == 0 && atomicAdd(P.queue + 1, 1) == P.n_extra - 1) {
-    P.queue[0] = 0;
-    P.queue[1] = 0;
-  }
+    // the last leading work-group to leave the queue puts the two queue counters back to zero for the next call
+    if (n_items > 0 && tid == 0 && atomicAdd(P.queue + 1, 1) == P.n_extra - 1) {
+      P.queue[0] = 0;
+      P.queue[1] = 0;
+    }
   }
 
-  {
-    bh = own_bh;
-    m = own_m;
-    if (SCHED == 1) {
-      i = own_rec.x;
-      const int n_list = own_rec.z;
-      begin_item();
-      if (n_list <= split_T) {  // a row the schedule cut belongs to the queue
-        if (n_list > 0) run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + own_rec.y, n_list, (uint32_t)own_rec.w);
-        write_output();
-      }
-    } else {
-      i = P.nbr - 1 - own_rank;  // from the last row up: long rows first for causal-like masks
-      begin_item();
-      const int nwin = num_windows(P, m, i, 0, P.nbc);
-      for (int win = 0; win < nwin; ++win) {
-        const int count = build_window<NW>(P, m, i, win, tiles_s, cnt_s, 0, P.nbc);
-        if (count > 0) run_window(count, false);
-      }
+  bh = own_bh;
+  m = own_m;
+  if (SCHED == 1) {
+    i = own_rec.x;
+    const int n_list = own_rec.z;
+    begin_item();
+    if (n_list <= split_T) {  // a row the schedule cut belongs to the queue
+      if (n_list > 0) run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + own_rec.y, n_list, (uint32_t)own_rec.w);
       write_output();
     }
+  } else {
+    i = P.nbr - 1 - own_rank;  // from the last row up: long rows first for causal-like masks
+    begin_item();
+    const int nwin = num_windows(P, m, i, 0, P.nbc);
+    for (int win = 0; win < nwin; ++win) {
+      const int count = build_window<NW>(P, m, i, win, tiles_s, cnt_s, 0, P.nbc);
+      if (count > 0) run_window(count, false);
+    }
+    write_output();
   }
 }
-
 
 // Leading work-groups that serve the queue of cut-row parts before their own block row (LIST mode).
 constexpr int kExtraWGs = 256;
