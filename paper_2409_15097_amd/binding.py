@@ -105,13 +105,23 @@ def _check(rc: int):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# A small call is all submission: 29 us of host time for the three calls of a step over 256 tokens, of which the library and the
+# launches are 10, and 8.8 were torch.cuda.current_stream() building a Stream object per call.  The raw handle of the current
+# device's current stream is what the launches need; torch's own code generators ask for it in the same way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream=None):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    torch.cuda._lazy_init()
+    return _raw_stream(_current_device())
 
 
 def _cdiv(a, b):
@@ -144,7 +154,7 @@ class BlockIndex:
     col_sched: Optional[torch.Tensor] = None
 
     def c_struct(self) -> _CIndex:
-        g = lambda t: None if t is None else t.data_ptr()
+        g = _ptr
         return _CIndex(self.Br, self.Bc, self.Mb, self.nbr, self.nbc, self.N, self.N if self.Nk is None else self.Nk,
                        g(self.blk_class), g(self.bin_blk_mat),
                        g(self.offset), g(self.total_ones), g(self.nz_lo), g(self.nz_hi), g(self.nz_cnt),
@@ -185,6 +195,8 @@ def bbm_build_block_mask_rect(mask: torch.Tensor, Br: int, Bc: int, idx: Optiona
 
 
 def _alloc_runs(idx: BlockIndex):
+    if not (idx.offset is None or idx.total_ones is None or idx.nz_lo is None or idx.nz_hi is None or idx.nz_cnt is None):
+        return
     for name in ("offset", "total_ones", "nz_lo", "nz_hi", "nz_cnt"):
         if getattr(idx, name) is None:
             setattr(idx, name, torch.empty((idx.Mb, idx.nbr), dtype=torch.int32, device=idx.blk_class.device))
@@ -288,7 +300,7 @@ def _cached_workspace(kind: str, nbytes: int, device, stream, shape) -> torch.Te
     """One workspace per (kind, device, stream), grown on demand.  The library leaves its counters at zero after every
     call, but where the counters end and the partial results begin depends on the problem's shape: the workspace is
     zero-filled when it is allocated and again whenever the shape changes (on the stream that uses it)."""
-    key = (kind, device.index, _stream(stream).value)
+    key = (kind, device.index, _stream(stream))
     ws, last_shape = _workspaces.get(key, (None, None))
     if ws is None or ws.numel() < nbytes:
         ws = torch.zeros(max(16, nbytes), dtype=torch.uint8, device=device)
@@ -301,20 +313,22 @@ def _cached_workspace(kind: str, nbytes: int, device, stream, shape) -> torch.Te
 
 
 def _fwd_args(q, k, v, idx, softmax_scale, out, lse, stream):
-    assert q.is_cuda and q.dtype == torch.bfloat16 and q.is_contiguous() and k.is_contiguous() and v.is_contiguous()
-    assert v.shape == k.shape and k.shape[:2] == q.shape[:2] and k.shape[3] == q.shape[3]
-    assert k.dtype == q.dtype and v.dtype == q.dtype
     B, H, N, d = q.shape
-    Nk = k.shape[2]
+    kshape = k.shape
+    Nk = kshape[2]
+    assert q.is_cuda and q.dtype == torch.bfloat16 and q.is_contiguous() and k.is_contiguous() and v.is_contiguous()
+    assert v.shape == kshape and kshape[0] == B and kshape[1] == H and kshape[3] == d
+    assert k.dtype == torch.bfloat16 and v.dtype == torch.bfloat16
     assert idx.N == N and (idx.N if idx.Nk is None else idx.Nk) == Nk, "the index was built for a mask of another size"
     if softmax_scale is None:
         softmax_scale = float(d) ** -0.5
-    ctx = torch.cuda.stream(stream) if stream is not None else _null_ctx()
-    with ctx:                                   # temporaries belong to the stream the kernels run on
-        if out is None:
-            out = torch.empty_like(q)
-        if lse is None:
-            lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
+    if out is None or lse is None:
+        ctx = torch.cuda.stream(stream) if stream is not None else _null_ctx()
+        with ctx:                               # temporaries belong to the stream the kernels run on
+            if out is None:
+                out = torch.empty_like(q)
+            if lse is None:
+                lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
     return B, H, N, Nk, d, softmax_scale, out, lse
 
 
@@ -332,9 +346,10 @@ def bbm_attn_fwd_rect(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, idx: Bl
     """q: bf16 CUDA tensor [B,H,Nq,d], k, v: [B,H,Nk,d], contiguous.  Returns (O bf16 [B,H,Nq,d], lse fp32 [B,H,Nq]).
     Equal Nq and Nk go through the square entry point of the library."""
     B, H, N, Nk, d, softmax_scale, out, lse = _fwd_args(q, k, v, idx, softmax_scale, out, lse, stream)
-    need = bbm_attn_fwd_workspace_bytes(B, H, N, d, idx.Br, idx.Bc, mode)
-    if workspace is None and need > 0:
-        workspace = _cached_workspace("fwd", need, q.device, stream, (B, H, N, d, idx.Br))
+    if workspace is None:
+        need = bbm_attn_fwd_workspace_bytes(B, H, N, d, idx.Br, idx.Bc, mode)
+        if need > 0:
+            workspace = _cached_workspace("fwd", need, q.device, stream, (B, H, N, d, idx.Br))
     cs = idx.c_struct()
     ws_bytes = 0 if workspace is None else workspace.numel()
     if Nk == N:
