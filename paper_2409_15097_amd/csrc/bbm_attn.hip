@@ -56,7 +56,7 @@ struct AttnParams {
   const int32_t* sched;
   int32_t* queue;     // [0] part items handed out, [1] leading work-groups done, [8 + rho*hbp + hb] finished parts of
                       // cut row rho; all zero between calls (each call puts back the zeros it disturbed)
-  float* partials;    // [(cut part)*hbp + hb][(regs + 2) * threads], layout: park_and_merge
+  float* partials;    // [(cut part)*hbp + hb][(regs + 2) * threads], layout: park
   int32_t hbp;        // (batch, head) pairs per mask plane: B*H if Mb == 1, else H
   int32_t n_extra;    // leading work-groups that serve the queue of cut-row parts (LIST mode)
   int32_t G;          // (batch, head) planes whose block rows are interleaved in launch order
@@ -199,7 +199,7 @@ __device__ __forceinline__ void mfma_ring(Load load, Mul mul, Between between) {
 // scales): c = 2^k * r with r in [1, 2); Q is multiplied by 2^k, which is exact in bf16, and r multiplies the
 // accumulator inside the exponential; running maxima are then kept in units of 1/r.
 template <int D, int NW, int SCHED, bool EXACT>
-__global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 1) void attn_fwd_kernel(const AttnParams P) {
+__global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) void attn_fwd_kernel(const AttnParams P) {
   constexpr int NT = NW * 64;
   constexpr int BR = NW * 32;
   // LDS tile layout ("blocks"): one asynchronous copy instruction of a wave fills one 1 KiB block with RPB rows
@@ -544,49 +544,50 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 1) void attn_fwd_
       P.lse[(int64_t)bh * N + qrow] = l_tot > 0.0f ? m_run * (rr / kLog2e) + __logf(l_tot) : -INFINITY;
   };
 
-  // Parks the unnormalised partial result of part `part` of `nparts` of the row whose records start at rec0, pstride apart, and
-  // -- in the work-group that arrives last at `counter` -- merges all of them in part order (the result does not depend on which
-  // part came last) and writes the row.  A record: [register / 4][thread][register % 4], then maximum and sum: 16 bytes a lane
-  // and access.
-  auto park_and_merge = [&](float* rec0, int64_t pstride, int part, int nparts, int32_t* counter, int next_item) {
-    int at = tid;
-    asm volatile("" : "+v"(at));  // keeps the addresses out of the tile loop
-    float* const rec = rec0 + part * pstride;
+  // A parked partial result: [register / 2][thread][register % 2], then (maximum, sum), 8 bytes a lane and access.
+  auto park = [&](float* rec, int at) {
 #pragma unroll
     for (int db = 0; db < DB; ++db)
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<float4*>(rec + ((db * 4 + g) * NT + at) * 4) =
-            make_float4(oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]);
-    rec[REGS * NT + at] = m_run;
-    rec[(REGS + 1) * NT + at] = l_run;
-    // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
-    // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
-    __syncthreads();
+      for (int e = 0; e < 16; e += 2) bbm::store_through(rec + ((db * 8 + e / 2) * NT + at) * 2, oacc[db][e], oacc[db][e + 1]);
+    bbm::store_through(rec + (REGS / 2 * NT + at) * 2, m_run, l_run);
+  };
+  auto this_thread = [&]() {
+    int at = tid;
+    asm volatile("" : "+v"(at));  // keeps the addresses out of the tile loop
+    return at;
+  };
+
+  // Cut rows: parks the result of part `part` of `nparts` of the row whose records start at rec0, pstride apart, and -- in the
+  // work-group that arrives last at `counter` -- merges all of them in part order (the result does not depend on which part
+  // came last) and writes the row.
+  auto park_and_merge = [&](float* rec0, int64_t pstride, int part, int nparts, int32_t* counter, int next_item) {
+    const int at = this_thread();
+    park(rec0 + part * pstride, at);
+    bbm::hand_over();
     if (tid == 0) {
-      __threadfence();
-      const int arrived = atomicAdd(counter, 1);
-      if (arrived == nparts - 1) __threadfence();  // only the merging work-group has to see the others' parts
-      item_s[1] = arrived;
+      item_s[1] = atomicAdd(counter, 1);
       item_s[0] = next_item;
     }
     __syncthreads();
     if (item_s[1] != nparts - 1) return;
     float m_all = -INFINITY;
-    for (int k = 0; k < nparts; ++k) m_all = fmaxf(m_all, rec0[k * pstride + REGS * NT + at]);
+    for (int k = 0; k < nparts; ++k) m_all = fmaxf(m_all, bbm::load_through(rec0 + k * pstride + (REGS / 2 * NT + at) * 2).x);
     const float m_fin = (m_all == -INFINITY) ? 0.0f : m_all;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
       for (int e = 0; e < 16; ++e) oacc[db][e] = 0.0f;
     l_run = 0.0f;
+#pragma unroll 1
     for (int k = 0; k < nparts; ++k) {
       const float* const rk = rec0 + k * pstride;
-      const float wgt = ex2(rk[REGS * NT + at] - m_fin);
-      l_run += wgt * rk[(REGS + 1) * NT + at];
+      const float2 ml = bbm::load_through(rk + (REGS / 2 * NT + at) * 2);
+      const float wgt = ex2(ml.x - m_fin);
+      l_run += wgt * ml.y;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
-        for (int g = 0; g < 4; ++g) {
-          const float4 x = *reinterpret_cast<const float4*>(rk + ((db * 4 + g) * NT + at) * 4);
-          oacc[db][4 * g] += wgt * x.x, oacc[db][4 * g + 1] += wgt * x.y, oacc[db][4 * g + 2] += wgt * x.z, oacc[db][4 * g + 3] += wgt * x.w;
+        for (int e = 0; e < 16; e += 2) {
+          const float2 x = bbm::load_through(rk + ((db * 8 + e / 2) * NT + at) * 2);
+          oacc[db][e] += wgt * x.x, oacc[db][e + 1] += wgt * x.y;
         }
     }
     m_run = m_all;
@@ -594,8 +595,53 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 1) void attn_fwd_
     if (tid == 0) *counter = 0;  // last user of this counter: leave it zero for the next call
   };
 
-  // ---- LIST mode on a small launch: work-group = (block row, part); the parts of a row run side by side and the last
-  // one to finish merges them in part order (same arithmetic as the parts of a cut row)
+  // Rows in S parts that run side by side: the parts meet in pairs, the pairs in pairs of pairs, ..  At every meeting the group
+  // that comes first parks its result and leaves, the second one merges it into its own and goes on, so the work-group that comes
+  // last of all reads one record per level, not all S, and parks nothing.  Which groups meet is fixed and the merge treats its two
+  // sides alike, so the result does not depend on who comes when.  `met` holds one bit per meeting: set by the first to come.
+  // 256 queries x 32 heads against 16640 keys, D = 128, 8 parts: with one work-group merging all records of a row behind
+  // device-wide fences, parking took 16-22 us and merging 26 us of 118.
+  auto merge_tree = [&](float* rec0, int64_t pstride, int part, int S, int32_t* met) {
+    const int at = this_thread();
+    int g = part, node0 = 0;
+#pragma unroll 1
+    for (int l = 0; (1 << l) < S; ++l, g >>= 1) {
+      const int groups = (S + (1 << l) - 1) >> l, other = g ^ 1;
+      const int32_t bit = 1 << (node0 + (g >> 1));
+      node0 += (groups + 1) >> 1;
+      if (other >= groups) continue;  // nobody to meet at this level
+      if (tid == 0) item_s[1] = __hip_atomic_load(met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit;
+      __syncthreads();
+      if (item_s[1] == 0) {
+        park(rec0 + ((int64_t)g << l) * pstride, at);
+        bbm::hand_over();
+        if (tid == 0) item_s[0] = atomicOr(met, bit) & bit;
+        __syncthreads();
+        if (item_s[0] == 0) return;
+      }
+      const float* const r = rec0 + ((int64_t)other << l) * pstride;
+      const float2 ml = bbm::load_through(r + (REGS / 2 * NT + at) * 2);
+      const float m_new = fmaxf(m_run, ml.x), m_fin = (m_new == -INFINITY) ? 0.0f : m_new;
+      const float w_own = ex2(m_run - m_fin), w_other = ex2(ml.x - m_fin);
+      {
+#pragma clang fp contract(off)  // both products are rounded, whichever side is the one in registers
+        l_run = w_own * l_run + w_other * ml.y;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          for (int e = 0; e < 16; e += 2) {
+            const float2 x = bbm::load_through(r + ((db * 8 + e / 2) * NT + at) * 2);
+            oacc[db][e] = w_own * oacc[db][e] + w_other * x.x;
+            oacc[db][e + 1] = w_own * oacc[db][e + 1] + w_other * x.y;
+          }
+      }
+      m_run = m_new;
+      __syncthreads();  // everyone has read item_s before the next level's is written
+    }
+    write_output();
+    if (tid == 0) *met = 0;  // last user of this word: leave it zero for the next call
+  };
+
+  // ---- a launch too small to fill the chip: work-group = (block row, part), merged by merge_tree
   if constexpr (SCHED == 2) {
     const int S = P.split;
     const int part = (int)blockIdx.x % S, rest = (int)blockIdx.x / S;
@@ -626,8 +672,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 1) void attn_fwd_
       q_pending = false;
     }
     const int row = m * P.nbr + i;
-    park_and_merge(P.partials + ((int64_t)row * S * P.hbp + hb) * ((REGS + 2) * NT), (int64_t)P.hbp * ((REGS + 2) * NT), part, S,
-                   P.queue + 8 + row * P.hbp + hb, 0);
+    merge_tree(P.partials + ((int64_t)row * S * P.hbp + hb) * ((REGS + 2) * NT), (int64_t)P.hbp * ((REGS + 2) * NT), part, S,
+               P.queue + 8 + row * P.hbp + hb);
     return;
   }
 
@@ -749,6 +795,7 @@ inline size_t partial_bytes(int64_t Mb, int64_t nbr, int64_t hbp, int d, int Br)
 // with 260 tiles per row and 64 rows, 4 / 8 parts take 0.114 / 0.108 ms against 0.32 ms unsplit; 128 rows of 256 tiles:
 // 0.265 ms unsplit, 0.154 / 0.114 / 0.144 with 2 / 4 / 8 parts; 384 and 512 rows lose 14-40 % with 2.
 constexpr int kSplitUpTo = 256, kSplitWide = 128, kSplitTarget = 512, kSplitMax = 8, kSplitMinTiles = 32;
+static_assert(kSplitMax <= 32, "one bit of a 32-bit word for each of the at most kSplitMax - 1 meetings of merge_tree");
 inline int split_parts(int64_t total_wgs, int64_t nbc) {
   if (total_wgs > kSplitUpTo) return 1;
   const int64_t min_tiles = total_wgs < kSplitWide ? kSplitMinTiles : 2 * kSplitMinTiles;

@@ -253,21 +253,20 @@ __device__ __forceinline__ void store_slab(const f32x16 (&acc)[D / 32], float mu
   }
 }
 
-// A parked partial sum: [register / 4][STRIDE lanes][register % 4], 16 bytes a lane and access; `at` = base + 4 * this lane.
+// A parked partial sum: [register / 2][STRIDE lanes][register % 2], 8 bytes a lane and access; `at` = base + 2 * this lane.
 template <int DB, int STRIDE>
 __device__ __forceinline__ void park(float* at, const f32x16 (&acc)[DB]) {
 #pragma unroll
   for (int db = 0; db < DB; ++db)
-    for (int g = 0; g < 4; ++g)
-      *reinterpret_cast<float4*>(at + (db * 4 + g) * 4 * STRIDE) = make_float4(acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]);
+    for (int e = 0; e < 16; e += 2) bbm::store_through(at + (db * 8 + e / 2) * 2 * STRIDE, acc[db][e], acc[db][e + 1]);
 }
 template <int DB, int STRIDE>
 __device__ __forceinline__ void add_parked(const float* at, f32x16 (&acc)[DB]) {
 #pragma unroll
   for (int db = 0; db < DB; ++db)
-    for (int g = 0; g < 4; ++g) {
-      const float4 x = *reinterpret_cast<const float4*>(at + (db * 4 + g) * 4 * STRIDE);
-      acc[db][4 * g] += x.x, acc[db][4 * g + 1] += x.y, acc[db][4 * g + 2] += x.z, acc[db][4 * g + 3] += x.w;
+    for (int e = 0; e < 16; e += 2) {
+      const float2 x = bbm::load_through(at + (db * 8 + e / 2) * 2 * STRIDE);
+      acc[db][e] += x.x, acc[db][e + 1] += x.y;
     }
 }
 
@@ -612,17 +611,12 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     // park the partial sums; the last part of the row to arrive adds them all up in part order
     float* const rec0 = P.row_partials + ((int64_t)q_first * P.hbp + hb) * (REGS * NT);
     const int64_t pstride = (int64_t)P.hbp * (REGS * NT);
-    int at = 4 * tid;
+    int at = 2 * tid;
     asm volatile("" : "+v"(at));  // see store_slab
     park<DB, NT>(rec0 + part * pstride + at, dq);
-    // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
-    // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
-    __syncthreads();
+    bbm::hand_over();
     if (tid == 0) {
-      __threadfence();
-      const int arrived = atomicAdd(P.row_queue + 8 + rho * P.hbp + hb, 1);
-      if (arrived == nparts - 1) __threadfence();  // only the merging work-group has to see the others' parts
-      item_s[1] = arrived;
+      item_s[1] = atomicAdd(P.row_queue + 8 + rho * P.hbp + hb, 1);
       item_s[0] = next_item;
     }
     __syncthreads();
@@ -999,18 +993,13 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
     }
     float* const rec0 = P.col_partials + ((int64_t)q_first * P.hbp + hb) * (2 * REGS * NTP);
     const int64_t pstride = (int64_t)P.hbp * (2 * REGS * NTP);
-    int at = 4 * (kh * 64 + lane);
+    int at = 2 * (kh * 64 + lane);
     asm volatile("" : "+v"(at));  // see store_slab
     float* const rec = rec0 + (qh == 0 ? REGS * NTP : 0);  // a record: [dK | dV]
     park<DB, NTP>(rec + part * pstride + at, dk);
-    // one thread publishes for the work-group: the barrier orders everyone's stores before its device-wide release,
-    // and its acquire before everyone's reads after the second barrier (four times fewer fences than one per wave)
-    __syncthreads();
+    bbm::hand_over();
     if (tid == 0) {
-      __threadfence();
-      const int arrived = atomicAdd(P.col_queue + 8 + rho * P.hbp + hb, 1);
-      if (arrived == nparts - 1) __threadfence();  // only the merging work-group has to see the others' parts
-      item_s[1] = arrived;
+      item_s[1] = atomicAdd(P.col_queue + 8 + rho * P.hbp + hb, 1);
       item_s[0] = next_item;
     }
     __syncthreads();
