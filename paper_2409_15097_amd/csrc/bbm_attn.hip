@@ -74,6 +74,7 @@ __device__ __forceinline__ float partner_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+constexpr int kSplitMinTiles = 8;        // list entries that a part of a row in a small launch keeps (split_parts)
 constexpr int kWin = 1024;               // tiles per schedule window (block columns, or list entries)
 constexpr uint32_t kNoTile = 0xffffffffu;  // sentinel after the last entry of a window
 constexpr uint32_t kZeroWord = 0x40000000u;  // entry flag: the tile's mask words are all zero and are not in memory
@@ -643,21 +644,24 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
 
   // ---- a launch too small to fill the chip: work-group = (block row, part), merged by merge_tree
   if constexpr (SCHED == 2) {
-    const int S = P.split;
-    const int part = (int)blockIdx.x % S, rest = (int)blockIdx.x / S;
+    const int part = (int)blockIdx.x % P.split, rest = (int)blockIdx.x / P.split;
+    int S = P.split;  // parts of this row
     bh = rest / P.nbr;
     i = P.nbr - 1 - (rest - bh * P.nbr);
     m = (P.Mb == 1) ? 0 : bh / P.H;
     const int hb = (P.Mb == 1) ? bh : bh - m * P.H;
-    begin_item();
-    if (P.mode == BBM_MODE_LIST) {  // equal shares of the row's list
+    if (P.mode == BBM_MODE_LIST) {  // equal shares of the row's list, none shorter than kSplitMinTiles entries if there are several
       const int32_t* rp = P.row_ptr + (int64_t)m * (P.nbr + 1) + i;
       const int p_row = rp[0], n_row = rp[1] - rp[0];
+      S = max(1, min(S, n_row / kSplitMinTiles));
+      if (part >= S) return;
       const int chunk = (n_row + S - 1) / S;
       const int p0 = p_row + part * chunk, nt = max(0, min(chunk, n_row - part * chunk));
       const uint32_t* __restrict__ list = P.col_idx + (int64_t)m * P.nbr * P.nbc + p0;
+      begin_item();
       if (nt > 0) run_list(list, nt, list[0]);
     } else {  // BITMAP, RUNS: equal shares of the block columns
+      begin_item();
       const int chunk = (P.nbc + S - 1) / S;
       const int clo = part * chunk, chi = min(P.nbc, clo + chunk);
       const int nwin = num_windows(P, m, i, clo, chi);
@@ -672,7 +676,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
       q_pending = false;
     }
     const int row = m * P.nbr + i;
-    merge_tree(P.partials + ((int64_t)row * S * P.hbp + hb) * ((REGS + 2) * NT), (int64_t)P.hbp * ((REGS + 2) * NT), part, S,
+    merge_tree(P.partials + ((int64_t)row * P.split * P.hbp + hb) * ((REGS + 2) * NT), (int64_t)P.hbp * ((REGS + 2) * NT), part, S,
                P.queue + 8 + row * P.hbp + hb);
     return;
   }
@@ -788,18 +792,35 @@ inline size_t partial_bytes(int64_t Mb, int64_t nbr, int64_t hbp, int d, int Br)
 
 // A launch of at most kSplitUpTo work-groups leaves CUs idle or with a single work-group (a few block rows of new
 // tokens against a long key/value cache; one long sequence with few heads): every block row is then computed in
-// split_parts() equal parts -- as many as give every CU two work-groups, but no more than leave a part kSplitMinTiles
-// block columns (twice that from kSplitWide work-groups on: with every CU already busy, parts of 16 tiles on average lost
-// 5 % on a causal mask of 4096, parts of 64 gained 24-39 % from 8192 on).  A part costs a prologue, a parked partial
-// result, a device-wide fence and a share of the merge: with 20 tiles per row, 8 parts were 3.5 times slower than none;
-// with 260 tiles per row and 64 rows, 4 / 8 parts take 0.114 / 0.108 ms against 0.32 ms unsplit; 128 rows of 256 tiles:
-// 0.265 ms unsplit, 0.154 / 0.114 / 0.144 with 2 / 4 / 8 parts; 384 and 512 rows lose 14-40 % with 2.
-constexpr int kSplitUpTo = 256, kSplitWide = 128, kSplitTarget = 512, kSplitMax = 8, kSplitMinTiles = 32;
+// split_parts() parts.  A part costs a prologue, one record parked (64 KiB at d = 128) and a share of the merge, so LIST mode
+// takes as many as give every CU one work-group and leave a part kSplitMinTiles block columns, or, if that leaves a part
+// kSplitLongTiles, as many as give it two, up to 8: numbers in between leave some CUs with two and some with one.  At
+// d = 128 a second work-group per CU takes twice kSplitLongTiles where memory is the bound: with one block row per head, or
+// from kSplitWide work-groups on.  The kernel lowers the number for rows whose list is shorter than that.
+// All keys seen, us, in 1 / 2 / 4 / 8 / 16 / 32 parts.  One block row of 128 queries per head, d = 128:
+//   1 head x 1024 keys 20 / 16 / 16;   x 4096 62 / 37 / 26 / 22 / 22;   x 16384 239 / 123 / 69 / 44 / 33 / 29
+//   16 heads x 4096 64 / 38 / 28 / 25 / 28;   x 16384 236 / 125 / 72 / 47 / 41 / 72;   32 x 8192 121 / 69 / 45 / 39 / 60
+//   64 x 8192 124 / 76 / 57 / 70;   64 x 16384 289 / 162 / 114 / 122;   128 x 4096 68 / 52 / 61;   256 x 4096 106 / 109
+// and d = 64: 64 x 32768 391 / 208 / 128 / 116 / 157;   128 x 8192 100 / 61 / 54 / 83;   256 x 4096 56 / 49 / 75.
+// Two block rows, d = 128: 32 heads x 8192 122 / 70 / 51 / 62;   x 16384 242 / 133 / 93 / 95 (with inputs that come from
+// memory 110 in 4, 106 in 8);   x 32768 544 / 303 / 193 / 157;   64 x 8192 135 / 91 / 95;   128 x 4096 80 / 86.
+// 32 block rows of one head x 32768, d = 128: 468 / 245 / 132 / 84 / 93.
+// BITMAP and RUNS, which cut the block columns into equal ranges and so do not know how long a part's list is, keep to parts of
+// kSplitLongTiles columns (twice that from kSplitWide work-groups on) and at most eight.
+constexpr int kSplitUpTo = 256, kSplitWide = 128, kSplitOne = 256, kSplitTwo = 512, kSplitMax = 32, kSplitLongTiles = 32;
 static_assert(kSplitMax <= 32, "one bit of a 32-bit word for each of the at most kSplitMax - 1 meetings of merge_tree");
-inline int split_parts(int64_t total_wgs, int64_t nbc) {
+inline int split_parts(int64_t total_wgs, int64_t nbr, int64_t nbc, int d, bool list) {
   if (total_wgs > kSplitUpTo) return 1;
-  const int64_t min_tiles = total_wgs < kSplitWide ? kSplitMinTiles : 2 * kSplitMinTiles;
-  const int64_t s = std::min<int64_t>(std::min<int64_t>(kSplitMax, kSplitTarget / total_wgs), nbc / min_tiles);
+  const int64_t two = kSplitTwo / total_wgs;
+  int64_t s;
+  if (list) {
+    const int64_t long_tiles = d == 128 && (nbr == 1 || total_wgs >= kSplitWide) ? 2 * kSplitLongTiles : kSplitLongTiles;
+    s = std::min<int64_t>({kSplitMax, kSplitOne / total_wgs, nbc / kSplitMinTiles});
+    if (nbc >= std::min<int64_t>(8, two) * long_tiles) s = std::max<int64_t>(s, std::min<int64_t>(8, two));
+  } else {
+    const int64_t min_tiles = total_wgs < kSplitWide ? kSplitLongTiles : 2 * kSplitLongTiles;
+    s = std::min<int64_t>(std::min<int64_t>(8, two), nbc / min_tiles);
+  }
   return s < 2 ? 1 : (int)s;
 }
 
@@ -814,7 +835,7 @@ int launch(AttnParams& P, int64_t Mb, void* workspace, size_t workspace_bytes, h
     P.part_cap = (int32_t)cap;
     // a launch too small to fill the chip computes every block row in parts (not the dense-tile baseline, which stands
     // for the plain one-program-per-query-block kernel)
-    if (P.mode != BBM_MODE_DENSE_BASELINE) P.split = split_parts(P.total_wgs, P.nbc);
+    if (P.mode != BBM_MODE_DENSE_BASELINE) P.split = split_parts(P.total_wgs, P.nbr, P.nbc, D, P.mode == BBM_MODE_LIST);
     while (P.split > 1 && (int64_t)P.total_wgs * P.split > cap) --P.split;  // every (row, part, head) parks a record
   }
   if (P.split > 1) {
@@ -836,7 +857,7 @@ extern "C" __attribute__((visibility("default"))) size_t bbm_attn_fwd_workspace_
   // sized for the larger of the two plane counts a caller may use (Mb = 1 or Mb = B): both give Mb*hbp = B*H
   // (N counts the queries; the number of keys is not known here, so the largest split of a small launch is assumed)
   const int64_t nbr = (N + Br - 1) / Br;
-  const int split = split_parts(B * H * nbr, 1 << 30);
+  const int split = split_parts(B * H * nbr, nbr, 1 << 30, d, true);
   if (split > 1) return queue_bytes(1, nbr, B * H) + (size_t)(B * H * nbr * split) * record_bytes(d, Br);
   if (mode == BBM_MODE_BITMAP || mode == BBM_MODE_RUNS) return 0;  // these only ever use it for a small launch
   return queue_bytes(1, nbr, B * H) + partial_bytes(1, nbr, B * H, d, Br);
@@ -933,7 +954,7 @@ int attn_fwd_impl(const char* fn, const void* q, const void* k, const void* v, v
   if (use_static) {
     workspace = nullptr;
     workspace_bytes = 0;
-    if (mode == BBM_MODE_LIST || (mode != BBM_MODE_DENSE_BASELINE && split_parts(B * H * nbr, nbc) > 1)) {
+    if (mode == BBM_MODE_LIST || (mode != BBM_MODE_DENSE_BASELINE && split_parts(B * H * nbr, nbr, nbc, d, mode == BBM_MODE_LIST) > 1)) {
       // the counters and at least one partial result per (batch, head) must fit; what else fits decides whether cut
       // rows and small launches are computed in parts (see launch())
       const size_t floor_bytes = queue_bytes(Mb, nbr, Mb == 1 ? B * H : H) + record_bytes(d, idx->Br);

@@ -409,3 +409,35 @@ def test_launch_of_128_to_256_work_groups_over_long_rows_is_computed_in_parts(d)
                 torch.cuda.synchronize()
                 assert_attention_close(ou, lu, O_ref, lse_ref)
                 assert not torch.equal(o.view(torch.int16), ou.view(torch.int16))      # another order of the sums
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nbc", [15, 16, 24, 41, 57, 136, 256, 300])
+def test_parts_of_a_small_launch_merge_in_pairs_for_any_number_of_parts(nbc, d):
+    """LIST mode with few work-groups takes a part per 8 list entries, at most 32: 1, 2, 3, 5, 7, 17 and 32 parts (the pairs that
+    are merged then have partners missing, or parts of unequal length), each row by its own list: all block columns, half of them,
+    seven (one part, nothing parked), none.  Against the oracle, twice, with the row counters back at zero."""
+    bbm = _bbm()
+    B, H, Nk, Nq = 1, 2, 64 * nbc - 13, 4 * 128 - 5
+    q = make_qkv(B, H, Nq, d, seed=61)[0]
+    _, k, v = make_qkv(B, H, Nk, d, seed=62)
+    mask = (np.random.default_rng(63).random((1, Nq, Nk)) < 0.7).astype(np.uint8)
+    mask[0, :, :64 * (nbc // 4)] = 1
+    mask[0, 128:256, 64 * (nbc // 2):] = 0
+    mask[0, 256:384, 64 * 7:] = 0
+    mask[0, 384:] = 0
+    O_ref, lse_ref = oracle.masked_attention(q, k, v, mask)
+    idx = bbm.build_index(torch.from_numpy(mask).cuda(), 128, 64)
+    need = bbm.bbm_attn_fwd_workspace_bytes(B, H, Nq, d, 128, 64, bbm.BBM_MODE_LIST)
+    ws = torch.zeros(need, dtype=torch.uint8, device="cuda")
+    qt, kt, vt = (bf16_tensor(x) for x in (q, k, v))
+    first = None
+    for _ in range(2):
+        o, lse = bbm.bbm_attn_fwd_rect(qt, kt, vt, idx, mode=bbm.BBM_MODE_LIST, workspace=ws)
+        torch.cuda.synchronize()
+        assert_attention_close(o, lse, O_ref, lse_ref)
+        assert int(ws[:4 * (8 + H * idx.nbr)].view(torch.int32).abs().sum()) == 0
+        if first is not None:
+            assert torch.equal(o.view(torch.int16), first[0].view(torch.int16)) and torch.equal(lse, first[1])
+        first = (o.clone(), lse.clone())
+    assert torch.all(o[0, :, 384:] == 0)
