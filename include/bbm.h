@@ -50,9 +50,12 @@ extern "C" {
                                      flagged full; rows the split schedule cut are computed part by part by extra
                                      work-groups and merged                                                            */
 /* Small launches, all three schedules above: at most 256 work-groups (B*H*nbr) over long rows leave compute units idle
- * or with a single work-group, so EVERY block row is computed in min(8, 512 / (B*H*nbr), nbc / t) equal parts (of its
- * list, resp. of the block columns) by as many work-groups and merged in part order; t = 32 block columns below 128
- * work-groups, 64 from there on; fewer than 2 parts means none.  This needs the workspace; BITMAP and RUNS, which
+ * or with a single work-group, so EVERY block row is computed in equal parts by as many work-groups, which merge them in
+ * pairs, and pairs of pairs, in an order that does not depend on who comes first.  LIST: up to 32 parts of the row's list, one
+ * work-group per compute unit while a part keeps 8 entries, two while it keeps 32 (64 at d = 128 with one block row per head
+ * or 128 work-groups and more); none where Nq = Nk and nbc < 64, so that what a short sequence gives
+ * does not depend on Br.  BITMAP and RUNS: min(8, 512 / (B*H*nbr), nbc / t) parts of the block columns, t = 32 below
+ * 128 work-groups, 64 from there on.  Fewer than 2 parts means none.  This needs the workspace; BITMAP and RUNS, which
  * otherwise need none, run one work-group per block row when none is given. */
 #define BBM_MODE_DENSE_BASELINE 3 /* paper Sec. 3 "naive masking": visit every block, apply the element mask everywhere */
 #define BBM_MODE_AUTO 4           /* LIST if the index carries list and schedule, else RUNS, else BITMAP               */

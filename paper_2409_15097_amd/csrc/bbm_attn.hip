@@ -55,12 +55,13 @@ struct AttnParams {
   // LIST mode: schedule (read-only), work-queue state and partial results of cut rows (in the caller's workspace)
   const int32_t* sched;
   int32_t* queue;     // [0] part items handed out, [1] leading work-groups done, [8 + rho*hbp + hb] finished parts of
-                      // cut row rho; all zero between calls (each call puts back the zeros it disturbed)
+                      // cut row rho, in a small launch the meetings of the row's parts that one side has come to
+                      // (merge_tree); all zero between calls (each call puts back the zeros it disturbed)
   float* partials;    // [(cut part)*hbp + hb][(regs + 2) * threads], layout: park
   int32_t hbp;        // (batch, head) pairs per mask plane: B*H if Mb == 1, else H
   int32_t n_extra;    // leading work-groups that serve the queue of cut-row parts (LIST mode)
   int32_t G;          // (batch, head) planes whose block rows are interleaved in launch order
-  int32_t split;      // parts per block row when the launch is too small to fill the chip (LIST mode), else 1
+  int32_t split;      // most parts per block row when the launch is too small to fill the chip, else 1
   int32_t part_cap;   // records of `partials` the workspace holds; a schedule whose parts need more is not followed
 };
 
@@ -187,8 +188,8 @@ __device__ __forceinline__ void mfma_ring(Load load, Mul mul, Between between) {
       std::make_integer_sequence<int, COUNT>{});
 }
 
-// One work-group per (block row, batch, head), tiles from build_window.  SCHED = 2 (LIST mode on a launch too small to
-// fill the chip): every block row is computed in P.split equal parts by as many work-groups, merged like cut rows.
+// One work-group per (block row, batch, head), tiles from build_window.  SCHED = 2 (a launch too small to fill the chip):
+// every block row is computed in up to P.split equal parts by as many work-groups, which merge them in pairs (merge_tree).
 // With SCHED = 1 (LIST mode) the first
 // P.n_extra work-groups, before turning to their own block row, take the parts of the block rows which the split
 // schedule cut from a queue; the work-group that completes a row's last part merges the parts in part order and
@@ -805,12 +806,15 @@ inline size_t partial_bytes(int64_t Mb, int64_t nbr, int64_t hbp, int d, int Br)
 // Two block rows, d = 128: 32 heads x 8192 122 / 70 / 51 / 62;   x 16384 242 / 133 / 93 / 95 (with inputs that come from
 // memory 110 in 4, 106 in 8);   x 32768 544 / 303 / 193 / 157;   64 x 8192 135 / 91 / 95;   128 x 4096 80 / 86.
 // 32 block rows of one head x 32768, d = 128: 468 / 245 / 132 / 84 / 93.
+// Self-attention (as many queries as keys: what a backward pass follows) over fewer than 2 * kSplitLongTiles block columns is
+// left whole: there the results, and through them the gradients, do not depend on the block height, and the number of parts does.
+// (Cut like the rest, 1 head x 1024 takes 16 us instead of 20.)
 // BITMAP and RUNS, which cut the block columns into equal ranges and so do not know how long a part's list is, keep to parts of
 // kSplitLongTiles columns (twice that from kSplitWide work-groups on) and at most eight.
 constexpr int kSplitUpTo = 256, kSplitWide = 128, kSplitOne = 256, kSplitTwo = 512, kSplitMax = 32, kSplitLongTiles = 32;
 static_assert(kSplitMax <= 32, "one bit of a 32-bit word for each of the at most kSplitMax - 1 meetings of merge_tree");
-inline int split_parts(int64_t total_wgs, int64_t nbr, int64_t nbc, int d, bool list) {
-  if (total_wgs > kSplitUpTo) return 1;
+inline int split_parts(int64_t total_wgs, int64_t nbr, int64_t nbc, int d, bool list, bool self) {
+  if (total_wgs > kSplitUpTo || (self && nbc < 2 * kSplitLongTiles)) return 1;
   const int64_t two = kSplitTwo / total_wgs;
   int64_t s;
   if (list) {
@@ -835,7 +839,7 @@ int launch(AttnParams& P, int64_t Mb, void* workspace, size_t workspace_bytes, h
     P.part_cap = (int32_t)cap;
     // a launch too small to fill the chip computes every block row in parts (not the dense-tile baseline, which stands
     // for the plain one-program-per-query-block kernel)
-    if (P.mode != BBM_MODE_DENSE_BASELINE) P.split = split_parts(P.total_wgs, P.nbr, P.nbc, D, P.mode == BBM_MODE_LIST);
+    if (P.mode != BBM_MODE_DENSE_BASELINE) P.split = split_parts(P.total_wgs, P.nbr, P.nbc, D, P.mode == BBM_MODE_LIST, P.N == P.Nk);
     while (P.split > 1 && (int64_t)P.total_wgs * P.split > cap) --P.split;  // every (row, part, head) parks a record
   }
   if (P.split > 1) {
@@ -857,7 +861,7 @@ extern "C" __attribute__((visibility("default"))) size_t bbm_attn_fwd_workspace_
   // sized for the larger of the two plane counts a caller may use (Mb = 1 or Mb = B): both give Mb*hbp = B*H
   // (N counts the queries; the number of keys is not known here, so the largest split of a small launch is assumed)
   const int64_t nbr = (N + Br - 1) / Br;
-  const int split = split_parts(B * H * nbr, nbr, 1 << 30, d, true);
+  const int split = split_parts(B * H * nbr, nbr, 1 << 30, d, true, false);
   if (split > 1) return queue_bytes(1, nbr, B * H) + (size_t)(B * H * nbr * split) * record_bytes(d, Br);
   if (mode == BBM_MODE_BITMAP || mode == BBM_MODE_RUNS) return 0;  // these only ever use it for a small launch
   return queue_bytes(1, nbr, B * H) + partial_bytes(1, nbr, B * H, d, Br);
@@ -954,7 +958,7 @@ int attn_fwd_impl(const char* fn, const void* q, const void* k, const void* v, v
   if (use_static) {
     workspace = nullptr;
     workspace_bytes = 0;
-    if (mode == BBM_MODE_LIST || (mode != BBM_MODE_DENSE_BASELINE && split_parts(B * H * nbr, nbr, nbc, d, mode == BBM_MODE_LIST) > 1)) {
+    if (mode == BBM_MODE_LIST || (mode != BBM_MODE_DENSE_BASELINE && split_parts(B * H * nbr, nbr, nbc, d, mode == BBM_MODE_LIST, N == Nk) > 1)) {
       // the counters and at least one partial result per (batch, head) must fit; what else fits decides whether cut
       // rows and small launches are computed in parts (see launch())
       const size_t floor_bytes = queue_bytes(Mb, nbr, Mb == 1 ? B * H : H) + record_bytes(d, idx->Br);

@@ -333,13 +333,13 @@ def test_small_launch_computes_every_block_row_in_parts():
     computes every block row in parts.  Rows with fewer tiles than parts, empty rows, a workspace reused by two calls
     (bit-identical results, counters back to zero), and agreement with the one-work-group-per-row schedules."""
     bbm = _bbm()
-    B, H, d, Nq, Nk = 1, 3, 64, 300, 16400          # 257 block columns: 8 parts per block row
+    B, H, d, Nq, Nk = 1, 3, 64, 300, 16400          # 257 block columns: up to 28 parts per block row at Br = 64
     q = make_qkv(B, H, Nq, d, seed=41)[0]
     _, k, v = make_qkv(B, H, Nk, d, seed=42)
     rng = np.random.default_rng(43)
     mask = (rng.random((1, Nq, Nk)) < 0.3).astype(np.uint8)
     mask[0, :, 3000:9000] = 1                      # full tiles, too
-    mask[0, :70, 200:] = 0                         # a block row with 4 tiles only (fewer than the 8 parts)
+    mask[0, :70, 200:] = 0                         # a block row with 4 tiles only
     mask[0, 128:192] = 0                           # an empty block row at Br = 64
     mask[0, 250:260, :] = 1
     O_ref, lse_ref = oracle.masked_attention(q, k, v, mask)

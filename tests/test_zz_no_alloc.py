@@ -51,7 +51,7 @@ def test_static_scratch_forward_matches_the_workspace_forward_on_two_calls_in_a_
         assert _same_bits(ws_out, st_out)
         O_ref, lse_ref = oracle.masked_attention(cfg["q"], cfg["k"], cfg["v"], cfg["mask"])
         assert_attention_close(st_out[0], st_out[1], O_ref, lse_ref)
-    # call 3, smaller again in work-groups: 3 heads x 3 block rows against 16400 keys, every block row in 8 parts
+    # call 3, smaller again in work-groups: 3 heads x 3 block rows against 16400 keys, every block row in parts
     B, H, d, Nq, Nk = 1, 3, 64, 300, 16400
     q = make_qkv(B, H, Nq, d, seed=41)[0]
     _, k, v = make_qkv(B, H, Nk, d, seed=42)
