@@ -314,6 +314,9 @@ size_t bbm_attn_bwd_workspace_bytes(int64_t B, int64_t H, int64_t N, int d, int 
  *     dV_j = sum_i p_ij dO_i,   D_i = <dO_i, O_i>,   dS_ij = p_ij (<dO_i, v_j> - D_i),
  *     dQ_i = softmax_scale * sum_j dS_ij k_j,        dK_j = softmax_scale * sum_i dS_ij q_i.
  * A query with A_i empty (lse = -inf) contributes nothing and gets dQ = 0; a key nobody attends gets dK = dV = 0.
+ * A pair that the mask forbids adds exact zeros also where <q_i, k_j> overflows: rows of q and k that nobody sees may hold
+ * anything finite (padding left as it was found).  A work-group whose sums come out as NaN, by such a pair or by a NaN or
+ * infinity among the values that are seen, goes through its tiles a second time.
  *
  *   q, k, v, o, d_o  device in, bf16 [B][H][N][d] contiguous, 16-byte aligned; o and lse as bbm_attn_fwd returned them.
  *   lse              device in, fp32 [B][H][N] (required).

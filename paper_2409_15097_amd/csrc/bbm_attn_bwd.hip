@@ -270,6 +270,13 @@ __device__ __forceinline__ void add_parked(const float* at, f32x16 (&acc)[DB]) {
     }
 }
 
+// (On the bits: the kernels are compiled with a flag that lets the compiler take any number for not a NaN.)
+__device__ __forceinline__ bool is_nan(float x) {
+  uint32_t bits = __float_as_uint(x);
+  asm volatile("" : "+v"(bits));
+  return (bits & 0x7fffffffu) > 0x7f800000u;
+}
+
 // 16 bytes at p (readable either way), or zeros: masked, since a choice between the two makes the compiler branch per load.
 __device__ __forceinline__ bf16x8 load_or_zero(const __bf16* __restrict__ p, bool ok) {
   uint4 x = *reinterpret_cast<const uint4*>(p);
@@ -315,6 +322,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   __shared__ __attribute__((aligned(16))) __bf16 v_s1[L::ELEMS];
   __shared__ uint32_t tiles_s[kWin + 4];
   __shared__ int item_s[2];
+  __shared__ int again_s;            // a wave's sums are not numbers
   __shared__ float delta_s[NW][32];  // <dO, O> of the waves' rows
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -352,7 +360,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     else
       tile_copy_piece<D, NW>(Vg + at, rows, copy_base, vd, n - LPW, wave);
   };
-  auto copy_all = [&](uint32_t e, __bf16* kd, __bf16* vd) {
+  auto copy_all = [&](uint32_t e, __bf16* kd, __bf16* vd) __attribute__((always_inline)) {
     const int rows = rows_of_tile(tile_of(e) * 64, N);
 #pragma unroll
     for (int n = 0; n < 2 * LPW; ++n) copy_piece(e, rows, kd, vd, n);
@@ -363,8 +371,14 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 
   // One tile: a chain of matrix instructions over its two 32-key halves, S0, dP0, S1, dP1, dQ0, dQ1, with everything else
   // behind them: the next tile's copies behind S0, the exponentials of a half behind its dP, dS0 behind S1, dS1 behind dQ0.
-  auto step = [&](auto pb, int it) __attribute__((always_inline)) {
+  // The mask is in the start values of the scores, -inf where it has no bit.  If the product of such a masked pair overflows
+  // (rows that nobody sees may hold anything finite) the sum is no number, and nor is then any of the query's dQ: the tiles are
+  // gone through again with the mask behind the product (`late`).  Behind the product at once, the mask costs 2-7 % of the
+  // backward pass at D = 64 and 1-4 % at D = 128, on tiles without a mask too; the second pass costs nothing where none is needed,
+  // to 1-2 % where rows are short (a word in LDS is read behind each).
+  auto step = [&](auto pb, auto late, int it) __attribute__((always_inline)) {
     constexpr int PB = decltype(pb)::value;
+    constexpr bool LATE = decltype(late)::value != 0;
     const uint64_t mw = mw_nxt;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -390,20 +404,20 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     static_assert(PER * (KS - 2) >= 16 && PER * (2 * DB - 2) >= 16, "all 16 must find room");
     f32x16 s[2], dp[2];
     uint32_t dsf[2][2][4];  // dS of [half][16-key step], pairs of bf16
-    // The scores start at the negated log-sum-exp, or at -inf, i.e. P = 0, where the mask has no bit.
+    float nl = nl_lane;
+    if constexpr (LATE) asm volatile("" : "+v"(nl));  // (else the compiler keeps 16 copies of it in registers throughout)
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
-      for (int e = 0; e < 16; ++e) s[kb][e] = nl_lane;
-    if (partial) {
+      for (int e = 0; e < 16; ++e) s[kb][e] = nl;  // the scores start at the negated log-sum-exp
+    auto mask_half = [&](int kb) {
+      const uint32_t w = (uint32_t)(mw >> (32 * kb)) >> (4 * hh);
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        const uint32_t w = (uint32_t)(mw >> (32 * kb)) >> (4 * hh);
-        for (int e = 0; e < 16; ++e) {
-          const uint32_t keep = (uint32_t)((int32_t)(w << (31 - (8 * (e / 4) + e % 4))) >> 31);  // all ones iff the bit is set
-          s[kb][e] = __uint_as_float((__float_as_uint(nl_lane) & keep) | (0xff800000u & ~keep));
-        }
+      for (int e = 0; e < 16; ++e) {
+        const uint32_t keep = (uint32_t)((int32_t)(w << (31 - (8 * (e / 4) + e % 4))) >> 31);  // all ones iff the bit is set
+        s[kb][e] = __uint_as_float((__float_as_uint(s[kb][e]) & keep) | (0xff800000u & ~keep));
       }
-    }
+    };
+    if (!LATE && partial) mask_half(0), mask_half(1);
     auto dp_start = [&](f32x16& acc) {
       if constexpr (D == 64) {
         acc = dp_init;
@@ -446,6 +460,8 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
           constexpr int GAP = 2 * LPW < KS ? KS / (2 * LPW) : 1;  // matrix instructions per copy
           if constexpr (n % GAP == 0 && n / GAP < 2 * LPW) copy_piece(e1, rows1, k_oth, v_oth, n / GAP);
           // a product is complete two matrix instructions after its last one was issued
+          if constexpr (LATE && (n == N1 + 2 || n == N3 + 2))
+            if (partial) mask_half(n / N2);
           if constexpr (n >= N1 + 2 && n < N2) exps(0, n - N1 - 2);
           if constexpr (n >= N2 + 2 && n < N3) ds(0, n - N2 - 2);
           if constexpr (n >= N3 + 2 && n < N4) exps(1, n - N3 - 2);
@@ -454,7 +470,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   };
 
   // this lane's query: Q * scale * log2(e) and dO as B operands, D = <dO, O>, the negated statistics
-  auto begin_item = [&](bool write_stats) {
+  auto begin_item = [&](bool write_stats) __attribute__((always_inline)) {
     head_off = (int64_t)bh * N * D;
     int ln = lane;
     asm volatile("" : "+v"(ln));  // keeps the addresses out of the loop over items, see store_slab
@@ -516,7 +532,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   auto run_list = [&](const uint32_t* __restrict__ list, int n_list, uint32_t first, bool write_stats) {
     Kg = P.k + (int64_t)bh * N * D;
     Vg = P.v + (int64_t)bh * N * D;
-    auto start_window = [&](int w0, uint32_t e) {  // the first tile's copies and the list
+    auto start_window = [&](int w0, uint32_t e) __attribute__((always_inline)) {  // the first tile's copies and the list
       e0 = e;
       copy_all(e0, k_s0, v_s0);
       const int count = min(kWin, n_list - w0);
@@ -524,23 +540,29 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
       if (tid < 3) tiles_s[count + tid] = kNoTile;
     };
     constexpr bool EARLY = NW <= 4;  // the waves' slabs of Q leave the buffers of parity 0 to the first tile
-    if (EARLY && n_list > 0) start_window(0, first);
-    begin_item(write_stats);
-    if (!EARLY || n_list == 0) __syncthreads();  // .. or to the epilogue, once every wave has read its slab
-    if (!EARLY && n_list > 0) start_window(0, first);
-    for (int w0 = 0; w0 < n_list; w0 += kWin) {
-      const int count = min(kWin, n_list - w0);
-      if (w0 > 0) start_window(w0, scalar(list[w0]));
-      request_mask(e0);
-      __syncthreads();
-      e1_v = tiles_s[1];
-      for (int it = 0; it < count; it += 2) {
-        step(IntC<0>{}, it);
-        if (it + 1 < count) step(IntC<1>{}, it + 1);
+    auto run = [&](auto late) __attribute__((always_inline)) {
+      if (EARLY && n_list > 0) start_window(0, first);
+      begin_item(write_stats);
+      if (!EARLY || n_list == 0) __syncthreads();  // .. or to the epilogue, once every wave has read its slab
+      if (!EARLY && n_list > 0) start_window(0, first);
+      for (int w0 = 0; w0 < n_list; w0 += kWin) {
+        const int count = min(kWin, n_list - w0);
+        if (w0 > 0) start_window(w0, scalar(list[w0]));
+        request_mask(e0);
+        __syncthreads();
+        if (decltype(late)::value != 0 && tid == 0) again_s = 0;  // (everyone has read it)
+        e1_v = tiles_s[1];
+        for (int it = 0; it < count; it += 2) {
+          step(IntC<0>{}, late, it);
+          if (it + 1 < count) step(IntC<1>{}, late, it + 1);
+        }
+        if (decltype(late)::value == 0 && __any(is_nan(dq[0][0]))) again_s = 1;
+        __builtin_amdgcn_s_waitcnt(0);  // (the zero rows that the last step copied)
+        __syncthreads();  // the next window rewrites the tile list and the buffers; the epilogue stages into them
       }
-      __builtin_amdgcn_s_waitcnt(0);  // (the zero rows that the last step copied)
-      __syncthreads();  // the next window rewrites the tile list and the buffers; the epilogue stages into them
-    }
+    };
+    run(IntC<0>{});
+    if (__builtin_expect(n_list > 0 && scalar(again_s) != 0, 0)) run(IntC<1>{});
   };
 
   auto write_dq = [&]() {
@@ -577,6 +599,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     if (n_list > 0) own_first = P.col_idx[(int64_t)own_m * P.nbr * P.nbc + list_pos];
   }
 
+  if (tid == 0) again_s = 0;
   // The first n_extra work-groups serve the queue of cut-row parts before their own row (nothing to do when no row was cut):
   // one loop for parts and own row, so that the tile loop is in the program once.
   const bool leading = nparts_all > 0 && (int)blockIdx.x < P.n_extra;
@@ -667,6 +690,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
   __shared__ __attribute__((aligned(16))) uint32_t mk_s1[2][64];
   __shared__ uint32_t tiles_s[kWin + 2];  // entries past the last one are read but not used
   __shared__ int item_s[2];
+  __shared__ int again_s;  // a wave's sums are not numbers
   // D = 128: the last pieces of the K operand, which find no room in the registers
   constexpr int KL = D == 128 ? 2 : 0;
   __shared__ __attribute__((aligned(16))) bf16x8 kl_s[KL ? KL : 1][NW][64];
@@ -711,13 +735,13 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
     else
       tile_copy_piece<D, NW>(Gg + at, rows, copy_base, td + L::ELEMS, n - LPW, wave);
   };
-  auto copy_stats = [&](int row0, int rows, bool partial, float* sts, uint32_t (*mkd)[64]) {
+  auto copy_stats = [&](int row0, int rows, bool partial, float* sts, uint32_t (*mkd)[64]) __attribute__((always_inline)) {
     if (qh == 0)
       copy_async<4>((kh == 0 ? nlg : ndg) + row0, rows * 4, lane_now() * 4, sts + kh * 64);
     else if (partial)  // (the words lie 8 bytes apart; this wave's half is the first or the second 4 bytes of each)
       copy_async<4>(mcol + 2 * (int64_t)row0, max(0, rows * 8 - 4), lane_now() * 8, mkd[kh]);
   };
-  auto copy_all = [&](int row0, int rows, __bf16* td) {
+  auto copy_all = [&](int row0, int rows, __bf16* td) __attribute__((always_inline)) {
 #pragma unroll
     for (int n = 0; n < 2 * LPW; ++n) copy_piece(row0, rows, td, n);
   };
@@ -727,8 +751,10 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
   uint32_t e0 = 0, e1 = 0;
   auto entry_of = [&](int s) { return scalar(tiles_s[s >> qs_shift]); };
   auto row_of = [&](uint32_t e, int s) { return (int)(((e & 0x7fffffffu) << qs_shift) + (s & ((1 << qs_shift) - 1))) * 64; };
-  auto step = [&](auto pb, int s) __attribute__((always_inline)) {
+  // `late`: the mask behind the product, see the dQ kernel (a sum here that is no number takes all of the key's dV with it).
+  auto step = [&](auto pb, auto late, int s) __attribute__((always_inline)) {
     constexpr int PB = decltype(pb)::value;
+    constexpr bool LATE = decltype(late)::value != 0;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     __bf16* const q_cur = PB ? t_s1 : t_s0;
@@ -757,7 +783,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
         const float4 x = *reinterpret_cast<const float4*>(nl_cur + 8 * g + hh4);
         sc[4 * g + 0] = x.x, sc[4 * g + 1] = x.y, sc[4 * g + 2] = x.z, sc[4 * g + 3] = x.w;
       }
-      if (partial) {  // -inf, i.e. P = 0, where the mask word (32 keys of a query row) has no bit
+      auto mask_scores = [&]() {  // -inf, i.e. P = 0, where the mask word (32 keys of a query row) has no bit
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const uint4 w = *reinterpret_cast<const uint4*>(mk_cur + 8 * g + hh4);
@@ -768,7 +794,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
             sc[4 * g + e] = __uint_as_float((__float_as_uint(sc[4 * g + e]) & keep) | (0xff800000u & ~keep));
           }
         }
-      }
+      };
+      if (!LATE && partial) mask_scores();
       // One chain of matrix instructions, S, dP, dV, dK, with everything else behind them: the next sub-tile's copies behind
       // S, the exponentials behind dP, dS behind dV.  At D = 128 the fp32 probabilities do not outlive dP (registers): dS is
       // formed from P as the dV product consumes it, rounded to bf16.
@@ -813,6 +840,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
                 dp[4 * g + 0] = x.x, dp[4 * g + 1] = x.y, dp[4 * g + 2] = x.z, dp[4 * g + 3] = x.w;
               }
             }
+            if constexpr (LATE && n == N1 + 2)
+              if (partial) mask_scores();
             if constexpr (n >= N1 + 2 && n < N2) {  // S is complete two matrix instructions after its last one was issued
 #pragma unroll
               for (int e = (n - N1 - 2) * PER; e < min(16, (n - N1 - 1) * PER); e += 2) {
@@ -845,52 +874,58 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
     ndg = P.ndelta + (int64_t)bh * N;
     // this wave's 32-bit half of the packed mask words of block column j (one word per query row)
     mcol = reinterpret_cast<const uint32_t*>(P.packed + ((int64_t)m * P.W + j) * (int64_t)N) + kh;
+    auto run = [&](auto late) __attribute__((always_inline)) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-      for (int e = 0; e < 16; ++e) dk[db][e] = dv[db][e] = 0.0f;
-    for (int w0 = 0; w0 < n_list; w0 += kWin) {
-      const int count = min(kWin, n_list - w0);
-      e0 = w0 > 0 ? scalar(list[w0]) : first;
-      const int row0 = row_of(e0, 0), rows0 = rows_of_tile(row0, N);
-      copy_stats(row0, rows0, (e0 >> 31) == 0, st_s0, mk_s0);
-      copy_all(row0, rows0, t_s0);
-      if (w0 == 0) {
-        // K and V come through the tile buffers of parity 1 as well (keys past N as zeros): straight from memory a lane would
-        // pick its row up in 16-byte pieces, 64 cache lines an instruction, and stand there for 7000 cycles of a column at
-        // D = 64, 12000 at D = 128.
-        const int64_t at = head_off + (int64_t)j * 64 * D;
-        const int keys = rows_of_tile(j * 64, N);
+      for (int db = 0; db < DB; ++db)
+        for (int e = 0; e < 16; ++e) dk[db][e] = dv[db][e] = 0.0f;
+      for (int w0 = 0; w0 < n_list; w0 += kWin) {
+        const int count = min(kWin, n_list - w0);
+        e0 = w0 > 0 ? scalar(list[w0]) : first;
+        const int row0 = row_of(e0, 0), rows0 = rows_of_tile(row0, N);
+        copy_stats(row0, rows0, (e0 >> 31) == 0, st_s0, mk_s0);
+        copy_all(row0, rows0, t_s0);
+        if (w0 == 0) {
+          // K and V come through the tile buffers of parity 1 as well (keys past N as zeros): straight from memory a lane would
+          // pick its row up in 16-byte pieces, 64 cache lines an instruction, and stand there for 7000 cycles of a column at
+          // D = 64, 12000 at D = 128.
+          const int64_t at = head_off + (int64_t)j * 64 * D;
+          const int keys = rows_of_tile(j * 64, N);
 #pragma unroll
-        for (int n = 0; n < LPW; ++n) {
-          tile_copy_piece<D, NW>(P.k + at, keys, copy_base, t_s1, n, wave);
-          tile_copy_piece<D, NW>(P.v + at, keys, copy_base, t_s1 + L::ELEMS, n, wave);
+          for (int n = 0; n < LPW; ++n) {
+            tile_copy_piece<D, NW>(P.k + at, keys, copy_base, t_s1, n, wave);
+            tile_copy_piece<D, NW>(P.v + at, keys, copy_base, t_s1 + L::ELEMS, n, wave);
+          }
         }
-      }
-      for (int t = tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      n_steps = count << qs_shift;
-      e1 = entry_of(1);
-      if (w0 == 0) {  // this lane's key: K * scale * log2(e) and V as B operands
-        const int half = (kh - qh) * (32 / L::NBLK) * D;  // (A addresses this wave's query half of a tile)
+        for (int t = tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        n_steps = count << qs_shift;
+        e1 = entry_of(1);
+        if (w0 == 0) {  // this lane's key: K * scale * log2(e) and V as B operands
+          const int half = (kh - qh) * (32 / L::NBLK) * D;  // (A addresses this wave's query half of a tile)
 #pragma unroll
-        for (int t = 0; t < KS; ++t) {
-          bf16x8 kt = A.row_frag(t_s1 + half, 0, t);
-          vf[t] = A.row_frag(t_s1 + L::ELEMS + half, 0, t);
-          for (int e = 0; e < 8; ++e) kt[e] = (__bf16)((float)kt[e] * c);
-          if (t >= KS - KL)
-            kl_s[t - (KS - KL)][wave][lane] = kt;  // (read back by this wave alone)
-          else
-            kf[t] = kt;
+          for (int t = 0; t < KS; ++t) {
+            bf16x8 kt = A.row_frag(t_s1 + half, 0, t);
+            vf[t] = A.row_frag(t_s1 + L::ELEMS + half, 0, t);
+            for (int e = 0; e < 8; ++e) kt[e] = (__bf16)((float)kt[e] * c);
+            if (t >= KS - KL)
+              kl_s[t - (KS - KL)][wave][lane] = kt;  // (read back by this wave alone)
+            else
+              kf[t] = kt;
+          }
         }
+        if (decltype(late)::value != 0 && tid == 0) again_s = 0;  // (everyone has read it)
+        for (int s = 0; s < n_steps; s += 2) {
+          step(IntC<0>{}, late, s);
+          if (s + 1 < n_steps) step(IntC<1>{}, late, s + 1);
+        }
+        if (decltype(late)::value == 0 && __any(is_nan(dv[0][0]))) again_s = 1;
+        __builtin_amdgcn_s_waitcnt(0);  // (the zero rows that the last step copied)
+        __syncthreads();  // the next window rewrites the list and the buffers; the epilogue stages into them
       }
-      for (int s = 0; s < n_steps; s += 2) {
-        step(IntC<0>{}, s);
-        if (s + 1 < n_steps) step(IntC<1>{}, s + 1);
-      }
-      __builtin_amdgcn_s_waitcnt(0);  // (the zero rows that the last step copied)
-      __syncthreads();  // the next window rewrites the list and the buffers; the epilogue stages into them
-    }
+    };
+    run(IntC<0>{});
+    if (__builtin_expect(n_list > 0 && scalar(again_s) != 0, 0)) run(IntC<1>{});
     // The two waves of a key half exchange: query half 0 hands over its dK and receives dV, query half 1 the other way round.
     float4* const mine = reinterpret_cast<float4*>(qh == 0 ? t_s0 : t_s1) + kh * (REGS / 4) * 64;
     const float4* const theirs = reinterpret_cast<const float4*>(qh == 0 ? t_s1 : t_s0) + kh * (REGS / 4) * 64;
@@ -960,6 +995,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
     }
   }
 
+  if (tid == 0) again_s = 0;
   // The first n_extra work-groups serve the queue of cut-column parts before their own column (nothing to do when no column
   // was cut): one loop for parts and own column, so that the tile loop is in the program once.
   const bool leading = nparts_all > 0 && (int)blockIdx.x < P.n_extra;

@@ -168,6 +168,64 @@ def test_edges_of_tile_halves_and_rows_without_tiles(N, d):
         assert torch.all(dk[:, :, 64:96] == 0) and torch.all(dv[:, :, 64:96] == 0)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("sharper", [1.0, 2.5])
+def test_values_in_rows_that_nobody_sees_do_not_reach_the_gradients(d, sharper):
+    """Padding left as it was found: query and key rows with an empty mask, in the middle of tiles that others use, hold the
+    largest finite numbers, whose products overflow to infinity.  A masked pair adds exact zeros, so all three gradients are bit
+    for bit what they are with zeros in those rows.  An infinity in such a key row still leaves every dK and dV untouched (dQ
+    multiplies it by zero)."""
+    B, H, N = 1, 2, 333
+    q, k, v = make_qkv(B, H, N, d, seed=71)
+    do = _d_o(B, H, N, d, seed=72)
+    mask = (np.random.default_rng(73).random((1, N, N)) < 0.6).astype(np.uint8)
+    mask[0, :128, 64:128] = 1                                 # full tiles as well
+    unseen = np.r_[140:144, 170, 200:211, 300:333]
+    mask[:, unseen] = 0
+    mask[:, :, unseen] = 0
+    scale = sharper * d ** -0.5
+
+    def grads(value, rows_of):
+        x = dict(q=q.copy(), k=k.copy(), v=v, mask=mask)
+        for name in "qk":
+            x[name][:, :, unseen] = value if name in rows_of else 0
+        return x, _gpu_grads(x, do, Br, scale=scale)
+
+    for Br in (64, 128, 256):
+        x, clean = grads(0, "qk")
+        ref = oracle.masked_attention_bwd(x["q"], x["k"], v, mask, do, scale=scale)
+        mags = oracle.masked_attention_bwd_magnitudes(x["q"], x["k"], v, mask, do, scale=scale)
+        _check(clean, ref, mags)
+        for value in (0x7f7f, 0xff7f):                        # +- the largest bf16
+            _, huge = grads(value, "qk")
+            for name, a, b in zip(("dQ", "dK", "dV"), huge, clean):
+                assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (name, Br, hex(value))
+        _, inf = grads(0x7f80, "k")
+        for name, a, b in zip(("dK", "dV"), inf[1:], clean[1:]):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (name, Br, "inf")
+
+
+def test_values_that_nobody_sees_in_cut_rows_and_columns():
+    """The same where block rows and columns are cut into parts and lists are longer than one window: bits with the largest finite
+    numbers in a row that nobody sees, in the middle of the long rows and columns, against bits with zeros there."""
+    B, H, N, d = 1, 1, 16500, 64
+    q, k, v = make_qkv(B, H, N, d, seed=31)
+    do = _d_o(B, H, N, d, seed=32)
+    i = np.arange(N)
+    mask = (np.abs(i[:, None] - i[None, :]) <= 40).astype(np.uint8)
+    mask[:, :64] = 1
+    mask[100:132] = 1
+    unseen = np.r_[33, 110:113, 5000:5003, 16499]
+    mask[unseen] = 0
+    mask[:, unseen] = 0
+    out = []
+    for value in (0, 0x7f7f):
+        q[:, :, unseen], k[:, :, unseen] = value, value
+        out.append(_gpu_grads(dict(q=q, k=k, v=v, mask=mask[None]), do, 64))
+    for name, a, b in zip(("dQ", "dK", "dV"), *out):
+        assert not torch.isnan(b.float()).any() and torch.equal(a.view(torch.int16), b.view(torch.int16)), name
+
+
 def test_custom_scale_d128():
     """Scales flatter and sharper than 1/sqrt(d) against the same bars."""
     cfg = small_variant("C3", N=640, B=2, H=2)
