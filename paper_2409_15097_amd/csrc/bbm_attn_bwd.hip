@@ -253,23 +253,6 @@ __device__ __forceinline__ void store_slab(const f32x16 (&acc)[D / 32], float mu
   }
 }
 
-// A parked partial sum: [register / 2][STRIDE lanes][register % 2], 8 bytes a lane and access; `at` = base + 2 * this lane.
-template <int DB, int STRIDE>
-__device__ __forceinline__ void park(float* at, const f32x16 (&acc)[DB]) {
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-    for (int e = 0; e < 16; e += 2) bbm::store_through(at + (db * 8 + e / 2) * 2 * STRIDE, acc[db][e], acc[db][e + 1]);
-}
-template <int DB, int STRIDE>
-__device__ __forceinline__ void add_parked(const float* at, f32x16 (&acc)[DB]) {
-#pragma unroll
-  for (int db = 0; db < DB; ++db)
-    for (int e = 0; e < 16; e += 2) {
-      const float2 x = bbm::load_through(at + (db * 8 + e / 2) * 2 * STRIDE);
-      acc[db][e] += x.x, acc[db][e + 1] += x.y;
-    }
-}
-
 // (On the bits: the kernels are compiled with a flag that lets the compiler take any number for not a NaN.)
 __device__ __forceinline__ bool is_nan(float x) {
   uint32_t bits = __float_as_uint(x);
@@ -631,12 +614,14 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
       if (n_list <= split_T) write_dq();
       return;
     }
-    // park the partial sums; the last part of the row to arrive adds them all up in part order
+    // park the partial sums; the last part of the row to arrive adds them all up in part order, two records' loads in flight at
+    // D = 64, one's at D = 128 (registers).  With a load at a time the backward pass took 161 instead of 147 us at 2 x 8 heads of
+    // 8192 tokens, window, global tokens and random blocks, D = 64, and 319 instead of 268 at 8 heads of 16384, D = 128.
     float* const rec0 = P.row_partials + ((int64_t)q_first * P.hbp + hb) * (REGS * NT);
     const int64_t pstride = (int64_t)P.hbp * (REGS * NT);
-    int at = 2 * tid;
+    int at = tid;
     asm volatile("" : "+v"(at));  // see store_slab
-    park<DB, NT>(rec0 + part * pstride + at, dq);
+    bbm::store_record<DB, NT>(bbm::record_rsrc(rec0 + part * pstride, REGS * NT), at, dq);
     bbm::hand_over();
     if (tid == 0) {
       item_s[1] = atomicAdd(P.row_queue + 8 + rho * P.hbp + hb, 1);
@@ -647,7 +632,11 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 #pragma unroll
       for (int db = 0; db < DB; ++db)
         for (int e = 0; e < 16; ++e) dq[db][e] = 0.0f;
-      for (int k = 0; k < nparts; ++k) add_parked<DB, NT>(rec0 + k * pstride + at, dq);
+      bbm::for_records<DB, NT, false, D == 64 ? 2 : 1>(rec0, pstride, nparts, at, [&](const f32x16 (&x)[DB], float2) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          for (int e = 0; e < 16; ++e) dq[db][e] += x[db][e];
+      });
       write_dq();
       if (tid == 0) P.row_queue[8 + rho * P.hbp + hb] = 0;  // last user of this counter: zero for the next call
     }
@@ -1029,10 +1018,10 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
     }
     float* const rec0 = P.col_partials + ((int64_t)q_first * P.hbp + hb) * (2 * REGS * NTP);
     const int64_t pstride = (int64_t)P.hbp * (2 * REGS * NTP);
-    int at = 2 * (kh * 64 + lane);
+    int at = kh * 64 + lane;
     asm volatile("" : "+v"(at));  // see store_slab
     float* const rec = rec0 + (qh == 0 ? REGS * NTP : 0);  // a record: [dK | dV]
-    park<DB, NTP>(rec + part * pstride + at, dk);
+    bbm::store_record<DB, NTP>(bbm::record_rsrc(rec + part * pstride, REGS * NTP), at, dk);
     bbm::hand_over();
     if (tid == 0) {
       item_s[1] = atomicAdd(P.col_queue + 8 + rho * P.hbp + hb, 1);
@@ -1043,7 +1032,11 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
 #pragma unroll
       for (int db = 0; db < DB; ++db)
         for (int e = 0; e < 16; ++e) dk[db][e] = 0.0f;
-      for (int k = 0; k < nparts; ++k) add_parked<DB, NTP>(rec + k * pstride + at, dk);
+      bbm::for_records<DB, NTP, false, D == 64 ? 2 : 1>(rec, pstride, nparts, at, [&](const f32x16 (&x)[DB], float2) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          for (int e = 0; e < 16; ++e) dk[db][e] += x[db][e];
+      });
       write_dkv();
       if (tid == 0) P.col_queue[8 + rho * P.hbp + hb] = 0;
     }

@@ -441,3 +441,38 @@ def test_parts_of_a_small_launch_merge_in_pairs_for_any_number_of_parts(nbc, d):
             assert torch.equal(o.view(torch.int16), first[0].view(torch.int16)) and torch.equal(lse, first[1])
         first = (o.clone(), lse.clone())
     assert torch.all(o[0, :, 384:] == 0)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Br", [64, 128, 256])
+def test_cut_rows_of_two_to_ten_parts(d, Br):
+    """LIST mode with more than 256 work-groups and a few long block rows: 10, 5, 3 and 2 parts (an even and an odd number, more than
+    the eight whose maxima are read together), the last part of a row shorter than the others.  Sampled rows against the oracle, twice
+    on one workspace, counters back at zero."""
+    bbm = _bbm()
+    nbr = 36
+    B, H, Nq, Nk = 1, 8, nbr * Br, 64 * 290 - 7
+    q = make_qkv(B, H, Nq, d, seed=81)[0]
+    _, k, v = make_qkv(B, H, Nk, d, seed=82)
+    rng = np.random.default_rng(83)
+    mask = np.zeros((1, Nq, Nk), dtype=np.uint8)
+    mask[0, :, :64] = rng.random((Nq, 64)) < 0.5
+    for row, tiles in ((3, 290), (9, 130), (10, 70), (20, 40)):
+        at = slice(row * Br, (row + 1) * Br)
+        mask[0, at, :64 * tiles] = rng.random((Br, min(Nk, 64 * tiles))) < 0.5
+        mask[0, at, 64 * 7:64 * 19] = 1                      # full tiles as well
+    idx = bbm.build_index(torch.from_numpy(mask).cuda(), Br, 64)
+    assert sorted({int(x) for x in idx.sched.cpu().numpy()[8:8 + 8 * 20].reshape(20, 8)[:, 4]}) == [2, 3, 5, 10]
+    ws = torch.zeros(bbm.bbm_attn_fwd_workspace_bytes(B, H, Nq, d, Br, 64, bbm.BBM_MODE_LIST), dtype=torch.uint8, device="cuda")
+    qt, kt, vt = (bf16_tensor(x) for x in (q, k, v))
+    samples = [(0, int(rng.integers(H)), row * Br + int(rng.integers(Br))) for row in (3, 9, 10, 20, 3, 9, 10, 20, 0, 35)]
+    O_ref, lse_ref = oracle.masked_attention_rows(q, k, v, mask, samples)
+    bi, hi, ri = (torch.tensor(x, device="cuda") for x in zip(*samples))
+    bits = []
+    for _ in range(2):
+        o, lse = bbm.bbm_attn_fwd_rect(qt, kt, vt, idx, mode=bbm.BBM_MODE_LIST, workspace=ws)
+        torch.cuda.synchronize()
+        assert_attention_close(o[bi, hi, ri], lse[bi, hi, ri], O_ref, lse_ref)
+        assert int(ws[:4 * (8 + H * nbr)].view(torch.int32).abs().sum()) == 0
+        bits.append((o.view(torch.int16).clone(), lse.clone()))
+    assert torch.equal(bits[0][0], bits[1][0]) and torch.equal(bits[0][1], bits[1][1])
