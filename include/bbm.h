@@ -32,7 +32,7 @@ extern "C" {
 #define BBM_OK 0
 #define BBM_EINVAL (-1)       /* NULL / misaligned pointer, non-positive size, inconsistent arguments */
 #define BBM_EUNSUPPORTED (-2) /* no kernel instance for this (d, Br, Bc) or block size               */
-#define BBM_EWORKSPACE (-3)   /* workspace smaller than bbm_attn_fwd_workspace_bytes(), or a problem beyond the static
+#define BBM_EWORKSPACE (-3)   /* workspace too small (see bbm_attn_fwd_workspace_bytes()), or a problem beyond the static
                                  scratch of bbm_attn_fwd_static                                       */
 #define BBM_EHIP (-4)         /* the HIP runtime reported a launch failure                            */
 
@@ -190,7 +190,8 @@ size_t bbm_sched_bytes(int64_t Mb, int64_t nbr);
 /*
  * Bytes of device workspace bbm_attn_fwd needs for this problem (0 if none).  Negative sizes return 0.  LIST (and AUTO)
  * must be given it; for BITMAP and RUNS it is what a small launch (see the modes) needs to be computed in parts, and
- * optional.
+ * optional.  The number of keys is not known here, so a small launch is taken to need the most parts of its mode.  LIST also
+ * accepts the bytes returned for BITMAP where those are not 0 (room for eight parts of a row), and takes fewer parts then.
  * Layout: (8 + B*H*ceil(N/Br)) int32 queue counters, rounded up to 256 bytes -- the only part that has to be zero --
  * then room for partial results: (d/2 + 2) * 2*Br floats per record, one record per (cut part, batch, head) resp.
  * per (block row, part, batch, head) of a small launch.  The room for cut rows stops at 32 MiB; a schedule whose parts
@@ -218,8 +219,8 @@ size_t bbm_attn_fwd_workspace_bytes(int64_t B, int64_t H, int64_t N, int d, int 
  *                    BITMAP: bin_blk_mat;  RUNS: bin_blk_mat, offset, total_ones, nz_lo, nz_hi;
  *                    LIST: row_ptr, col_idx, sched;  DENSE_BASELINE: bin_blk_mat or blk_class (an empty block has no packed words).
  *   mode             BBM_MODE_*.
- *   workspace        device scratch of at least bbm_attn_fwd_workspace_bytes(...) bytes, 16-byte aligned (may be NULL
- *                    if 0).  LIST mode keeps its queue counters and the partial results of cut block rows there.
+ *   workspace        device scratch of bbm_attn_fwd_workspace_bytes(...) bytes, 16-byte aligned (may be NULL
+ *                    if 0; see there for the fewest that LIST accepts).  LIST mode keeps its queue counters and the partial results of cut block rows there.
  *                    The workspace's counters (see bbm_attn_fwd_workspace_bytes; zero-filling all of it is fine too)
  *                    must be ZERO-FILLED ONCE after it is allocated; every call puts back the zeros it disturbed, so
  *                    the same workspace can serve any number of later calls of the same (B, H, N, d, Br) without being

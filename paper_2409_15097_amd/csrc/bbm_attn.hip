@@ -862,7 +862,7 @@ extern "C" __attribute__((visibility("default"))) size_t bbm_attn_fwd_workspace_
   // sized for the larger of the two plane counts a caller may use (Mb = 1 or Mb = B): both give Mb*hbp = B*H
   // (N counts the queries; the number of keys is not known here, so the largest split of a small launch is assumed)
   const int64_t nbr = (N + Br - 1) / Br;
-  const int split = split_parts(B * H * nbr, nbr, 1 << 30, d, true, false);
+  const int split = split_parts(B * H * nbr, nbr, 1 << 30, d, mode == BBM_MODE_LIST || mode == BBM_MODE_AUTO, false);
   if (split > 1) return queue_bytes(1, nbr, B * H) + (size_t)(B * H * nbr * split) * record_bytes(d, Br);
   if (mode == BBM_MODE_BITMAP || mode == BBM_MODE_RUNS) return 0;  // these only ever use it for a small launch
   return queue_bytes(1, nbr, B * H) + partial_bytes(1, nbr, B * H, d, Br);
@@ -973,8 +973,13 @@ int attn_fwd_impl(const char* fn, const void* q, const void* k, const void* v, v
       if (int rc = launch_status(fn)) return rc;
     }
   } else {
-    // LIST mode cannot do without its workspace; BITMAP and RUNS use one, if given, to compute a small launch in parts
-    const size_t need = mode == BBM_MODE_LIST ? bbm_attn_fwd_workspace_bytes(B, H, N, d, idx->Br, idx->Bc, mode) : 0;
+    // LIST mode cannot do without its workspace; BITMAP and RUNS use one, if given, to compute a small launch in parts.  What
+    // the parts of BITMAP and RUNS need (at most eight of a row) will do for LIST as well: launch() takes as many as find room.
+    size_t need = 0;
+    if (mode == BBM_MODE_LIST) {
+      need = bbm_attn_fwd_workspace_bytes(B, H, N, d, idx->Br, idx->Bc, BBM_MODE_BITMAP);
+      if (need == 0) need = bbm_attn_fwd_workspace_bytes(B, H, N, d, idx->Br, idx->Bc, mode);
+    }
     if (need > 0 && (!workspace || workspace_bytes < need))
       return fail(BBM_EWORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need, workspace ? workspace_bytes : (size_t)0);
     if (need > 0 && !aligned(workspace, 16)) return fail(BBM_EINVAL, "%s: workspace must be 16-byte aligned", fn);

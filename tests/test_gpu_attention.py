@@ -476,3 +476,29 @@ def test_cut_rows_of_two_to_ten_parts(d, Br):
         assert int(ws[:4 * (8 + H * nbr)].view(torch.int32).abs().sum()) == 0
         bits.append((o.view(torch.int16).clone(), lse.clone()))
     assert torch.equal(bits[0][0], bits[1][0]) and torch.equal(bits[0][1], bits[1][1])
+
+
+def test_small_launch_accepts_a_workspace_with_room_for_eight_parts():
+    """LIST asks for up to 32 parts of a row and accepts the size that suffices for eight (what BITMAP and RUNS ask for): fewer
+    parts, the same values up to the order of the merge.  Anything smaller is refused."""
+    bbm = _bbm()
+    B, H, d, Nq, Nk, Br = 1, 2, 64, 130, 5000, 64
+    q = make_qkv(B, H, Nq, d, seed=91)[0]
+    _, k, v = make_qkv(B, H, Nk, d, seed=92)
+    mask = (np.random.default_rng(93).random((1, Nq, Nk)) < 0.4).astype(np.uint8)
+    O_ref, lse_ref = oracle.masked_attention(q, k, v, mask)
+    idx = bbm.build_index(torch.from_numpy(mask).cuda(), Br, 64)
+    counters = -(-(8 + H * idx.nbr) * 4 // 256) * 256
+    record = (d // 2 + 2) * 2 * Br * 4
+    most = bbm.bbm_attn_fwd_workspace_bytes(B, H, Nq, d, Br, 64, bbm.BBM_MODE_LIST)
+    eight = bbm.bbm_attn_fwd_workspace_bytes(B, H, Nq, d, Br, 64, bbm.BBM_MODE_BITMAP)
+    assert most == counters + H * idx.nbr * 32 * record and eight == counters + H * idx.nbr * 8 * record
+    qt, kt, vt = (bf16_tensor(x) for x in (q, k, v))
+    for size in (most, eight):
+        ws = torch.zeros(size, dtype=torch.uint8, device="cuda")
+        o, lse = bbm.bbm_attn_fwd_rect(qt, kt, vt, idx, mode=bbm.BBM_MODE_LIST, workspace=ws)
+        torch.cuda.synchronize()
+        assert_attention_close(o, lse, O_ref, lse_ref)
+        assert int(ws[:counters].view(torch.int32).abs().sum()) == 0
+    with pytest.raises(RuntimeError, match="workspace"):
+        bbm.bbm_attn_fwd_rect(qt, kt, vt, idx, mode=bbm.BBM_MODE_LIST, workspace=torch.zeros(eight - 16, dtype=torch.uint8, device="cuda"))
