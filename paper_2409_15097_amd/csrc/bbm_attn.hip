@@ -646,7 +646,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
 
   // ---- a launch too small to fill the chip: work-group = (block row, part), merged by merge_tree
   if constexpr (SCHED == 2) {
-    const int part = (int)blockIdx.x % P.split, rest = (int)blockIdx.x / P.split;
+    int part = (int)blockIdx.x % P.split;
+    const int rest = (int)blockIdx.x / P.split;
     int S = P.split;  // parts of this row
     bh = rest / P.nbr;
     i = P.nbr - 1 - (rest - bh * P.nbr);
@@ -656,6 +657,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
       const int32_t* rp = P.row_ptr + (int64_t)m * (P.nbr + 1) + i;
       const int p_row = rp[0], n_row = rp[1] - rp[0];
       S = max(1, min(S, n_row / kSplitMinTiles));
+      // Work-groups go to the eight XCDs in turn: if the same ones of every row were left over, some XCDs would get no work (rows
+      // of 6 to 10 entries, left whole: a window over 8 heads of 4096, D = 64, 14.3 -> 12.6 us; over one head of 16384, D = 128,
+      // 25.7 -> 20.8).  Rows in all their parts keep the order in which the rows of a head read one part's keys on one XCD.
+      if (S < P.split) part = (part + rest * P.split / 8) % P.split;
       if (part >= S) return;
       const int chunk = (n_row + S - 1) / S;
       const int p0 = p_row + part * chunk, nt = max(0, min(chunk, n_row - part * chunk));
@@ -807,6 +812,9 @@ inline size_t partial_bytes(int64_t Mb, int64_t nbr, int64_t hbp, int d, int Br)
 // Two block rows, d = 128: 32 heads x 8192 122 / 70 / 51 / 62;   x 16384 242 / 133 / 93 / 95 (with inputs that come from
 // memory 110 in 4, 106 in 8);   x 32768 544 / 303 / 193 / 157;   64 x 8192 135 / 91 / 95;   128 x 4096 80 / 86.
 // 32 block rows of one head x 32768, d = 128: 468 / 245 / 132 / 84 / 93.
+// Lists are not known here.  At d = 64, 256 work-groups over 64 block columns (8 heads of 4096 queries) go from 63 to 37 us in two
+// parts on a causal mask, from 61 to 41 with global tokens; rows of 6 to 12 entries, left whole, pay for 256 work-groups that leave at
+// once: a window 12.8 -> 12.6, packed sequences 17.0 -> 17.1, a dilated window 16.4 -> 17.5.
 // Self-attention (as many queries as keys: what a backward pass follows) over fewer than 2 * kSplitLongTiles block columns is
 // left whole: there the results, and through them the gradients, do not depend on the block height, and the number of parts does.
 // (Cut like the rest, 1 head x 1024 takes 16 us instead of 20.)

@@ -502,3 +502,25 @@ def test_small_launch_accepts_a_workspace_with_room_for_eight_parts():
         assert int(ws[:counters].view(torch.int32).abs().sum()) == 0
     with pytest.raises(RuntimeError, match="workspace"):
         bbm.bbm_attn_fwd_rect(qt, kt, vt, idx, mode=bbm.BBM_MODE_LIST, workspace=torch.zeros(eight - 16, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H", [1, 3, 8])
+def test_small_launch_with_rows_in_fewer_parts_than_the_launch_has(H, d):
+    """Self-attention over 64 and more block columns, at most 256 work-groups: rows of one, two, .. parts beside rows in all of them.
+    Which work-group of a row takes which part differs from row to row there; every part has to be taken once."""
+    bbm = _bbm()
+    N = 64 * 64 + 5
+    q, k, v = make_qkv(1, H, N, d, seed=95 + H)
+    rng = np.random.default_rng(96)
+    i, j = np.arange(N)[:, None], np.arange(N)[None, :]
+    mask = (np.abs(i - j) <= 100).astype(np.uint8)                                     # 4 to 6 entries a block row
+    for row in range(0, N, 384):                                                      # every third one longer, 8 to 65 entries
+        mask[row:row + 128] |= (j < 64 * (8 + row // 64)).astype(np.uint8) & (rng.random((min(128, N - row), N)) < 0.6).astype(np.uint8)
+    O_ref, lse_ref = oracle.masked_attention(q, k, v, mask[None])
+    qt, kt, vt = (bf16_tensor(x) for x in (q, k, v))
+    for Br in (64, 128, 256):
+        idx = bbm.build_index(torch.from_numpy(mask[None]).cuda(), Br, 64)
+        o, lse = bbm.bbm_attn_fwd(qt, kt, vt, idx, mode=bbm.BBM_MODE_LIST)
+        torch.cuda.synchronize()
+        assert_attention_close(o, lse, O_ref, lse_ref)
