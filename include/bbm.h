@@ -53,8 +53,8 @@ extern "C" {
  * or with a single work-group, so EVERY block row is computed in equal parts by as many work-groups, which merge them in
  * pairs, and pairs of pairs, in an order that does not depend on who comes first.  LIST: up to 32 parts of the row's list, one
  * work-group per compute unit while a part keeps 8 entries, two while it keeps 32 (64 at d = 128 with one block row per head
- * or 128 work-groups and more); none where Nq = Nk and nbc < 64, so that what a short sequence gives
- * does not depend on Br.  BITMAP and RUNS: min(8, 512 / (B*H*nbr), nbc / t) parts of the block columns, t = 32 below
+ * or 128 work-groups and more); none where Nq = Nk and nbc < 64: such calls have always been left whole, and what they
+ * give does not depend on Br (with parts it does, by the order of the sums).  BITMAP and RUNS: min(8, 512 / (B*H*nbr), nbc / t) parts of the block columns, t = 32 below
  * 128 work-groups, 64 from there on.  Fewer than 2 parts means none.  This needs the workspace; BITMAP and RUNS, which
  * otherwise need none, run one work-group per block row when none is given. */
 #define BBM_MODE_DENSE_BASELINE 3 /* paper Sec. 3 "naive masking": visit every block, apply the element mask everywhere */

@@ -816,10 +816,12 @@ inline size_t partial_bytes(int64_t Mb, int64_t nbr, int64_t hbp, int d, int Br)
 // parts on a causal mask, from 61 to 41 with global tokens; rows of 6 to 12 entries, left whole, pay for 256 work-groups that leave at
 // once: a window 12.8 -> 12.6, packed sequences 17.0 -> 17.1, a dilated window 16.4 -> 17.5.
 // Self-attention (as many queries as keys: what a backward pass follows) over fewer than 2 * kSplitLongTiles block columns is
-// left whole: there the results, and through them the gradients, do not depend on the block height, and the number of parts does.
-// (Cut like the rest, 1 head x 1024 takes 16 us instead of 20.)
+// left whole, as it always was: there the results, and through them the gradients, do not depend on the block height.  The number
+// of parts does, so from 64 block columns on they do too.  What that costs: 2 causal heads of 4032 at d = 128 take 72 us, of 4096,
+// in 4 parts, 29; cut like the rest, 1 head x 1024 would take 16 us instead of 20.
 // BITMAP and RUNS, which cut the block columns into equal ranges and so do not know how long a part's list is, keep to parts of
-// kSplitLongTiles columns (twice that from kSplitWide work-groups on) and at most eight.
+// kSplitLongTiles columns (twice that from kSplitWide work-groups on) and at most eight.  Those limits were measured when one
+// work-group merged all parts behind device-wide fences, not since.
 constexpr int kSplitUpTo = 256, kSplitWide = 128, kSplitOne = 256, kSplitTwo = 512, kSplitMax = 32, kSplitLongTiles = 32;
 static_assert(kSplitMax <= 32, "one bit of a 32-bit word for each of the at most kSplitMax - 1 meetings of merge_tree");
 inline int split_parts(int64_t total_wgs, int64_t nbr, int64_t nbc, int d, bool list, bool self) {

@@ -333,7 +333,7 @@ def test_small_launch_computes_every_block_row_in_parts():
     computes every block row in parts.  Rows with fewer tiles than parts, empty rows, a workspace reused by two calls
     (bit-identical results, counters back to zero), and agreement with the one-work-group-per-row schedules."""
     bbm = _bbm()
-    B, H, d, Nq, Nk = 1, 3, 64, 300, 16400          # 257 block columns: up to 28 parts per block row at Br = 64
+    B, H, d, Nq, Nk = 1, 3, 64, 300, 16400          # 257 block columns: up to 17, 28, 32 parts at Br = 64, 128, 256
     q = make_qkv(B, H, Nq, d, seed=41)[0]
     _, k, v = make_qkv(B, H, Nk, d, seed=42)
     rng = np.random.default_rng(43)
@@ -376,9 +376,9 @@ def test_small_launch_computes_every_block_row_in_parts():
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_launch_of_128_to_256_work_groups_over_long_rows_is_computed_in_parts(d):
-    """One sequence, 8 heads, 2048 new queries against 8300 keys (130 block columns): 256 work-groups at Br = 64 and 128
-    at Br = 128 (2 parts each: at least 64 block columns per part), 64 at Br = 256 (4 parts of at least 32).  Every
-    schedule against the oracle, and against its own unsplit run."""
+    """One sequence, 8 heads, 2048 new queries against 8300 keys (130 block columns): 256 work-groups at Br = 64 (2 parts), 128 at
+    Br = 128 (4 parts for LIST at d = 64, else 2), 64 at Br = 256 (4 parts).  Every schedule against the oracle, and BITMAP and RUNS
+    against their own unsplit run."""
     bbm = _bbm()
     B, H, Nq, Nk = 1, 8, 2048, 8300
     q = make_qkv(B, H, Nq, d, seed=51)[0]

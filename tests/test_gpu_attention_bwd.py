@@ -144,27 +144,33 @@ def test_ragged_sizes_with_empty_rows_and_unattended_keys(N, d):
         assert torch.all(dk[:, :, dead] == 0) and torch.all(dv[:, :, dead] == 0)
 
 
-@pytest.mark.parametrize("N", [31, 33, 96, 129, 160, 288])
+@pytest.mark.parametrize("N", [31, 33, 96, 129, 160, 288, 640])
 @pytest.mark.parametrize("d", [64, 128])
 def test_edges_of_tile_halves_and_rows_without_tiles(N, d):
-    """Lengths around a wave's 32 rows, a 64-row tile and a block row, where copies past the last row come as zeros; one block row
-    of 32 to 256 queries without a single tile (its zeros leave through the slabs that Q came in by), a block column without
-    queries, and one 32 x 32 quarter of a tile alone, which only one of four waves may work on."""
+    """Lengths around a wave's 32 rows, a 64-row tile and a block row, where copies past the last row come as zeros; a block column
+    without queries, and one 32 x 32 quarter of a tile alone, which only one of four waves may work on.  N = 640: a block row of
+    64, 128 and 256 queries without a single tile (its zeros leave through the slabs that Q came in by), rows with tiles behind it."""
     B, H = 1, 3
     q, k, v = make_qkv(B, H, N, d, seed=7 * N + d)
     do = _d_o(B, H, N, d, seed=7 * N + d + 5)
     rng = np.random.default_rng(N + d)
     m = (rng.random((N, N)) < 0.3).astype(np.uint8)
-    m[N // 2:] = 0                                           # the lower half of the rows sees nothing ..
-    m[-1, max(0, N - 33):] = 1                               # .. but for the last row and the keys at the end
+    if N == 640:
+        m[256:512] = 0
+    else:
+        m[N // 2:] = 0                                       # the lower half of the rows sees nothing ..
+        m[-1, max(0, N - 33):] = 1                           # .. but for the last row and the keys at the end
     m[:, 64:96] = 0
+    blind = slice(256, 512) if N == 640 else slice(N // 2, N - 1)
     mask = m[None]
     ref = oracle.masked_attention_bwd(q, k, v, mask, do)
     mags = oracle.masked_attention_bwd_magnitudes(q, k, v, mask, do)
     for Br in (64, 128, 256):
-        dq, dk, dv = _gpu_grads(dict(q=q, k=k, v=v, mask=mask), do, Br)
+        idx = _bbm().build_index(torch.from_numpy(mask).cuda(), Br, 64, columns=True)
+        assert N != 640 or int(idx.row_ptr[0, 512 // Br]) == int(idx.row_ptr[0, 512 // Br - 1])
+        dq, dk, dv = _gpu_grads(dict(q=q, k=k, v=v, mask=mask), do, Br, idx=idx)
         _check((dq, dk, dv), ref, mags, tag=f"bwd edges N={N} d={d} Br={Br}")
-        assert torch.all(dq[:, :, N // 2:-1] == 0)
+        assert torch.all(dq[:, :, blind] == 0)
         assert torch.all(dk[:, :, 64:96] == 0) and torch.all(dv[:, :, 64:96] == 0)
 
 
