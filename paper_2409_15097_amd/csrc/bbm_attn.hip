@@ -14,18 +14,14 @@
 // The element mask of a 32x64 score slab is one 64-bit word per query row (word-column-major packed mask),
 // tested with compile-time bit positions.
 #include "bbm_internal.h"
+#include "bbm_mfma.h"
 
 #include <algorithm>
 #include <mutex>
-#include <utility>
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+using bbm::bf16x2, bbm::bf16x4, bbm::bf16x8, bbm::f32x16, bbm::IntC, bbm::mfma_ring, bbm::partner_sum, bbm::s16x4, bbm::scalar;
 
 constexpr int kBc = 64;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -69,10 +65,6 @@ __device__ __forceinline__ float partner_max(float x) {
   // lanes l and l^32 exchange: swap(x, x) gives {x[l%32], x[l%32 + 32]} in some order on every lane
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float partner_sum(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 constexpr int kSplitMinTiles = 8;        // list entries that a part of a row in a small launch keeps (split_parts)
@@ -155,37 +147,6 @@ __device__ __forceinline__ int num_windows(const AttnParams& P, int m, int i, in
   if (hi <= lo) return 0;
   if (P.mode != BBM_MODE_DENSE_BASELINE) lo &= ~63;
   return (hi - lo + kWin - 1) / kWin;
-}
-
-template <int V>
-struct IntC {
-  static constexpr int value = V;
-};
-
-__device__ __forceinline__ uint32_t scalar(uint32_t uniform) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)uniform); }
-
-// A chain of COUNT matrix instructions whose LDS operands are read R instructions ahead: load(n) reads the operand of
-// instruction n, mul(n, operand) issues it, between(n) is whatever is to be issued behind it.  Left alone the compiler reads
-// one operand, waits, multiplies and only then reads the next; the scheduling barriers pin the order.  (n comes as a type,
-// IntC<n>: the chain has to be unrolled whole.)
-template <typename F, int... N>
-__device__ __forceinline__ void for_each_n(F f, std::integer_sequence<int, N...>) {
-  (f(IntC<N>{}), ...);
-}
-template <int COUNT, int R, typename Load, typename Mul, typename Between>
-__device__ __forceinline__ void mfma_ring(Load load, Mul mul, Between between) {
-  bf16x8 f[R];
-  for_each_n([&](auto n) { f[decltype(n)::value] = load(n); }, std::make_integer_sequence<int, R>{});
-  __builtin_amdgcn_sched_barrier(0);
-  for_each_n(
-      [&](auto i) {
-        constexpr int n = decltype(i)::value;
-        mul(i, f[n % R]);
-        if constexpr (n + R < COUNT) f[n % R] = load(IntC<n + R>{});
-        between(i);
-        __builtin_amdgcn_sched_barrier(0);
-      },
-      std::make_integer_sequence<int, COUNT>{});
 }
 
 // One work-group per (block row, batch, head), tiles from build_window.  SCHED = 2 (a launch too small to fill the chip):

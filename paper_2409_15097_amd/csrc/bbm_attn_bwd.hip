@@ -15,17 +15,13 @@
 // Both start the score accumulators at -lse (in exponent units) and the dP accumulators at -D, so that exp2 and one
 // multiplication per element give P and dS.
 #include "bbm_internal.h"
+#include "bbm_mfma.h"
 
 #include <algorithm>
-#include <utility>
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+using bbm::bf16x2, bbm::bf16x4, bbm::bf16x8, bbm::f32x16, bbm::IntC, bbm::mfma_ring, bbm::partner_sum, bbm::s16x4, bbm::scalar;
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kWin = 128;                   // list entries per LDS window
@@ -69,16 +65,6 @@ struct BwdParams {
   int32_t n_extra;         // leading work-groups that serve the queue of parts before their own row/column
 };
 
-__device__ __forceinline__ float partner_sum(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-template <int V>
-struct IntC {
-  static constexpr int value = V;
-};
-
 // Sum over each group of RC = 8 or 16 consecutive lanes, in all of them.
 template <int RC>
 __device__ __forceinline__ float row_sum(float x) {
@@ -105,8 +91,6 @@ struct TL {
   static constexpr int TBLK = 512 + 32;     // block stride in elements
   static constexpr int ELEMS = NBLK * TBLK;
 };
-
-__device__ __forceinline__ uint32_t scalar(uint32_t uniform) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)uniform); }
 
 // Two floats rounded to bf16, the first in the low half; eight of them as a matrix operand.
 __device__ __forceinline__ uint32_t pack(float a, float b) {
@@ -198,31 +182,6 @@ struct TileAddr {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7));
   }
 };
-
-// A chain of COUNT matrix instructions (or groups of them) whose LDS operands are read R instructions ahead: load(n) reads the
-// operand of instruction n, mul(n, operand) issues it, between(n) is whatever is to be issued behind it.  Left alone the
-// compiler reads one operand, waits, multiplies and only then reads the next, so that every matrix instruction stands behind
-// a whole LDS latency; the scheduling barriers keep it from going back to that order where registers are short.
-// (n comes as a type, IntC<n>: the chain has to be unrolled whole, longer than the compiler unrolls a loop.)
-template <typename F, int... N>
-__device__ __forceinline__ void for_each_n(F f, std::integer_sequence<int, N...>) {
-  (f(IntC<N>{}), ...);
-}
-template <int COUNT, int R, typename Load, typename Mul, typename Between>
-__device__ __forceinline__ void mfma_ring(Load load, Mul mul, Between between) {
-  bf16x8 f[R];
-  for_each_n([&](auto n) { f[decltype(n)::value] = load(n); }, std::make_integer_sequence<int, R>{});
-  __builtin_amdgcn_sched_barrier(0);
-  for_each_n(
-      [&](auto i) {
-        constexpr int n = decltype(i)::value;
-        mul(i, f[n % R]);
-        if constexpr (n + R < COUNT) f[n % R] = load(IntC<n + R>{});
-        between(i);
-        __builtin_amdgcn_sched_barrier(0);
-      },
-      std::make_integer_sequence<int, COUNT>{});
-}
 
 // acc * mult, rounded to bf16, to rows row0 .. of a [N][D] matrix: lane l holds row l%32 of the wave's 32-row slab,
 // columns 32*db + 8*(e/4) + 4*(l/32) + e%4.  The slab is staged in LDS (`stage`, 32*D elements, this wave's own) so
