@@ -78,6 +78,17 @@ __device__ __forceinline__ float row_sum(float x) {
   return x;
 }
 
+// A kernel's arguments where they lie in memory (its only parameter, at the start of the argument segment).  Taken by value they are
+// read into scalar registers when the kernel starts, more than there are, and kept in lanes of vector registers for the next item:
+// 110-160 lane accesses before the first matrix instruction, now 20-90; this way they are read again where they are wanted.
+typedef const BwdParams __attribute__((address_space(4)))* Args;
+__device__ __forceinline__ Args kernel_args() { return (Args)__builtin_amdgcn_kernarg_segment_ptr(); }
+// A pointer of the arguments points to global memory (the compiler cannot see that, and would take it for one into LDS as well).
+template <typename T>
+__device__ __forceinline__ T* global(T* p) {
+  return (T*)(T __attribute__((address_space(1)))*)p;
+}
+
 // LDS layout of a 64-row x D tile, shared by every tile of both kernels.  One asynchronous copy instruction of a wave
 // fills one 1 KiB block with RPB rows that lie NBLK rows apart: row r sits in block r % NBLK at slot r / NBLK; blocks
 // are 1 KiB + 64 B apart, and the 16-byte chunk c of row r sits at chunk position c ^ ((r >> 2) & 3).  With that both
@@ -248,7 +259,8 @@ __device__ __forceinline__ int logical_wg(int wg, int total) {
 // whole, against each of these not so: packed sequences of 4096, D = 64, 65.1 -> 55.8 us, of 3001, D = 128, 40.7 -> 35.9; 2 x 32
 // heads of 8192 causal tokens, D = 128, 1470 -> 1400; 4 x 16 of 4096, D = 64, 226 -> 220 (exponentials beside the matrix pipe).
 template <int D, int NW, bool EXACT>
-__global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW == 4) ? 3 : 1) void attn_bwd_dq_kernel(const BwdParams P) {
+__global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW == 4) ? 3 : 1) void attn_bwd_dq_kernel(const BwdParams) {
+  Args P = kernel_args();
   using L = TL<D>;
   constexpr int NT = NW * 64;
   constexpr int BR = NW * 32;
@@ -270,9 +282,9 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lq = lane & 31, hh = lane >> 5;
-  const int N = (int)P.N;
-  const float c = P.qscale;
-  const float rr = EXACT ? P.rmul : 1.0f;
+  const int N = (int)P->N;
+  const float c = P->qscale;
+  const float rr = EXACT ? P->rmul : 1.0f;
   auto ex2 = [&](float x) { return __builtin_amdgcn_exp2f(EXACT ? rr * x : x); };
 
   // ---- per-item state
@@ -282,6 +294,9 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   const __bf16* __restrict__ Vg;
   const uint64_t* __restrict__ mrow;
   bf16x8 qf[KS], dof[KS];
+  // Where there is room, 16 registers hold dP's start value throughout.  (With them the instance for sharper scales kept 63-76 others in
+  // scratch memory: backward of packed sequences of 4096, 139-147 us, now 117.)
+  constexpr bool START_REGS = D == 64 && !EXACT;
   f32x16 dp_init, dq[DB];
   float nl_lane = 0.0f, nd_lane = 0.0f;
 
@@ -316,8 +331,8 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   // The mask is in the start values of the scores, -inf where it has no bit.  If the product of such a masked pair overflows
   // (rows that nobody sees may hold anything finite) the sum is no number, and nor is then any of the query's dQ: the tiles are
   // gone through again with the mask behind the product (`late`).  Behind the product at once, the mask costs 2-7 % of the
-  // backward pass at D = 64 and 1-4 % at D = 128, on tiles without a mask too; the second pass costs nothing where none is needed,
-  // to 1-2 % where rows are short (a word in LDS is read behind each).
+  // backward pass at D = 64 and 1-4 % at D = 128, on tiles without a mask too.  The second pass costs nothing where none is needed, as
+  // long as it leaves the first one its registers: operands one ahead, start values from one register, no argument kept for it.
   auto step = [&](auto pb, auto late, int it) __attribute__((always_inline)) {
     constexpr int PB = decltype(pb)::value;
     constexpr bool LATE = decltype(late)::value != 0;
@@ -361,10 +376,12 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     };
     if (!LATE && partial) mask_half(0), mask_half(1);
     auto dp_start = [&](f32x16& acc) {
-      if constexpr (D == 64) {
+      if constexpr (START_REGS && !LATE) {
         acc = dp_init;
       } else {  // registers are short: the start value is kept as one scalar per lane
-        for (int e = 0; e < 16; ++e) acc[e] = nd_lane;
+        float nd = nd_lane;
+        if constexpr (LATE || D == 64) asm volatile("" : "+v"(nd));
+        for (int e = 0; e < 16; ++e) acc[e] = nd;
       }
     };
     auto exps = [&](int kb, int slot) {
@@ -376,7 +393,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
       for (int e = slot * PER; e < min(16, (slot + 1) * PER); e += 2)
         dsf[kb][e / 8][e % 8 / 2] = pack(s[kb][e] * dp[kb][e], s[kb][e + 1] * dp[kb][e + 1]);
     };
-    mfma_ring<N6, kRing>(
+    mfma_ring<N6, LATE ? 1 : kRing>(
         [&](auto i) {
           constexpr int n = decltype(i)::value;
           if constexpr (n < N4)
@@ -418,7 +435,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     asm volatile("" : "+v"(ln));  // keeps the addresses out of the loop over items, see store_slab
     const int wrow = i * BR + wave * 32, qrow = wrow + (ln & 31);
     const bool q_ok = qrow < N;
-    mrow = P.packed + (int64_t)m * P.W * N + (q_ok ? qrow : 0);
+    mrow = global(P->packed) + (int64_t)m * P->W * N + (q_ok ? qrow : 0);
     // The wave's 32 rows of Q, dO and O are contiguous pieces of memory and are fetched as such, 1 KiB an instruction: a lane
     // that picks its row up in 16-byte pieces touches 64 cache lines an instruction.  Q goes to a staging slab in the tile
     // buffers (of parity 1 while at most four waves want one), dO follows through registers, where <dO, O> is formed; chunk c of row r sits at position c ^ (r % RC).
@@ -428,10 +445,10 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 #pragma unroll
     for (int n = 0; n < 32 / L::RPB; ++n) {
       const int r = n * L::RPB + g_row;
-      copy_async<16>(P.q + head_off + (int64_t)wrow * D, rows * D * 2, (uint32_t)(r * D + (g_chunk ^ (r % L::RC)) * 8) * 2u, stage + n * 512);
+      copy_async<16>(P->q + head_off + (int64_t)wrow * D, rows * D * 2, (uint32_t)(r * D + (g_chunk ^ (r % L::RC)) * 8) * 2u, stage + n * 512);
       const int64_t at = head_off + (int64_t)(r < rows ? wrow + r : 0) * D + g_chunk * 8;
-      gr[n] = load_or_zero(P.d_o + at, r < rows);
-      orow[n] = load_or_zero(P.o + at, r < rows);
+      gr[n] = load_or_zero(global(P->d_o) + at, r < rows);
+      orow[n] = load_or_zero(global(P->o) + at, r < rows);
     }
 #pragma unroll
     for (int n = 0; n < 32 / L::RPB; ++n) {
@@ -455,15 +472,15 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 #pragma unroll
     for (int t = 0; t < KS; ++t) dof[t] = frag(t);
     const float delta = delta_s[wave][ln & 31];
-    const float lse_i = q_ok ? P.lse[(int64_t)bh * N + qrow] : -INFINITY;
+    const float lse_i = q_ok ? global(P->lse)[(int64_t)bh * N + qrow] : -INFINITY;
     const float nl = (lse_i == -INFINITY) ? -INFINITY : -lse_i * (kLog2e / rr);
     if (write_stats && q_ok && (ln >> 5) == 0) {
-      P.nl2[(int64_t)bh * N + qrow] = nl;
-      P.ndelta[(int64_t)bh * N + qrow] = -delta;
+      global(global(P->nl2))[(int64_t)bh * N + qrow] = nl;
+      global(P->ndelta)[(int64_t)bh * N + qrow] = -delta;
     }
     nl_lane = nl;
     nd_lane = -delta;
-    if constexpr (D == 64)
+    if constexpr (START_REGS)
       for (int e = 0; e < 16; ++e) dp_init[e] = -delta;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -472,8 +489,8 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 
   // The tiles list[0 .. n_list) (the first of which, `first`, is known already) for this work-group's queries.
   auto run_list = [&](const uint32_t* __restrict__ list, int n_list, uint32_t first, bool write_stats) {
-    Kg = P.k + (int64_t)bh * N * D;
-    Vg = P.v + (int64_t)bh * N * D;
+    Kg = P->k + (int64_t)bh * N * D;
+    Vg = P->v + (int64_t)bh * N * D;
     auto start_window = [&](int w0, uint32_t e) __attribute__((always_inline)) {  // the first tile's copies and the list
       e0 = e;
       copy_all(e0, k_s0, v_s0);
@@ -509,25 +526,25 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 
   auto write_dq = [&]() {
     __bf16* const stage = ((wave >> 1) == 0 ? k_s0 : (wave >> 1) == 1 ? k_s1 : (wave >> 1) == 2 ? v_s0 : v_s1) + (wave & 1) * 32 * D;
-    store_slab<D>(dq, P.scale, stage, P.dq + head_off, i * BR + wave * 32, N, lane);
+    store_slab<D>(dq, P->scale, stage, global(P->dq) + head_off, i * BR + wave * 32, N, lane);
   };
 
   // ---- which block row is this work-group's own: rank-major interleave of G (batch, head) planes, as in the forward
   int own_bh, own_m, rank;
   {
-    const int logical = logical_wg((int)blockIdx.x, P.total_wgs);
-    const int grp = logical / (P.G * P.nbr), within = logical - grp * (P.G * P.nbr);
-    const int g_planes = min(P.G, P.total_wgs / P.nbr - grp * P.G);
+    const int logical = logical_wg((int)blockIdx.x, P->total_wgs);
+    const int grp = logical / (P->G * P->nbr), within = logical - grp * (P->G * P->nbr);
+    const int g_planes = min(P->G, P->total_wgs / P->nbr - grp * P->G);
     rank = within / g_planes;
-    own_bh = grp * P.G + (within - rank * g_planes);
-    own_m = (P.Mb == 1) ? 0 : own_bh / P.H;
+    own_bh = grp * P->G + (within - rank * g_planes);
+    own_m = (P->Mb == 1) ? 0 : own_bh / P->H;
   }
   int own_i, list_pos, n_list, nparts_all = 0, split_T = 0x7fffffff;
   uint32_t own_first = 0;
-  if (P.sched) {
-    const int2 hdr = *reinterpret_cast<const int2*>(P.sched);
-    const int4 rec = *reinterpret_cast<const int4*>(P.sched + bbm::sched_order_base(P.Mb, P.nbr) +
-                                                    bbm::kSchedRowInts * (int64_t)(own_m * P.nbr + rank));
+  if (global(P->sched)) {
+    const int2 hdr = *reinterpret_cast<const int2*>(global(P->sched));
+    const int4 rec = *reinterpret_cast<const int4*>(global(P->sched) + bbm::sched_order_base(P->Mb, P->nbr) +
+                                                    bbm::kSchedRowInts * (int64_t)(own_m * P->nbr + rank));
     nparts_all = hdr.x;
     split_T = hdr.y;
     own_i = rec.x;
@@ -535,17 +552,17 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     n_list = rec.z;
     own_first = (uint32_t)rec.w;
   } else {
-    own_i = P.nbr - 1 - rank;
-    list_pos = P.row_ptr[(int64_t)own_m * (P.nbr + 1) + own_i];
-    n_list = P.row_ptr[(int64_t)own_m * (P.nbr + 1) + own_i + 1] - list_pos;
-    if (n_list > 0) own_first = P.col_idx[(int64_t)own_m * P.nbr * P.nbc + list_pos];
+    own_i = P->nbr - 1 - rank;
+    list_pos = global(P->row_ptr)[(int64_t)own_m * (P->nbr + 1) + own_i];
+    n_list = global(P->row_ptr)[(int64_t)own_m * (P->nbr + 1) + own_i + 1] - list_pos;
+    if (n_list > 0) own_first = global(P->col_idx)[(int64_t)own_m * P->nbr * P->nbc + list_pos];
   }
 
   if (tid == 0) again_s = 0;
   // The first n_extra work-groups serve the queue of cut-row parts before their own row (nothing to do when no row was cut):
   // one loop for parts and own row, so that the tile loop is in the program once.
-  const bool leading = nparts_all > 0 && (int)blockIdx.x < P.n_extra;
-  const int n_items = leading ? nparts_all * P.hbp : 0;
+  const bool leading = nparts_all > 0 && (int)blockIdx.x < P->n_extra;
+  const int n_items = leading ? nparts_all * P->hbp : 0;
   int item = blockIdx.x;  // the first item is the work-group's own index; later ones come from the counter
   for (;;) {
     const bool is_part = item < n_items;
@@ -553,22 +570,22 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     int next_item = 0, part = 0, nparts = 0, q_first = 0, rho = 0, hb = 0;
     uint32_t first = own_first;
     if (is_part) {
-      if (tid == 0) next_item = P.n_extra + atomicAdd(P.row_queue, 1);
+      if (tid == 0) next_item = P->n_extra + atomicAdd(global(P->row_queue), 1);
       hb = item / nparts_all;
-      const int32_t* seg = P.sched + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
+      const int32_t* seg = global(P->sched) + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
       const int row = seg[0];
       pos = seg[1], n_run = seg[2], part = seg[3], nparts = seg[4], q_first = seg[5], rho = seg[6], first = (uint32_t)seg[7];
-      m = row / P.nbr;
-      i = row - m * P.nbr;
-      bh = (P.Mb == 1) ? hb : m * P.H + hb;
+      m = row / P->nbr;
+      i = row - m * P->nbr;
+      bh = (P->Mb == 1) ? hb : m * P->H + hb;
     } else {
-      if (leading && tid == 0 && atomicAdd(P.row_queue + 1, 1) == P.n_extra - 1) {  // the last leading work-group to leave the queue
-        P.row_queue[0] = 0;
-        P.row_queue[1] = 0;
+      if (leading && tid == 0 && atomicAdd(global(P->row_queue) + 1, 1) == P->n_extra - 1) {  // the last leading work-group to leave the queue
+        global(P->row_queue)[0] = 0;
+        global(P->row_queue)[1] = 0;
       }
       m = own_m, i = own_i, bh = own_bh;
     }
-    run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + pos, n_run, scalar(first), !is_part);
+    run_list(global(P->col_idx) + (int64_t)m * P->nbr * P->nbc + pos, n_run, scalar(first), !is_part);
     if (!is_part) {
       if (n_list <= split_T) write_dq();
       return;
@@ -576,14 +593,14 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     // park the partial sums; the last part of the row to arrive adds them all up in part order, two records' loads in flight at
     // D = 64, one's at D = 128 (registers).  With a load at a time the backward pass took 161 instead of 147 us at 2 x 8 heads of
     // 8192 tokens, window, global tokens and random blocks, D = 64, and 319 instead of 268 at 8 heads of 16384, D = 128.
-    float* const rec0 = P.row_partials + ((int64_t)q_first * P.hbp + hb) * (REGS * NT);
-    const int64_t pstride = (int64_t)P.hbp * (REGS * NT);
+    float* const rec0 = global(P->row_partials) + ((int64_t)q_first * P->hbp + hb) * (REGS * NT);
+    const int64_t pstride = (int64_t)P->hbp * (REGS * NT);
     int at = tid;
     asm volatile("" : "+v"(at));  // see store_slab
     bbm::store_record<DB, NT>(bbm::record_rsrc(rec0 + part * pstride, REGS * NT), at, dq);
     bbm::hand_over();
     if (tid == 0) {
-      item_s[1] = atomicAdd(P.row_queue + 8 + rho * P.hbp + hb, 1);
+      item_s[1] = atomicAdd(global(P->row_queue) + 8 + rho * P->hbp + hb, 1);
       item_s[0] = next_item;
     }
     __syncthreads();
@@ -597,7 +614,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
           for (int e = 0; e < 16; ++e) dq[db][e] += x[db][e];
       });
       write_dq();
-      if (tid == 0) P.row_queue[8 + rho * P.hbp + hb] = 0;  // last user of this counter: zero for the next call
+      if (tid == 0) global(P->row_queue)[8 + rho * P->hbp + hb] = 0;  // last user of this counter: zero for the next call
     }
     item = (int)scalar((uint32_t)item_s[0]);  // (a scalar: everything that addresses the item follows from it)
     __syncthreads();  // everyone has read the item, and the staged sums, before the next item's copies and list land
@@ -607,7 +624,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 // ------------------------------------------------------------------------------------------------------------------
 // dK, dV
 // ------------------------------------------------------------------------------------------------------------------
-// One work-group per (block column, batch, head); the first P.n_extra work-groups first serve the queue of
+// One work-group per (block column, batch, head); the first P->n_extra work-groups first serve the queue of
 // the parts of cut block columns, as the dQ kernel does for cut block rows.
 // Four waves, (key half) x (query half of every 64-query sub-tile): each computes all four products of its 32 keys and its 32
 // queries, so P and dS never leave its registers; the sums of the two query halves meet through LDS behind the last sub-tile.
@@ -620,7 +637,8 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 // Registers are what the form lives by.  D = 128: 256, two operand pieces in LDS, two waves a SIMD; one register more in scratch
 // memory inside the loop costs a wait for the tile copies in flight (a form with 16 of them took 3240 us).  D = 64: 168, three.
 template <int D, bool EXACT>
-__global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(const BwdParams P) {
+__global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(const BwdParams) {
+  Args P = kernel_args();
   using L = TL<D>;
   constexpr int NW = 4, NT = 64 * NW;
   constexpr int NTP = 128;  // lanes that hold one of the two sums: stride of the parked records
@@ -647,9 +665,9 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kh = wave & 1;   // key half of the column block
   const int qh = wave >> 1;  // query half of the sub-tile; behind the last one, 0: this wave writes dV, 1: dK
-  const int N = (int)P.N;
-  const float c = P.qscale;
-  const float rr = EXACT ? P.rmul : 1.0f;
+  const int N = (int)P->N;
+  const float c = P->qscale;
+  const float rr = EXACT ? P->rmul : 1.0f;
   auto ex2 = [&](float x) { return __builtin_amdgcn_exp2f(EXACT ? rr * x : x); };
 
   // ---- per-item state
@@ -670,7 +688,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
     A.ta[i] += 2 * qh * (D == 64 ? 2 * D : D);
   }
 
-  const int qs_shift = P.br == 64 ? 0 : P.br == 128 ? 1 : 2;  // 64-query sub-tiles per block row: 1, 2, 4
+  const int qs_shift = P->br == 64 ? 0 : P->br == 128 ? 1 : 2;  // 64-query sub-tiles per block row: 1, 2, 4
   // Copies of the 64-query sub-tile from row0 on into the buffers of one parity: Q and dO tiles, the negated statistics of its
   // queries (-lse*log2 e and -D) and, if the block is partial, the two 32-bit halves of its mask words, a wave for each of the
   // four.  Queries past N come as zeros everywhere: with Q = dO = D = 0 they add exact zeros.
@@ -753,7 +771,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
       static_assert(PER * (KS - 2) >= 16 && PER * (2 * DB - 2) >= 16, "all 16 must find room");
       uint32_t pf[2][4], dsf[2][4];  // pairs of bf16
       bf16x8 kl[2];
-      mfma_ring<N4, kRing>(
+      mfma_ring<N4, LATE ? 1 : kRing>(
           [&](auto i) {
             constexpr int n = decltype(i)::value;
             if constexpr (n < N2)
@@ -816,13 +834,20 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
   // The query blocks list[0 .. n_list) (the first of which, `first`, is known already) of this work-group's 64 keys.
   auto run_list = [&](const uint32_t* __restrict__ list, int n_list, uint32_t first) {
     head_off = (int64_t)bh * N * D;
-    Qg = P.q + head_off;
-    Gg = P.d_o + head_off;
-    nlg = P.nl2 + (int64_t)bh * N;
-    ndg = P.ndelta + (int64_t)bh * N;
+    Qg = P->q + head_off;
+    Gg = global(P->d_o) + head_off;
+    nlg = global(global(P->nl2)) + (int64_t)bh * N;
+    ndg = global(P->ndelta) + (int64_t)bh * N;
     // this wave's 32-bit half of the packed mask words of block column j (one word per query row)
-    mcol = reinterpret_cast<const uint32_t*>(P.packed + ((int64_t)m * P.W + j) * (int64_t)N) + kh;
+    mcol = reinterpret_cast<const uint32_t*>(global(P->packed) + ((int64_t)m * P->W + j) * (int64_t)N) + kh;
     auto run = [&](auto late) __attribute__((always_inline)) {
+      // The last column's operands end here: set in the first window only, they would be kept from item to item (56 registers at
+      // D = 128, and as many of the merge's in scratch memory).
+#pragma unroll
+      for (int t = 0; t < KS; ++t) {
+        asm("" : "=v"(vf[t]));
+        if (t < KS - KL) asm("" : "=v"(kf[t < KS - KL ? t : 0]));
+      }
 #pragma unroll
       for (int db = 0; db < DB; ++db)
         for (int e = 0; e < 16; ++e) dk[db][e] = dv[db][e] = 0.0f;
@@ -840,8 +865,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
           const int keys = rows_of_tile(j * 64, N);
 #pragma unroll
           for (int n = 0; n < LPW; ++n) {
-            tile_copy_piece<D, NW>(P.k + at, keys, copy_base, t_s1, n, wave);
-            tile_copy_piece<D, NW>(P.v + at, keys, copy_base, t_s1 + L::ELEMS, n, wave);
+            tile_copy_piece<D, NW>(P->k + at, keys, copy_base, t_s1, n, wave);
+            tile_copy_piece<D, NW>(P->v + at, keys, copy_base, t_s1 + L::ELEMS, n, wave);
           }
         }
         for (int t = tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
@@ -906,9 +931,9 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
   auto write_dkv = [&]() {
     const int row0 = j * 64 + kh * 32;
     if (qh == 0)
-      store_slab<D>(dk, 1.0f, t_s0 + L::ELEMS + kh * 32 * D, P.dv + head_off, row0, N, lane);
+      store_slab<D>(dk, 1.0f, t_s0 + L::ELEMS + kh * 32 * D, global(P->dv) + head_off, row0, N, lane);
     else
-      store_slab<D>(dk, P.scale, t_s0 + kh * 32 * D, P.dk + head_off, row0, N, lane);
+      store_slab<D>(dk, P->scale, t_s0 + kh * 32 * D, global(P->dk) + head_off, row0, N, lane);
   };
 
   // This work-group's own block column: rank-major interleave of G (batch, head) planes as in the dQ kernel, ranks by list
@@ -917,73 +942,73 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
   int own_bh, own_m, own_j, own_pos, own_n;
   uint32_t own_first = 0;
   {
-    const int logical = logical_wg((int)blockIdx.x, P.total_wgs);
-    if (P.csched) {
-      const int2 hdr = *reinterpret_cast<const int2*>(P.csched);
+    const int logical = logical_wg((int)blockIdx.x, P->total_wgs);
+    if (global(P->csched)) {
+      const int2 hdr = *reinterpret_cast<const int2*>(global(P->csched));
       nparts_all = hdr.x;
       split_T = hdr.y;
-      const int grp = logical / (P.Gc * P.nbc), within = logical - grp * (P.Gc * P.nbc);
-      const int g_planes = min(P.Gc, P.total_wgs / P.nbc - grp * P.Gc);
+      const int grp = logical / (P->Gc * P->nbc), within = logical - grp * (P->Gc * P->nbc);
+      const int g_planes = min(P->Gc, P->total_wgs / P->nbc - grp * P->Gc);
       const int rank = within / g_planes;
-      own_bh = grp * P.Gc + (within - rank * g_planes);
-      own_m = (P.Mb == 1) ? 0 : own_bh / P.H;
-      const int4 rec = *reinterpret_cast<const int4*>(P.csched + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * P.Mb * P.nbc +
-                                                      bbm::kSchedRowInts * (int64_t)(own_m * P.nbc + rank));
+      own_bh = grp * P->Gc + (within - rank * g_planes);
+      own_m = (P->Mb == 1) ? 0 : own_bh / P->H;
+      const int4 rec = *reinterpret_cast<const int4*>(global(P->csched) + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * P->Mb * P->nbc +
+                                                      bbm::kSchedRowInts * (int64_t)(own_m * P->nbc + rank));
       own_j = rec.x;
       own_pos = rec.y;
       own_n = rec.z;
       own_first = (uint32_t)rec.w;
     } else {
-      own_bh = logical / P.nbc;
-      own_j = logical - own_bh * P.nbc;
-      own_m = (P.Mb == 1) ? 0 : own_bh / P.H;
-      own_pos = P.col_ptr[(int64_t)own_m * (P.nbc + 1) + own_j];
-      own_n = P.col_ptr[(int64_t)own_m * (P.nbc + 1) + own_j + 1] - own_pos;
-      if (own_n > 0) own_first = P.row_idx[(int64_t)own_m * P.nbr * P.nbc + own_pos];
+      own_bh = logical / P->nbc;
+      own_j = logical - own_bh * P->nbc;
+      own_m = (P->Mb == 1) ? 0 : own_bh / P->H;
+      own_pos = global(P->col_ptr)[(int64_t)own_m * (P->nbc + 1) + own_j];
+      own_n = global(P->col_ptr)[(int64_t)own_m * (P->nbc + 1) + own_j + 1] - own_pos;
+      if (own_n > 0) own_first = global(P->row_idx)[(int64_t)own_m * P->nbr * P->nbc + own_pos];
     }
   }
 
   if (tid == 0) again_s = 0;
   // The first n_extra work-groups serve the queue of cut-column parts before their own column (nothing to do when no column
   // was cut): one loop for parts and own column, so that the tile loop is in the program once.
-  const bool leading = nparts_all > 0 && (int)blockIdx.x < P.n_extra;
-  const int n_items = leading ? nparts_all * P.hbp : 0;
+  const bool leading = nparts_all > 0 && (int)blockIdx.x < P->n_extra;
+  const int n_items = leading ? nparts_all * P->hbp : 0;
   int item = blockIdx.x;  // the first item is the work-group's own index; later ones come from the counter
   for (;;) {
     const bool is_part = item < n_items;
     int pos, n_list, next_item = 0, part = 0, nparts = 0, q_first = 0, rho = 0, hb = 0;
     uint32_t first = own_first;
     if (is_part) {
-      if (tid == 0) next_item = P.n_extra + atomicAdd(P.col_queue, 1);
+      if (tid == 0) next_item = P->n_extra + atomicAdd(global(P->col_queue), 1);
       hb = item / nparts_all;
-      const int32_t* seg = P.csched + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
+      const int32_t* seg = global(P->csched) + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
       const int col = seg[0];
       pos = seg[1], n_list = seg[2], part = seg[3], nparts = seg[4], q_first = seg[5], rho = seg[6], first = (uint32_t)seg[7];
-      m = col / P.nbc;
-      j = col - m * P.nbc;
-      bh = (P.Mb == 1) ? hb : m * P.H + hb;
+      m = col / P->nbc;
+      j = col - m * P->nbc;
+      bh = (P->Mb == 1) ? hb : m * P->H + hb;
     } else {
-      if (leading && tid == 0 && atomicAdd(P.col_queue + 1, 1) == P.n_extra - 1) {  // the last leading work-group to leave the queue
-        P.col_queue[0] = 0;
-        P.col_queue[1] = 0;
+      if (leading && tid == 0 && atomicAdd(global(P->col_queue) + 1, 1) == P->n_extra - 1) {  // the last leading work-group to leave the queue
+        global(P->col_queue)[0] = 0;
+        global(P->col_queue)[1] = 0;
       }
       if (own_n > split_T) return;  // a column the schedule cut belongs to the queue
       m = own_m, j = own_j, bh = own_bh, pos = own_pos, n_list = own_n;
     }
-    run_list(P.row_idx + (int64_t)m * P.nbr * P.nbc + pos, n_list, scalar(first));
+    run_list(global(P->row_idx) + (int64_t)m * P->nbr * P->nbc + pos, n_list, scalar(first));
     if (!is_part) {
       write_dkv();
       return;
     }
-    float* const rec0 = P.col_partials + ((int64_t)q_first * P.hbp + hb) * (2 * REGS * NTP);
-    const int64_t pstride = (int64_t)P.hbp * (2 * REGS * NTP);
+    float* const rec0 = global(P->col_partials) + ((int64_t)q_first * P->hbp + hb) * (2 * REGS * NTP);
+    const int64_t pstride = (int64_t)P->hbp * (2 * REGS * NTP);
     int at = kh * 64 + lane;
     asm volatile("" : "+v"(at));  // see store_slab
     float* const rec = rec0 + (qh == 0 ? REGS * NTP : 0);  // a record: [dK | dV]
     bbm::store_record<DB, NTP>(bbm::record_rsrc(rec + part * pstride, REGS * NTP), at, dk);
     bbm::hand_over();
     if (tid == 0) {
-      item_s[1] = atomicAdd(P.col_queue + 8 + rho * P.hbp + hb, 1);
+      item_s[1] = atomicAdd(global(P->col_queue) + 8 + rho * P->hbp + hb, 1);
       item_s[0] = next_item;
     }
     __syncthreads();
@@ -997,7 +1022,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(con
           for (int e = 0; e < 16; ++e) dk[db][e] += x[db][e];
       });
       write_dkv();
-      if (tid == 0) P.col_queue[8 + rho * P.hbp + hb] = 0;
+      if (tid == 0) global(P->col_queue)[8 + rho * P->hbp + hb] = 0;
     }
     item = (int)scalar((uint32_t)item_s[0]);  // (a scalar: everything that addresses the item follows from it)
     __syncthreads();  // everyone has read the item, and the staged sums, before the next item's copies and list land
