@@ -5,9 +5,9 @@
 // The ordering is the published algorithm with every choice fixed (the library header states them): neighbours of node
 // i are the non-zero entries of mask row i, a component starts at its unvisited node of minimum degree (ties: smallest
 // index), each breadth-first level is ordered by (position of the earliest parent, degree, index), the result is
-// reversed.  One kernel packs the mask rows to bits and counts degrees; the levels are then walked by pairs of kernels
-// (expand, rank) with no host round trip and no grid-wide barrier, every node's row being scanned once, when the node is
-// in the frontier; a last kernel of one work-group walks whatever the fixed number of pairs left.
+// reversed.  One kernel packs the mask rows to bits and counts degrees; the levels are then walked by a kernel each, which ranks a
+// level and finds the next one at the same time, with no host round trip and no grid-wide barrier, every node's row being scanned
+// once; a last kernel of one work-group walks whatever the fixed number of them left.
 #include "bbm_internal.h"
 
 #include <algorithm>
@@ -19,7 +19,7 @@ constexpr int kMaxNodes = 65536;            // visited set and one mask row must
 constexpr size_t kLdsBytes = 160 * 1024;
 constexpr int kOrderThreads = 1024;
 constexpr int kPackThreads = 256;
-constexpr int kRounds = 48;                 // parallel rounds (one breadth-first level, or one component start, each)
+constexpr int kRounds = 48;                 // parallel rounds, a breadth-first level each
 constexpr int kRankChunk = 2048;            // keys of a level staged in LDS at a time
 constexpr int kRankPerThread = 4;           // keys a thread ranks per sweep
 constexpr int kBatch = 8;                   // row words a thread of the level walk has in flight
@@ -41,11 +41,18 @@ __device__ __forceinline__ void transpose4x4(uint32_t a, uint32_t b, uint32_t c,
   out[3] = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u);
 }
 
-// State of the level walk in the workspace: two records of kStInts int32 that the rounds use in turn.  A round reads its own
-// record, counts its candidates there and writes the other one whole, so no kernel resets what another may still be
-// reading.  A record holds whether the walk has ended, the frontier's places [lo, hi) in the ordering (everything placed
-// lies below hi), and the number of candidates.
-enum { kStDone = 0, kStLvlLo = 1, kStLvlHi = 2, kStCand = 3, kStInts = 4 };
+// The level walk in the workspace: two records that the rounds use in turn, one read and one written, so no kernel resets what
+// another may still be reading.  The node numbers are cut into regions of kRegCols; a record holds whether the walk has
+// ended, how many nodes are placed, and per region the nodes of the level to come that lie in it (how many; the list itself
+// has an array of its own) and its unvisited node of minimum (degree, index).
+constexpr int kRegWords = 8, kRegCols = 64 * kRegWords, kMaxRegs = kMaxNodes / kRegCols;
+enum { kStDone = 0, kStPlaced = 1, kStInts = 4 };
+struct WalkRecord {
+  int32_t* state;        // [kStInts]
+  int32_t* count;        // [regions]
+  uint64_t* lowest;      // [regions] degree << 32 | node, ~0 where every node is visited
+  uint32_t* list;        // [regions][kRegCols] node | parent << 16, nodes in ascending order
+};
 
 typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));  // 16 bytes at any address: one instruction
 
@@ -58,17 +65,9 @@ typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1))); 
 // instructions.
 __global__ __launch_bounds__(kPackThreads) void rcm_pack_kernel(const uint8_t* __restrict__ mask, int N, int64_t row_stride, int W,
                                                                 uint16_t* __restrict__ bits, int32_t* __restrict__ degree,
-                                                                int32_t* __restrict__ parent_pos, uint64_t* __restrict__ visited,
-                                                                uint64_t* __restrict__ claimed, int32_t* __restrict__ state) {
+                                                                int32_t* __restrict__ parent_pos) {
   __shared__ int red_s[kPackThreads / 64];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  if (row == 0) {  // the walk's sets (nodes past N count as visited) and state
-    for (int w = tid; w < W; w += kPackThreads) {
-      visited[w] = (w == W - 1 && (N & 63)) ? ~0ull << (N & 63) : 0ull;
-      claimed[w] = 0;
-    }
-    if (tid < kStInts) state[tid] = 0;
-  }
   const uint8_t* __restrict__ src = mask + (int64_t)row * row_stride;
   uint16_t* __restrict__ dst = bits + (int64_t)row * W * 4;
   const int pieces = 4 * W;
@@ -111,8 +110,6 @@ __global__ __launch_bounds__(kPackThreads) void rcm_pack_kernel(const uint8_t* _
     parent_pos[row] = INT_MAX;
   }
 }
-
-constexpr int kExpandWGs = 1024, kExpandThreads = 256;
 
 __device__ __forceinline__ uint64_t level_key(int parent, int degree, int v) {
   return ((uint64_t)(uint32_t)parent << 40) | ((uint64_t)(uint32_t)degree << 20) | (uint64_t)(uint32_t)v;
@@ -185,152 +182,229 @@ __device__ __forceinline__ int min_degree_unvisited(const int32_t* __restrict__ 
   return best == ~0ull ? -1 : (int)(best & 0xffffffffull);
 }
 
-// Parallel expansion of the current level: every frontier node's bit row is scanned once, an unvisited neighbour gets its
-// earliest parent (atomic minimum of the parent's position) and enters the candidate list once.  Returns at once when there
-// is no frontier.
-// What bounds it is the atomics, so a wave takes 64 words of a run of consecutive frontier nodes and each lane remembers
-// the bits of its word that it has seen: only the first node of the run that has a bit sends an atomic (later ones have
-// later positions), and the `claimed` set is asked once per run and word instead of once per edge.  Runs of 8 nodes keep
-// enough waves for small levels; longer runs from 1024 nodes on save atomics.
-__global__ __launch_bounds__(kExpandThreads) void rcm_expand_kernel(const uint64_t* __restrict__ bits, const int32_t* __restrict__ order,
-                                                                    const uint64_t* __restrict__ visited, uint64_t* claimed,
-                                                                    int32_t* parent_pos, int32_t* cand, int32_t* state, int W) {
-  const int lvl_lo = state[kStLvlLo], lvl_hi = state[kStLvlHi];
-  if (state[kStDone] || lvl_lo >= lvl_hi) return;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int F = lvl_hi - lvl_lo;
-  const int run = F <= 1024 ? kBatch : F <= 2048 ? 2 * kBatch : 4 * kBatch;
-  const int strips = (W + 63) / 64, tasks = strips * ((F + run - 1) / run);
-  for (int task = blockIdx.x * (kExpandThreads / 64) + wave; task < tasks; task += gridDim.x * (kExpandThreads / 64)) {
-    const int w = (task % strips) * 64 + lane;
-    const int f_first = lvl_lo + (task / strips) * run, f_end = min(f_first + run, lvl_hi);
-    const uint64_t before = w < W ? visited[w] : ~0ull;
-    uint64_t seen = before;
-    for (int f0 = f_first; f0 < f_end; f0 += kBatch) {
-      uint64_t word[kBatch];
+constexpr int kLevelThreads = 1024, kLevelWaves = kLevelThreads / 64;
+constexpr int kLevelStage = 4096;    // keys of a level staged in LDS at a time
+constexpr int kRankWGs = 192;        // ranking work-groups of a round; with the at most kMaxRegs expanding ones all find a CU
+constexpr int kRankSlice = (kMaxNodes + kRankWGs - 1) / kRankWGs;
+
+__device__ __forceinline__ uint64_t wave_min64(uint64_t x) {
 #pragma unroll
-      for (int t = 0; t < kBatch; ++t)  // past the run's end: its last node once more, which has nothing new
-        word[t] = w < W ? bits[(int64_t)order[min(f0 + t, f_end - 1)] * W + w] : 0;
+  for (int d = 32; d >= 1; d >>= 1) x = min(x, (uint64_t)__shfl_xor((unsigned long long)x, d));
+  return x;
+}
+
+// One round of the walk: the current level (the lists `in` holds, or, when those are empty, the start of the next component) is
+// ranked and expanded side by side.  What makes that possible: which parent of a node comes first is a comparison of the
+// parents' keys, not of their places, so the expansion does not wait for the ranking; the places it leaves are needed a round
+// later, for the keys of the level found now.
+//   work-group < regions: expands the whole level into the nodes of its own region.  Every bit row of the level is read once over
+//     all regions, 8 words of it here; a node's earliest parent is a minimum in LDS, so there are no atomics on memory, and the
+//     list, the visited words and the region's unvisited minimum are this work-group's alone.
+//   the others: a node's place in the level is the number of smaller keys, counted by a wave, of which every work-group stages all.
+// What bounds it is the chain of dependent round trips: counts, list, places and degrees, bit rows, results; the ranking is done
+// before the expansion is, and the minima in LDS are 0.5 us of it.  Before, a round was an expanding kernel (atomics on memory, a
+// candidate list behind one counter) and a ranking one: a level of 1700 nodes of the 32768-node power-law graph took 8 + 9 us, now
+// 12.4.  The whole ordering, of which 200 us are the packing at 32768 nodes, us: 1000 nodes 259-348 -> 140-154, 8192 335-395 ->
+// 166-180, 16000 364-407 -> 236-246, 32768 623 -> 467.  Regions of 4 words instead of 8 (32768 nodes): 554.  All levels in one launch
+// whose work-groups wait for each other's flags: 105, 152, 230, 481; not worth the waiting.  Every region's first 64 nodes asked
+// for along with the counts: no difference.
+__global__ __launch_bounds__(kLevelThreads) void rcm_level_kernel(const uint64_t* __restrict__ bits, const int32_t* __restrict__ degree,
+                                                                  uint64_t* __restrict__ visited, int32_t* pos, int32_t* __restrict__ perm,
+                                                                  const WalkRecord in, const WalkRecord out, int N, int W, int regions) {
+  __shared__ uint64_t key_s[kLevelStage];
+  __shared__ unsigned long long best_s[kRegCols];  // the smallest parent's key
+  __shared__ uint64_t own_s[kRankSlice];
+  __shared__ int rank_s[kRankSlice];
+  __shared__ int first_s[kMaxRegs + 1];  // place of a region's list in the level
+  __shared__ int found_s[kRegWords];
+  __shared__ uint64_t lowest_s[kRegWords];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool done = in.state[kStDone] != 0;
+  const int placed = in.state[kStPlaced];
+  // every wave: the regions' counts, kPer a lane, added up
+  constexpr int kPer = kMaxRegs / 64;
+  int c[kPer], own = 0;
 #pragma unroll
-      for (int t = 0; t < kBatch; ++t) {
-        uint64_t b = word[t] & ~seen;
-        seen |= b;
-        while (b) {
-          atomicMin(&parent_pos[64 * w + __builtin_ctzll(b)], f0 + t);  // result unused: the atomics pipeline
-          b &= b - 1;
+  for (int t = 0; t < kPer; ++t) c[t] = kPer * lane + t < regions ? in.count[kPer * lane + t] : 0;
+  if (done) {
+    if (blockIdx.x == 0 && tid == 0) out.state[kStDone] = 1;
+    return;
+  }
+#pragma unroll
+  for (int t = 0; t < kPer; ++t) own += c[t];
+  int upto = own;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int other = __shfl_up(upto, d);
+    if (lane >= d) upto += other;
+  }
+  int L = __shfl(upto, 63), start = -1;
+  if (L == 0) {  // the next component starts at its unvisited node of minimum (degree, index)
+    uint64_t low = ~0ull;
+    for (int reg = lane; reg < regions; reg += 64) low = min(low, in.lowest[reg]);
+    low = wave_min64(low);
+    if (low == ~0ull) {
+      if (blockIdx.x == 0 && tid == 0) out.state[kStDone] = 1;
+      return;
+    }
+    start = (int)(low & 0xffffffffull);
+    L = 1;
+  }
+  if (blockIdx.x == 0 && tid == 0) {
+    out.state[kStDone] = 0;
+    out.state[kStPlaced] = placed + L;
+  }
+  if (wave == 0) {
+    int at = upto - own;
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+      first_s[kPer * lane + t] = at;
+      at += c[t];
+    }
+    if (lane == 63) first_s[kMaxRegs] = upto;
+  }
+
+  // Keys [from, to) of the level into dst (all threads; barriers on both sides).  A wave takes every 16th region, the first 64
+  // nodes of each with all loads in flight.
+  auto stage = [&](int from, int to, uint64_t* dst) {
+    __syncthreads();
+    if (start >= 0) {
+      if (tid == 0) dst[0] = (uint64_t)start;
+    } else {
+      constexpr int kFly = kMaxRegs / kLevelWaves;
+      uint32_t e[kFly];
+      int at[kFly], ps[kFly], dg[kFly];
+#pragma unroll
+      for (int t = 0; t < kFly; ++t) {
+        const int r = wave + t * kLevelWaves;
+        at[t] = first_s[r] + lane;
+        if (at[t] >= first_s[r + 1] || at[t] < from || at[t] >= to) at[t] = -1;
+        e[t] = at[t] >= 0 ? in.list[r * kRegCols + lane] : 0;
+      }
+#pragma unroll
+      for (int t = 0; t < kFly; ++t) {
+        ps[t] = pos[e[t] >> 16];
+        dg[t] = degree[e[t] & 0xffffu];
+      }
+#pragma unroll
+      for (int t = 0; t < kFly; ++t)
+        if (at[t] >= 0) dst[at[t] - from] = level_key(ps[t], dg[t], (int)(e[t] & 0xffffu));
+      for (int r = wave; r < regions; r += kLevelWaves)
+        for (int a = first_s[r] + 64 + lane; a < min(first_s[r + 1], to); a += 64)
+          if (a >= from) {
+            const uint32_t x = in.list[r * kRegCols + a - first_s[r]];
+            dst[a - from] = level_key(pos[x >> 16], degree[x & 0xffffu], (int)(x & 0xffffu));
+          }
+    }
+    __syncthreads();
+  };
+
+  if ((int)blockIdx.x < regions) {
+    // neighbouring regions, which share the cache lines of the bit rows, on one XCD
+    constexpr int kShare = 16 / kRegWords;
+    int reg = blockIdx.x;
+    if ((reg | (8 * kShare - 1)) < regions) reg = (reg & ~(8 * kShare - 1)) | ((reg & 7) * kShare) | ((reg >> 3) & (kShare - 1));
+    const int own_word = lane & (kRegWords - 1), w = reg * kRegWords + own_word;
+    uint64_t before = w < W ? visited[w] : ~0ull;
+    if (start >= 0 && (start >> 6) == w) before |= 1ull << (start & 63);
+    const int col = reg * kRegCols + tid, dg_own = tid < kRegCols && col < N ? degree[col] : 0;
+    if (tid < kRegCols) best_s[tid] = ~0ull;
+    const uint64_t* const base = bits + min(w, W - 1);
+    for (int j0 = 0; j0 < L; j0 += kLevelStage) {
+      const int n = min(kLevelStage, L - j0);
+      stage(j0, j0 + n, key_s);
+      constexpr int kFly = 16, kNodes = kLevelThreads / kRegWords;  // loads of a lane in flight, nodes of a load
+      for (int f0 = tid / kRegWords; f0 < n; f0 += kFly * kNodes) {
+        uint64_t word[kFly];
+#pragma unroll
+        for (int t = 0; t < kFly; ++t) word[t] = base[(int64_t)(key_s[min(f0 + t * kNodes, n - 1)] & 0xfffffull) * W];
+#pragma unroll
+        for (int t = 0; t < kFly; ++t) {
+          uint64_t b = f0 + t * kNodes < n ? word[t] & ~before : 0;
+          while (b) {
+            atomicMin(&best_s[own_word * 64 + __builtin_ctzll(b)], (unsigned long long)key_s[f0 + t * kNodes]);
+            b &= b - 1;
+          }
         }
       }
     }
-    uint64_t fresh = seen & ~before;
-    if (fresh) fresh &= ~atomicOr(reinterpret_cast<unsigned long long*>(&claimed[w]), (unsigned long long)fresh);
-    // one entry of the candidate list per fresh bit: a scan over the wave, one addition to the counter per wave
-    const int n = __popcll(fresh);
-    int upto = n;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int other = __shfl_up(upto, d);
-      if (lane >= d) upto += other;
+    __syncthreads();
+    uint64_t best = ~0ull, fresh = 0;
+    if (wave < kRegWords) {  // a wave per word
+      best = best_s[tid];
+      fresh = __ballot(best != ~0ull);
+      const uint64_t after = (uint64_t)__shfl((unsigned long long)before, wave) | fresh;
+      if (lane == 0 && reg * kRegWords + wave < W) visited[reg * kRegWords + wave] = after;
+      const uint64_t low = wave_min64((after >> lane) & 1ull ? ~0ull : (uint64_t)(uint32_t)dg_own << 32 | (uint32_t)col);
+      if (lane == 0) {
+        found_s[wave] = __popcll(fresh);
+        lowest_s[wave] = low;
+      }
     }
-    const int total = __shfl(upto, 63);
-    if (total == 0) continue;
-    int base = 0;
-    if (lane == 0) base = atomicAdd(&state[kStCand], total);
-    base = __shfl(base, 0) + upto - n;
-    while (fresh) {
-      cand[base++] = 64 * w + __builtin_ctzll(fresh);
-      fresh &= fresh - 1;
+    __syncthreads();
+    if (wave < kRegWords) {
+      int at = __popcll(fresh & ((1ull << lane) - 1ull));
+      for (int t = 0; t < wave; ++t) at += found_s[t];
+      if (best != ~0ull) out.list[reg * kRegCols + at] = (uint32_t)col | (uint32_t)(best & 0xffffull) << 16;
+    }
+    if (tid == 0) {
+      int total = 0;
+      uint64_t low = ~0ull;
+      for (int t = 0; t < kRegWords; ++t) {
+        total += found_s[t];
+        low = min(low, lowest_s[t]);
+      }
+      out.count[reg] = total;
+      out.lowest[reg] = low;
+    }
+  } else {
+    const int slices = (int)gridDim.x - regions, len = (L + slices - 1) / slices;
+    const int lo = ((int)blockIdx.x - regions) * len, hi = min(L, lo + len);
+    if (lo >= hi) return;
+    for (int t = tid; t < hi - lo; t += kLevelThreads) rank_s[t] = 0;
+    if (L > kLevelStage) stage(lo, hi, own_s);
+    for (int j0 = 0; j0 < L; j0 += kLevelStage) {
+      const int n = min(kLevelStage, L - j0);
+      stage(j0, j0 + n, key_s);
+      for (int c = wave; c < hi - lo; c += kLevelWaves) {
+        const uint64_t mine = L > kLevelStage ? own_s[c] : key_s[lo + c];
+        int r = 0;
+#pragma unroll 8
+        for (int j = lane; j < n; j += 64) r += key_s[j] < mine ? 1 : 0;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) r += __shfl_xor(r, d);
+        if (lane == 0) rank_s[c] += r;  // (this wave's alone)
+        if (lane == 0 && j0 + n == L) {
+          const int v = (int)(mine & 0xfffffull), p = placed + rank_s[c];
+          pos[v] = p;
+          perm[N - 1 - p] = v;
+        }
+      }
     }
   }
 }
 
-// Ranking of the candidates the expansion found, and the next round's record (many work-groups).  A candidate's rank is the
-// number of smaller keys: every work-group stages all keys of the level through LDS, building them from the candidate
-// list as it goes, and 16, 4 or 1 neighbouring lanes share the counting for one candidate, so that levels of up to 4096
-// nodes still use all work-groups (one lane per candidate: 54 us for a level of 3500 nodes).  The candidate is placed
-// behind the nodes ordered so far and marked visited.  Work-group 0 also writes the record of the next round, the level
-// these candidates make; when the expansion found none (a component is finished, or nothing has started yet) it starts
-// the next component at its node of minimum degree.
-// The whole ordering of the 32768-node power-law graph: 1.54 ms with three kernels a round, an atomic per edge and one lane
-// per candidate; 0.62 ms now, of which 0.20 ms are the packing and about 0.1 ms the rounds left over at its end (2 us a launch).
-constexpr int kRankWGs = 256, kRankThreads = 256, kRankStage = 8;  // kRankStage keys of a thread's staging share in flight
-__global__ __launch_bounds__(kRankThreads) void rcm_rank_kernel(const int32_t* __restrict__ degree, const int32_t* __restrict__ parent_pos,
-                                                                const int32_t* __restrict__ cand, int32_t* __restrict__ order,
-                                                                int32_t* __restrict__ perm, uint64_t* visited,
-                                                                const int32_t* __restrict__ state, int32_t* __restrict__ next, int N) {
-  __shared__ __attribute__((aligned(16))) uint64_t chunk_s[kRankChunk];
-  __shared__ unsigned long long min_s[kRankThreads / 64];
-  const int tid = threadIdx.x;
-  auto write_next = [&](int done, int lo, int hi) {
-    next[kStDone] = done;
-    next[kStLvlLo] = lo;
-    next[kStLvlHi] = hi;
-    next[kStCand] = 0;
-  };
-  if (state[kStDone]) {
-    if (blockIdx.x == 0 && tid == 0) write_next(1, 0, 0);
-    return;
+// What the first round reads: nothing placed, no level, every region's node of minimum (degree, index).
+__global__ __launch_bounds__(kRegCols) void rcm_start_kernel(const int32_t* __restrict__ degree, uint64_t* __restrict__ visited,
+                                                             const WalkRecord out, int N, int W) {
+  __shared__ uint64_t lowest_s[kRegWords];
+  const int reg = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, col = reg * kRegCols + tid;
+  const uint64_t low = wave_min64(col < N ? (uint64_t)(uint32_t)degree[col] << 32 | (uint32_t)col : ~0ull);
+  if ((tid & 63) == 0) {
+    const int w = reg * kRegWords + wave;
+    lowest_s[wave] = low;
+    if (w < W) visited[w] = w == W - 1 && (N & 63) ? ~0ull << (N & 63) : 0ull;  // nodes past N count as visited
   }
-  const int n_done = state[kStLvlHi], L = state[kStCand];
-  if (L == 0) {
-    if (blockIdx.x != 0) return;
-    const int start = min_degree_unvisited<kRankThreads>(degree, N, [&](int w) { return visited[w]; }, min_s, tid);
-    if (tid == 0) {
-      if (start < 0) {
-        write_next(1, 0, 0);
-      } else {
-        order[n_done] = start;
-        perm[N - 1 - n_done] = start;
-        visited[start >> 6] |= 1ull << (start & 63);
-        write_next(0, n_done, n_done + 1);
-      }
-    }
-    return;
-  }
-  if (blockIdx.x == 0 && tid == 0) write_next(0, n_done, n_done + L);
-  auto key_of = [&](int c) {
-    const int v = cand[c];
-    return level_key(parent_pos[v], degree[v], v);
-  };
-  const int ways_log2 = L <= 16 * kRankWGs ? 4 : L <= 64 * kRankWGs ? 2 : 0;  // lanes that share one candidate
-  const int ways = 1 << ways_log2, per_wg = kRankThreads >> ways_log2, way = tid & (ways - 1);
-  for (int c0 = (int)blockIdx.x * per_wg; c0 < L; c0 += (int)gridDim.x * per_wg) {  // uniform in the work-group
-    const int c = c0 + (tid >> ways_log2);
-    const uint64_t mine = c < L ? key_of(c) : 0;
-    int r = 0;
-    for (int j0 = 0; j0 < L; j0 += kRankChunk) {
-      const int n = min(kRankChunk, L - j0);
-      __syncthreads();  // the previous chunk has been read
-      for (int j = tid; j < n; j += kRankStage * kRankThreads) {  // a key is three dependent loads: keep several going
-        int v[kRankStage], pp[kRankStage], dg[kRankStage];
-#pragma unroll
-        for (int t = 0; t < kRankStage; ++t) v[t] = cand[j0 + min(j + t * kRankThreads, n - 1)];
-#pragma unroll
-        for (int t = 0; t < kRankStage; ++t) {
-          pp[t] = parent_pos[v[t]];
-          dg[t] = degree[v[t]];
-        }
-#pragma unroll
-        for (int t = 0; t < kRankStage; ++t)
-          if (j + t * kRankThreads < n) chunk_s[j + t * kRankThreads] = level_key(pp[t], dg[t], v[t]);
-      }
-      const int padded = (n + 8 * ways - 1) & ~(8 * ways - 1);  // at most kRankChunk, a multiple of 8 * ways
-      if (tid < padded - n) chunk_s[n + tid] = ~0ull;           // keys that count for nobody
-      __syncthreads();
-      for (int j = way; j < padded; j += 8 * ways) {  // 8 keys per LDS round trip
-        uint64_t k[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) k[t] = chunk_s[j + t * ways];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) r += k[t] < mine ? 1 : 0;
-      }
-    }
-    for (int d = 1; d < ways; d <<= 1) r += __shfl_xor(r, d);
-    if (c < L && way == 0) {
-      const int v = (int)(mine & 0xfffffull);
-      order[n_done + r] = v;
-      perm[N - 1 - n_done - r] = v;
-      atomicOr(reinterpret_cast<unsigned long long*>(&visited[v >> 6]), 1ull << (v & 63));
+  __syncthreads();
+  if (tid == 0) {
+    uint64_t all = ~0ull;
+    for (int t = 0; t < kRegWords; ++t) all = min(all, lowest_s[t]);
+    out.count[reg] = 0;
+    out.lowest[reg] = all;
+    if (reg == 0) {
+      out.state[kStDone] = 0;
+      out.state[kStPlaced] = 0;
     }
   }
 }
@@ -340,21 +414,44 @@ __global__ __launch_bounds__(kRankThreads) void rcm_rank_kernel(const int32_t* _
 // by some threads and read by others are separated by an agent-scope fence and a barrier.
 __global__ __launch_bounds__(kOrderThreads) void rcm_finish_kernel(const uint64_t* __restrict__ bits, const int32_t* __restrict__ degree,
                                                                    int32_t* parent_pos, int32_t* order, int32_t* cand, uint64_t* keys,
-                                                                   const uint64_t* __restrict__ visited_g, const int32_t* __restrict__ state,
-                                                                   int N, int W, int32_t* __restrict__ perm) {
+                                                                   const uint64_t* __restrict__ visited_g, const WalkRecord left, int N, int W,
+                                                                   int regions, int32_t* __restrict__ perm) {
   __shared__ uint64_t visited[kMaxNodes / 64];
   __shared__ uint64_t claimed[kMaxNodes / 64];  // nodes some frontier node has reached (they become visited within the level)
   __shared__ uint64_t chunk_s[kRankChunk];
   __shared__ unsigned long long min_s[kOrderThreads / 64];
   __shared__ int count_s;
+  __shared__ int first_s[kMaxRegs + 1];
   const int tid = threadIdx.x;
   auto sync_global = [&]() {
     __threadfence();
     __syncthreads();
   };
-  if (state[kStDone]) return;
-  int lvl_lo = state[kStLvlLo], lvl_hi = state[kStLvlHi];
-  int n_done = lvl_hi;
+  if (left.state[kStDone]) return;
+  int n_done = left.state[kStPlaced];
+  // the level that the last round found: listed and marked visited, not ranked (its parents' places are where `order` will be)
+  if (tid == 0) {
+    int sum = 0;
+    for (int r = 0; r < regions; ++r) {
+      first_s[r] = sum;
+      sum += left.count[r];
+    }
+    first_s[regions] = sum;
+  }
+  __syncthreads();
+  for (int r = tid >> 6; r < regions; r += kOrderThreads / 64)
+    for (int c = first_s[r] + (tid & 63); c < first_s[r + 1]; c += 64) {
+      const uint32_t e = left.list[r * kRegCols + c - first_s[r]];
+      keys[c] = level_key(order[e >> 16], degree[e & 0xffffu], (int)(e & 0xffffu));
+    }
+  sync_global();
+  rank_level(keys, first_s[regions], chunk_s, tid, [&](int r, int v) {
+    order[n_done + r] = v;
+    perm[N - 1 - n_done - r] = v;
+  });
+  int lvl_lo = n_done, lvl_hi = n_done + first_s[regions];
+  n_done = lvl_hi;
+  sync_global();
   {
     for (int w = tid; w < kMaxNodes / 64; w += kOrderThreads) {
       visited[w] = w < W ? visited_g[w] : ~0ull;  // nodes past N were marked visited when the set was initialised
@@ -528,7 +625,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restric
 
 inline size_t round256(size_t n) { return (n + 255) / 256 * 256; }
 struct RcmLayout {
-  size_t bits, degree, parent, order, cand, keys, visited, claimed, state, total;
+  size_t bits, degree, parent, order, cand, keys, visited, walk, state, total;
   explicit RcmLayout(int64_t N) {
     const size_t W = (size_t)((N + 63) / 64);
     size_t o = 0;
@@ -546,7 +643,7 @@ struct RcmLayout {
     o += round256((size_t)N * 8);
     visited = o;
     o += round256(W * 8);
-    claimed = o;
+    walk = o;  // 24 bytes a region of 8 words: the two records' counts and minima
     o += round256(W * 8);
     state = o;
     o += round256(2 * kStInts * 4);
@@ -584,23 +681,26 @@ extern "C" __attribute__((visibility("default"))) int bbm_rcm_order(const uint8_
   const int W = (int)ceil_div(N, 64);
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint64_t* visited = reinterpret_cast<uint64_t*>(ws + lay.visited);
-  uint64_t* claimed = reinterpret_cast<uint64_t*>(ws + lay.claimed);
-  int32_t* state = reinterpret_cast<int32_t*>(ws + lay.state);
-  rcm_pack_kernel<<<(unsigned)N, kPackThreads, 0, s>>>(mask, (int)N, row_stride_bytes, W, reinterpret_cast<uint16_t*>(bits), degree, parent, visited,
-                                                       claimed, state);
+  const int regions = (int)ceil_div(W, kRegWords);
+  uint64_t* const lowest = reinterpret_cast<uint64_t*>(ws + lay.walk);
+  int32_t* const count = reinterpret_cast<int32_t*>(lowest + 2 * regions);
+  int32_t* const state = reinterpret_cast<int32_t*>(ws + lay.state);
+  // while the rounds last, the places of the nodes are kept where the finisher's order will be, the two lists where its candidates
+  // and keys will be
+  const WalkRecord rec[2] = {{state, count, lowest, reinterpret_cast<uint32_t*>(cand)},
+                             {state + kStInts, count + regions, lowest + regions, reinterpret_cast<uint32_t*>(keys)}};
+  rcm_pack_kernel<<<(unsigned)N, kPackThreads, 0, s>>>(mask, (int)N, row_stride_bytes, W, reinterpret_cast<uint16_t*>(bits), degree, parent);
   int rc = launch_status("bbm_rcm_order (pack)");
   if (rc != BBM_OK) return rc;
-  // the first ranking, of no candidates, starts the first component; then kRounds rounds of (expansion, ranking); the finisher
-  // walks whatever is left.  Kernels that find the walk finished return at once.
-  rcm_rank_kernel<<<1, kRankThreads, 0, s>>>(degree, parent, cand, order, perm, visited, state, state + kStInts, (int)N);
-  for (int r = 1; r <= kRounds; ++r) {
-    int32_t *const st = state + kStInts * (r & 1), *const next = state + kStInts * (~r & 1);
-    rcm_expand_kernel<<<kExpandWGs, kExpandThreads, 0, s>>>(bits, order, visited, claimed, parent, cand, st, W);
-    rcm_rank_kernel<<<kRankWGs, kRankThreads, 0, s>>>(degree, parent, cand, order, perm, visited, st, next, (int)N);
-  }
+  // kRounds rounds of a level each; the finisher walks whatever is left.  Kernels that find the walk finished return at once.
+  rcm_start_kernel<<<(unsigned)regions, kRegCols, 0, s>>>(degree, visited, rec[0], (int)N, W);
+  const int rank_wgs = (int)std::min<int64_t>(kRankWGs, ceil_div(N, kLevelWaves));
+  static_assert(kRounds % 2 == 0, "the finisher's record and list are those of the last round");
+  for (int r = 0; r < kRounds; ++r)
+    rcm_level_kernel<<<(unsigned)(regions + rank_wgs), kLevelThreads, 0, s>>>(bits, degree, visited, order, perm, rec[r & 1], rec[~r & 1], (int)N, W, regions);
   rc = launch_status("bbm_rcm_order (rounds)");
   if (rc != BBM_OK) return rc;
-  rcm_finish_kernel<<<1, kOrderThreads, 0, s>>>(bits, degree, parent, order, cand, keys, visited, state + kStInts * ((kRounds + 1) & 1), (int)N, W, perm);
+  rcm_finish_kernel<<<1, kOrderThreads, 0, s>>>(bits, degree, parent, order, cand, keys, visited, rec[0], (int)N, W, regions, perm);
   return launch_status("bbm_rcm_order");
 }
 

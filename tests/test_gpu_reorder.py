@@ -52,6 +52,18 @@ def _cases():
     yield "big star", big                                            # a level larger than one ranking sweep (4096 keys)
     yield "huge star", _star(16500)                                  # more than 64 * 256 nodes in a level: one lane per candidate
     yield "graph workload", masks.graph_mask(1024, 5, reorder="none", xm=8.0, cap=60)[0]
+    lopsided = np.eye(9001, dtype=np.uint8)                           # 18 regions of 512 nodes, the last one of 297: 16 share lines in pairs
+    rng = np.random.default_rng(9)
+    lopsided[rng.integers(0, 9001, 20000), rng.integers(0, 9001, 20000)] = 1
+    yield "not symmetric", lopsided                                  # a node's neighbours need not have it as theirs
+    wide = np.eye(3000, dtype=np.uint8)                               # 60 levels of 50 nodes: the finisher takes a ranked level over
+    for l in range(59):
+        a, b = np.meshgrid(np.arange(50 * l, 50 * l + 50), np.arange(50 * l + 50, 50 * l + 100))
+        keep = rng.random(a.shape) < 0.2
+        keep[:, 0] = True
+        wide[a[keep], b[keep]] = wide[b[keep], a[keep]] = 1
+    pi = rng.permutation(3000)
+    yield "more levels than rounds", wide[pi][:, pi]
     yield "single node", np.ones((1, 1), dtype=np.uint8)
     yield "no self loops", (_sym(64, 4, 0.05) * (1 - np.eye(64, dtype=np.uint8))).astype(np.uint8)
 
