@@ -67,10 +67,30 @@ __device__ __forceinline__ float partner_max(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// s_waitcnt until at most n of the wave's memory operations are under way (they end in the order in which they were issued)
+constexpr int wait_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | (n >> 4) << 14; }
+
+// A barrier behind which LDS writes are seen, and which does not wait for copies on their way there.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 constexpr int kSplitMinTiles = 8;        // list entries that a part of a row in a small launch keeps (split_parts)
 constexpr int kWin = 1024;               // tiles per schedule window (block columns, or list entries)
 constexpr uint32_t kNoTile = 0xffffffffu;  // sentinel after the last entry of a window
 constexpr uint32_t kZeroWord = 0x40000000u;  // entry flag: the tile's mask words are all zero and are not in memory
+
+// A kernel's arguments where they lie in memory (its only parameter, at the start of the argument segment): taken by value they are
+// read into scalar registers when the kernel starts, more than there are, and kept in lanes of vector registers.
+typedef const AttnParams __attribute__((address_space(4)))* Args;
+__device__ __forceinline__ Args kernel_args() { return (Args)__builtin_amdgcn_kernarg_segment_ptr(); }
+// A pointer of the arguments points to global memory (the compiler cannot see that, and would take it for one into LDS as well).
+template <typename T>
+__device__ __forceinline__ T* global(T* p) {
+  return (T*)(T __attribute__((address_space(1)))*)p;
+}
 
 // Builds, in LDS, the ascending list of tiles one block row visits inside one schedule window; entry =
 // block column | (1 << 31 if the element mask can be skipped there).  Returns the number of entries (uniform).
@@ -78,28 +98,28 @@ constexpr uint32_t kZeroWord = 0x40000000u;  // entry flag: the tile's mask word
 // [clo, chi): the block columns this work-group is responsible for (all of them unless the block row is computed in
 // parts).
 template <int NW>
-__device__ __forceinline__ int build_window(const AttnParams& P, int m, int i, int win, uint32_t* tiles_s, int* cnt_s, int clo, int chi) {
+__device__ __forceinline__ int build_window(Args P, int m, int i, int win, uint32_t* tiles_s, int* cnt_s, int clo, int chi) {
   constexpr int NT = NW * 64;
   constexpr int CH = kWin / 64;  // 64-column chunks per window
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t r = (int64_t)m * P.nbr + i;
+  const int64_t r = (int64_t)m * P->nbr + i;
   int count;
-  if (P.mode == BBM_MODE_DENSE_BASELINE) {
+  if (P->mode == BBM_MODE_DENSE_BASELINE) {
     const int j0 = clo + win * kWin;
     count = min(kWin, chi - j0);
     // an empty block's packed words are never written by the block reduction: flag it, the mask word is then 0
-    const uint8_t* row = P.bin_blk_mat + r * P.nbc;
+    const uint8_t* row = global(P->bin_blk_mat) + r * P->nbc;
     for (int t = tid; t < count; t += NT) tiles_s[t] = (uint32_t)(j0 + t) | (row[j0 + t] == 0 ? kZeroWord : 0u);
   } else {
     int lo = clo, hi = chi, run_lo = 0, run_hi = 0;
-    if (P.mode == BBM_MODE_RUNS) {
-      lo = max(clo, P.nz_lo[r]);
-      hi = min(chi, P.nz_hi[r]);
-      run_lo = P.offset[r];
-      run_hi = run_lo + P.total_ones[r];
+    if (P->mode == BBM_MODE_RUNS) {
+      lo = max(clo, global(P->nz_lo)[r]);
+      hi = min(chi, global(P->nz_hi)[r]);
+      run_lo = global(P->offset)[r];
+      run_hi = run_lo + global(P->total_ones)[r];
     }
     const int j0 = (lo & ~63) + win * kWin;
-    const uint8_t* row = P.bin_blk_mat + r * P.nbc;
+    const uint8_t* row = global(P->bin_blk_mat) + r * P->nbc;
     uint64_t nz[(CH + NW - 1) / NW];
 #pragma unroll
     for (int n = 0; n < (CH + NW - 1) / NW; ++n) {
@@ -124,7 +144,7 @@ __device__ __forceinline__ int build_window(const AttnParams& P, int m, int i, i
         for (int c2 = 0; c2 < ch; ++c2) before += cnt_s[c2];
         if ((nz[n] >> lane) & 1ull) {
           const int j = j0 + 64 * ch + lane;
-          const bool in_run = (P.mode == BBM_MODE_RUNS) && j >= run_lo && j < run_hi;
+          const bool in_run = (P->mode == BBM_MODE_RUNS) && j >= run_lo && j < run_hi;
           tiles_s[before + __popcll(nz[n] & ((1ull << lane) - 1ull))] = (uint32_t)j | (in_run ? 0x80000000u : 0u);
         }
       }
@@ -137,22 +157,22 @@ __device__ __forceinline__ int build_window(const AttnParams& P, int m, int i, i
 }
 
 // Number of schedule windows of the block columns [clo, chi) of one block row (uniform).
-__device__ __forceinline__ int num_windows(const AttnParams& P, int m, int i, int clo, int chi) {
+__device__ __forceinline__ int num_windows(Args P, int m, int i, int clo, int chi) {
   int lo = clo, hi = chi;
-  if (P.mode == BBM_MODE_RUNS) {
-    const int64_t r = (int64_t)m * P.nbr + i;
-    lo = max(clo, P.nz_lo[r]);
-    hi = min(chi, P.nz_hi[r]);
+  if (P->mode == BBM_MODE_RUNS) {
+    const int64_t r = (int64_t)m * P->nbr + i;
+    lo = max(clo, global(P->nz_lo)[r]);
+    hi = min(chi, global(P->nz_hi)[r]);
   }
   if (hi <= lo) return 0;
-  if (P.mode != BBM_MODE_DENSE_BASELINE) lo &= ~63;
+  if (P->mode != BBM_MODE_DENSE_BASELINE) lo &= ~63;
   return (hi - lo + kWin - 1) / kWin;
 }
 
 // One work-group per (block row, batch, head), tiles from build_window.  SCHED = 2 (a launch too small to fill the chip):
-// every block row is computed in up to P.split equal parts by as many work-groups, which merge them in pairs (merge_tree).
+// every block row is computed in up to P->split equal parts by as many work-groups, which merge them in pairs (merge_tree).
 // With SCHED = 1 (LIST mode) the first
-// P.n_extra work-groups, before turning to their own block row, take the parts of the block rows which the split
+// P->n_extra work-groups, before turning to their own block row, take the parts of the block rows which the split
 // schedule cut from a queue; the work-group that completes a row's last part merges the parts in part order and
 // writes the row, and the row's own work-group skips it.
 //
@@ -162,7 +182,8 @@ __device__ __forceinline__ int num_windows(const AttnParams& P, int m, int i, in
 // scales): c = 2^k * r with r in [1, 2); Q is multiplied by 2^k, which is exact in bf16, and r multiplies the
 // accumulator inside the exponential; running maxima are then kept in units of 1/r.
 template <int D, int NW, int SCHED, bool EXACT>
-__global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) void attn_fwd_kernel(const AttnParams P) {
+__global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) void attn_fwd_kernel(const AttnParams) {
+  Args P = kernel_args();
   constexpr int NT = NW * 64;
   constexpr int BR = NW * 32;
   // LDS tile layout ("blocks"): one asynchronous copy instruction of a wave fills one 1 KiB block with RPB rows
@@ -192,18 +213,16 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction: keep it in a scalar register
-  const int lq = lane & 31, hh = lane >> 5;
-  const int64_t N = P.N, Nk = P.Nk;
-  const float c = P.qscale;
-  const float rr = EXACT ? P.rmul : 1.0f;
+  const int64_t N = P->N, Nk = P->Nk;
+  const float c = P->qscale;
+  const float rr = EXACT ? P->rmul : 1.0f;
   auto ex2 = [&](float x) { return __builtin_amdgcn_exp2f(EXACT ? rr * x : x); };
 
   // ---- per-item state (SCHED = false: exactly one item, derived from blockIdx)
   int m, i, bh;
   const __bf16* __restrict__ Kg;
   const __bf16* __restrict__ Vg;
-  int64_t head_off, qrow;
-  bool q_ok;
+  int64_t head_off;
   const uint64_t* __restrict__ mrow;
   bf16x8 qf[KS];
   f32x16 oacc[DB];
@@ -215,44 +234,56 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // Q through LDS needs a 32 x D staging slab per wave in the two buffers of parity 1 (two slabs each)
   constexpr bool Q_VIA_LDS = NW <= 4;
   bool q_pending = false;
-  const int g_row = lane / RC, g_chunk = lane % RC;  // row and 16-byte chunk this lane moves in a 1 KiB copy
+  // What a lane reads and copies where.  Found anew for every item: kept across the merge of a cut row, some of it lay in scratch
+  // memory at d = 128, and the own row's list was asked for only when its first tile had landed (the wait for the reload).
+  int lq, hh;          // query row of the wave's 32, half of the keys
+  int g_row, g_chunk;  // row and 16-byte chunk this lane moves in a 1 KiB copy
+  int kaddr, vaddr;    // see k_frag, v_frag
+  uint32_t g_off;      // see copy_piece
+  auto lane_places = [&]() __attribute__((always_inline)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    lq = ln & 31, hh = ln >> 5;
+    g_row = ln / RC, g_chunk = ln % RC;
+    kaddr = (lq % NBLK) * KBLK + (lq / NBLK) * D + hh * 8;
+    const int vy = (ln & 15) >> 2, vg = (ln >> 4) & 1, vx = (ln & 3) >> 1;
+    vaddr = (4 * hh + vy) * VBLK + (2 * vg + vx) * 8 + 4 * (ln & 1);
+    g_off = (uint32_t)((wave + g_row * NBLK) * D + g_chunk * 8) * 2u;
+  };
   auto q_stage = [&]() { return (wave / 2 == 0 ? k_s1 : v_s1) + (wave % 2) * 32 * D; };
   auto begin_item = [&]() {
+    lane_places();
     head_off = (int64_t)bh * N * D;
-    Kg = P.k + (int64_t)bh * Nk * D;
-    Vg = P.v + (int64_t)bh * Nk * D;
-    qrow = (int64_t)i * BR + wave * 32 + lq;
-    q_ok = qrow < N;
+    Kg = global(P->k) + (int64_t)bh * Nk * D;
+    Vg = global(P->v) + (int64_t)bh * Nk * D;
+    const int64_t qrow = (int64_t)i * BR + wave * 32 + lq;
+    const bool q_ok = qrow < N;
     // packed mask words of this lane's query row (rows past N borrow row 0: their results are never stored)
-    mrow = P.packed + (int64_t)m * P.W * N + (q_ok ? qrow : 0);
+    mrow = global(P->packed) + (int64_t)m * P->W * N + (q_ok ? qrow : 0);
+    // The wave's 32 x D slab of Q is one contiguous piece of memory: it is copied asynchronously, 1 KiB per instruction,
+    // into this wave's staging slab (tile buffer 1, idle until the second tile is requested), where the MFMA fragments are picked
+    // up.  Chunk j of row r lands at chunk position j ^ (r % RC) of row r.  Eight waves find no room there and read their fragments
+    // themselves.  Rows past N come as zeros (their results are never stored).  (The buffer form: the compiler takes the global
+    // form of the copy for a possible access to LDS by another path, and waits for all that is under way where it needs an
+    // earlier load.)
+    const int64_t row0 = (int64_t)i * BR + wave * 32;
+    const int rows = (int)max<int64_t>(0, min<int64_t>(32, N - row0));
+    const __amdgpu_buffer_rsrc_t slab = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(global(P->q)) + head_off + row0 * D, 0,
+                                                                          (int)scalar(rows * D * 2), 0x00027000);
     if constexpr (Q_VIA_LDS) {
-      // The wave's 32 x D slab of Q is one contiguous piece of memory: copy it asynchronously, 1 KiB per instruction,
-      // into this wave's staging slab (tile buffer 1, idle until the second tile is requested) and pick the MFMA
-      // fragments up from there in fetch_q.  Chunk j of row r lands at chunk position j ^ (r % RC) of row r.  Rows
-      // past N re-read row N-1 (their results are never stored).
-      const int64_t row0 = (int64_t)i * BR + wave * 32;
-      const char* slab = reinterpret_cast<const char*>(P.q + head_off + row0 * D);
-      const int last = (int)min<int64_t>(31, N - 1 - row0);  // >= 0 for every wave that owns a real row
       __bf16* const stage = q_stage();
 #pragma unroll
       for (int n = 0; n < 32 / RPB; ++n) {
-        const int r = min(n * RPB + g_row, last);
-        const uint32_t off = (uint32_t)(r * D + ((g_chunk ^ (r % RC)) * 8)) * 2u;
-        if (last >= 0)
-          __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)(slab + off),
-                                           (void __attribute__((address_space(3)))*)(stage + n * 512), 16, 0, 0);
+        const int r = n * RPB + g_row;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(slab, (void __attribute__((address_space(3)))*)(stage + n * 512), 16,
+                                                 (uint32_t)(r * D + ((g_chunk ^ (r % RC)) * 8)) * 2u, 0, 0, 0);
       }
-      q_pending = true;
     } else {
 #pragma unroll
-      for (int t = 0; t < KS; ++t) {
-        if (q_ok)
-          qf[t] = *reinterpret_cast<const bf16x8*>(P.q + head_off + qrow * D + 16 * t + 8 * hh);
-        else
-          for (int e = 0; e < 8; ++e) qf[t][e] = (__bf16)0.0f;
-        for (int e = 0; e < 8; ++e) qf[t][e] = (__bf16)((float)qf[t][e] * c);
-      }
+      for (int t = 0; t < KS; ++t)
+        qf[t] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(slab, (lq * D + 16 * t + 8 * hh) * 2, 0, 0));
     }
+    q_pending = true;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
       for (int e = 0; e < 16; ++e) oacc[db][e] = 0.0f;
@@ -266,7 +297,6 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // instruction n (0 .. 2*LPW-1) of the wave for the tile of list entry e; keys past Nk (`rows` of the 64 lie below it) come as
   // zeros from the bounds check of the buffer resource: they sit in a tile that is never "full", so the element mask gives them
   // probability exactly 0, and zeros add nothing.
-  const uint32_t g_off = (uint32_t)((wave + g_row * NBLK) * D + g_chunk * 8) * 2u;
   auto copy_piece = [&](int jt, int rows, __bf16* kd, __bf16* vd, int n) {
     const int p = n % LPW, blk = p * NW + wave;
     const __bf16* const tile = (n < LPW ? Kg : Vg) + (int64_t)jt * (kBc * D);
@@ -284,7 +314,6 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   };
 
   // K fragment of MFMA k-step t, key block kb: row 32*kb + lq, chunk 2t + hh.
-  const int kaddr = (lq % NBLK) * KBLK + (lq / NBLK) * D + hh * 8;
   auto k_frag = [&](const __bf16* ks, int kb, int t) {
     return *reinterpret_cast<const bf16x8*>(ks + kaddr + kb * (32 / NBLK) * D + t * 16);
   };
@@ -293,8 +322,6 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // vr = 16u + 8a + 4hh + y (y = (lane%16)/4), 16-byte chunk 4db + 2g + x (g = (lane/16)%2, x = (lane%4)/2),
   // elements 4*(lane%2).. of it, and receives keys 16u + 8a + 4hh + 0..3 of column 32db + lane%32 -- the key
   // order of the bf16 probabilities taken straight from the S^T accumulators.
-  const int vy = (lane & 15) >> 2, vg = (lane >> 4) & 1, vx = (lane & 3) >> 1;
-  const int vaddr = (4 * hh + vy) * VBLK + (2 * vg + vx) * 8 + 4 * (lane & 1);
   auto v_frag = [&](const __bf16* vs, int u, int db) {
     s16x4 part[2];
 #pragma unroll
@@ -336,7 +363,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
     // a partial tile in which none of this wave's 32 queries sees a key adds exact zeros: such a wave only takes part
     // in the copies and barriers of the step (not in the dense-tile baseline, which stands for a kernel that knows
     // nothing about the mask's structure)
-    const bool live = !partial || (SCHED == 0 && P.mode == BBM_MODE_DENSE_BASELINE) || __ballot(mw != 0ull) != 0ull;
+    const bool live = !partial || (SCHED == 0 && P->mode == BBM_MODE_DENSE_BASELINE) || __ballot(mw != 0ull) != 0ull;
     if (!live && more) copy_all(jt1, k_oth, v_oth);
     e0 = e1;
     if (live) {
@@ -438,14 +465,28 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // start_tile0 was already called for tiles_s[0].
   auto run_window = [&](int count, bool started) {
     if (!started) start_tile0(tiles_s[0]);
-    if (Q_VIA_LDS && q_pending) {  // first window of a block row: Q fragments out of the staging slab
-      __builtin_amdgcn_s_waitcnt(0);  // this wave's own copies have landed (no other wave touches its slab)
-      const __bf16* stage = q_stage();
+    if (q_pending) {  // first window of a block row: Q fragments
+      if constexpr (Q_VIA_LDS) {
+        __builtin_amdgcn_s_waitcnt(wait_vm(2 * LPW));  // this wave's own copies of Q have landed, behind which it asked for the first tile
+        auto pick_up = [&](const __bf16* stage) __attribute__((always_inline)) {
 #pragma unroll
-      for (int t = 0; t < KS; ++t) {
-        qf[t] = *reinterpret_cast<const bf16x8*>(stage + lq * D + (((2 * t + hh) ^ (lq % RC)) * 8));
-        for (int e = 0; e < 8; ++e) qf[t][e] = (__bf16)((float)qf[t][e] * c);
+          for (int t = 0; t < KS; ++t) qf[t] = *reinterpret_cast<const bf16x8*>(stage + lq * D + (((2 * t + hh) ^ (lq % RC)) * 8));
+        };
+        // (By variable, not through a pointer to either, which the compiler would make of this without the asm: it then waits for
+        // no other copies.)
+        if (wave < 2) {
+          pick_up(k_s1 + wave * 32 * D);
+#pragma unroll
+          for (int t = 0; t < KS; ++t) asm volatile("; from k_s1" : "+v"(qf[t]));
+        } else {
+          pick_up(v_s1 + (wave & 1) * 32 * D);
+#pragma unroll
+          for (int t = 0; t < KS; ++t) asm volatile("; from v_s1" : "+v"(qf[t]));
+        }
       }
+#pragma unroll
+      for (int t = 0; t < KS; ++t)
+        for (int e = 0; e < 8; ++e) qf[t][e] = (__bf16)((float)qf[t][e] * c);
       q_pending = false;
     }
     e1_v = tiles_s[1];
@@ -458,14 +499,20 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   };
 
   // Runs nt >= 1 consecutive list entries, the first of which is already known: its copies start before the list
-  // itself has been fetched.
-  auto run_list = [&](const uint32_t* __restrict__ list, int nt, uint32_t first) {
+  // itself has been fetched.  `ahead` is this thread's entry, from ask_list: asked for before Q and the first tile, it does not wait
+  // behind their 64 KiB, and what is left to do before the first product (list to LDS, Q's fragments) is done while the tile is on
+  // its way.  Kernel time against asking behind them and waiting for all at once, with the epilogue's stores by buffer and the
+  // arguments left in memory, us: packed sequences of 3001, D = 128, 24.1 -> 22.2, of 4096, D = 64, 34.3 -> 33.1, D = 128 at 256
+  // queries a block row 82.3 -> 80.3, at 64 91.6 -> 88.9; tree prefill 132.9 -> 131.0; a 4096-token window over 8 heads 11.4 -> 11.2.
+  auto ask_list = [&](const uint32_t* __restrict__ list, int nt) { return list[max(0, min(tid, nt - 1))]; };
+  auto run_list = [&](const uint32_t* __restrict__ list, int nt, uint32_t first, uint32_t ahead) {
     start_tile0(first);
     for (int w0 = 0; w0 < nt; w0 += kWin) {
       const int count = min(kWin, nt - w0);
-      for (int t = tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
+      if (w0 == 0) tiles_s[tid] = tid < nt ? ahead : kNoTile;
+      for (int t = w0 == 0 ? tid + NT : tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
       if (tid < 3) tiles_s[count + tid] = kNoTile;
-      __syncthreads();
+      lds_barrier();  // (the first tile may still be on its way)
       run_window(count, w0 == 0);
     }
   };
@@ -496,15 +543,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
       }
     }
     const int64_t row0 = (int64_t)i * BR + wave * 32;
-    __bf16* og = P.o + head_off + row0 * D;
-#pragma unroll
-    for (int n = 0; n < 32 / RPB; ++n) {
-      const int r = n * RPB + gro;
-      const bf16x8 ov = *reinterpret_cast<const bf16x8*>(stage + r * D + ((gco ^ (r % RC)) * 8));
-      if (row0 + r < N) *reinterpret_cast<bf16x8*>(og + r * D + gco * 8) = ov;
-    }
-    if (q_ok && P.lse && hh == 0)
-      P.lse[(int64_t)bh * N + qrow] = l_tot > 0.0f ? m_run * (rr / kLog2e) + __logf(l_tot) : -INFINITY;
+    bbm::store_rows<D>(stage, global(P->o) + head_off + row0 * D, (int)max<int64_t>(0, min<int64_t>(32, N - row0)), gro, gco);
+    if (row0 + lqo < N && global(P->lse) && hho == 0)
+      global(P->lse)[(int64_t)bh * N + row0 + lqo] = l_tot > 0.0f ? m_run * (rr / kLog2e) + __logf(l_tot) : -INFINITY;
   };
 
   // A parked partial result: the accumulators, then a (maximum, sum) pair per thread.
@@ -607,31 +648,33 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
 
   // ---- a launch too small to fill the chip: work-group = (block row, part), merged by merge_tree
   if constexpr (SCHED == 2) {
-    int part = (int)blockIdx.x % P.split;
-    const int rest = (int)blockIdx.x / P.split;
-    int S = P.split;  // parts of this row
-    bh = rest / P.nbr;
-    i = P.nbr - 1 - (rest - bh * P.nbr);
-    m = (P.Mb == 1) ? 0 : bh / P.H;
-    const int hb = (P.Mb == 1) ? bh : bh - m * P.H;
-    if (P.mode == BBM_MODE_LIST) {  // equal shares of the row's list, none shorter than kSplitMinTiles entries if there are several
-      const int32_t* rp = P.row_ptr + (int64_t)m * (P.nbr + 1) + i;
+    int part = (int)blockIdx.x % P->split;
+    const int rest = (int)blockIdx.x / P->split;
+    int S = P->split;  // parts of this row
+    bh = rest / P->nbr;
+    i = P->nbr - 1 - (rest - bh * P->nbr);
+    m = (P->Mb == 1) ? 0 : bh / P->H;
+    const int hb = (P->Mb == 1) ? bh : bh - m * P->H;
+    if (P->mode == BBM_MODE_LIST) {  // equal shares of the row's list, none shorter than kSplitMinTiles entries if there are several
+      const int32_t* rp = global(P->row_ptr) + (int64_t)m * (P->nbr + 1) + i;
       const int p_row = rp[0], n_row = rp[1] - rp[0];
       S = max(1, min(S, n_row / kSplitMinTiles));
       // Work-groups go to the eight XCDs in turn: if the same ones of every row were left over, some XCDs would get no work (rows
       // of 6 to 10 entries, left whole: a window over 8 heads of 4096, D = 64, 14.3 -> 12.6 us; over one head of 16384, D = 128,
       // 25.7 -> 20.8).  Rows in all their parts keep the order in which the rows of a head read one part's keys on one XCD.
-      if (S < P.split) part = (part + rest * P.split / 8) % P.split;
+      if (S < P->split) part = (part + rest * P->split / 8) % P->split;
       if (part >= S) return;
       const int chunk = (n_row + S - 1) / S;
-      const int p0 = p_row + part * chunk, nt = max(0, min(chunk, n_row - part * chunk));
-      const uint32_t* __restrict__ list = P.col_idx + (int64_t)m * P.nbr * P.nbc + p0;
+      const int nt = max(0, min(chunk, n_row - part * chunk));
+      const int p0 = p_row + (nt > 0 ? part * chunk : 0);  // (an entry is asked for in any case: of a row without any, there is one behind it)
+      const uint32_t* __restrict__ list = global(P->col_idx) + (int64_t)m * P->nbr * P->nbc + p0;
+      const uint32_t first = list[0], ahead = ask_list(list, nt);
       begin_item();
-      if (nt > 0) run_list(list, nt, list[0]);
+      if (nt > 0) run_list(list, nt, first, ahead);
     } else {  // BITMAP, RUNS: equal shares of the block columns
       begin_item();
-      const int chunk = (P.nbc + S - 1) / S;
-      const int clo = part * chunk, chi = min(P.nbc, clo + chunk);
+      const int chunk = (P->nbc + S - 1) / S;
+      const int clo = part * chunk, chi = min(P->nbc, clo + chunk);
       const int nwin = num_windows(P, m, i, clo, chi);
       for (int win = 0; win < nwin; ++win) {
         const int count = build_window<NW>(P, m, i, win, tiles_s, cnt_s, clo, chi);
@@ -643,9 +686,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
       __syncthreads();
       q_pending = false;
     }
-    const int row = m * P.nbr + i;
-    merge_tree(P.partials + ((int64_t)row * P.split * P.hbp + hb) * ((REGS + 2) * NT), (int64_t)P.hbp * ((REGS + 2) * NT), part, S,
-               P.queue + 8 + row * P.hbp + hb);
+    const int row = m * P->nbr + i;
+    merge_tree(global(P->partials) + ((int64_t)row * P->split * P->hbp + hb) * ((REGS + 2) * NT), (int64_t)P->hbp * ((REGS + 2) * NT), part, S,
+               global(P->queue) + 8 + row * P->hbp + hb);
     return;
   }
 
@@ -657,15 +700,15 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   int own_bh, own_m, own_rank;
   {
     const int wg = (int)blockIdx.x;
-    const int T = P.total_wgs;
+    const int T = P->total_wgs;
     const int xcd = wg & 7, slot = wg >> 3;
     const int per = T >> 3, rem = T & 7;
     const int logical = xcd * per + (xcd < rem ? xcd : rem) + slot;
-    const int grp = logical / (P.G * P.nbr), within = logical - grp * (P.G * P.nbr);
-    const int g_planes = min(P.G, T / P.nbr - grp * P.G);
+    const int grp = logical / (P->G * P->nbr), within = logical - grp * (P->G * P->nbr);
+    const int g_planes = min(P->G, T / P->nbr - grp * P->G);
     own_rank = within / g_planes;
-    own_bh = grp * P.G + (within - own_rank * g_planes);
-    own_m = (P.Mb == 1) ? 0 : own_bh / P.H;
+    own_bh = grp * P->G + (within - own_rank * g_planes);
+    own_m = (P->Mb == 1) ? 0 : own_bh / P->H;
   }
   // LIST mode: the schedule's header (parts, split threshold) and this work-group's row record -- which block row has
   // its rank, where its list lies and how it starts -- are requested together: one round trip, not three
@@ -673,14 +716,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   int nparts_all = 0, split_T = 0;
   if (SCHED == 1) {
     static_assert(bbm::kSchedNParts == 0 && bbm::kSchedSplitT == 1, "the header is read as one 8-byte pair");
-    const int2 hdr = *reinterpret_cast<const int2*>(P.sched);
-    own_rec = *reinterpret_cast<const int4*>(P.sched + bbm::sched_order_base(P.Mb, P.nbr) +
-                                             bbm::kSchedRowInts * (int64_t)(own_m * P.nbr + own_rank));
+    const int2 hdr = *reinterpret_cast<const int2*>(global(P->sched));
+    own_rec = *reinterpret_cast<const int4*>(global(P->sched) + bbm::sched_order_base(P->Mb, P->nbr) +
+                                             bbm::kSchedRowInts * (int64_t)(own_m * P->nbr + own_rank));
     nparts_all = hdr.x;
     split_T = hdr.y;
     // a workspace too small for the partial results of every (part, head) item: no row is computed in parts
     // (the same decision in every work-group: it depends on the header and the launch only)
-    if ((int64_t)nparts_all * P.hbp > (int64_t)P.part_cap) {
+    if ((int64_t)nparts_all * P->hbp > (int64_t)P->part_cap) {
       nparts_all = 0;
       split_T = 0x7fffffff;
     }
@@ -689,31 +732,33 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // (nothing to do, and no cost, when the schedule cut no row).  The tile loop is in the program twice, here and below: with one
   // loop for parts and own row the short rows of packed sequences took 44.9 us instead of 41.8, a 16384-token window 123 instead
   // of 115 (the backward kernels, which are short of registers, gained from it).
-  if (SCHED == 1 && (int)blockIdx.x < P.n_extra) {
-    const int n_items = nparts_all * P.hbp;
+  if (SCHED == 1 && (int)blockIdx.x < P->n_extra) {
+    const int n_items = nparts_all * P->hbp;
     // The first item of a work-group is its own index; later ones come from the queue counter, which therefore stands
     // for "n_extra items already handed out".
     int item = blockIdx.x;
     while (item < n_items) {
       int next_item = 0;
-      if (tid == 0) next_item = P.n_extra + atomicAdd(P.queue, 1);  // asked now, needed after this item
+      if (tid == 0) next_item = P->n_extra + atomicAdd(global(P->queue), 1);  // asked now, needed after this item
       const int hb = item / nparts_all;
-      const int32_t* seg = P.sched + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
+      const int32_t* seg = global(P->sched) + bbm::kSchedPartBase + (int64_t)bbm::kSchedPartInts * (item - hb * nparts_all);
       const int row = seg[0], p0 = seg[1], nt = seg[2], part = seg[3], nparts = seg[4], q_first = seg[5], rho = seg[6];
-      m = row / P.nbr;
-      i = row - m * P.nbr;
-      bh = (P.Mb == 1) ? hb : m * P.H + hb;
+      m = row / P->nbr;
+      i = row - m * P->nbr;
+      bh = (P->Mb == 1) ? hb : m * P->H + hb;
+      const uint32_t* const list = global(P->col_idx) + (int64_t)m * P->nbr * P->nbc + p0;
+      const uint32_t ahead = ask_list(list, nt);
       begin_item();
-      run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + p0, nt, (uint32_t)seg[7]);
-      park_and_merge(P.partials + ((int64_t)q_first * P.hbp + hb) * ((REGS + 2) * NT), (int64_t)P.hbp * ((REGS + 2) * NT), part, nparts,
-                     P.queue + 8 + rho * P.hbp + hb, next_item);
+      run_list(list, nt, (uint32_t)seg[7], ahead);
+      park_and_merge(global(P->partials) + ((int64_t)q_first * P->hbp + hb) * ((REGS + 2) * NT), (int64_t)P->hbp * ((REGS + 2) * NT), part, nparts,
+                     global(P->queue) + 8 + rho * P->hbp + hb, next_item);
       item = (int)scalar((uint32_t)item_s[0]);  // (a scalar: everything that addresses the item follows from it)
       __syncthreads();  // everyone has read the item, and the staged output, before the next item's copies and list land
     }
     // the last leading work-group to leave the queue puts the two queue counters back to zero for the next call
-    if (n_items > 0 && tid == 0 && atomicAdd(P.queue + 1, 1) == P.n_extra - 1) {
-      P.queue[0] = 0;
-      P.queue[1] = 0;
+    if (n_items > 0 && tid == 0 && atomicAdd(global(P->queue) + 1, 1) == P->n_extra - 1) {
+      global(P->queue)[0] = 0;
+      global(P->queue)[1] = 0;
     }
   }
 
@@ -722,17 +767,19 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   if (SCHED == 1) {
     i = own_rec.x;
     const int n_list = own_rec.z;
+    const uint32_t* const list = global(P->col_idx) + (int64_t)m * P->nbr * P->nbc + own_rec.y;
+    const uint32_t ahead = ask_list(list, n_list);
     begin_item();
     if (n_list <= split_T) {  // a row the schedule cut belongs to the queue
-      if (n_list > 0) run_list(P.col_idx + (int64_t)m * P.nbr * P.nbc + own_rec.y, n_list, (uint32_t)own_rec.w);
+      if (n_list > 0) run_list(list, n_list, (uint32_t)own_rec.w, ahead);
       write_output();
     }
   } else {
-    i = P.nbr - 1 - own_rank;  // from the last row up: long rows first for causal-like masks
+    i = P->nbr - 1 - own_rank;  // from the last row up: long rows first for causal-like masks
     begin_item();
-    const int nwin = num_windows(P, m, i, 0, P.nbc);
+    const int nwin = num_windows(P, m, i, 0, P->nbc);
     for (int win = 0; win < nwin; ++win) {
-      const int count = build_window<NW>(P, m, i, win, tiles_s, cnt_s, 0, P.nbc);
+      const int count = build_window<NW>(P, m, i, win, tiles_s, cnt_s, 0, P->nbc);
       if (count > 0) run_window(count, false);
     }
     write_output();

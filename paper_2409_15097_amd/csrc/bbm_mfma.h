@@ -121,6 +121,21 @@ __device__ __forceinline__ void for_records(const float* first, int64_t stride, 
     add(y, py);
   }
 }
+// The first `rows` (0 .. 32) rows of a 32 x D bf16 slab from LDS, where 16-byte chunk c of row r sits at chunk position c ^ (r % (D / 8)),
+// to memory as whole rows; row0, chunk: this lane's place in a piece of 1 KiB.  Rows past those lie outside the buffer: a branch
+// and a 64-bit address a piece instead took a third of the epilogue's instructions.
+template <int D>
+__device__ __forceinline__ void store_rows(const __bf16* stage, __bf16* dst, int rows, int row0, int chunk) {
+  constexpr int RC = D / 8, RPB = 64 / RC;
+  const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(dst, 0, (int)scalar((uint32_t)(rows * D * 2)), 0x00027000);
+  const int at = (row0 * D + chunk * 8) * 2;
+#pragma unroll
+  for (int n = 0; n < 32 / RPB; ++n) {
+    const int r = n * RPB + row0;
+    const u32x4 x = *reinterpret_cast<const u32x4*>(stage + r * D + (chunk ^ (r % RC)) * 8);
+    __builtin_amdgcn_raw_buffer_store_b128(x, out, at + n * RPB * D * 2, 0, 0);
+  }
+}
 __device__ __forceinline__ void hand_over() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();

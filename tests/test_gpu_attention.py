@@ -524,3 +524,25 @@ def test_small_launch_with_rows_in_fewer_parts_than_the_launch_has(H, d):
         o, lse = bbm.bbm_attn_fwd(qt, kt, vt, idx, mode=bbm.BBM_MODE_LIST)
         torch.cuda.synchronize()
         assert_attention_close(o, lse, O_ref, lse_ref)
+
+
+@pytest.mark.parametrize("Br,length", [(64, 127), (64, 128), (64, 129), (128, 255), (128, 256), (128, 257), (256, 511), (256, 512), (256, 513)])
+def test_lists_around_one_entry_per_thread(Br, length):
+    """A thread asks for one entry of its row's list before anything else, the rest follows in a loop: lists of one entry per
+    thread, one fewer and one more; 40 queries, so that waves without a query copy nothing; 257 heads, so that no row is cut.
+    (Reference in float32 on the GPU, first and last head: its own error is far below the bar.)"""
+    bbm = _bbm()
+    H, Nq, Nk, d = 257, 40, 64 * length - 5, 64
+    gen = torch.Generator(device="cuda").manual_seed(length)
+    q, k, v = (torch.randn((1, H, n, d), generator=gen, device="cuda").to(torch.bfloat16) for n in (Nq, Nk, Nk))
+    mask = (torch.rand((1, Nq, Nk), generator=gen, device="cuda") < 0.4).to(torch.uint8)
+    idx = bbm.build_index(mask, Br, 64)
+    assert int(idx.row_ptr[0, 1]) == length
+    print(f"list of {length} Br={Br}", flush=True)
+    o, lse = bbm.bbm_attn_fwd_rect(q, k, v, idx, mode=bbm.BBM_MODE_LIST)
+    for h in (0, H - 1):
+        s = (q[0, h].float() @ k[0, h].float().T) * d ** -0.5
+        s = s.masked_fill(mask[0] == 0, float("-inf"))
+        ref = torch.softmax(s, 1) @ v[0, h].float()
+        assert_attention_close(o[:, h:h + 1], lse[:, h:h + 1], ref[None, None].double().cpu().numpy(),
+                               torch.logsumexp(s, 1)[None, None].double().cpu().numpy())
