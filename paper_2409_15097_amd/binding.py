@@ -1,7 +1,7 @@
 """ctypes binding of libbbm.so.  Argument marshalling only; see include/bbm.h for the contract."""
 import ctypes as C
 import os
-from dataclasses import dataclass
+from dataclasses import dataclass, field
 from typing import Optional
 
 import torch
@@ -57,6 +57,8 @@ def _load():
     L.bbm_build_sparse_index.argtypes = [vp, i64, i64, i64, vp, vp, vp, vp]
     L.bbm_build_index.restype = ci
     L.bbm_build_index.argtypes = [vp, i64, i64, i64, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+    L.bbm_build_mask_index.restype = ci
+    L.bbm_build_mask_index.argtypes = [vp, i64, i64, i64, i64, ci, ci, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     L.bbm_sched_bytes.restype = C.c_size_t
     L.bbm_sched_bytes.argtypes = [i64, i64]
     L.bbm_attn_fwd_workspace_bytes.restype = C.c_size_t
@@ -152,6 +154,8 @@ class BlockIndex:
     col_ptr: Optional[torch.Tensor] = None
     row_idx: Optional[torch.Tensor] = None
     col_sched: Optional[torch.Tensor] = None
+    # one int32 that build_index's single launch counts its work-groups in, zero between calls (a copy gets one of its own)
+    arrivals: Optional[torch.Tensor] = field(default=None, init=False, repr=False, compare=False)
 
     def c_struct(self) -> _CIndex:
         g = _ptr
@@ -173,11 +177,23 @@ def bbm_build_block_mask_rect(mask: torch.Tensor, Br: int, Bc: int, idx: Optiona
                               want_bin: bool = True, want_packed: bool = True, stream=None) -> BlockIndex:
     """mask: uint8 CUDA tensor [Mb,Nq,Nk] (row stride may exceed Nk).  As bbm_build_block_mask; a square mask goes
     through the square entry point of the library."""
+    idx = _alloc_classes(mask, Br, Bc, idx, want_bin, want_packed)
+    Mb, N, Nk = mask.shape
+    if Nk == N:
+        _check(lib.bbm_build_block_mask(_ptr(mask), Mb, N, mask.stride(1), Br, Bc, _ptr(idx.blk_class),
+                                        _ptr(idx.bin_blk_mat), _ptr(idx.packed_mask), _stream(stream)))
+    else:
+        _check(lib.bbm_build_block_mask_rect(_ptr(mask), Mb, N, Nk, mask.stride(1), Br, Bc, _ptr(idx.blk_class),
+                                             _ptr(idx.bin_blk_mat), _ptr(idx.packed_mask), _stream(stream)))
+    return idx
+
+
+def _alloc_classes(mask, Br, Bc, idx, want_bin=True, want_packed=True) -> BlockIndex:
     assert mask.is_cuda and mask.dtype == torch.uint8 and mask.dim() == 3 and mask.stride(2) == 1
     Mb, N, Nk = mask.shape
     assert Mb == 1 or mask.stride(0) == N * mask.stride(1)
-    nbr, nbc = _cdiv(N, Br), _cdiv(Nk, Bc)
     if idx is None:
+        nbr, nbc = _cdiv(N, Br), _cdiv(Nk, Bc)
         dev = mask.device
         idx = BlockIndex(Br, Bc, Mb, nbr, nbc, N, Nk=None if Nk == N else Nk)
         idx.blk_class = torch.empty((Mb, nbr, nbc), dtype=torch.uint8, device=dev)
@@ -185,12 +201,6 @@ def bbm_build_block_mask_rect(mask: torch.Tensor, Br: int, Bc: int, idx: Optiona
             idx.bin_blk_mat = torch.empty((Mb, nbr, nbc), dtype=torch.uint8, device=dev)
         if want_packed:
             idx.packed_mask = torch.empty((Mb, _cdiv(Nk, 64), N), dtype=torch.int64, device=dev)
-    if Nk == N:
-        _check(lib.bbm_build_block_mask(_ptr(mask), Mb, N, mask.stride(1), Br, Bc, _ptr(idx.blk_class),
-                                        _ptr(idx.bin_blk_mat), _ptr(idx.packed_mask), _stream(stream)))
-    else:
-        _check(lib.bbm_build_block_mask_rect(_ptr(mask), Mb, N, Nk, mask.stride(1), Br, Bc, _ptr(idx.blk_class),
-                                             _ptr(idx.bin_blk_mat), _ptr(idx.packed_mask), _stream(stream)))
     return idx
 
 
@@ -242,6 +252,13 @@ def bbm_build_index(idx: BlockIndex, stream=None) -> BlockIndex:
 
 def bbm_build_col_index(idx: BlockIndex, stream=None) -> BlockIndex:
     """Per-column block list (what the backward pass walks for dK and dV) from idx.blk_class."""
+    _alloc_columns(idx)
+    _check(lib.bbm_build_col_index(_ptr(idx.blk_class), idx.Mb, idx.nbr, idx.nbc, _ptr(idx.col_ptr), _ptr(idx.row_idx),
+                                   _ptr(idx.col_sched), _stream(stream)))
+    return idx
+
+
+def _alloc_columns(idx: BlockIndex):
     dev = idx.blk_class.device
     if idx.col_ptr is None:
         idx.col_ptr = torch.empty((idx.Mb, idx.nbc + 1), dtype=torch.int32, device=dev)
@@ -249,9 +266,6 @@ def bbm_build_col_index(idx: BlockIndex, stream=None) -> BlockIndex:
         idx.row_idx = torch.zeros(idx.Mb * idx.nbr * idx.nbc, dtype=torch.int32, device=dev)
     if idx.col_sched is None:
         idx.col_sched = torch.empty(bbm_col_sched_bytes(idx.Mb, idx.nbc) // 4, dtype=torch.int32, device=dev)
-    _check(lib.bbm_build_col_index(_ptr(idx.blk_class), idx.Mb, idx.nbr, idx.nbc, _ptr(idx.col_ptr), _ptr(idx.row_idx),
-                                   _ptr(idx.col_sched), _stream(stream)))
-    return idx
 
 
 def bbm_col_sched_bytes(Mb: int, nbc: int) -> int:
@@ -260,17 +274,34 @@ def bbm_col_sched_bytes(Mb: int, nbc: int) -> int:
 
 def build_index(mask: torch.Tensor, Br: int, Bc: int = 64, idx: Optional[BlockIndex] = None, stream=None,
                 fused: bool = True, columns: bool = False) -> BlockIndex:
-    """The whole preprocessing stage: block classes, then run index + block list + schedule (through the one-call
-    entry point, or with fused=False through the two separate ones); columns=True adds the per-column list the
-    backward pass needs."""
-    idx = bbm_build_block_mask_rect(mask, Br, Bc, idx=idx, stream=stream)
-    if fused:
-        bbm_build_index(idx, stream=stream)
-    else:
+    """The whole preprocessing stage: block classes, then run index + block list + schedule (all in one library call, or with
+    fused=False through the separate ones); columns=True adds the per-column list the backward pass needs."""
+    if not fused:
+        idx = bbm_build_block_mask_rect(mask, Br, Bc, idx=idx, stream=stream)
         bbm_build_runs(idx, stream=stream)
         bbm_build_sparse_index(idx, stream=stream)
+        if columns:
+            bbm_build_col_index(idx, stream=stream)
+        return idx
+    idx = _alloc_classes(mask, Br, Bc, idx)
+    Mb, N, Nk = mask.shape
+    if idx.blk_class is None or (idx.Mb, idx.nbr, idx.nbc) != (Mb, _cdiv(N, Br), _cdiv(Nk, Bc)):  # each part takes what it is told
+        bbm_build_block_mask_rect(mask, Br, Bc, idx=idx, stream=stream)
+        bbm_build_index(idx, stream=stream)
+        return bbm_build_col_index(idx, stream=stream) if columns else idx
+    _alloc_runs(idx)
+    _alloc_list(idx)
     if columns:
-        bbm_build_col_index(idx, stream=stream)
+        _alloc_columns(idx)
+    if idx.arrivals is None and not torch.cuda.is_current_stream_capturing():  # (zeros that are there before a recorded call runs)
+        with (torch.cuda.stream(stream) if stream is not None else _null_ctx()):
+            idx.arrivals = torch.zeros(1, dtype=torch.int32, device=mask.device)
+    p = _ptr
+    _check(lib.bbm_build_mask_index(p(mask), Mb, N, Nk, mask.stride(1), Br, Bc, p(idx.blk_class), p(idx.bin_blk_mat), p(idx.packed_mask),
+                                    p(idx.offset), p(idx.total_ones), p(idx.nz_lo), p(idx.nz_hi), p(idx.nz_cnt), p(idx.row_ptr),
+                                    p(idx.col_idx), p(idx.sched), p(idx.col_ptr) if columns else None,
+                                    p(idx.row_idx) if columns else None, p(idx.col_sched) if columns else None, p(idx.arrivals),
+                                    _stream(stream)))
     return idx
 
 

@@ -205,23 +205,30 @@ extern "C" __attribute__((visibility("default"))) size_t bbm_col_sched_bytes(int
   return (size_t)(bbm::kSchedPartBase + (bbm::kSchedPartInts + bbm::kSchedRowInts) * Mb * nbc) * sizeof(int32_t);
 }
 
+namespace bbm {
+int check_col_index_args(const char* fn, const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc, const LineArgs& cols) {
+  if (!blk_class || !cols.ptr || !cols.list) return fail(BBM_EINVAL, "%s: blk_class, col_ptr, row_idx must not be NULL", fn);
+  if (Mb < 1 || nbr < 1 || nbc < 1)
+    return fail(BBM_EINVAL, "%s: Mb=%lld, nbr=%lld, nbc=%lld must be >= 1", fn, (long long)Mb, (long long)nbr, (long long)nbc);
+  if (!aligned(cols.ptr, 4) || !aligned(cols.list, 4)) return fail(BBM_EINVAL, "%s: col_ptr, row_idx must be 4-byte aligned", fn);
+  if (cols.sched && !aligned(cols.sched, 32)) return fail(BBM_EINVAL, "%s: col_sched must be 32-byte aligned", fn);
+  if (cols.sched && Mb * nbc >= (1ll << 24)) return fail(BBM_EINVAL, "%s: Mb*nbc must be below 2^24 for a schedule", fn);
+  if (nbr * nbc >= (1ll << 31) || Mb >= (1ll << 31)) return fail(BBM_EINVAL, "%s: nbr*nbc and Mb must be below 2^31", fn);
+  return BBM_OK;
+}
+}  // namespace bbm
+
 extern "C" __attribute__((visibility("default"))) int bbm_build_col_index(const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc,
                                                                          int32_t* col_ptr, uint32_t* row_idx, int32_t* col_sched,
                                                                          void* stream) {
   using namespace bbm;
   clear_error();
-  if (!blk_class || !col_ptr || !row_idx) return fail(BBM_EINVAL, "bbm_build_col_index: blk_class, col_ptr, row_idx must not be NULL");
-  if (Mb < 1 || nbr < 1 || nbc < 1)
-    return fail(BBM_EINVAL, "bbm_build_col_index: Mb=%lld, nbr=%lld, nbc=%lld must be >= 1", (long long)Mb, (long long)nbr, (long long)nbc);
-  if (!aligned(col_ptr, 4) || !aligned(row_idx, 4)) return fail(BBM_EINVAL, "bbm_build_col_index: col_ptr, row_idx must be 4-byte aligned");
-  if (col_sched && !aligned(col_sched, 32)) return fail(BBM_EINVAL, "bbm_build_col_index: col_sched must be 32-byte aligned");
-  if (col_sched && Mb * nbc >= (1ll << 24)) return fail(BBM_EINVAL, "bbm_build_col_index: Mb*nbc must be below 2^24 for a schedule");
-  if (nbr * nbc >= (1ll << 31) || Mb >= (1ll << 31)) return fail(BBM_EINVAL, "bbm_build_col_index: nbr*nbc and Mb must be below 2^31");
+  if (int rc = check_col_index_args("bbm_build_col_index", blk_class, Mb, nbr, nbc, LineArgs{col_ptr, row_idx, col_sched})) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (line_index_fits(true, Mb, nbr, nbc)) {
     const auto kernel = nbc < 16 ? line_index_kernel<true, kLineShort> : line_index_kernel<true, kLineNormal>;
     kernel<<<(unsigned)ceil_div(Mb * nbc, kLineWaves), kLineWaves * 64, 0, st>>>(
-        blk_class, (int)Mb, (int)nbr, (int)nbc, col_ptr, row_idx, col_sched, nullptr, nullptr, nullptr, nullptr, nullptr);
+        blk_class, (int)Mb, (int)nbr, (int)nbc, LineOut{col_ptr, row_idx, col_sched, nullptr, nullptr, nullptr, nullptr, nullptr});
     return launch_status("bbm_build_col_index(one launch)");
   }
   if (ceil_div(Mb * nbc, kColWaves) >= (1ll << 31)) return fail(BBM_EINVAL, "bbm_build_col_index: Mb*nbc too large");

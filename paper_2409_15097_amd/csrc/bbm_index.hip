@@ -421,7 +421,7 @@ bool launch_one_kernel(const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_
                       : nbc < 16 ? bbm::line_index_kernel<false, bbm::kLineShort> : bbm::line_index_kernel<false, bbm::kLineNormal>;
   const int64_t units = Mb * nbr * (strips ? bbm::ceil_div(nbc, bbm::kLineStrip) : 1);
   kernel<<<(unsigned)bbm::ceil_div(units, bbm::kLineWaves), bbm::kLineWaves * 64, 0, s>>>(
-      blk_class, (int)Mb, (int)nbr, (int)nbc, row_ptr, col_idx, sched, offset, total_ones, nz_lo, nz_hi, nz_cnt);
+      blk_class, (int)Mb, (int)nbr, (int)nbc, bbm::LineOut{row_ptr, col_idx, sched, offset, total_ones, nz_lo, nz_hi, nz_cnt});
   return true;
 }
 
@@ -498,3 +498,18 @@ extern "C" __attribute__((visibility("default"))) int bbm_build_index(const uint
   if (rc) return rc;
   return launch_list(blk_class, Mb, nbr, nbc, row_ptr, col_idx, sched, nz_cnt, scan_launch, s);
 }
+
+namespace bbm {
+int check_index_args(const char* fn, const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc, const LineArgs& rows) {
+  int rc = check_runs_args(fn, blk_class, Mb, nbr, nbc, rows.offset, rows.total_ones, rows.nz_lo, rows.nz_hi, rows.nz_cnt);
+  return rc ? rc : check_list_args(fn, blk_class, Mb, nbr, nbc, rows.ptr, rows.list, rows.sched);
+}
+
+bool launch_rows_and_columns(const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc, const LineArgs& rows, const LineArgs& cols, hipStream_t s) {
+  if (!line_index_fits(false, Mb, nbr, nbc) || !line_index_fits(true, Mb, nbr, nbc)) return false;
+  const int64_t row_wgs = ceil_div(Mb * nbr, kLineWaves), col_wgs = ceil_div(Mb * nbc, kLineWaves);
+  const auto kernel = nbc < 16 ? line_index_both_kernel<kLineShort> : line_index_both_kernel<kLineNormal>;
+  kernel<<<(unsigned)(row_wgs + col_wgs), kLineWaves * 64, 0, s>>>(blk_class, (int)Mb, (int)nbr, (int)nbc, (int)row_wgs, rows, cols);
+  return true;
+}
+}  // namespace bbm

@@ -65,4 +65,17 @@ inline int32_t interleaved_planes(int64_t planes, int64_t streamed_bytes) {
   return (int32_t)(g < 1 ? 1 : g > 8 ? 8 : g);
 }
 
+// What is written for the lines of one direction: ptr, list, sched as row_ptr, col_idx, sched (or col_ptr, row_idx, col_sched),
+// and the run index (block rows only).
+struct LineArgs {
+  int32_t* ptr;
+  uint32_t* list;
+  int32_t* sched;
+  int32_t *offset = nullptr, *total_ones = nullptr, *nz_lo = nullptr, *nz_hi = nullptr, *nz_cnt = nullptr;
+};
+int check_index_args(const char* fn, const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc, const LineArgs& rows);
+int check_col_index_args(const char* fn, const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc, const LineArgs& cols);
+// Both indexes in one launch; false, and nothing launched, for class matrices that take several.
+bool launch_rows_and_columns(const uint8_t* blk_class, int64_t Mb, int64_t nbr, int64_t nbc, const LineArgs& rows, const LineArgs& cols, hipStream_t s);
+
 }  // namespace bbm

@@ -155,22 +155,144 @@ inline bool line_index_fits(bool cols, int64_t Mb, int64_t nbr, int64_t nbc) {
 enum { kLineNormal = 0, kLineShort = 1, kLineLong = 2 };
 constexpr int kLineLongFrom = 1024, kLineStrip = 512;
 constexpr int kLineMaxStrips = (int)(kLineMaxBytesRows / kLineStrip + kLineMaxBytesRows / kLineLongFrom);  // whole strips + a partial one a row
+using LineOut = LineArgs;
+
+// One line, by a wave, from the counts len_s of all lines (strip_s: of all strips); own_block(base): this lane's block of the 64
+// from `base` on, `next` the first of them.
+template <bool COLS, int KIND, typename Block>
+__device__ __forceinline__ void emit_line(Block own_block, uint8_t next, const int* len_s, const int* strip_s, int line, int seg, int S,
+                                          int first_block, int past_block, int Mb, int nbr, int nbc, const LineOut& o) {
+  constexpr bool LONG = KIND == kLineLong;
+  const int lane = threadIdx.x & 63;
+  const int L = COLS ? nbc : nbr, nlines = Mb * L, m = line / L, i = line - m * L;
+  int32_t *const ptr = o.ptr, *const sched = o.sched, *const offset = o.offset;
+  // ---- this wave's line: its place in the plane's list, and the split threshold (a mean over all lines)
+  const int* const cp = len_s + m * L;
+  const int n = cp[i];
+  int above = 0, total = 0, nonempty = 0;
+  for (int b = lane; b < nlines; b += 64) {
+    const int x = len_s[b];
+    total += x;
+    nonempty += x > 0 ? 1 : 0;
+    above += b >= m * L && b < line ? x : 0;
+  }
+  const int start = wave_sum(above);
+  total = wave_sum(total);
+  nonempty = wave_sum(nonempty);
+  const int mean = nonempty > 0 ? (total + nonempty - 1) / nonempty : 0;
+  const int T = max(COLS ? kColSchedMinSplit : kSchedMinSplit, 2 * mean);
+  if (lane == 0 && seg == 0) {
+    ptr[(int64_t)m * (L + 1) + i] = start;
+    if (i == L - 1) ptr[(int64_t)m * (L + 1) + L] = start + n;
+  }
+
+  // parts and cut lines: before this line (lines in (plane, line) order), and in all
+  const int np = n > T ? (n + T - 1) / T : 0;
+  const int chunk = np > 0 ? (n + np - 1) / np : 1;
+  int32_t* parts = nullptr;
+  if (sched && (np > 0 || line == 0)) {
+    int q = 0, rho = 0, all_parts = 0, all_cut = 0;
+    for (int b = lane; b < nlines; b += 64) {
+      const int x = len_s[b];
+      const int np_b = x > T ? (x + T - 1) / T : 0;
+      all_parts += np_b;
+      all_cut += np_b > 0 ? 1 : 0;
+      q += b < line ? np_b : 0;
+      rho += b < line && np_b > 0 ? 1 : 0;
+    }
+    q = wave_sum(q);
+    rho = wave_sum(rho);
+    if (line == 0 && seg == 0) {
+      all_parts = wave_sum(all_parts);
+      all_cut = wave_sum(all_cut);
+      if (lane < kSchedPartBase)
+        sched[lane] = lane == kSchedNParts ? all_parts : lane == kSchedSplitT ? T : lane == kSchedNCutRows ? all_cut : 0;
+    }
+    parts = sched + kSchedPartBase + (int64_t)kSchedPartInts * q;
+    for (int k = lane; k < (seg == 0 ? np : 0); k += 64) {
+      int32_t* rec = parts + kSchedPartInts * k;
+      rec[0] = line;
+      rec[1] = start + k * chunk;
+      rec[2] = min(chunk, n - k * chunk);
+      rec[3] = k;
+      rec[4] = np;
+      rec[5] = q;
+      rec[6] = rho;
+    }
+  }
+
+  // the list; the lane that writes the entry a part starts with also leaves it in the part's record
+  uint32_t* const out = o.list + (int64_t)m * nbr * nbc + start;
+  int written = 0, first = -1;
+  if (LONG)
+    for (int k = 0; k < seg; ++k) written += strip_s[line * S + k];
+  WaveRunScan rs;
+#pragma unroll 1  // short code: at this length of a launch, fetching instructions is a good part of it
+  for (int base = first_block; base < past_block; base += 64) {
+    const uint8_t c = next;
+    next = own_block(base + 64);
+    const uint64_t nz = __ballot(c != BBM_BLOCK_EMPTY);
+    const uint64_t full = __ballot(c == BBM_BLOCK_FULL);
+    if (!COLS && offset) rs.feed(full, nz, base, lane);
+    if (written == 0 && nz != 0) {  // the line's first entry (this happens once: written > 0 from here on)
+      const int bit = ctz64(nz);
+      first = (int)((uint32_t)(base + bit) | (((full >> bit) & 1ull) ? 0x80000000u : 0u));
+    }
+    if (c != BBM_BLOCK_EMPTY) {
+      const int pos = written + __popcll(nz & ((1ull << lane) - 1ull));
+      const uint32_t entry = (uint32_t)(base + lane) | (c == BBM_BLOCK_FULL ? 0x80000000u : 0u);
+      out[pos] = entry;
+      if (np > 0 && sched && pos % chunk == 0 && pos / chunk < np) parts[kSchedPartInts * (pos / chunk) + 7] = (int32_t)entry;
+    }
+    written += __popcll(nz);
+  }
+  if (!COLS && offset) {
+    int run_len, run_start;
+    rs.finish(run_len, run_start);
+    if (lane == 0) {
+      offset[line] = run_start;
+      o.total_ones[line] = run_len;
+      o.nz_lo[line] = rs.lo;
+      o.nz_hi[line] = rs.hi;
+      o.nz_cnt[line] = rs.cnt;
+    }
+  }
+  if (!sched || (LONG && first == -1 && (n > 0 || seg > 0))) return;  // the record is left to the wave that has the line's first entry
+
+  // launch-order record: groups of gsz lines by their longest list, longest first (ties: the higher group first); inside
+  // a group the longest line first (ties: the higher line first)
+  const int gsz = COLS ? 1 : launch_group_rows(T);
+  const int ng = (L + gsz - 1) / gsz, g = i / gsz;
+  auto group_max = [&](int gg) {
+    int t = 0;
+    for (int j = gg * gsz; j < min(L, (gg + 1) * gsz); ++j) t = max(t, cp[j]);
+    return t;
+  };
+  const int longest = group_max(g);
+  int before = 0;
+  for (int gg = lane; gg < ng; gg += 64) {
+    const int t = group_max(gg);
+    before += (t > longest || (t == longest && gg > g)) ? 1 : 0;
+  }
+  int rank = wave_sum(before) * gsz;
+  const int last = ng - 1, last_lines = L - last * gsz;  // the last group may be short
+  if (last != g && group_max(last) >= longest) rank -= gsz - last_lines;
+  for (int j = g * gsz; j < min(L, (g + 1) * gsz); ++j) rank += (cp[j] > n || (cp[j] == n && j > i)) ? 1 : 0;
+  if (lane == 0)
+    reinterpret_cast<int4*>(sched + kSchedPartBase + (int64_t)kSchedPartInts * nlines)[(int64_t)m * L + rank] = make_int4(i, start, n, first);
+}
+
 template <bool COLS, int KIND>
-__global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8_t* __restrict__ cls, int Mb, int nbr, int nbc,
-                                                                     int32_t* __restrict__ ptr, uint32_t* __restrict__ list,
-                                                                     int32_t* __restrict__ sched, int32_t* __restrict__ offset,
-                                                                     int32_t* __restrict__ total_ones, int32_t* __restrict__ nz_lo,
-                                                                     int32_t* __restrict__ nz_hi, int32_t* __restrict__ nz_cnt) {
+__device__ __forceinline__ void line_index(const uint8_t* __restrict__ cls, int wg, int* len_s, int* strip_s, int Mb, int nbr, int nbc,
+                                           const LineOut& out) {
   constexpr bool SHORT = KIND == kLineShort, LONG = KIND == kLineLong;
   static_assert(!(COLS && LONG), "strips are of block rows");
-  __shared__ int len_s[LONG ? kLineMaxBytesRows / kLineLongFrom : kLineMaxLines];
-  __shared__ int strip_s[LONG ? kLineMaxStrips : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int L = COLS ? nbc : nbr, depth = COLS ? nbr : nbc;  // lines per plane, blocks per line
   const int nlines = Mb * L;
   const int S = LONG ? (depth + kLineStrip - 1) / kLineStrip : 1;  // strips of a line
-  const int unit = (int)blockIdx.x * kLineWaves + wave;      // this wave's strip, or line (waves past the last only count)
+  const int unit = wg * kLineWaves + wave;      // this wave's strip, or line (waves past the last only count)
   const int line = LONG ? unit / S : unit, seg = LONG ? unit - line * S : 0;
   const int own = min(line, nlines - 1);
   const int m = own / L, i = own - m * L;
@@ -325,120 +447,28 @@ __global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8
   __syncthreads();
   if (line >= nlines) return;
 
-  // ---- this wave's line: its place in the plane's list, and the split threshold (a mean over all lines)
-  const int* const cp = len_s + m * L;
-  const int n = cp[i];
-  int above = 0, total = 0, nonempty = 0;
-  for (int b = lane; b < nlines; b += 64) {
-    const int x = len_s[b];
-    total += x;
-    nonempty += x > 0 ? 1 : 0;
-    above += b >= m * L && b < line ? x : 0;
-  }
-  const int start = wave_sum(above);
-  total = wave_sum(total);
-  nonempty = wave_sum(nonempty);
-  const int mean = nonempty > 0 ? (total + nonempty - 1) / nonempty : 0;
-  const int T = max(COLS ? kColSchedMinSplit : kSchedMinSplit, 2 * mean);
-  if (lane == 0 && seg == 0) {
-    ptr[(int64_t)m * (L + 1) + i] = start;
-    if (i == L - 1) ptr[(int64_t)m * (L + 1) + L] = start + n;
-  }
+  emit_line<COLS, KIND>(own_block, next, len_s, strip_s, line, seg, S, first_block, past_block, Mb, nbr, nbc, out);
+}
 
-  // parts and cut lines: before this line (lines in (plane, line) order), and in all
-  const int np = n > T ? (n + T - 1) / T : 0;
-  const int chunk = np > 0 ? (n + np - 1) / np : 1;
-  int32_t* parts = nullptr;
-  if (sched && (np > 0 || line == 0)) {
-    int q = 0, rho = 0, all_parts = 0, all_cut = 0;
-    for (int b = lane; b < nlines; b += 64) {
-      const int x = len_s[b];
-      const int np_b = x > T ? (x + T - 1) / T : 0;
-      all_parts += np_b;
-      all_cut += np_b > 0 ? 1 : 0;
-      q += b < line ? np_b : 0;
-      rho += b < line && np_b > 0 ? 1 : 0;
-    }
-    q = wave_sum(q);
-    rho = wave_sum(rho);
-    if (line == 0 && seg == 0) {
-      all_parts = wave_sum(all_parts);
-      all_cut = wave_sum(all_cut);
-      if (lane < kSchedPartBase)
-        sched[lane] = lane == kSchedNParts ? all_parts : lane == kSchedSplitT ? T : lane == kSchedNCutRows ? all_cut : 0;
-    }
-    parts = sched + kSchedPartBase + (int64_t)kSchedPartInts * q;
-    for (int k = lane; k < (seg == 0 ? np : 0); k += 64) {
-      int32_t* rec = parts + kSchedPartInts * k;
-      rec[0] = line;
-      rec[1] = start + k * chunk;
-      rec[2] = min(chunk, n - k * chunk);
-      rec[3] = k;
-      rec[4] = np;
-      rec[5] = q;
-      rec[6] = rho;
-    }
-  }
+// The index of block rows (COLS = false) or block columns in a launch of its own.
+template <bool COLS, int KIND>
+__global__ __launch_bounds__(kLineWaves * 64) void line_index_kernel(const uint8_t* __restrict__ cls, int Mb, int nbr, int nbc, const LineOut out) {
+  __shared__ int len_s[KIND == kLineLong ? kLineMaxBytesRows / kLineLongFrom : kLineMaxLines];
+  __shared__ int strip_s[KIND == kLineLong ? kLineMaxStrips : 1];
+  line_index<COLS, KIND>(cls, (int)blockIdx.x, len_s, strip_s, Mb, nbr, nbc, out);
+}
 
-  // the list; the lane that writes the entry a part starts with also leaves it in the part's record
-  uint32_t* const out = list + (int64_t)m * nbr * nbc + start;
-  int written = 0, first = -1;
-  if (LONG)
-    for (int k = 0; k < seg; ++k) written += strip_s[line * S + k];
-  WaveRunScan rs;
-#pragma unroll 1  // short code: at this length of a launch, fetching instructions is a good part of it
-  for (int base = first_block; base < past_block; base += 64) {
-    const uint8_t c = next;
-    next = own_block(base + 64);
-    const uint64_t nz = __ballot(c != BBM_BLOCK_EMPTY);
-    const uint64_t full = __ballot(c == BBM_BLOCK_FULL);
-    if (!COLS && offset) rs.feed(full, nz, base, lane);
-    if (written == 0 && nz != 0) {  // the line's first entry (this happens once: written > 0 from here on)
-      const int bit = ctz64(nz);
-      first = (int)((uint32_t)(base + bit) | (((full >> bit) & 1ull) ? 0x80000000u : 0u));
-    }
-    if (c != BBM_BLOCK_EMPTY) {
-      const int pos = written + __popcll(nz & ((1ull << lane) - 1ull));
-      const uint32_t entry = (uint32_t)(base + lane) | (c == BBM_BLOCK_FULL ? 0x80000000u : 0u);
-      out[pos] = entry;
-      if (np > 0 && sched && pos % chunk == 0 && pos / chunk < np) parts[kSchedPartInts * (pos / chunk) + 7] = (int32_t)entry;
-    }
-    written += __popcll(nz);
-  }
-  if (!COLS && offset) {
-    int run_len, run_start;
-    rs.finish(run_len, run_start);
-    if (lane == 0) {
-      offset[line] = run_start;
-      total_ones[line] = run_len;
-      nz_lo[line] = rs.lo;
-      nz_hi[line] = rs.hi;
-      nz_cnt[line] = rs.cnt;
-    }
-  }
-  if (!sched || (LONG && first == -1 && (n > 0 || seg > 0))) return;  // the record is left to the wave that has the line's first entry
-
-  // launch-order record: groups of gsz lines by their longest list, longest first (ties: the higher group first); inside
-  // a group the longest line first (ties: the higher line first)
-  const int gsz = COLS ? 1 : launch_group_rows(T);
-  const int ng = (L + gsz - 1) / gsz, g = i / gsz;
-  auto group_max = [&](int gg) {
-    int t = 0;
-    for (int j = gg * gsz; j < min(L, (gg + 1) * gsz); ++j) t = max(t, cp[j]);
-    return t;
-  };
-  const int longest = group_max(g);
-  int before = 0;
-  for (int gg = lane; gg < ng; gg += 64) {
-    const int t = group_max(gg);
-    before += (t > longest || (t == longest && gg > g)) ? 1 : 0;
-  }
-  int rank = wave_sum(before) * gsz;
-  const int last = ng - 1, last_lines = L - last * gsz;  // the last group may be short
-  if (last != g && group_max(last) >= longest) rank -= gsz - last_lines;
-  for (int j = g * gsz; j < min(L, (g + 1) * gsz); ++j) rank += (cp[j] > n || (cp[j] == n && j > i)) ? 1 : 0;
-  if (lane == 0)
-    reinterpret_cast<int4*>(sched + kSchedPartBase + (int64_t)kSchedPartInts * nlines)[(int64_t)m * L + rank] = make_int4(i, start, n, first);
+// Both in one launch: the first row_wgs work-groups take the rows.  Block reduction + both, us from a graph, in three launches / two:
+// 1 plane of 2 x 4 blocks 9.3 / 6.8, 10 x 20 10.5 / 7.3, 32 x 64 12.2 / 8.7, 4 planes of it 23.2 / 18.5, 64 x 128 23.2 / 18.3.  The
+// training step of packed sequences of 3001 124.8 -> 118.9, of 4 x 4096 195.6 -> 192.3.
+template <int KIND>
+__global__ __launch_bounds__(kLineWaves * 64) void line_index_both_kernel(const uint8_t* __restrict__ cls, int Mb, int nbr, int nbc, int row_wgs,
+                                                                          const LineOut rows, const LineOut cols) {
+  __shared__ int len_s[kLineMaxLines];
+  if ((int)blockIdx.x < row_wgs)
+    line_index<false, KIND>(cls, (int)blockIdx.x, len_s, len_s, Mb, nbr, nbc, rows);
+  else
+    line_index<true, KIND>(cls, (int)blockIdx.x - row_wgs, len_s, len_s, Mb, nbr, nbc, cols);
 }
 
 }  // namespace

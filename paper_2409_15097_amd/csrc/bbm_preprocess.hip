@@ -7,6 +7,8 @@
 // turns its 16 bytes into 16 bits and keeps a running OR / AND over the rows it sees.  The bits go to LDS as uint16
 // quarters of the 64-bit words and leave word-column major, so the global writes of the packed mask are contiguous too.
 #include "bbm_internal.h"
+#include "bbm_line_index.h"
+#include "bbm_mask_index.h"
 
 namespace {
 
@@ -35,12 +37,27 @@ __device__ __forceinline__ uint32_t bits16(u32x4_any x) {
   return nz_nibble(x.x) | (nz_nibble(x.y) << 4) | (nz_nibble(x.z) << 8) | (nz_nibble(x.w) << 12);
 }
 
-template <int LPR, int U, bool STREAM>
+// INDEX: the work-group that finishes last also writes the index of the block rows, a wave each, from the class bytes in LDS.  Nobody
+// waits: the others have ended.  Classes are written through and read around the XCDs' caches and counted without a fence (a
+// device-wide release makes an XCD's cache write back all it holds).  What it saves is a launch, most of it on the host: both
+// stages of 256 x 256 take 16.3 -> 13.5 us of a step of 256 tokens that is submitted call by call, 61.0 -> 60.0 of a decoding step of
+// 256 x 1280, 6.6 -> 6.2 and 6.9 -> 6.4 replayed from a graph.  The last work-group works alone, so one pass over its waves is the
+// limit: 10 block rows of 1280 146.0 -> 147.1 of a step, 7.1 -> 8.5 from a graph; with the block columns 6.8 -> 7.8, 7.1 -> 9.9.
+constexpr int kFusedBytes = 4096, kFusedRows = kWaves, kAgentScope = 16;  // sc1
+struct FusedIndex {
+  bbm::LineArgs rows;
+  int32_t* arrivals;  // work-groups that have ended; zero between calls
+};
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t class_rsrc(const uint8_t* blk_class, int64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(blk_class), 0, (int)bytes, 0x00027000);
+}
+
+template <int LPR, int U, bool STREAM, bool INDEX = false>
 __global__ __launch_bounds__(kThreads) void block_reduce_kernel(const uint8_t* __restrict__ mask, int64_t Nr, int64_t N,
                                                                 int64_t row_stride, int Br, int Bc, int64_t nbr,
                                                                 int64_t nbc, uint8_t* __restrict__ blk_class,
                                                                 uint8_t* __restrict__ bin_blk_mat,
-                                                                uint64_t* __restrict__ packed) {
+                                                                uint64_t* __restrict__ packed, const FusedIndex fused) {
   constexpr int kCols = 16 * LPR;              // mask columns of a work-group
   constexpr int kWords = LPR / 4;              // 64-bit words of a row
   constexpr int kRowsPerLoad = kWaves * 64 / LPR;  // rows the work-group's wavefronts read with one load each
@@ -120,7 +137,10 @@ __global__ __launch_bounds__(kThreads) void block_reduce_kernel(const uint8_t* _
     if (lane < LPR && (lane % g) == 0 && j < nbc) {
       const uint8_t cls = any_v == 0 ? BBM_BLOCK_EMPTY : (all_v == 0xffffu ? BBM_BLOCK_FULL : BBM_BLOCK_PARTIAL);
       const int64_t o = (m * nbr + i) * nbc + j;
-      blk_class[o] = cls;
+      if constexpr (INDEX)
+        __builtin_amdgcn_raw_buffer_store_b8(cls, class_rsrc(blk_class, (int64_t)gridDim.z * nbr * nbc), (int)o, 0, kAgentScope);
+      else
+        blk_class[o] = cls;
       if (bin_blk_mat) bin_blk_mat[o] = cls != BBM_BLOCK_EMPTY;
     }
   }
@@ -144,6 +164,37 @@ __global__ __launch_bounds__(kThreads) void block_reduce_kernel(const uint8_t* _
       if (wl < kWords && w0 + wl < W && rl < rows && word_any[wl] != 0) packed[(m * W + w0 + wl) * Nr + r0 + rl] = stage64[wl * BrP + rl];
     }
   }
+  if constexpr (INDEX) {
+    __shared__ int arrived_s;
+    __shared__ int len_s[kFusedRows];
+    static_assert(sizeof(stage) >= kFusedBytes, "the class bytes take the place of the packed words");
+    if (wave == 0) {  // which wrote the classes
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (lane == 0) arrived_s = __hip_atomic_fetch_add(fused.arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (arrived_s != (int)(gridDim.x * gridDim.y * gridDim.z) - 1) return;
+    const int Mb = gridDim.z, bytes = Mb * (int)(nbr * nbc);
+    uint8_t* const cls_s = reinterpret_cast<uint8_t*>(stage);
+    const __amdgpu_buffer_rsrc_t src = class_rsrc(blk_class, bytes);
+    uint8_t c[kFusedBytes / kThreads];
+#pragma unroll
+    for (int t = 0; t < kFusedBytes / kThreads; ++t) c[t] = __builtin_amdgcn_raw_buffer_load_b8(src, t * kThreads + threadIdx.x, 0, kAgentScope);
+    if (threadIdx.x == 0) __hip_atomic_store(fused.arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // zero for the next call
+#pragma unroll
+    for (int t = 0; t < kFusedBytes / kThreads; ++t) cls_s[t * kThreads + threadIdx.x] = c[t];
+    __syncthreads();
+    const int line = wave;  // (plane, block row)
+    auto own_block = [&](int base) { return base + lane < (int)nbc ? cls_s[line * (int)nbc + base + lane] : (uint8_t)0; };
+    if (line < Mb * (int)nbr) {
+      int n = 0;
+      for (int base = 0; base < (int)nbc; base += 64) n += __popcll(__ballot(own_block(base) != 0));
+      if (lane == 0) len_s[line] = n;
+    }
+    __syncthreads();
+    if (line < Mb * (int)nbr)
+      bbm::emit_line<false, bbm::kLineNormal>(own_block, own_block(0), len_s, nullptr, line, 0, 1, 0, (int)nbc, Mb, (int)nbr, (int)nbc, fused.rows);
+  }
 }
 
 }  // namespace
@@ -155,7 +206,7 @@ struct IntC {
 };
 
 int build_block_mask_impl(const char* fn, const uint8_t* mask, int64_t Mb, int64_t Nq, int64_t Nk, int64_t row_stride_bytes, int Br, int Bc,
-                          uint8_t* blk_class, uint8_t* bin_blk_mat, uint64_t* packed_mask, void* stream) {
+                          uint8_t* blk_class, uint8_t* bin_blk_mat, uint64_t* packed_mask, void* stream, FusedIndex* fused = nullptr) {
   using namespace bbm;
   clear_error();
   if (!mask || !blk_class) return fail(BBM_EINVAL, "%s: mask and blk_class must not be NULL", fn);
@@ -173,11 +224,21 @@ int build_block_mask_impl(const char* fn, const uint8_t* mask, int64_t Mb, int64
   // and the attention kernel behind it finds more of Q, K, V still cached (whole step -2.5 % at 1 GiB, -3.5 % at 256 MiB);
   // a 64 MiB mask that is rebuilt from the cache it still sits in loses 20 % that way
   const bool streamed = bytes >= kStreamFromBytes;
+  const bool with_index = fused && fused->arrivals && !streamed && Mb * nbr * nbc <= kFusedBytes && Mb * nbr <= kFusedRows;
+  bool index_written = false;
   auto go = [&](auto lpr, auto unroll) {
     constexpr int LPR = decltype(lpr)::value, U = decltype(unroll)::value;
+    if constexpr (LPR == 16) {
+      if (with_index) {
+        block_reduce_kernel<LPR, U, false, true><<<dim3((unsigned)ceil_div(Nk, 16 * LPR), (unsigned)nbr, (unsigned)Mb), kThreads, 0, s>>>(
+            mask, Nq, Nk, row_stride_bytes, Br, Bc, nbr, nbc, blk_class, bin_blk_mat, packed_mask, *fused);
+        index_written = true;
+        return;
+      }
+    }
     const auto kernel = streamed ? block_reduce_kernel<LPR, U, true> : block_reduce_kernel<LPR, U, false>;
     kernel<<<dim3((unsigned)ceil_div(Nk, 16 * LPR), (unsigned)nbr, (unsigned)Mb), kThreads, 0, s>>>(
-        mask, Nq, Nk, row_stride_bytes, Br, Bc, nbr, nbc, blk_class, bin_blk_mat, packed_mask);
+        mask, Nq, Nk, row_stride_bytes, Br, Bc, nbr, nbc, blk_class, bin_blk_mat, packed_mask, FusedIndex{});
   };
   // What a work-group reads is Br rows x 16*LPR bytes.  Blocks of more than 64 rows: 256-byte segments (LPR = 16) give the most
   // work-groups and the shortest chain of loads; rows that do not start on 128-byte lines cost one line more per segment, so
@@ -193,6 +254,7 @@ int build_block_mask_impl(const char* fn, const uint8_t* mask, int64_t Mb, int64
   else if (Br <= 32) go(IntC<64>{}, IntC<4>{});
   else if (Br <= 64) bytes > kWideFromBytes ? go(IntC<32>{}, IntC<4>{}) : go(IntC<16>{}, IntC<2>{});
   else bytes > kWideFromBytes && !line_rows ? go(IntC<32>{}, IntC<8>{}) : go(IntC<16>{}, IntC<4>{});
+  if (fused && !index_written) fused->arrivals = nullptr;  // the index is left to launches of its own
   return launch_status(fn);
 }
 }  // namespace
@@ -207,4 +269,30 @@ extern "C" __attribute__((visibility("default"))) int bbm_build_block_mask_rect(
                                          int64_t row_stride_bytes, int Br, int Bc, uint8_t* blk_class,
                                          uint8_t* bin_blk_mat, uint64_t* packed_mask, void* stream) {
   return build_block_mask_impl("bbm_build_block_mask_rect", mask, Mb, Nq, Nk, row_stride_bytes, Br, Bc, blk_class, bin_blk_mat, packed_mask, stream);
+}
+
+extern "C" __attribute__((visibility("default"))) int bbm_build_mask_index(
+    const uint8_t* mask, int64_t Mb, int64_t Nq, int64_t Nk, int64_t row_stride_bytes, int Br, int Bc, uint8_t* blk_class, uint8_t* bin_blk_mat,
+    uint64_t* packed_mask, int32_t* offset, int32_t* total_ones, int32_t* nz_lo, int32_t* nz_hi, int32_t* nz_cnt, int32_t* row_ptr,
+    uint32_t* col_idx, int32_t* sched, int32_t* col_ptr, uint32_t* row_idx, int32_t* col_sched, int32_t* arrivals, void* stream) {
+  using namespace bbm;
+  clear_error();
+  const char* const fn = "bbm_build_mask_index";
+  const bool columns = col_ptr || row_idx || col_sched;
+  const LineArgs cols{col_ptr, row_idx, col_sched};
+  FusedIndex fused{{row_ptr, col_idx, sched, offset, total_ones, nz_lo, nz_hi, nz_cnt}, columns ? nullptr : arrivals};
+  if (Nq >= 1 && Nk >= 1 && Br >= 1 && Bc >= 1) {  // (otherwise the block reduction's own checks fail)
+    const int64_t nbr = ceil_div(Nq, Br), nbc = ceil_div(Nk, Bc);
+    int rc = check_index_args(fn, blk_class, Mb, nbr, nbc, fused.rows);
+    if (rc == BBM_OK && columns) rc = check_col_index_args(fn, blk_class, Mb, nbr, nbc, cols);
+    if (rc != BBM_OK) return rc;
+  }
+  if (arrivals && !aligned(arrivals, 4)) return fail(BBM_EINVAL, "%s: arrivals must be 4-byte aligned", fn);
+  int rc = build_block_mask_impl(fn, mask, Mb, Nq, Nk, row_stride_bytes, Br, Bc, blk_class, bin_blk_mat, packed_mask, stream, &fused);
+  if (rc != BBM_OK || fused.arrivals) return rc;
+  const int64_t nbr = ceil_div(Nq, Br), nbc = ceil_div(Nk, Bc);
+  if (columns && launch_rows_and_columns(blk_class, Mb, nbr, nbc, fused.rows, cols, static_cast<hipStream_t>(stream))) return launch_status(fn);
+  rc = bbm_build_index(blk_class, Mb, nbr, nbc, offset, total_ones, nz_lo, nz_hi, nz_cnt, row_ptr, col_idx, sched, stream);
+  if (rc != BBM_OK || !columns) return rc;
+  return bbm_build_col_index(blk_class, Mb, nbr, nbc, col_ptr, row_idx, col_sched, stream);
 }
