@@ -230,12 +230,9 @@ __device__ __forceinline__ bool is_nan(float x) {
   return (bits & 0x7fffffffu) > 0x7f800000u;
 }
 
-// 16 bytes at p (readable either way), or zeros: masked, since a choice between the two makes the compiler branch per load.
-__device__ __forceinline__ bf16x8 load_or_zero(const __bf16* __restrict__ p, bool ok) {
-  uint4 x = *reinterpret_cast<const uint4*>(p);
-  const uint32_t keep = ok ? 0xffffffffu : 0u;
-  x.x &= keep, x.y &= keep, x.z &= keep, x.w &= keep;
-  return __builtin_bit_cast(bf16x8, x);
+// The `bytes` bytes at the wave-uniform p: loads past them give zeros, stores are dropped.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)scalar(bytes), 0x00027000);
 }
 
 // XCD-aware logical work-group id: work-groups are handed to the 8 XCDs round-robin; give each XCD a contiguous range
@@ -300,14 +297,14 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   f32x16 dp_init, dq[DB];
   float nl_lane = 0.0f, nd_lane = 0.0f;
 
+  // (found anew for every item, see store_slab: kept across the merge of a cut row, some of it lay in scratch memory)
   TileAddr<D> A;
-  A.init(lane);
+  uint32_t copy_base;
 
   auto tile_of = [](uint32_t e) { return (int)(e & 0x7fffffffu); };
   // e0: this step's list entry, e1: the next one's (as it came from LDS: made a scalar when the step starts)
   uint32_t e0, e1_v;
   uint64_t mw_nxt = 0;
-  const uint32_t copy_base = tile_copy_base<D, NW>(wave, lane);
   constexpr int LPW = L::NBLK / NW;  // copy instructions of a wave per tile
   // Tile e, n = 0 .. 2*LPW-1.  Keys past N come as zeros; their tile is never full, so the mask gives them probability 0.
   auto copy_piece = [&](uint32_t e, int rows, __bf16* kd, __bf16* vd, int n) {
@@ -429,10 +426,13 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   };
 
   // this lane's query: Q * scale * log2(e) and dO as B operands, D = <dO, O>, the negated statistics
-  auto begin_item = [&](bool write_stats) __attribute__((always_inline)) {
+  // between() is run when all of it has been asked for.
+  auto begin_item = [&](bool write_stats, auto between) __attribute__((always_inline)) {
     head_off = (int64_t)bh * N * D;
     int ln = lane;
     asm volatile("" : "+v"(ln));  // keeps the addresses out of the loop over items, see store_slab
+    A.init(ln);
+    copy_base = tile_copy_base<D, NW>(wave, ln);
     const int wrow = i * BR + wave * 32, qrow = wrow + (ln & 31);
     const bool q_ok = qrow < N;
     mrow = global(P->packed) + (int64_t)m * P->W * N + (q_ok ? qrow : 0);
@@ -441,15 +441,20 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     // buffers (of parity 1 while at most four waves want one), dO follows through registers, where <dO, O> is formed; chunk c of row r sits at position c ^ (r % RC).
     __bf16* const stage = (wave / 2 == 0 ? k_s1 : wave / 2 == 1 ? v_s1 : wave / 2 == 2 ? k_s0 : v_s0) + (wave % 2) * 32 * D;
     const int g_row = ln / L::RC, g_chunk = ln % L::RC, rows = max(0, min(32, N - wrow));
+    // (Rows past N come as zeros, by the bounds of the buffers.)
     bf16x8 gr[32 / L::RPB], orow[32 / L::RPB];
+    const int64_t slab = head_off + (int64_t)wrow * D;
+    const __amdgpu_buffer_rsrc_t do_r = buffer_of(P->d_o + slab, rows * D * 2), o_r = buffer_of(P->o + slab, rows * D * 2);
+    const int64_t row_at = (int64_t)bh * N + wrow;
+    const uint32_t lse_bits = __builtin_amdgcn_raw_buffer_load_b32(buffer_of(P->lse + row_at, rows * 4), (ln & 31) * 4, 0, 0);
 #pragma unroll
     for (int n = 0; n < 32 / L::RPB; ++n) {
-      const int r = n * L::RPB + g_row;
-      copy_async<16>(P->q + head_off + (int64_t)wrow * D, rows * D * 2, (uint32_t)(r * D + (g_chunk ^ (r % L::RC)) * 8) * 2u, stage + n * 512);
-      const int64_t at = head_off + (int64_t)(r < rows ? wrow + r : 0) * D + g_chunk * 8;
-      gr[n] = load_or_zero(global(P->d_o) + at, r < rows);
-      orow[n] = load_or_zero(global(P->o) + at, r < rows);
+      const int r = n * L::RPB + g_row, at = (r * D + g_chunk * 8) * 2;
+      copy_async<16>(P->q + slab, rows * D * 2, (uint32_t)(r * D + (g_chunk ^ (r % L::RC)) * 8) * 2u, stage + n * 512);
+      gr[n] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(do_r, at, 0, 0));
+      orow[n] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(o_r, at, 0, 0));
     }
+    between();
 #pragma unroll
     for (int n = 0; n < 32 / L::RPB; ++n) {
       float x = 0.0f;
@@ -472,11 +477,11 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 #pragma unroll
     for (int t = 0; t < KS; ++t) dof[t] = frag(t);
     const float delta = delta_s[wave][ln & 31];
-    const float lse_i = q_ok ? global(P->lse)[(int64_t)bh * N + qrow] : -INFINITY;
+    const float lse_i = q_ok ? __uint_as_float(lse_bits) : -INFINITY;
     const float nl = (lse_i == -INFINITY) ? -INFINITY : -lse_i * (kLog2e / rr);
-    if (write_stats && q_ok && (ln >> 5) == 0) {
-      global(global(P->nl2))[(int64_t)bh * N + qrow] = nl;
-      global(P->ndelta)[(int64_t)bh * N + qrow] = -delta;
+    if (write_stats && (ln >> 5) == 0) {
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(nl), buffer_of(P->nl2 + row_at, rows * 4), (ln & 31) * 4, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(-delta), buffer_of(P->ndelta + row_at, rows * 4), (ln & 31) * 4, 0, 0);
     }
     nl_lane = nl;
     nd_lane = -delta;
@@ -491,22 +496,34 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
   auto run_list = [&](const uint32_t* __restrict__ list, int n_list, uint32_t first, bool write_stats) {
     Kg = P->k + (int64_t)bh * N * D;
     Vg = P->v + (int64_t)bh * N * D;
-    auto start_window = [&](int w0, uint32_t e) __attribute__((always_inline)) {  // the first tile's copies and the list
+    static_assert(NT >= kWin, "an entry of a window a thread");
+    auto ask_list = [&](int w0) __attribute__((always_inline)) { return list[w0 + max(0, min(tid, n_list - w0 - 1))]; };
+    auto put_list = [&](int w0, uint32_t entry) __attribute__((always_inline)) {
+      const int count = min(kWin, n_list - w0);
+      if (tid < count) tiles_s[tid] = entry;
+      if (tid < 3) tiles_s[count + tid] = kNoTile;
+    };
+    auto start_tile = [&](uint32_t e) __attribute__((always_inline)) {
       e0 = e;
       copy_all(e0, k_s0, v_s0);
-      const int count = min(kWin, n_list - w0);
-      for (int t = tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
-      if (tid < 3) tiles_s[count + tid] = kNoTile;
     };
     constexpr bool EARLY = NW <= 4;  // the waves' slabs of Q leave the buffers of parity 0 to the first tile
     auto run = [&](auto late) __attribute__((always_inline)) {
-      if (EARLY && n_list > 0) start_window(0, first);
-      begin_item(write_stats);
+      // The list, the rows of Q, dO and O, their log-sum-exp and the first tile are asked for in one go, by buffer.  With the list's way to
+      // LDS behind the tile, the rows behind that and the log-sum-exp behind those it was three round trips to memory in series, and
+      // addresses in vector registers pushed others into scratch memory.  The whole backward pass, us: packed sequences of 3001, D = 128,
+      // 67.2 -> 66.0, 4096, D = 128, 64 queries a block row 270.8 -> 264.8, 256 a block row 267.7 -> 264.0, a 4096-token window over 8
+      // heads 22.9 -> 22.5; 4096, D = 64, where three work-groups a CU hide it, 113.9 -> 113.6.
+      const uint32_t ahead = ask_list(0);
+      begin_item(write_stats, [&]() __attribute__((always_inline)) {
+        if (EARLY && n_list > 0) start_tile(first);
+      });
       if (!EARLY || n_list == 0) __syncthreads();  // .. or to the epilogue, once every wave has read its slab
-      if (!EARLY && n_list > 0) start_window(0, first);
+      if (!EARLY && n_list > 0) start_tile(first);
       for (int w0 = 0; w0 < n_list; w0 += kWin) {
         const int count = min(kWin, n_list - w0);
-        if (w0 > 0) start_window(w0, scalar(list[w0]));
+        if (w0 > 0) start_tile(scalar(list[w0]));
+        put_list(w0, w0 > 0 ? ask_list(w0) : ahead);
         request_mask(e0);
         __syncthreads();
         if (decltype(late)::value != 0 && tid == 0) again_s = 0;  // (everyone has read it)
