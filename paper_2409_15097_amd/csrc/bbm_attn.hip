@@ -453,6 +453,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
     }
   };
 
+  // What begin_item asked for stays in front of what follows: Q's copies are waited for by the number of operations behind them.
+  auto q_copies_first = [&]() { __builtin_amdgcn_sched_barrier(0); };
+
   // Starts the asynchronous copies of a window's first tile e (into buffer 0) and asks for its mask word.
   auto start_tile0 = [&](uint32_t e) {
     e0 = scalar(e);
@@ -464,7 +467,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // Runs the tiles listed in tiles_s[0 .. count) (followed by sentinels) through the pipeline; `started` says that
   // start_tile0 was already called for tiles_s[0].
   auto run_window = [&](int count, bool started) {
-    if (!started) start_tile0(tiles_s[0]);
+    if (!started) {
+      q_copies_first();
+      start_tile0(tiles_s[0]);
+    }
     if (q_pending) {  // first window of a block row: Q fragments
       if constexpr (Q_VIA_LDS) {
         __builtin_amdgcn_s_waitcnt(wait_vm(2 * LPW));  // this wave's own copies of Q have landed, behind which it asked for the first tile
@@ -506,6 +512,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // queries a block row 82.3 -> 80.3, at 64 91.6 -> 88.9; tree prefill 132.9 -> 131.0; a 4096-token window over 8 heads 11.4 -> 11.2.
   auto ask_list = [&](const uint32_t* __restrict__ list, int nt) { return list[max(0, min(tid, nt - 1))]; };
   auto run_list = [&](const uint32_t* __restrict__ list, int nt, uint32_t first, uint32_t ahead) {
+    q_copies_first();
     start_tile0(first);
     for (int w0 = 0; w0 < nt; w0 += kWin) {
       const int count = min(kWin, nt - w0);
