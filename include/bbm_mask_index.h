@@ -16,7 +16,8 @@ extern "C" {
  * the indexes of block rows and block columns share one where each would take one, and with `arrivals` a small mask without
  * columns (at most 8 block rows over all planes and 4096 blocks) is served by a single one.
  *   arrivals         one int32 in device memory, zero when it is first used and not written by the caller afterwards (every call
- *                    leaves it zero again); not shared by calls that may run at the same time.  NULL: not used.
+ *                    leaves it zero again); not shared by calls that may run at the same time.  A call that is being recorded
+ *                    into a graph leaves it alone.  NULL: not used.
  */
 int bbm_build_mask_index(const uint8_t* mask, int64_t Mb, int64_t Nq, int64_t Nk, int64_t row_stride_bytes, int Br, int Bc,
                          uint8_t* blk_class, uint8_t* bin_blk_mat, uint64_t* packed_mask, int32_t* offset,

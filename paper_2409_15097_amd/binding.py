@@ -154,8 +154,10 @@ class BlockIndex:
     col_ptr: Optional[torch.Tensor] = None
     row_idx: Optional[torch.Tensor] = None
     col_sched: Optional[torch.Tensor] = None
-    # one int32 that build_index's single launch counts its work-groups in, zero between calls (a copy gets one of its own)
+    # one int32 that build_index's single launch counts its work-groups in, zero between calls, and the stream whose calls use it: those
+    # are never under way together.  Calls on other streams, and recorded ones, do without (a copy gets one of its own).
     arrivals: Optional[torch.Tensor] = field(default=None, init=False, repr=False, compare=False)
+    arrivals_stream: Optional[int] = field(default=None, init=False, repr=False, compare=False)
 
     def c_struct(self) -> _CIndex:
         g = _ptr
@@ -275,7 +277,8 @@ def bbm_col_sched_bytes(Mb: int, nbc: int) -> int:
 def build_index(mask: torch.Tensor, Br: int, Bc: int = 64, idx: Optional[BlockIndex] = None, stream=None,
                 fused: bool = True, columns: bool = False) -> BlockIndex:
     """The whole preprocessing stage: block classes, then run index + block list + schedule (all in one library call, or with
-    fused=False through the separate ones); columns=True adds the per-column list the backward pass needs."""
+    fused=False through the separate ones); columns=True adds the per-column list the backward pass needs.  Calls that may run at
+    the same time, on several streams or as a replayed graph, may share idx only as long as they build it from equal masks."""
     if not fused:
         idx = bbm_build_block_mask_rect(mask, Br, Bc, idx=idx, stream=stream)
         bbm_build_runs(idx, stream=stream)
@@ -293,15 +296,17 @@ def build_index(mask: torch.Tensor, Br: int, Bc: int = 64, idx: Optional[BlockIn
     _alloc_list(idx)
     if columns:
         _alloc_columns(idx)
-    if idx.arrivals is None and not torch.cuda.is_current_stream_capturing():  # (zeros that are there before a recorded call runs)
+    st = _stream(stream)
+    if idx.arrivals is None:
         with (torch.cuda.stream(stream) if stream is not None else _null_ctx()):
-            idx.arrivals = torch.zeros(1, dtype=torch.int32, device=mask.device)
+            if not torch.cuda.is_current_stream_capturing():  # (zeros that are there before a recorded call runs)
+                idx.arrivals, idx.arrivals_stream = torch.zeros(1, dtype=torch.int32, device=mask.device), st
     p = _ptr
     _check(lib.bbm_build_mask_index(p(mask), Mb, N, Nk, mask.stride(1), Br, Bc, p(idx.blk_class), p(idx.bin_blk_mat), p(idx.packed_mask),
                                     p(idx.offset), p(idx.total_ones), p(idx.nz_lo), p(idx.nz_hi), p(idx.nz_cnt), p(idx.row_ptr),
                                     p(idx.col_idx), p(idx.sched), p(idx.col_ptr) if columns else None,
-                                    p(idx.row_idx) if columns else None, p(idx.col_sched) if columns else None, p(idx.arrivals),
-                                    _stream(stream)))
+                                    p(idx.row_idx) if columns else None, p(idx.col_sched) if columns else None,
+                                    p(idx.arrivals) if idx.arrivals_stream == st else None, st))
     return idx
 
 

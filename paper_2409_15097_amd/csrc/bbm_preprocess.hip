@@ -41,8 +41,8 @@ __device__ __forceinline__ uint32_t bits16(u32x4_any x) {
 // waits: the others have ended.  Classes are written through and read around the XCDs' caches and counted without a fence (a
 // device-wide release makes an XCD's cache write back all it holds).  What it saves is a launch, most of it on the host: both
 // stages of 256 x 256 take 16.3 -> 13.5 us of a step of 256 tokens that is submitted call by call, 61.0 -> 60.0 of a decoding step of
-// 256 x 1280, 6.6 -> 6.2 and 6.9 -> 6.4 replayed from a graph.  The last work-group works alone, so one pass over its waves is the
-// limit: 10 block rows of 1280 146.0 -> 147.1 of a step, 7.1 -> 8.5 from a graph; with the block columns 6.8 -> 7.8, 7.1 -> 9.9.
+// 256 x 1280 (replayed from a graph 6.6 -> 6.2 and 6.9 -> 6.4, which is not taken: see `recorded`).  The last work-group works alone,
+// so one pass over its waves is the limit: 10 block rows of 1280 146.0 -> 147.1 of a step; with the block columns 6.8 -> 7.8, 7.1 -> 9.9.
 constexpr int kFusedBytes = 4096, kFusedRows = kWaves, kAgentScope = 16;  // sc1
 struct FusedIndex {
   bbm::LineArgs rows;
@@ -170,7 +170,8 @@ __global__ __launch_bounds__(kThreads) void block_reduce_kernel(const uint8_t* _
     static_assert(sizeof(stage) >= kFusedBytes, "the class bytes take the place of the packed words");
     if (wave == 0) {  // which wrote the classes
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      if (lane == 0) arrived_s = __hip_atomic_fetch_add(fused.arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // (the last one's count puts it back to zero for the next call)
+      if (lane == 0) arrived_s = (int)atomicInc(reinterpret_cast<unsigned*>(fused.arrivals), gridDim.x * gridDim.y * gridDim.z - 1);
     }
     __syncthreads();
     if (arrived_s != (int)(gridDim.x * gridDim.y * gridDim.z) - 1) return;
@@ -180,7 +181,6 @@ __global__ __launch_bounds__(kThreads) void block_reduce_kernel(const uint8_t* _
     uint8_t c[kFusedBytes / kThreads];
 #pragma unroll
     for (int t = 0; t < kFusedBytes / kThreads; ++t) c[t] = __builtin_amdgcn_raw_buffer_load_b8(src, t * kThreads + threadIdx.x, 0, kAgentScope);
-    if (threadIdx.x == 0) __hip_atomic_store(fused.arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // zero for the next call
 #pragma unroll
     for (int t = 0; t < kFusedBytes / kThreads; ++t) cls_s[t * kThreads + threadIdx.x] = c[t];
     __syncthreads();
@@ -224,7 +224,14 @@ int build_block_mask_impl(const char* fn, const uint8_t* mask, int64_t Mb, int64
   // and the attention kernel behind it finds more of Q, K, V still cached (whole step -2.5 % at 1 GiB, -3.5 % at 256 MiB);
   // a 64 MiB mask that is rebuilt from the cache it still sits in loses 20 % that way
   const bool streamed = bytes >= kStreamFromBytes;
-  const bool with_index = fused && fused->arrivals && !streamed && Mb * nbr * nbc <= kFusedBytes && Mb * nbr <= kFusedRows;
+  // A recorded call does without the counter: its replays may run beside other calls, whose work-groups would be counted with theirs.
+  auto recorded = [&]() {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(s, &status) == hipSuccess;
+    if (!known) (void)hipGetLastError();  // (what is wrong with the stream is for the launches to say)
+    return !known || status != hipStreamCaptureStatusNone;
+  };
+  const bool with_index = fused && fused->arrivals && !streamed && Mb * nbr * nbc <= kFusedBytes && Mb * nbr <= kFusedRows && !recorded();
   bool index_written = false;
   auto go = [&](auto lpr, auto unroll) {
     constexpr int LPR = decltype(lpr)::value, U = decltype(unroll)::value;

@@ -101,3 +101,84 @@ def test_recorded_calls_replay_with_eager_ones_in_between(first_in_the_graph):
         mask.copy_(masks[1])
         bbm.build_index(mask, 128, 64, idx=idx)  # an eager call into the same index
         _assert_same(idx, bbm.build_index(masks[1], 128, 64, fused=False), False)
+
+
+MARK = 1 << 20                                   # no call has that many work-groups: one that counts moves it, one that does not leaves it
+
+
+def _band(N, w):
+    i = torch.arange(N, device="cuda")
+    return ((i[:, None] - i[None, :]).abs() <= w).to(torch.uint8)[None].contiguous()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("columns", [False, True])
+@pytest.mark.parametrize("Mb,Nq,Nk,Br", SIZES)
+def test_which_sizes_one_launch_takes(Mb, Nq, Nk, Br, columns):
+    import paper_2409_15097_amd as bbm
+    mask = (torch.rand((Mb, Nq, Nk), device="cuda") < 0.01).to(torch.uint8)
+    idx = bbm.build_index(mask, Br, 64, columns=columns)
+    idx.arrivals.fill_(MARK)
+    bbm.build_index(mask, Br, 64, idx=idx, columns=columns)
+    rows = Mb * -(-Nq // Br)
+    one = not columns and rows <= 8 and rows * -(-Nk // 64) <= 4096 and not (Br == 64 and Mb * Nq * Nk > 8 << 20)
+    work_groups = rows * -(-Nk // 256)
+    assert int(idx.arrivals) == (work_groups - 1 if one else MARK)   # (an increment past its limit gives zero)
+
+
+@pytest.mark.gpu
+def test_calls_on_another_stream_do_not_share_the_counter():
+    import paper_2409_15097_amd as bbm
+    first, second = _band(1000, 3), _band(1000, 300)
+    idx = bbm.build_index(first, 128, 64)
+    idx.arrivals.fill_(MARK)                     # what a call under way on this stream might have left there
+    torch.cuda.synchronize()
+    other = torch.cuda.Stream()
+    bbm.build_index(second, 128, 64, idx=idx, stream=other)
+    other.synchronize()
+    assert int(idx.arrivals) == MARK
+    _assert_same(idx, bbm.build_index(second, 128, 64, fused=False), False)
+    idx.arrivals.zero_()                         # and the stream that it belongs to goes on with it
+    bbm.build_index(first, 128, 64, idx=idx)
+    _assert_same(idx, bbm.build_index(first, 128, 64, fused=False), False)
+    assert int(idx.arrivals) == 0
+
+
+@pytest.mark.gpu
+def test_recorded_calls_leave_the_counter_alone():
+    import paper_2409_15097_amd as bbm
+    mask = _band(1000, 3)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    idx = bbm.build_index(mask, 128, 64, stream=side)   # the counter belongs to the stream that is recorded below
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        bbm.build_index(mask, 128, 64, idx=idx)
+    idx.arrivals.fill_(MARK)                     # an eager call whose work-groups have not all been counted
+    for w in (200, 3, 1000):
+        mask.copy_(_band(1000, w))
+        graph.replay()
+        _assert_same(idx, bbm.build_index(mask, 128, 64, fused=False), False)
+    assert int(idx.arrivals) == MARK
+
+
+@pytest.mark.gpu
+def test_a_counter_is_not_made_while_the_stream_of_the_call_is_recorded():
+    """The stream of the call is recorded, the current one is not."""
+    import dataclasses
+    import paper_2409_15097_amd as bbm
+    mask = _band(1000, 3)
+    idx = dataclasses.replace(bbm.build_index(mask, 128, 64))
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        with torch.cuda.stream(other):
+            assert not torch.cuda.is_current_stream_capturing()
+            bbm.build_index(mask, 128, 64, idx=idx, stream=side)
+    assert idx.arrivals is None
+    for w in (200, 3):
+        mask.copy_(_band(1000, w))
+        graph.replay()
+        _assert_same(idx, bbm.build_index(mask, 128, 64, fused=False), False)
