@@ -234,15 +234,26 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // Q through LDS needs a 32 x D staging slab per wave in the two buffers of parity 1 (two slabs each)
   constexpr bool Q_VIA_LDS = NW <= 4;
   bool q_pending = false;
-  // What a lane reads and copies where.  Found anew for every item: kept across the merge of a cut row, some of it lay in scratch
-  // memory at d = 128, and the own row's list was asked for only when its first tile had landed (the wait for the reload).
+  // The row's list is asked for before Q and the first tile (and Q's fragments are picked up while that tile is under way), or behind
+  // them, and everything is waited for at once: then it costs a trip to memory, but Q and the tile set off earlier, which matters
+  // more where other work-groups of the CU fill the waiting.  Work-groups of whole rows, forward in us, list first / behind:
+  //   D = 64, 128 queries a row: windows of 3 x 9 x 1500 9.31 / 8.92, of 5 x 12 x 914 9.55 / 8.95, of 2 x 8 x 8192 34.4 / 33.5
+  //   D = 64, 256 queries: packed sequences 45.4 / 45.0, 1 x 2 x 256 9.00 / 8.87, a window of 3 x 9 x 1500 11.18 / 11.08
+  //   D = 64, 64 queries: a window of 3 x 9 x 1500 8.14 / 8.25, 1 x 2 x 256 6.26 / 6.38
+  //   D = 128, 128 queries: windows of 3 x 9 x 1500 14.3 / 13.5, of 2 x 8 x 8192 51.5 / 49.9; packed sequences of 3001 21.6 / 22.0
+  //   D = 128, 64 queries: packed sequences 87.8 / 89.4, of 3001 23.4 / 23.9; 256 queries: of 3001 26.9 / 27.3, a window of 914 16.1 / 16.4
+  constexpr bool LIST_FIRST = SCHED != 1 || (D == 128 ? NW != 4 : NW == 2);
+  // What a lane reads and copies where.  Found anew for every item at D = 128: kept across the merge of a cut row, some of it lay in
+  // scratch memory, and the own row's list was asked for only when its first tile had landed (the wait for the reload).  At D = 64
+  // there is room for it (packed sequences of 3001, 64 queries a row, 13.56 -> 13.40 us), except beside the merge of small launches
+  // (a window over 8 heads of 4096 11.5 us with, 11.8 without).
   int lq, hh;          // query row of the wave's 32, half of the keys
   int g_row, g_chunk;  // row and 16-byte chunk this lane moves in a 1 KiB copy
   int kaddr, vaddr;    // see k_frag, v_frag
   uint32_t g_off;      // see copy_piece
   auto lane_places = [&]() __attribute__((always_inline)) {
     int ln = lane;
-    asm volatile("" : "+v"(ln));
+    if constexpr (D == 128 || SCHED == 2) asm volatile("" : "+v"(ln));
     lq = ln & 31, hh = ln >> 5;
     g_row = ln / RC, g_chunk = ln % RC;
     kaddr = (lq % NBLK) * KBLK + (lq / NBLK) * D + hh * 8;
@@ -265,7 +276,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
     // up.  Chunk j of row r lands at chunk position j ^ (r % RC) of row r.  Eight waves find no room there and read their fragments
     // themselves.  Rows past N come as zeros (their results are never stored).  (The buffer form: the compiler takes the global
     // form of the copy for a possible access to LDS by another path, and waits for all that is under way where it needs an
-    // earlier load.)
+    // earlier load.  This alone: packed sequences of 3001 23.7 -> 22.7 us at D = 128, 13.44 -> 13.40 at D = 64.)
     const int64_t row0 = (int64_t)i * BR + wave * 32;
     const int rows = (int)max<int64_t>(0, min<int64_t>(32, N - row0));
     const __amdgpu_buffer_rsrc_t slab = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(global(P->q)) + head_off + row0 * D, 0,
@@ -473,21 +484,28 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
     }
     if (q_pending) {  // first window of a block row: Q fragments
       if constexpr (Q_VIA_LDS) {
-        __builtin_amdgcn_s_waitcnt(wait_vm(2 * LPW));  // this wave's own copies of Q have landed, behind which it asked for the first tile
-        auto pick_up = [&](const __bf16* stage) __attribute__((always_inline)) {
+        if constexpr (LIST_FIRST) {
+          __builtin_amdgcn_s_waitcnt(wait_vm(2 * LPW));  // this wave's own copies of Q have landed, behind which it asked for the first tile
+          auto pick_up = [&](const __bf16* stage) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < KS; ++t) qf[t] = *reinterpret_cast<const bf16x8*>(stage + lq * D + (((2 * t + hh) ^ (lq % RC)) * 8));
+          };
+          // (By variable, not through a pointer to either, which the compiler would make of this without the asm: it then waits for
+          // no other copies.)
+          if (wave < 2) {
+            pick_up(k_s1 + wave * 32 * D);
+#pragma unroll
+            for (int t = 0; t < KS; ++t) asm volatile("; from k_s1" : "+v"(qf[t]));
+          } else {
+            pick_up(v_s1 + (wave & 1) * 32 * D);
+#pragma unroll
+            for (int t = 0; t < KS; ++t) asm volatile("; from v_s1" : "+v"(qf[t]));
+          }
+        } else {
+          __builtin_amdgcn_s_waitcnt(0);
+          const __bf16* const stage = q_stage();
 #pragma unroll
           for (int t = 0; t < KS; ++t) qf[t] = *reinterpret_cast<const bf16x8*>(stage + lq * D + (((2 * t + hh) ^ (lq % RC)) * 8));
-        };
-        // (By variable, not through a pointer to either, which the compiler would make of this without the asm: it then waits for
-        // no other copies.)
-        if (wave < 2) {
-          pick_up(k_s1 + wave * 32 * D);
-#pragma unroll
-          for (int t = 0; t < KS; ++t) asm volatile("; from k_s1" : "+v"(qf[t]));
-        } else {
-          pick_up(v_s1 + (wave & 1) * 32 * D);
-#pragma unroll
-          for (int t = 0; t < KS; ++t) asm volatile("; from v_s1" : "+v"(qf[t]));
         }
       }
 #pragma unroll
@@ -505,19 +523,21 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   };
 
   // Runs nt >= 1 consecutive list entries, the first of which is already known: its copies start before the list
-  // itself has been fetched.  `ahead` is this thread's entry, from ask_list: asked for before Q and the first tile, it does not wait
-  // behind their 64 KiB, and what is left to do before the first product (list to LDS, Q's fragments) is done while the tile is on
-  // its way.  Kernel time against asking behind them and waiting for all at once, with the epilogue's stores by buffer and the
-  // arguments left in memory, us: packed sequences of 3001, D = 128, 24.1 -> 22.2, of 4096, D = 64, 34.3 -> 33.1, D = 128 at 256
-  // queries a block row 82.3 -> 80.3, at 64 91.6 -> 88.9; tree prefill 132.9 -> 131.0; a 4096-token window over 8 heads 11.4 -> 11.2.
-  auto ask_list = [&](const uint32_t* __restrict__ list, int nt) { return list[max(0, min(tid, nt - 1))]; };
+  // itself has been fetched.  `ahead` is this thread's entry, from ask_list, where the list is asked for first: it does not wait
+  // behind the 64 KiB of Q and the first tile, and what is left to do before the first product (list to LDS, Q's fragments) is
+  // done while the tile is on its way.
+  auto ask_list = [&](const uint32_t* __restrict__ list, int nt) { return LIST_FIRST ? list[max(0, min(tid, nt - 1))] : 0u; };
   auto run_list = [&](const uint32_t* __restrict__ list, int nt, uint32_t first, uint32_t ahead) {
-    q_copies_first();
+    if constexpr (LIST_FIRST) q_copies_first();
     start_tile0(first);
     for (int w0 = 0; w0 < nt; w0 += kWin) {
       const int count = min(kWin, nt - w0);
-      if (w0 == 0) tiles_s[tid] = tid < nt ? ahead : kNoTile;
-      for (int t = w0 == 0 ? tid + NT : tid; t < count; t += NT) tiles_s[t] = list[w0 + t];
+      int t = tid;
+      if (LIST_FIRST && w0 == 0) {
+        tiles_s[t] = t < nt ? ahead : kNoTile;
+        t += NT;
+      }
+      for (; t < count; t += NT) tiles_s[t] = list[w0 + t];
       if (tid < 3) tiles_s[count + tid] = kNoTile;
       lds_barrier();  // (the first tile may still be on its way)
       run_window(count, w0 == 0);
@@ -655,15 +675,17 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
 
   // ---- a launch too small to fill the chip: work-group = (block row, part), merged by merge_tree
   if constexpr (SCHED == 2) {
-    int part = (int)blockIdx.x % P->split;
-    const int rest = (int)blockIdx.x / P->split;
-    int S = P->split;  // parts of this row
-    bh = rest / P->nbr;
-    i = P->nbr - 1 - (rest - bh * P->nbr);
-    m = (P->Mb == 1) ? 0 : bh / P->H;
-    const int hb = (P->Mb == 1) ? bh : bh - m * P->H;
-    if (P->mode == BBM_MODE_LIST) {  // equal shares of the row's list, none shorter than kSplitMinTiles entries if there are several
-      const int32_t* rp = global(P->row_ptr) + (int64_t)m * (P->nbr + 1) + i;
+    int nbr = P->nbr, Mb = P->Mb, H = P->H, split = P->split, mode = P->mode;
+    asm volatile("" : "+s"(nbr), "+s"(Mb), "+s"(H), "+s"(split), "+s"(mode));  // in one go, see below
+    int part = (int)blockIdx.x % split;
+    const int rest = (int)blockIdx.x / split;
+    int S = split;  // parts of this row
+    bh = rest / nbr;
+    i = nbr - 1 - (rest - bh * nbr);
+    m = (Mb == 1) ? 0 : bh / H;
+    const int hb = (Mb == 1) ? bh : bh - m * H;
+    if (mode == BBM_MODE_LIST) {  // equal shares of the row's list, none shorter than kSplitMinTiles entries if there are several
+      const int32_t* rp = global(P->row_ptr) + (int64_t)m * (nbr + 1) + i;
       const int p_row = rp[0], n_row = rp[1] - rp[0];
       S = max(1, min(S, n_row / kSplitMinTiles));
       // Work-groups go to the eight XCDs in turn: if the same ones of every row were left over, some XCDs would get no work (rows
@@ -704,33 +726,40 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // Launch order inside a group of G consecutive (batch, head) planes: rank-major, i.e. rank 0 of every plane of the
   // group, then rank 1 of every plane, ...  The hardware starts work-groups in index order as slots free up, so
   // with ranks sorted by length long rows start early everywhere and the short ones fill the tail.
+  // The arguments this takes are asked for in one go (hence the asm).  The compiler would read each where it is needed, and a scalar
+  // load is waited for together with all that are under way: one of them stood between the schedule's header and the row's record
+  // below, which then followed each other on their ways to memory.  (Header and record through the constant address space, so
+  // that they are scalar loads: no kernel that reads a schedule writes one.)
   int own_bh, own_m, own_rank;
+  int T = P->total_wgs, G = P->G, nbr = P->nbr, Mb = P->Mb, H = P->H, hbp = P->hbp, part_cap = P->part_cap;
+  uint64_t sched_at = reinterpret_cast<uint64_t>(P->sched);
+  asm volatile("" : "+s"(T), "+s"(G), "+s"(nbr), "+s"(Mb), "+s"(H), "+s"(hbp), "+s"(part_cap), "+s"(sched_at));
   {
     const int wg = (int)blockIdx.x;
-    const int T = P->total_wgs;
     const int xcd = wg & 7, slot = wg >> 3;
     const int per = T >> 3, rem = T & 7;
     const int logical = xcd * per + (xcd < rem ? xcd : rem) + slot;
-    const int grp = logical / (P->G * P->nbr), within = logical - grp * (P->G * P->nbr);
-    const int g_planes = min(P->G, T / P->nbr - grp * P->G);
+    const int grp = logical / (G * nbr), within = logical - grp * (G * nbr);
+    const int g_planes = min(G, T / nbr - grp * G);
     own_rank = within / g_planes;
-    own_bh = grp * P->G + (within - own_rank * g_planes);
-    own_m = (P->Mb == 1) ? 0 : own_bh / P->H;
+    own_bh = grp * G + (within - own_rank * g_planes);
+    own_m = (Mb == 1) ? 0 : own_bh / H;
   }
   // LIST mode: the schedule's header (parts, split threshold) and this work-group's row record -- which block row has
   // its rank, where its list lies and how it starts -- are requested together: one round trip, not three
-  int4 own_rec = make_int4(0, 0, 0, -1);
+  typedef int32_t int4x __attribute__((ext_vector_type(4)));
+  int4x own_rec = {0, 0, 0, -1};
   int nparts_all = 0, split_T = 0;
   if (SCHED == 1) {
-    static_assert(bbm::kSchedNParts == 0 && bbm::kSchedSplitT == 1, "the header is read as one 8-byte pair");
-    const int2 hdr = *reinterpret_cast<const int2*>(global(P->sched));
-    own_rec = *reinterpret_cast<const int4*>(global(P->sched) + bbm::sched_order_base(P->Mb, P->nbr) +
-                                             bbm::kSchedRowInts * (int64_t)(own_m * P->nbr + own_rank));
-    nparts_all = hdr.x;
-    split_T = hdr.y;
+    const auto sched = reinterpret_cast<const int4x __attribute__((address_space(4)))*>(sched_at);
+    const int4x hdr = sched[0];
+    static_assert(bbm::kSchedPartBase % 4 == 0 && bbm::kSchedPartInts % 4 == 0 && bbm::kSchedRowInts == 4, "records of 16 bytes");
+    own_rec = sched[bbm::sched_order_base(Mb, nbr) / 4 + own_m * nbr + own_rank];
+    nparts_all = hdr[bbm::kSchedNParts];
+    split_T = hdr[bbm::kSchedSplitT];
     // a workspace too small for the partial results of every (part, head) item: no row is computed in parts
     // (the same decision in every work-group: it depends on the header and the launch only)
-    if ((int64_t)nparts_all * P->hbp > (int64_t)P->part_cap) {
+    if ((int64_t)nparts_all * hbp > (int64_t)part_cap) {
       nparts_all = 0;
       split_T = 0x7fffffff;
     }

@@ -546,3 +546,25 @@ def test_lists_around_one_entry_per_thread(Br, length):
         ref = torch.softmax(s, 1) @ v[0, h].float()
         assert_attention_close(o[:, h:h + 1], lse[:, h:h + 1], ref[None, None].double().cpu().numpy(),
                                torch.logsumexp(s, 1)[None, None].double().cpu().numpy())
+
+
+@pytest.mark.parametrize("Br,length", [(64, 1), (64, 128), (64, 129), (128, 1), (128, 256), (128, 257), (256, 1), (256, 512), (256, 513)])
+def test_lists_around_one_entry_per_thread_at_d128(Br, length):
+    """At d = 128 rows of 64 and 256 queries ask for their list first, those of 128 behind the first tile (at d = 64 it is those of 64
+    that ask first).  Row 0 without a tile: its work-group asks, and finds nothing."""
+    bbm = _bbm()
+    H, Nq, Nk, d = 257, Br + 40, 64 * length - 5, 128
+    gen = torch.Generator(device="cuda").manual_seed(length)
+    q, k, v = (torch.randn((1, H, n, d), generator=gen, device="cuda").to(torch.bfloat16) for n in (Nq, Nk, Nk))
+    mask = (torch.rand((1, Nq, Nk), generator=gen, device="cuda") < 0.4).to(torch.uint8)
+    mask[:, :Br] = 0
+    idx = bbm.build_index(mask, Br, 64)
+    assert idx.row_ptr[0].tolist() == [0, 0, length]
+    print(f"list of {length} Br={Br} d={d}", flush=True)
+    o, lse = bbm.bbm_attn_fwd_rect(q, k, v, idx, mode=bbm.BBM_MODE_LIST)
+    for h in (0, H - 1):
+        s = (q[0, h].float() @ k[0, h].float().T) * d ** -0.5
+        s = s.masked_fill(mask[0] == 0, float("-inf"))
+        ref = torch.softmax(s, 1).nan_to_num(0.0) @ v[0, h].float()
+        assert_attention_close(o[:, h:h + 1], lse[:, h:h + 1], ref[None, None].double().cpu().numpy(),
+                               torch.logsumexp(s, 1)[None, None].double().cpu().numpy())
