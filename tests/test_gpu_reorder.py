@@ -49,8 +49,8 @@ def _cases():
     big[:, 4321] = 1
     big[np.arange(0, 4999, 2), np.arange(1, 5000, 2)] = 1                # unequal degrees among the 4999 nodes of the level
     big[np.arange(1, 5000, 2), np.arange(0, 4999, 2)] = 1
-    yield "big star", big                                            # a level larger than one ranking sweep (4096 keys)
-    yield "huge star", _star(16500)                                  # more than 64 * 256 nodes in a level: one lane per candidate
+    yield "big star", big                                            # a level larger than one chunk of keys (4096)
+    yield "huge star", _star(16500)                                  # a level of several chunks of keys, its ranks in slices of 86
     yield "graph workload", masks.graph_mask(1024, 5, reorder="none", xm=8.0, cap=60)[0]
     lopsided = np.eye(9001, dtype=np.uint8)                           # 18 regions of 512 nodes, the last one of 297: 16 share lines in pairs
     rng = np.random.default_rng(9)
@@ -77,6 +77,42 @@ def test_rcm_order_matches_oracle(name, A):
     torch.cuda.synchronize()
     want = oracle.reverse_cuthill_mckee(A)
     assert np.array_equal(perm.cpu().numpy().astype(np.int64), want)
+
+
+def _late_parents():
+    """A level of 4999 nodes, two chunks of keys, with 2000 children of two parents each: one with a low number, in the first chunk,
+    and one with a high number, which comes first in the level because its degree is smaller."""
+    A = np.eye(7001, dtype=np.uint8)
+    level, child = 1 + np.arange(5000), 5001 + np.arange(2000)
+    pairs = [(np.zeros(5000, dtype=int), level), (level[:2499], level[1:2500]), (child, level[:2000]), (child, level[::-1][:2000])]
+    for a, b in pairs:
+        A[a, b] = A[b, a] = 1
+    degree = A.sum(1)
+    assert (degree[level[::-1][:2000]] < degree[level[:2000]]).all()
+    return A
+
+
+def _scattered_chords(N, seed):
+    """A ring with chords, its labels scattered: levels of up to a third of the nodes, parents and children all over the numbers."""
+    rng = np.random.default_rng(seed)
+    label = rng.permutation(N)
+    A = np.zeros((N, N), dtype=np.uint8)
+    a = np.concatenate([np.arange(N), rng.integers(0, N, N // 2)])
+    b = np.concatenate([(np.arange(N) + 1) % N, rng.integers(0, N, N // 2)])
+    A[label[a], label[b]] = A[label[b], label[a]] = 1
+    return A
+
+
+# 40000: 79 regions of node numbers, where the workloads have 64 at most, and numbers that take all 16 bits of a list entry
+@pytest.mark.parametrize("make", [_late_parents, lambda: _scattered_chords(20000, 1), lambda: _scattered_chords(40000, 2)],
+                         ids=["parents in a later chunk", "20000 nodes", "40000 nodes"])
+def test_rcm_order_of_levels_in_several_chunks_with_children(make):
+    bbm = _bbm()
+    A = make()
+    print(f"rcm N={A.shape[0]}", flush=True)
+    perm = bbm.bbm_rcm_order(torch.from_numpy(A).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(perm.cpu().numpy().astype(np.int64), oracle.reverse_cuthill_mckee(A))
 
 
 def test_rcm_order_with_a_padded_row_stride_and_unaligned_rows():
