@@ -184,7 +184,9 @@ __device__ __forceinline__ int min_degree_unvisited(const int32_t* __restrict__ 
 
 constexpr int kLevelThreads = 1024, kLevelWaves = kLevelThreads / 64;
 constexpr int kLevelStage = 4096;    // keys of a level staged in LDS at a time
-constexpr int kRankWGs = 192;        // ranking work-groups of a round; with the at most kMaxRegs expanding ones all find a CU
+// Ranking work-groups of a round.  A CU holds one work-group of this kernel: with the expanding ones, one a region, all start at once
+// up to 64 regions (32768 nodes).  Above, the last of at most 320 start when others end.
+constexpr int kRankWGs = 192;
 constexpr int kRankSlice = (kMaxNodes + kRankWGs - 1) / kRankWGs;
 
 __device__ __forceinline__ uint64_t wave_min64(uint64_t x) {
@@ -205,7 +207,10 @@ __device__ __forceinline__ uint64_t wave_min64(uint64_t x) {
 // before the expansion is, and the minima in LDS are 0.5 us of it.  Before, a round was an expanding kernel (atomics on memory, a
 // candidate list behind one counter) and a ranking one: a level of 1700 nodes of the 32768-node power-law graph took 8 + 9 us, now
 // 12.4.  The whole ordering, of which 200 us are the packing at 32768 nodes, us: 1000 nodes 259-348 -> 140-154, 8192 335-395 ->
-// 166-180, 16000 364-407 -> 236-246, 32768 623 -> 467.  Regions of 4 words instead of 8 (32768 nodes): 554.  All levels in one launch
+// 166-180, 16000 364-407 -> 236-246, 32768 623 -> 467; 65536, where the launch is larger than the chip, 1608 -> 1487.  Large levels, of random
+// graphs of 16 to 512 edges a node: 8192 nodes 295 -> 170, 32768 930-1000 -> 490-540, 65536 2240-2340 -> 1860-2160; stars of 32768 and
+// 65536 1005 -> 540, 2342 -> 2188; a band of 8192 nodes (many small levels) 428 -> 327.  Thousands of components, which the last kernel
+// walks, take what they took (32768 nodes with 4 edges each 31.4 ms).  Regions of 4 words instead of 8 (32768 nodes): 554.  All levels in one launch
 // whose work-groups wait for each other's flags: 105, 152, 230, 481; not worth the waiting.  Every region's first 64 nodes asked
 // for along with the counts: no difference.
 __global__ __launch_bounds__(kLevelThreads) void rcm_level_kernel(const uint64_t* __restrict__ bits, const int32_t* __restrict__ degree,
