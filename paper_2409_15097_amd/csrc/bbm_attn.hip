@@ -21,7 +21,7 @@
 
 namespace {
 
-using bbm::bf16x2, bbm::bf16x4, bbm::bf16x8, bbm::f32x16, bbm::IntC, bbm::mfma_ring, bbm::partner_sum, bbm::s16x4, bbm::scalar;
+using bbm::bf16x2, bbm::bf16x4, bbm::bf16x8, bbm::f32x16, bbm::global, bbm::IntC, bbm::mfma_ring, bbm::partner_sum, bbm::s16x4, bbm::scalar;
 
 constexpr int kBc = 64;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -82,15 +82,7 @@ constexpr int kWin = 1024;               // tiles per schedule window (block col
 constexpr uint32_t kNoTile = 0xffffffffu;  // sentinel after the last entry of a window
 constexpr uint32_t kZeroWord = 0x40000000u;  // entry flag: the tile's mask words are all zero and are not in memory
 
-// A kernel's arguments where they lie in memory (its only parameter, at the start of the argument segment): taken by value they are
-// read into scalar registers when the kernel starts, more than there are, and kept in lanes of vector registers.
-typedef const AttnParams __attribute__((address_space(4)))* Args;
-__device__ __forceinline__ Args kernel_args() { return (Args)__builtin_amdgcn_kernarg_segment_ptr(); }
-// A pointer of the arguments points to global memory (the compiler cannot see that, and would take it for one into LDS as well).
-template <typename T>
-__device__ __forceinline__ T* global(T* p) {
-  return (T*)(T __attribute__((address_space(1)))*)p;
-}
+typedef bbm::InPlace<AttnParams> Args;
 
 // Builds, in LDS, the ascending list of tiles one block row visits inside one schedule window; entry =
 // block column | (1 << 31 if the element mask can be skipped there).  Returns the number of entries (uniform).
@@ -183,7 +175,7 @@ __device__ __forceinline__ int num_windows(Args P, int m, int i, int clo, int ch
 // accumulator inside the exponential; running maxima are then kept in units of 1/r.
 template <int D, int NW, int SCHED, bool EXACT>
 __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) void attn_fwd_kernel(const AttnParams) {
-  Args P = kernel_args();
+  Args P = bbm::kernel_args<AttnParams>();
   constexpr int NT = NW * 64;
   constexpr int BR = NW * 32;
   // LDS tile layout ("blocks"): one asynchronous copy instruction of a wave fills one 1 KiB block with RPB rows

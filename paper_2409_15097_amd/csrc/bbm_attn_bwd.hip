@@ -21,7 +21,7 @@
 
 namespace {
 
-using bbm::bf16x2, bbm::bf16x4, bbm::bf16x8, bbm::f32x16, bbm::IntC, bbm::mfma_ring, bbm::partner_sum, bbm::s16x4, bbm::scalar;
+using bbm::bf16x2, bbm::bf16x4, bbm::bf16x8, bbm::f32x16, bbm::global, bbm::IntC, bbm::mfma_ring, bbm::partner_sum, bbm::s16x4, bbm::scalar;
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kWin = 128;                   // list entries per LDS window
@@ -78,16 +78,7 @@ __device__ __forceinline__ float row_sum(float x) {
   return x;
 }
 
-// A kernel's arguments where they lie in memory (its only parameter, at the start of the argument segment).  Taken by value they are
-// read into scalar registers when the kernel starts, more than there are, and kept in lanes of vector registers for the next item:
-// 110-160 lane accesses before the first matrix instruction, now 20-90; this way they are read again where they are wanted.
-typedef const BwdParams __attribute__((address_space(4)))* Args;
-__device__ __forceinline__ Args kernel_args() { return (Args)__builtin_amdgcn_kernarg_segment_ptr(); }
-// A pointer of the arguments points to global memory (the compiler cannot see that, and would take it for one into LDS as well).
-template <typename T>
-__device__ __forceinline__ T* global(T* p) {
-  return (T*)(T __attribute__((address_space(1)))*)p;
-}
+typedef bbm::InPlace<BwdParams> Args;
 
 // LDS layout of a 64-row x D tile, shared by every tile of both kernels.  One asynchronous copy instruction of a wave
 // fills one 1 KiB block with RPB rows that lie NBLK rows apart: row r sits in block r % NBLK at slot r / NBLK; blocks
@@ -257,7 +248,7 @@ __device__ __forceinline__ int logical_wg(int wg, int total) {
 // heads of 8192 causal tokens, D = 128, 1470 -> 1400; 4 x 16 of 4096, D = 64, 226 -> 220 (exponentials beside the matrix pipe).
 template <int D, int NW, bool EXACT>
 __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW == 4) ? 3 : 1) void attn_bwd_dq_kernel(const BwdParams) {
-  Args P = kernel_args();
+  Args P = bbm::kernel_args<BwdParams>();
   using L = TL<D>;
   constexpr int NT = NW * 64;
   constexpr int BR = NW * 32;
@@ -655,7 +646,7 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
 // memory inside the loop costs a wait for the tile copies in flight (a form with 16 of them took 3240 us).  D = 64: 168, three.
 template <int D, bool EXACT>
 __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bwd_dkv_kernel(const BwdParams) {
-  Args P = kernel_args();
+  Args P = bbm::kernel_args<BwdParams>();
   using L = TL<D>;
   constexpr int NW = 4, NT = 64 * NW;
   constexpr int NTP = 128;  // lanes that hold one of the two sums: stride of the parked records

@@ -18,6 +18,20 @@ struct IntC {
   static constexpr int value = V;
 };
 
+// A kernel's arguments where they lie in memory (its only parameter, at the start of the argument segment).  Taken by value they are
+// read into scalar registers when the kernel starts, more than there are, and kept in lanes of vector registers for the next item:
+// 110-160 lane accesses before the backward kernels' first matrix instruction, 20-90 this way, where they are read again where they
+// are wanted.
+template <typename Params>
+using InPlace = const Params __attribute__((address_space(4)))*;
+template <typename Params>
+__device__ __forceinline__ InPlace<Params> kernel_args() { return (InPlace<Params>)__builtin_amdgcn_kernarg_segment_ptr(); }
+// A pointer of the arguments points to global memory (the compiler cannot see that, and would take it for one into LDS as well).
+template <typename T>
+__device__ __forceinline__ T* global(T* p) {
+  return (T*)(T __attribute__((address_space(1)))*)p;
+}
+
 __device__ __forceinline__ uint32_t scalar(uint32_t uniform) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)uniform); }
 
 __device__ __forceinline__ float partner_sum(float x) {
