@@ -187,7 +187,8 @@ struct TileAddr {
 
 // acc * mult, rounded to bf16, to rows row0 .. of a [N][D] matrix: lane l holds row l%32 of the wave's 32-row slab,
 // columns 32*db + 8*(e/4) + 4*(l/32) + e%4.  The slab is staged in LDS (`stage`, 32*D elements, this wave's own) so
-// that the global stores are whole rows: 16-byte chunk ch of row r sits at chunk position ch ^ (r % RC).
+// that the global stores are whole rows: 16-byte chunk ch of row r sits at chunk position ch ^ (r % RC).  (With the forward's
+// store_rows, by buffer, more registers of these kernels lie in scratch memory: 1 to 2 % slower at D = 64.)
 template <int D>
 __device__ __forceinline__ void store_slab(const f32x16 (&acc)[D / 32], float mult, __bf16* stage, __bf16* __restrict__ dst,
                                            int row0, int N, int lane) {
@@ -501,10 +502,12 @@ __global__ __launch_bounds__(NW * 64, (D == 128 && NW >= 4) ? 2 : (D == 64 && NW
     constexpr bool EARLY = NW <= 4;  // the waves' slabs of Q leave the buffers of parity 0 to the first tile
     auto run = [&](auto late) __attribute__((always_inline)) {
       // The list, the rows of Q, dO and O, their log-sum-exp and the first tile are asked for in one go, by buffer.  With the list's way to
-      // LDS behind the tile, the rows behind that and the log-sum-exp behind those it was three round trips to memory in series, and
-      // addresses in vector registers pushed others into scratch memory.  The whole backward pass, us: packed sequences of 3001, D = 128,
-      // 67.2 -> 66.0, 4096, D = 128, 64 queries a block row 270.8 -> 264.8, 256 a block row 267.7 -> 264.0, a 4096-token window over 8
-      // heads 22.9 -> 22.5; 4096, D = 64, where three work-groups a CU hide it, 113.9 -> 113.6.
+      // LDS behind the tile, the rows behind that and the log-sum-exp behind those it was three round trips to memory in series.
+      // Registers are not what it saves: in scratch memory lie none at D = 128, before or now, and at D = 64, four waves, 7 instead of
+      // 5 (7 instead of 9 with the sharper scale), outside the tile loop.  The whole backward pass, us: D = 128, packed sequences of
+      // 3001 68.1 -> 66.3, 4096 at 64 / 128 / 256 queries a block row 272.8 -> 267.4, 256.3 -> 250.2, 274.5 -> 269.3, a dilated window over 8
+      // heads of 4096 51.9 -> 49.9 at 64; D = 64, where three work-groups a CU hide most of it, packed sequences of 4096 119.4 -> 118.1,
+      // 116.9 -> 115.7, 131.8 -> 129.5, a window of 2 x 8 x 8192 96.7 -> 95.7, 95.7 -> 95.6, 102.1 -> 101.6, 1 x 2 x 256 16.6 -> 16.3.
       const uint32_t ahead = ask_list(0);
       begin_item(write_stats, [&]() __attribute__((always_inline)) {
         if (EARLY && n_list > 0) start_tile(first);
