@@ -17,6 +17,7 @@
 #include "bbm_mfma.h"
 
 #include <algorithm>
+#include <cstddef>
 #include <mutex>
 
 namespace {
@@ -228,13 +229,15 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   bool q_pending = false;
   // The row's list is asked for before Q and the first tile (and Q's fragments are picked up while that tile is under way), or behind
   // them, and everything is waited for at once: then it costs a trip to memory, but Q and the tile set off earlier, which matters
-  // more where other work-groups of the CU fill the waiting.  Work-groups of whole rows, forward in us, list first / behind:
-  //   D = 64, 128 queries a row: windows of 3 x 9 x 1500 9.31 / 8.92, of 5 x 12 x 914 9.55 / 8.95, of 2 x 8 x 8192 34.4 / 33.5
-  //   D = 64, 256 queries: packed sequences 45.4 / 45.0, 1 x 2 x 256 9.00 / 8.87, a window of 3 x 9 x 1500 11.18 / 11.08
-  //   D = 64, 64 queries: a window of 3 x 9 x 1500 8.14 / 8.25, 1 x 2 x 256 6.26 / 6.38
-  //   D = 128, 128 queries: windows of 3 x 9 x 1500 14.3 / 13.5, of 2 x 8 x 8192 51.5 / 49.9; packed sequences of 3001 21.6 / 22.0
-  //   D = 128, 64 queries: packed sequences 87.8 / 89.4, of 3001 23.4 / 23.9; 256 queries: of 3001 26.9 / 27.3, a window of 914 16.1 / 16.4
-  constexpr bool LIST_FIRST = SCHED != 1 || (D == 128 ? NW != 4 : NW == 2);
+  // more where other work-groups of the CU fill the waiting.  Work-groups of whole rows, forward in us on other tensors call by call,
+  // list first / behind:
+  //   D = 64, 64 queries a row: windows of 3 x 9 x 1500 9.75 / 9.60, of 5 x 12 x 914 10.40 / 10.13; packed sequences of 3001 15.24 / 15.40
+  //   D = 64, 128 queries: windows of 3 x 9 x 1500 10.49 / 9.96, of 5 x 12 x 914 11.15 / 10.68; packed sequences of 4096 38.7 / 38.5
+  //   D = 64, 256 queries: within 0.4 %
+  //   D = 128, 64 queries: packed sequences of 3001 25.8 / 26.9, of 4096 101.9 / 104.8, a window of 5 x 12 x 914 19.8 / 20.7
+  //   D = 128, 128 queries: a window of 3 x 9 x 1500 15.5 / 14.5; packed sequences of 3001 24.2 / 24.4, of 4096 82.1 / 82.5
+  //   D = 128, 256 queries: packed sequences of 3001 29.2 / 28.8, of 4096 94.3 / 93.4
+  constexpr bool LIST_FIRST = SCHED != 1 || (D == 128 && NW == 2);
   // What a lane reads and copies where.  Found anew for every item at D = 128: kept across the merge of a cut row, some of it lay in
   // scratch memory, and the own row's list was asked for only when its first tile had landed (the wait for the reload).  At D = 64
   // there is room for it (packed sequences of 3001, 64 queries a row, 13.56 -> 13.40 us), except beside the merge of small launches
@@ -668,7 +671,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // ---- a launch too small to fill the chip: work-group = (block row, part), merged by merge_tree
   if constexpr (SCHED == 2) {
     int nbr = P->nbr, Mb = P->Mb, H = P->H, split = P->split, mode = P->mode;
-    asm volatile("" : "+s"(nbr), "+s"(Mb), "+s"(H), "+s"(split), "+s"(mode));  // in one go, see below
+    asm volatile("" : "+s"(nbr), "+s"(Mb), "+s"(H), "+s"(split), "+s"(mode) : "s"(P->q));  // in one go, see below
     int part = (int)blockIdx.x % split;
     const int rest = (int)blockIdx.x / split;
     int S = split;  // parts of this row
@@ -718,14 +721,19 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // Launch order inside a group of G consecutive (batch, head) planes: rank-major, i.e. rank 0 of every plane of the
   // group, then rank 1 of every plane, ...  The hardware starts work-groups in index order as slots free up, so
   // with ranks sorted by length long rows start early everywhere and the short ones fill the tail.
-  // The arguments this takes are asked for in one go (hence the asm).  The compiler would read each where it is needed, and a scalar
-  // load is waited for together with all that are under way: one of them stood between the schedule's header and the row's record
-  // below, which then followed each other on their ways to memory.  (Header and record through the constant address space, so
-  // that they are scalar loads: no kernel that reads a schedule writes one.)
+  // The arguments this takes are asked for in one go (hence the asm), and with them one from every cache line of the argument
+  // segment, which is cold when a kernel starts.  The compiler would read each where it is needed, a trip to memory for every line
+  // in turn; and since a scalar load is waited for together with all that are under way, one of them stood between the schedule's
+  // header and the row's record below, which then followed each other, too.  Over 45 shapes on other tensors call by call: 1 % of the
+  // forward, a dilated window of 2 x 7 x 670, D = 64, 256 queries a row, 10.41 -> 10.23 us, windows of 5 x 12 x 914, D = 128, 64 queries
+  // a row, 20.3 -> 19.8.  (Header and record through the constant address space, so that they are scalar loads: no kernel that reads
+  // a schedule writes one.)
+  static_assert(sizeof(AttnParams) <= 256 && offsetof(AttnParams, q) / 64 == 0 && offsetof(AttnParams, H) / 64 == 1 && offsetof(AttnParams, nbr) / 64 == 2 &&
+                    offsetof(AttnParams, G) / 64 == 3 && offsetof(AttnParams, split) / 64 == 3, "one argument of every line is among those below");
   int own_bh, own_m, own_rank;
-  int T = P->total_wgs, G = P->G, nbr = P->nbr, Mb = P->Mb, H = P->H, hbp = P->hbp, part_cap = P->part_cap;
+  int T = P->total_wgs, G = P->G, nbr = P->nbr, Mb = P->Mb, H = P->H, hbp = P->hbp, part_cap = P->part_cap, nbc = P->nbc, n_extra = P->n_extra;
   uint64_t sched_at = reinterpret_cast<uint64_t>(P->sched);
-  asm volatile("" : "+s"(T), "+s"(G), "+s"(nbr), "+s"(Mb), "+s"(H), "+s"(hbp), "+s"(part_cap), "+s"(sched_at));
+  asm volatile("" : "+s"(T), "+s"(G), "+s"(nbr), "+s"(Mb), "+s"(H), "+s"(hbp), "+s"(part_cap), "+s"(nbc), "+s"(n_extra), "+s"(sched_at) : "s"(P->q));
   {
     const int wg = (int)blockIdx.x;
     const int xcd = wg & 7, slot = wg >> 3;
@@ -760,7 +768,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   // (nothing to do, and no cost, when the schedule cut no row).  The tile loop is in the program twice, here and below: with one
   // loop for parts and own row the short rows of packed sequences took 44.9 us instead of 41.8, a 16384-token window 123 instead
   // of 115 (the backward kernels, which are short of registers, gained from it).
-  if (SCHED == 1 && (int)blockIdx.x < P->n_extra) {
+  if (SCHED == 1 && (int)blockIdx.x < n_extra) {
     const int n_items = nparts_all * P->hbp;
     // The first item of a work-group is its own index; later ones come from the queue counter, which therefore stands
     // for "n_extra items already handed out".
@@ -795,7 +803,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : NW >= 4 ? 2 : 1) 
   if (SCHED == 1) {
     i = own_rec.x;
     const int n_list = own_rec.z;
-    const uint32_t* const list = global(P->col_idx) + (int64_t)m * P->nbr * P->nbc + own_rec.y;
+    const uint32_t* const list = global(P->col_idx) + (int64_t)m * nbr * nbc + own_rec.y;
     const uint32_t ahead = ask_list(list, n_list);
     begin_item();
     if (n_list <= split_T) {  // a row the schedule cut belongs to the queue

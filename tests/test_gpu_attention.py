@@ -550,8 +550,8 @@ def test_lists_around_one_entry_per_thread(Br, length):
 
 @pytest.mark.parametrize("Br,length", [(64, 1), (64, 128), (64, 129), (128, 1), (128, 256), (128, 257), (256, 1), (256, 512), (256, 513)])
 def test_lists_around_one_entry_per_thread_at_d128(Br, length):
-    """At d = 128 rows of 64 and 256 queries ask for their list first, those of 128 behind the first tile (at d = 64 it is those of 64
-    that ask first).  Row 0 without a tile: its work-group asks, and finds nothing."""
+    """Rows of 64 queries ask for their list first at d = 128, all others behind the first tile.  Row 0 without a tile: its work-group
+    asks, and finds nothing."""
     bbm = _bbm()
     H, Nq, Nk, d = 257, Br + 40, 64 * length - 5, 128
     gen = torch.Generator(device="cuda").manual_seed(length)
